@@ -280,60 +280,7 @@ __device__ inline uint64_t filter_candidates(uint64_t pk, uint64_t row, int k, i
 // ---- canonical distances --------------------------------------------------
 // Float metrics accumulate one fused multiply-add per dimension, in dimension
 // order, in float32; bytes accumulate exact int32 squares.  The result is the
-// order-preserving code of the distance.
-template <int METRIC>
-struct DistOf;
-
-template <>
-struct DistOf<kL2F32> {
-  using elem = float;
-  __device__ static uint32_t eval(const float* a, const float* b, int d) {
-    float acc = 0.f;
-    int j = 0;
-    if ((d & 3) == 0) {
-      const float4* a4 = reinterpret_cast<const float4*>(a);
-      const float4* b4 = reinterpret_cast<const float4*>(b);
-      for (; j < (d >> 2); ++j) {
-        float4 x = a4[j], y = b4[j];
-        float t;
-        t = x.x - y.x; acc = __fmaf_rn(t, t, acc);
-        t = x.y - y.y; acc = __fmaf_rn(t, t, acc);
-        t = x.z - y.z; acc = __fmaf_rn(t, t, acc);
-        t = x.w - y.w; acc = __fmaf_rn(t, t, acc);
-      }
-    } else {
-      for (; j < d; ++j) {
-        float t = a[j] - b[j];
-        acc = __fmaf_rn(t, t, acc);
-      }
-    }
-    return ord_f32(acc);
-  }
-};
-
-template <>
-struct DistOf<kAngularF32> {
-  using elem = float;
-  __device__ static uint32_t eval(const float* a, const float* b, int d) {
-    float acc = 0.f;
-    int j = 0;
-    if ((d & 3) == 0) {
-      const float4* a4 = reinterpret_cast<const float4*>(a);
-      const float4* b4 = reinterpret_cast<const float4*>(b);
-      for (; j < (d >> 2); ++j) {
-        float4 x = a4[j], y = b4[j];
-        acc = __fmaf_rn(x.x, y.x, acc);
-        acc = __fmaf_rn(x.y, y.y, acc);
-        acc = __fmaf_rn(x.z, y.z, acc);
-        acc = __fmaf_rn(x.w, y.w, acc);
-      }
-    } else {
-      for (; j < d; ++j) acc = __fmaf_rn(a[j], b[j], acc);
-    }
-    return ord_f32(1.0f - acc);
-  }
-};
-
+// order-preserving code of the distance.  JoinTraits (below) states one step and the code.
 // Chi-square distance of non-negative vectors: sum of (a - b)^2 / (a + b) over
 // the dimensions with a + b > 0; every operation rounded on its own (there is no
 // multiply feeding an add, so nothing can fuse), correctly rounded division.
@@ -341,15 +288,6 @@ __device__ inline float chi2_term(float a, float b, float acc) {
   const float diff = __fsub_rn(a, b), sum = __fadd_rn(a, b);
   return sum > 0.f ? __fadd_rn(acc, __fdiv_rn(__fmul_rn(diff, diff), sum)) : acc;
 }
-template <>
-struct DistOf<kChi2F32> {
-  using elem = float;
-  __device__ static uint32_t eval(const float* a, const float* b, int d) {
-    float acc = 0.f;
-    for (int j = 0; j < d; ++j) acc = chi2_term(a[j], b[j], acc);
-    return ord_f32(acc);
-  }
-};
 
 // Cosine distance of vectors of any length: 1 - a.b / sqrt(|a|^2 |b|^2); a zero
 // vector is at distance 1 from everything.  The inner product and the squared
@@ -362,47 +300,6 @@ __device__ inline uint32_t cosine_code(float dot, float na, float nb) {
   const float den = sqrtf(__fmul_rn(na, nb));
   return ord_f32(den > 0.f ? __fsub_rn(1.0f, __fdiv_rn(dot, den)) : 1.0f);
 }
-template <>
-struct DistOf<kCosineF32> {
-  using elem = float;
-  __device__ static uint32_t eval(const float* a, const float* b, int d) {
-    float dot = 0.f, na = 0.f, nb = 0.f;
-    for (int j = 0; j < d; ++j) {
-      const float x = a[j], y = b[j];
-      dot = __fmaf_rn(x, y, dot);
-      na = __fmaf_rn(x, x, na);
-      nb = __fmaf_rn(y, y, nb);
-    }
-    return cosine_code(dot, na, nb);
-  }
-};
-
-template <>
-struct DistOf<kL2U8> {
-  using elem = uint8_t;
-  __device__ static uint32_t eval(const uint8_t* a, const uint8_t* b, int d) {
-    int32_t acc = 0;
-    int j = 0;
-    if ((d & 3) == 0) {
-      const uint32_t* a4 = reinterpret_cast<const uint32_t*>(a);
-      const uint32_t* b4 = reinterpret_cast<const uint32_t*>(b);
-      for (; j < (d >> 2); ++j) {
-        uint32_t x = a4[j], y = b4[j];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          int32_t t = (int32_t)((x >> (8 * q)) & 0xff) - (int32_t)((y >> (8 * q)) & 0xff);
-          acc += t * t;
-        }
-      }
-    } else {
-      for (; j < d; ++j) {
-        int32_t t = (int32_t)a[j] - (int32_t)b[j];
-        acc += t * t;
-      }
-    }
-    return ord_i32(acc);
-  }
-};
 
 // Vectors may live in two arrays (the two sets of a merge): rows below `split`
 // come from the first, the others from the second.
@@ -419,8 +316,8 @@ struct VecSrc {
   }
 };
 
-// The same arithmetic one step at a time (one dimension of one pair), for the
-// kernels that walk many pairs through staged chunks of dimensions.
+// The canonical arithmetic one step at a time (one dimension of one pair), for kernels that
+// walk many pairs through staged chunks of dimensions.
 template <int METRIC>
 struct JoinTraits;
 template <>
@@ -475,8 +372,7 @@ struct JoinTraits<kL2U8> {
 // where `on`).  The 64 rows and the row of s are staged through the wave's LDS
 // tile in chunks of kEvalChunk dimensions with coalesced reads (8 lanes per row
 // chunk), then every lane accumulates its own pair in dimension order: the
-// arithmetic of DistOf<METRIC>::eval, without 64 lanes each walking a row of its
-// own through HBM.  All 64 lanes must call it together.
+// canonical arithmetic, without 64 lanes each walking a row of its own through HBM.  All 64 lanes must call it together.
 constexpr int kEvalChunk = 32;
 constexpr int kEvalStride = kEvalChunk + 1;  // odd stride: lanes walk their rows free of bank conflicts
 constexpr int kEvalTileWords = 65 * kEvalStride;

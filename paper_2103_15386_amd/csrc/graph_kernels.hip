@@ -531,60 +531,6 @@ __global__ __launch_bounds__(kBlock) void k_merge_final(int64_t n, MergeIds mi, 
 }
 
 // ---------------------------------------------------------------------------
-// Exhaustive exact K-NN of a query node (ground truth for Recall@K): each wave
-// scans a quarter of the data set, one candidate per lane, and keeps the best
-// 64 in its lanes; the four lists are merged at the end.
-template <int METRIC>
-__global__ __launch_bounds__(kBlock) void k_exact_knn(const void* vec, int64_t n, int d,
-                                                      const int32_t* queries, int K,
-                                                      int32_t* ids_out, void* dist_out) {
-  using D = DistOf<METRIC>;
-  using T = typename D::elem;
-  __shared__ uint64_t part[kWavesPerBlock][kWave];
-  const int lane = lane_id();
-  const int wave = wave_id();
-  const int64_t q = blockIdx.x;
-  const uint32_t s = (uint32_t)queries[q];
-  const T* base = reinterpret_cast<const T*>(vec);
-  // a query id that is no node reads nothing and gets the "none" answer (-1, largest distance)
-  const bool valid = (int64_t)s < n;
-  const T* qrow = base + (valid ? (int64_t)s * d : 0);
-  uint64_t best = kKeyMax;  // ascending in lanes; lanes >= K stay unused
-  for (int64_t c0 = (int64_t)wave * kWave; valid && c0 < n; c0 += kBlock) {
-    const int64_t c = c0 + lane;
-    uint64_t key = kKeyMax;
-    if (c < n && c != (int64_t)s) {
-      uint32_t code = D::eval(qrow, base + c * d, d);
-      key = ((uint64_t)code << 32) | (uint64_t)c;
-    }
-    const uint64_t last = readlane64(best, K - 1);
-    if (key >= last) key = kKeyMax;
-    if (__ballot(key != kKeyMax) == 0ull) continue;
-    key = wave_sort(key, lane);
-    best = wave_merge_smallest(best, key, lane);
-    if (lane >= K) best = kKeyMax;
-  }
-  part[wave][lane] = best;
-  __syncthreads();
-  if (wave == 0) {
-    for (int w = 1; w < kWavesPerBlock; ++w) {
-      best = wave_merge_smallest(best, part[w][lane], lane);
-      if (lane >= K) best = kKeyMax;
-    }
-    if (lane < K) {
-      const bool have = best != kKeyMax;
-      ids_out[q * K + lane] = have ? (int32_t)(uint32_t)best : -1;
-      uint32_t code = (uint32_t)(best >> 32);
-      if (METRIC == kL2U8)
-        reinterpret_cast<int32_t*>(dist_out)[q * K + lane] = have ? unord_i32(code) : 0x7fffffff;
-      else
-        reinterpret_cast<float*>(dist_out)[q * K + lane] =
-            have ? unord_f32(code) : __uint_as_float(0x7f800000u);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Exclusive scan, three passes: per-block scan of 1024 elements, scan of the
 // block sums by one block, add-back.
 constexpr int kScanPerThread = 4;
@@ -880,30 +826,6 @@ hipError_t launch_merge_final(const Shape& sh, const DevState& ds, const MergeId
   else
     k_merge_final<true><<<grid, kBlock, 0, st>>>(sh.n, mi, sh.k, ds.G, ds.aside, ids_out,
                                                  dist_out);
-  return hipGetLastError();
-}
-
-hipError_t launch_exact_knn(const void* vec, int64_t n, int32_t d, int32_t metric,
-                            const int32_t* queries, int64_t nq, int32_t K, int32_t* ids_out,
-                            void* dist_out, hipStream_t st) {
-  if (nq == 0) return hipSuccess;
-  const unsigned grid = (unsigned)nq;
-  switch (metric) {
-    case kL2F32:
-      k_exact_knn<kL2F32><<<grid, kBlock, 0, st>>>(vec, n, d, queries, K, ids_out, dist_out);
-      break;
-    case kAngularF32:
-      k_exact_knn<kAngularF32><<<grid, kBlock, 0, st>>>(vec, n, d, queries, K, ids_out, dist_out);
-      break;
-    case kChi2F32:
-      k_exact_knn<kChi2F32><<<grid, kBlock, 0, st>>>(vec, n, d, queries, K, ids_out, dist_out);
-      break;
-    case kCosineF32:
-      k_exact_knn<kCosineF32><<<grid, kBlock, 0, st>>>(vec, n, d, queries, K, ids_out, dist_out);
-      break;
-    default:
-      k_exact_knn<kL2U8><<<grid, kBlock, 0, st>>>(vec, n, d, queries, K, ids_out, dist_out);
-  }
   return hipGetLastError();
 }
 
