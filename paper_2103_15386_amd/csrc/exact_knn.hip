@@ -1,17 +1,22 @@
 // Exhaustive exact K-NN of query nodes (ground truth of Recall@K).
 //
-// A workgroup answers Q queries (Q = 8, 4, 2 or 1 by the number of queries); its wavefronts
-// take tiles of 64 rows in turn, one row per lane, so a value of a row is used for Q distances
-// while the queries' values are the same for the whole wavefront and come through scalar
-// registers.  The rows pass through the wavefront's own LDS tile, kChunk words of every row at
-// a time, with coalesced reads and the next chunk in flight in registers while this one is
-// evaluated; no barriers between the wavefronts until the end.  The distance of a
-// pair is accumulated in the canonical order (JoinTraits).
+// A workgroup of 16 wavefronts answers Q queries (Q = 8, 4, 2 or 1 by the number of queries);
+// its wavefronts take tiles of 128 rows in turn, two rows per lane.  The rows pass through the
+// wavefront's own LDS tile, 16 words of every row at a time, with coalesced reads and the next
+// chunk in flight in registers while this one is evaluated; the queries' words lie behind the
+// rows' and are read by all lanes at once.  Per four dimensions a lane reads 2 + Q 16-byte
+// pieces from LDS for 8 Q steps of the canonical sums (JoinTraits).  No barriers between the
+// wavefronts until the end.
 //
 // Every wavefront keeps the best 64 of its tiles for each query in its lanes; the smallest
-// K-th best key of any wavefront, kept in LDS, turns most tiles away with one comparison.
+// K-th best key of any wavefront, kept in LDS, turns most tiles away with one comparison per
+// query and row.
 //
-// Bound: vector-ALU issue, Q (angular) or 2 Q (squared L2) instructions per dimension and row.
+// 2000 queries x 10^6 x 96 under the angular distance: 9.8 ms, 39 TFLOP/s (455 ms with one
+// query per workgroup and a row per lane straight from memory; 18 ms with one row per lane and
+// the queries through scalar loads, whose latency it waited for).  Bound: vector-ALU issue
+// (0.75 busy; 4.9 ms at the full rate without packed instructions, squared L2 takes two
+// instructions per dimension and pair), then LDS reads (0.56 busy).
 #include "device_utils.hpp"
 #include "kernels.hpp"
 
@@ -21,13 +26,18 @@ namespace {
 
 constexpr int kEWaves = 16;               // wavefronts per workgroup, 4 per SIMD
 constexpr int kEBlock = kEWaves * kWave;  // 1024 threads
-constexpr int kChunkF = 32;               // float dimensions per chunk
-constexpr int kChunkB = 16;               // words of four bytes per chunk of uint8 rows
-// row strides of the tile: rows start at multiples of 16 bytes, and 8 lanes of a 16-byte access
-// to 8 consecutive rows touch all banks once
-constexpr int kStrideF = kChunkF + 4, kStrideB = kChunkB + 4;
+constexpr int kLaneRows = 2;              // rows per lane and tile
+constexpr int kTile = kLaneRows * kWave;  // rows per tile
+constexpr int kChunk = 16;                // words (floats, or four bytes) per row and chunk
+constexpr int kPieces = kChunk / 4;       // 16-byte pieces per row and chunk
+constexpr int kRowsAtOnce = kWave / kPieces;
+constexpr int kLoads = kTile / kRowsAtOnce;
 
-using uniform_f32 = const __attribute__((address_space(4))) float;  // read by scalar loads
+// Where piece `part` of a row lies in the tile, in words: the pieces of four rows change places
+// so that 16 lanes reading the same piece of 16 consecutive rows touch every bank once.
+__device__ inline int piece_at(int row, int part) {
+  return row * kChunk + ((part ^ (row >> 2)) & (kPieces - 1)) * 4;
+}
 
 __device__ inline void tile_fence() {  // the lanes of a wavefront exchange data through LDS
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -35,9 +45,9 @@ __device__ inline void tile_fence() {  // the lanes of a wavefront exchange data
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The smallest K keys seen so far, ascending over the lanes.  A tile that offers only a few
-// keys enters them one by one (a lane shift each), otherwise the tile is sorted and merged.
-__device__ inline void take_tile(uint64_t& best, uint64_t key, uint64_t* shared_last, int K,
+// Enter the keys below the K-th best of any wavefront in the ascending list `best`.  A few
+// keys are entered one by one (a lane shift each), more are sorted and merged.
+__device__ inline void take_keys(uint64_t& best, uint64_t key, uint64_t* shared_last, int K,
                                  int lane) {
   uint64_t bound = *reinterpret_cast<volatile uint64_t*>(shared_last);
   bound = vmin(bound, readlane64(best, K - 1));
@@ -65,205 +75,227 @@ __device__ inline void take_tile(uint64_t& best, uint64_t key, uint64_t* shared_
     atomicMin(reinterpret_cast<unsigned long long*>(shared_last), (unsigned long long)last);
 }
 
-template <int METRIC, int Q>
+// ALIGNED: rows are multiples of 16 bytes (and not longer than 64 MiB).
+template <int METRIC, int Q, bool ALIGNED>
 __global__ __launch_bounds__(kEBlock) void k_exact_knn(const void* vec, int64_t n, int d,
                                                        const int32_t* queries, int64_t nq, int K,
                                                        int32_t* ids_out, void* dist_out) {
   constexpr bool kBytes = METRIC == kL2U8;
-  constexpr int kChunk = kBytes ? kChunkB : kChunkF;    // words per row and chunk
-  constexpr int kStride = kBytes ? kStrideB : kStrideF;
-  constexpr int kRows = kBytes ? kWave + Q : kWave;     // bytes: the queries' words as well
-  constexpr int kPerRow = kChunk / 4;                   // lanes that read a row's chunk
-  constexpr int kRowsAtOnce = kWave / kPerRow;
-  constexpr int kLoads = (kRows + kRowsAtOnce - 1) / kRowsAtOnce;
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-  __shared__ uint64_t last_of[Q];
+  __shared__ uint64_t last_of[8];
   const int lane = lane_id(), wave = wave_id();
-  uint32_t* const tile = lds + wave * (kRows * kStride);
+  uint32_t* const tile = lds + wave * ((kTile + Q) * kChunk);
   const int64_t q0 = (int64_t)blockIdx.x * Q;
-  // a query id that is no node reads row 0 and gets the "none" answer (-1, largest distance)
-  uint32_t qid[Q];
-  bool valid[Q];
-#pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    const uint32_t s = q0 + q < nq ? (uint32_t)queries[q0 + q] : 0xffffffffu;
-    qid[q] = __builtin_amdgcn_readfirstlane(s);
-    valid[q] = (int64_t)qid[q] < n;
-  }
-  auto query_row = [&](int q) { return valid[q] ? (int64_t)qid[q] : 0; };
-  if (threadIdx.x < Q) last_of[threadIdx.x] = kKeyMax;
+  if (threadIdx.x < 8) last_of[threadIdx.x] = kKeyMax;
   __syncthreads();
-  float qnorm[Q];
-  if constexpr (METRIC == kCosineF32) {
-    float acc = 0.f;
-    const float* mine = reinterpret_cast<const float*>(vec);
-#pragma unroll
-    for (int q = 0; q < Q; ++q)
-      if (lane == q) mine += query_row(q) * d;
-    for (int j = 0; j < d; ++j) acc = __fmaf_rn(mine[j], mine[j], acc);
-#pragma unroll
-    for (int q = 0; q < Q; ++q)
-      qnorm[q] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(acc), q));
-  }
   const int words = kBytes ? (d + 3) >> 2 : d;  // words per row
-  const bool aligned = kBytes ? (d & 15) == 0 : (d & 3) == 0;  // rows are multiples of 16 bytes
-  const int part = (lane & (kPerRow - 1)) * 4, rsel = lane / kPerRow;
+  const int64_t row_bytes = kBytes ? d : (int64_t)d * 4;
+  const char* const rows = reinterpret_cast<const char*>(vec);
+  const int part = lane & (kPieces - 1), rsel = lane / kPieces;
+
+  // lanes 4 q .. 4 q + 3 bring the pieces of query q.  A query id that is no node reads row 0
+  // and gets the "none" answer (-1, largest distance).
+  const int my_q = rsel < Q ? rsel : 0;
+  const char* query_row;
+  {
+    const uint32_t s = q0 + my_q < nq ? (uint32_t)queries[q0 + my_q] : 0xffffffffu;
+    query_row = rows + ((int64_t)s < n ? (int64_t)s * row_bytes : 0);
+  }
+  uint32_t qid[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+    qid[q] = __builtin_amdgcn_readfirstlane(q0 + q < nq ? (uint32_t)queries[q0 + q] : 0xffffffffu);
+
+  // A tile is always 128 rows: the last one is moved back (its rows before `c0` have been
+  // seen); only with fewer than 128 rows in all are places of the tile left without a row.
+  const int64_t last_tile = n > kTile ? n - kTile : 0;
+  const int rows_here = n < kTile ? (int)n : kTile;
+  // ALIGNED: this lane's share of the chunk at word w0 of the rows of a tile, four lanes per
+  // row.  What lies beyond the rows' end is not used: the last piece is read once more.
+  uint4 reg[kLoads], qreg;
+  auto fetch = [&](int64_t c0, int w0) {
+    const char* const first_row = rows + (c0 < last_tile ? c0 : last_tile) * row_bytes;
+    const int w = w0 + 4 * part;
+    const uint32_t at = 4u * (uint32_t)(w < words ? w : words - 4);
+    const uint32_t off = (uint32_t)(rsel * row_bytes) + at;
+    if (rows_here == kTile) {
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i)
+        reg[i] = *reinterpret_cast<const uint4*>(first_row + i * kRowsAtOnce * row_bytes + off);
+    } else {
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i) {
+        reg[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (i * kRowsAtOnce + rsel < rows_here)
+          reg[i] = *reinterpret_cast<const uint4*>(first_row + i * kRowsAtOnce * row_bytes + off);
+      }
+    }
+    qreg = *reinterpret_cast<const uint4*>(query_row + at);
+  };
+  auto put = [&]() {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i)
+      *reinterpret_cast<uint4*>(tile + piece_at(i * kRowsAtOnce + rsel, part)) = reg[i];
+    if (rsel < Q) *reinterpret_cast<uint4*>(tile + (kTile + rsel) * kChunk + 4 * part) = qreg;
+  };
+  // other rows: word by word, 16 lanes per row, straight to the tile; what lies beyond the
+  // rows' end is zero (for bytes it takes part in the dot products)
+  auto bring = [&](int64_t c0, int w0) {
+    const char* const first_row = rows + (c0 < last_tile ? c0 : last_tile) * row_bytes;
+    const int col = lane & (kChunk - 1), w = w0 + col;
+#pragma unroll 4
+    for (int i = 0; i < (kTile + Q + 3) / 4; ++i) {
+      const int r = 4 * i + lane / kChunk;
+      if (r >= kTile + Q || (r < kTile && r >= rows_here) || w >= words) continue;
+      const char* src = first_row + r * row_bytes;
+      if (r >= kTile) {
+        const uint32_t s = q0 + r - kTile < nq ? (uint32_t)queries[q0 + r - kTile] : 0xffffffffu;
+        src = rows + ((int64_t)s < n ? (int64_t)s * row_bytes : 0);
+      }
+      uint32_t v = 0u;
+      if (!kBytes || (d & 3) == 0) {
+        v = reinterpret_cast<const uint32_t*>(src)[w];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (4 * w + e < d) v |= (uint32_t)(uint8_t)src[4 * (int64_t)w + e] << (8 * e);
+      }
+      tile[r < kTile ? piece_at(r, col >> 2) + (col & 3) : r * kChunk + col] = v;
+    }
+    if (w >= words && kBytes)
+      for (int i = 0; i < (kTile + Q + 3) / 4; ++i) {
+        const int r = 4 * i + lane / kChunk;
+        if (r < kTile + Q)
+          tile[r < kTile ? piece_at(r, col >> 2) + (col & 3) : r * kChunk + col] = 0u;
+      }
+  };
 
   uint64_t best[Q];
 #pragma unroll
   for (int q = 0; q < Q; ++q) best[q] = kKeyMax;
-
-  // this lane's share of the chunk at word w0 of the rows of the tile that starts at row c0
-  uint4 reg[kLoads];
-  auto fetch = [&](int64_t c0, int w0) {
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-      const int r = i * kRowsAtOnce + rsel;
-      int64_t row = c0 + r;
-      bool on = row < n;
-      if (kBytes && i * kRowsAtOnce + kRowsAtOnce > kWave && r >= kWave) {
-        row = 0;
-        on = r < kRows;
-#pragma unroll
-        for (int q = 0; q < Q; ++q)
-          if (r == kWave + q) row = query_row(q);
-      }
-      const int w = w0 + part;
-      uint32_t v[4] = {0u, 0u, 0u, 0u};
-      if (on) {
-        if (!kBytes) {
-          const float* src = reinterpret_cast<const float*>(vec) + row * d + w;
-          if (aligned) {
-            if (w < words) {
-              const uint4 x = *reinterpret_cast<const uint4*>(src);
-              v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-            }
-          } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-              if (w + j < words) v[j] = __float_as_uint(src[j]);
-          }
-        } else {
-          const uint8_t* src = reinterpret_cast<const uint8_t*>(vec) + row * d + 4 * (int64_t)w;
-          if (aligned) {
-            if (w < words) {
-              const uint4 x = *reinterpret_cast<const uint4*>(src);
-              v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-            }
-          } else if ((d & 3) == 0) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-              if (w + j < words) v[j] = reinterpret_cast<const uint32_t*>(src)[j];
-          } else {
-#pragma unroll
-            for (int j = 0; j < 16; ++j)
-              if (4 * w + j < d) v[j >> 2] |= (uint32_t)src[j] << (8 * (j & 3));
-          }
-        }
-      }
-      reg[i] = make_uint4(v[0], v[1], v[2], v[3]);
-    }
-  };
-  auto put = [&]() {
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-      const int r = i * kRowsAtOnce + rsel;
-      if (r < kRows) *reinterpret_cast<uint4*>(tile + r * kStride + part) = reg[i];
-    }
-  };
-
-  const int64_t step = (int64_t)kEBlock;
-  const int64_t first = (int64_t)wave * kWave;
-  if (first < n) fetch(first, 0);
+  constexpr int64_t step = (int64_t)kEWaves * kTile;
+  const int64_t first = (int64_t)wave * kTile;
+  if (ALIGNED && first < n) fetch(first, 0);
   for (int64_t c0 = first; c0 < n; c0 += step) {
-    float acc[Q], norm = 0.f;
-    uint32_t dot[Q], qq[Q], cc = 0u;
+    // floats: running sums; bytes: inner products (and the squared norms)
+    typename JoinTraits<kBytes ? kL2U8 : METRIC>::acc acc[Q][kLaneRows];
+    float qnorm[Q], norm[kLaneRows];
+    uint32_t qq[Q], cc[kLaneRows];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      acc[q] = 0.f;
-      dot[q] = qq[q] = 0u;
+      qnorm[q] = 0.f;
+      qq[q] = 0u;
+#pragma unroll
+      for (int i = 0; i < kLaneRows; ++i) acc[q][i] = 0;
+    }
+#pragma unroll
+    for (int i = 0; i < kLaneRows; ++i) {
+      norm[i] = 0.f;
+      cc[i] = 0u;
     }
     for (int w0 = 0; w0 < words; w0 += kChunk) {
       tile_fence();  // the chunk before this one has been read
-      put();
+      if (ALIGNED) put();
+      else bring(c0, w0);
       tile_fence();
-      // request the next chunk, of this tile or of the next one
-      if (w0 + kChunk < words) fetch(c0, w0 + kChunk);
-      else if (c0 + step < n) fetch(c0 + step, 0);
+      if (ALIGNED) {  // request the next chunk, of this tile or of the next one
+        if (w0 + kChunk < words) fetch(c0, w0 + kChunk);
+        else if (c0 + step < n) fetch(c0 + step, 0);
+      }
       const int width = words - w0 < kChunk ? words - w0 : kChunk;
-      if constexpr (kBytes) {
-        for (int j = 0; j < width; j += 4) {  // words past the end are zeros
-          const uint4 x = *reinterpret_cast<const uint4*>(tile + lane * kStride + j);
-          cc = __builtin_amdgcn_udot4(x.x, x.x, cc, false);
-          cc = __builtin_amdgcn_udot4(x.y, x.y, cc, false);
-          cc = __builtin_amdgcn_udot4(x.z, x.z, cc, false);
-          cc = __builtin_amdgcn_udot4(x.w, x.w, cc, false);
+#pragma unroll 1
+      for (int j = 0; j < width; j += 4) {
+        uint4 x[kLaneRows];
+#pragma unroll
+        for (int i = 0; i < kLaneRows; ++i)
+          x[i] = *reinterpret_cast<const uint4*>(tile + piece_at(i * kWave + lane, j >> 2));
+        if constexpr (kBytes) {
+          auto dot4 = [](const uint4& a, const uint4& b, uint32_t s) {
+            s = __builtin_amdgcn_udot4(a.x, b.x, s, false);
+            s = __builtin_amdgcn_udot4(a.y, b.y, s, false);
+            s = __builtin_amdgcn_udot4(a.z, b.z, s, false);
+            return __builtin_amdgcn_udot4(a.w, b.w, s, false);
+          };
+#pragma unroll
+          for (int i = 0; i < kLaneRows; ++i) cc[i] = dot4(x[i], x[i], cc[i]);
 #pragma unroll
           for (int q = 0; q < Q; ++q) {
-            const uint4 y = *reinterpret_cast<const uint4*>(tile + (kWave + q) * kStride + j);
-            dot[q] = __builtin_amdgcn_udot4(x.x, y.x, dot[q], false);
-            dot[q] = __builtin_amdgcn_udot4(x.y, y.y, dot[q], false);
-            dot[q] = __builtin_amdgcn_udot4(x.z, y.z, dot[q], false);
-            dot[q] = __builtin_amdgcn_udot4(x.w, y.w, dot[q], false);
-            qq[q] = __builtin_amdgcn_udot4(y.x, y.x, qq[q], false);
-            qq[q] = __builtin_amdgcn_udot4(y.y, y.y, qq[q], false);
-            qq[q] = __builtin_amdgcn_udot4(y.z, y.z, qq[q], false);
-            qq[q] = __builtin_amdgcn_udot4(y.w, y.w, qq[q], false);
+            const uint4 y = *reinterpret_cast<const uint4*>(tile + (kTile + q) * kChunk + j);
+            qq[q] = dot4(y, y, qq[q]);
+#pragma unroll
+            for (int i = 0; i < kLaneRows; ++i)
+              acc[q][i] = (int32_t)dot4(x[i], y, (uint32_t)acc[q][i]);
           }
-        }
-      } else {
-        uniform_f32* qrow[Q];
+        } else {
+          auto f = [](uint32_t b) { return __uint_as_float(b); };
+          auto steps = [&](int c) {  // the first c dimensions of these four
 #pragma unroll
-        for (int q = 0; q < Q; ++q)
-          qrow[q] = (uniform_f32*)(reinterpret_cast<uintptr_t>(vec) +
-                                   (size_t)(query_row(q) * d + w0) * 4);
-        auto pair_step = [&](float y, int j) {
-          if constexpr (METRIC == kCosineF32) norm = __fmaf_rn(y, y, norm);
+            for (int q = 0; q < Q; ++q) {
+              const uint4 y = *reinterpret_cast<const uint4*>(tile + (kTile + q) * kChunk + j);
+              const uint32_t yw[4] = {y.x, y.y, y.z, y.w};
 #pragma unroll
-          for (int q = 0; q < Q; ++q) JoinTraits<METRIC>::step(qrow[q][j], y, acc[q]);
-        };
-        const float* mine = reinterpret_cast<const float*>(tile) + lane * kStride;
-        int j = 0;
-#pragma unroll 1
-        for (; j + 3 < width; j += 4) {
-          const float4 y = *reinterpret_cast<const float4*>(mine + j);
-          pair_step(y.x, j);
-          pair_step(y.y, j + 1);
-          pair_step(y.z, j + 2);
-          pair_step(y.w, j + 3);
+              for (int e = 0; e < 4; ++e) {
+                if (e < c) {
+                  if constexpr (METRIC == kCosineF32)
+                    qnorm[q] = __fmaf_rn(f(yw[e]), f(yw[e]), qnorm[q]);
+#pragma unroll
+                  for (int i = 0; i < kLaneRows; ++i) {
+                    const uint32_t xw[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
+                    JoinTraits<METRIC>::step(f(yw[e]), f(xw[e]), acc[q][i]);
+                  }
+                }
+              }
+            }
+            if constexpr (METRIC == kCosineF32) {
+#pragma unroll
+              for (int i = 0; i < kLaneRows; ++i) {
+                const uint32_t xw[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                  if (e < c) norm[i] = __fmaf_rn(f(xw[e]), f(xw[e]), norm[i]);
+              }
+            }
+          };
+          if (ALIGNED || j + 4 <= width) steps(4);
+          else steps(width - j);
         }
-        for (; j < width; ++j) pair_step(mine[j], j);
       }
     }
-    const int64_t c = c0 + lane;
+    // bounds of the queries' lists, read once per tile: upper halves, so "not above" may
+    // enter; take_keys compares whole keys
+    const uint32_t my_bound =
+        (uint32_t)(*reinterpret_cast<volatile uint64_t*>(&last_of[lane & 7]) >> 32);
+    const int64_t tile0 = c0 < last_tile ? c0 : last_tile;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      uint32_t code;
-      if constexpr (kBytes) code = ord_i32((int32_t)(qq[q] + cc - 2u * dot[q]));
-      else if constexpr (METRIC == kCosineF32) code = cosine_code(acc[q], qnorm[q], norm);
-      else code = JoinTraits<METRIC>::code(acc[q]);
-      uint64_t key = ((uint64_t)code << 32) | (uint64_t)c;
-      if (c >= n || c == (int64_t)qid[q]) key = kKeyMax;
-      take_tile(best[q], key, &last_of[q], K, lane);
+      const uint32_t bound = __builtin_amdgcn_readlane(my_bound, q);
+#pragma unroll
+      for (int i = 0; i < kLaneRows; ++i) {
+        uint32_t code;
+        if constexpr (kBytes) code = ord_i32((int32_t)(qq[q] + cc[i] - 2u * (uint32_t)acc[q][i]));
+        else if constexpr (METRIC == kCosineF32) code = cosine_code(acc[q][i], qnorm[q], norm[i]);
+        else code = JoinTraits<METRIC>::code(acc[q][i]);
+        if (__ballot(code <= bound) == 0ull) continue;
+        const int64_t c = tile0 + i * kWave + lane;
+        uint64_t key = ((uint64_t)code << 32) | (uint64_t)c;
+        if (c < c0 || c >= n || c == (int64_t)qid[q]) key = kKeyMax;
+        take_keys(best[q], key, &last_of[q], K, lane);
+      }
     }
   }
 
-  // the wavefronts' lists of a query, merged by the first wavefront that is numbered like it
+  // the wavefronts' lists of query q, merged by wavefront q
   __syncthreads();  // the tiles are no longer in use
-  uint64_t* const part_lists = reinterpret_cast<uint64_t*>(lds);  // [Q][kEWaves][64]
+  uint64_t* const lists = reinterpret_cast<uint64_t*>(lds);  // [Q][kEWaves][64]
 #pragma unroll
-  for (int q = 0; q < Q; ++q) part_lists[(q * kEWaves + wave) * kWave + lane] = best[q];
+  for (int q = 0; q < Q; ++q) lists[(q * kEWaves + wave) * kWave + lane] = best[q];
   __syncthreads();
   if (wave >= Q || q0 + wave >= nq) return;
-  bool have_query = false;
-#pragma unroll
-  for (int q = 0; q < Q; ++q)
-    if (wave == q) have_query = valid[q];
-  uint64_t all = part_lists[wave * kEWaves * kWave + lane];
+  uint64_t all = lists[wave * kEWaves * kWave + lane];
   for (int w = 1; w < kEWaves; ++w)
-    all = wave_merge_smallest(all, part_lists[(wave * kEWaves + w) * kWave + lane], lane);
+    all = wave_merge_smallest(all, lists[(wave * kEWaves + w) * kWave + lane], lane);
   if (lane < K) {
-    const bool have = have_query && all != kKeyMax;
+    const bool have = (int64_t)(uint32_t)queries[q0 + wave] < n && all != kKeyMax;
     const int64_t at = (q0 + wave) * K + lane;
     const uint32_t code = (uint32_t)(all >> 32);
     ids_out[at] = have ? (int32_t)(uint32_t)all : -1;
@@ -278,15 +310,18 @@ __global__ __launch_bounds__(kEBlock) void k_exact_knn(const void* vec, int64_t 
 template <int METRIC, int Q>
 hipError_t launch(const void* vec, int64_t n, int32_t d, const int32_t* queries, int64_t nq,
                   int32_t K, int32_t* ids_out, void* dist_out, hipStream_t st) {
-  constexpr size_t tiles = (size_t)kEWaves * (METRIC == kL2U8 ? (kWave + Q) * kStrideB
-                                                              : kWave * kStrideF) * 4;
+  constexpr size_t tiles = (size_t)kEWaves * (kTile + Q) * kChunk * 4;
   constexpr size_t lists = (size_t)Q * kEBlock * 8;
   constexpr size_t bytes = tiles > lists ? tiles : lists;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_exact_knn<METRIC, Q>),
+  // (offsets inside a tile are 32-bit there: 16 rows of at most 64 MiB)
+  const bool aligned = METRIC == kL2U8 ? (d & 15) == 0 && d <= (1 << 26)
+                                       : (d & 3) == 0 && d <= (1 << 24);
+  auto* const kernel = aligned ? k_exact_knn<METRIC, Q, true> : k_exact_knn<METRIC, Q, false>;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   if (e != hipSuccess) return e;
-  k_exact_knn<METRIC, Q><<<(unsigned)((nq + Q - 1) / Q), kEBlock, bytes, st>>>(
-      vec, n, d, queries, nq, K, ids_out, dist_out);
+  kernel<<<(unsigned)((nq + Q - 1) / Q), kEBlock, bytes, st>>>(vec, n, d, queries, nq, K, ids_out,
+                                                               dist_out);
   return hipGetLastError();
 }
 
