@@ -430,6 +430,52 @@ __device__ inline uint32_t wave_distances(const VecSrc& vs, uint32_t s, uint32_t
   else return TR::code(acc);
 }
 
+// The nodes with work to do, listed by class: list c at nodes + c n, its length in count[c]
+// (cleared by the sampling stage); the order inside a list is of no consequence.  A workgroup
+// of 256 takes 256 PER consecutive nodes, numbers those of each class in LDS - one addition
+// per wavefront and class that occurs in it - and reserves their places with one device-wide
+// addition per class.  class_of(s): the class of node s, or -1.
+template <int CLASSES, int PER, typename F>
+__device__ inline void list_nodes_by_class(int64_t n, int32_t* nodes, uint32_t* count,
+                                           F class_of) {
+  __shared__ uint32_t here[CLASSES], base[CLASSES];
+  const int64_t first = block_linear() * (256 * PER);
+  const int lane = lane_id();
+  if (threadIdx.x < CLASSES) here[threadIdx.x] = 0u;
+  int cls[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int64_t s = first + j * 256 + threadIdx.x;
+    cls[j] = s < n ? class_of(s) : -1;
+  }
+  __syncthreads();
+  uint32_t number[PER];  // within the workgroup
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    number[j] = 0u;
+    uint64_t left = __ballot(cls[j] >= 0);
+    while (left != 0ull) {
+      const int l = __ffsll((unsigned long long)left) - 1;
+      const int c = __builtin_amdgcn_readlane(cls[j], l);
+      const uint64_t same = __ballot(cls[j] == c);
+      uint32_t at = 0u;
+      if (lane == l) at = atomicAdd(&here[c], (uint32_t)__popcll(same));
+      at = __builtin_amdgcn_readlane(at, l);
+      if (cls[j] == c) number[j] = at + (uint32_t)__popcll(same & lanes_below(lane));
+      left &= ~same;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < CLASSES && here[threadIdx.x] != 0u)
+    base[threadIdx.x] = atomicAdd(&count[threadIdx.x], here[threadIdx.x]);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < PER; ++j)
+    if (cls[j] >= 0)
+      nodes[(int64_t)cls[j] * n + base[cls[j]] + number[j]] =
+          (int32_t)(first + j * 256 + threadIdx.x);
+}
+
 // Numbering inside one merge (Sec. 5.1 shards).  The two sets are the ranges
 // [base1, base1 + n1) and [base2, base2 + n2) of a larger collection; inside
 // the merge S1 is 0..n1-1, S2 is n1..n-1, and any other object (a list entry

@@ -40,7 +40,7 @@ thread_local std::string g_last_error = "";
 struct Layout {
   size_t off_G, off_kth, off_snew, off_sold, off_cnew, off_cold, off_ron,
       off_roo, off_csn, off_cso, off_capn, off_capo, off_pslot, off_poff, off_bins, off_scan,
-      off_cnt, off_snap, off_aside, off_shadow, off_norms, off_flag, off_bkc, off_bko, off_stg_ent,
+      off_cnt, off_snap, off_aside, off_shadow, off_norms, off_flag, off_bkc, off_stg_ent,
       off_stg_cur, off_cls_nodes, off_cls_count, total;
 };
 
@@ -145,7 +145,6 @@ Layout make_layout(const gnnd_params* q, bool with_aside) {
   L.off_norms = take(needs_norms(q) ? n * 4 : 0);  // squared norms
   L.off_flag = take(256);
   L.off_bkc = take(2 * 4096 * 4);
-  L.off_bko = take(2 * 4097 * 8);
   const bool staged = stage_possible(q);
   L.off_stg_ent = take(staged ? n * slots_per_node * 8 : 0);
   L.off_stg_cur = take(staged ? (size_t)kStageBuckets * 8 : 0);
@@ -183,7 +182,6 @@ struct gnnd_ctx {
   int prof_count;   // iterations recorded in the current window
   int prof_missed;  // iterations that found the window full (not recorded)
   std::vector<hipEvent_t> prof;  // kProfEvents events per iteration of the window
-  uint64_t* snap;  // device copy of the counters taken when the iteration began
   std::string err;
 };
 
@@ -219,11 +217,10 @@ void bind(gnnd_ctx* c, const Layout& L) {
   d.scan_tmp = (uint64_t*)(w + L.off_scan);
   d.counters = (uint64_t*)(w + L.off_cnt);
   d.aside = (uint64_t*)(w + L.off_aside);
-  c->snap = (uint64_t*)(w + L.off_snap);
+  d.snap = (uint64_t*)(w + L.off_snap);
   d.shadow = (int8_t*)(w + L.off_shadow);
   c->flag_dev = (int*)(w + L.off_flag);
   d.bk_cnt = (uint32_t*)(w + L.off_bkc);
-  d.bk_off = (uint64_t*)(w + L.off_bko);
   const bool staged = stage_possible(&c->prm);
   d.stg_ent = staged ? (uint64_t*)(w + L.off_stg_ent) : nullptr;
   d.stg_cur = staged ? (unsigned long long*)(w + L.off_stg_cur) : nullptr;
@@ -345,7 +342,7 @@ int read_stats(gnnd_ctx* c, gnnd_iter_stats* out) {
   uint64_t host[2 * N];
   hipError_t e = hipMemcpyAsync(host, c->ds.counters, N * 8, hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(host + N, c->snap, N * 8, hipMemcpyDeviceToHost, c->stream);
+    e = hipMemcpyAsync(host + N, c->ds.snap, N * 8, hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "reading counters");
   uint64_t tot[C_SLOTS] = {0};
@@ -366,10 +363,8 @@ int read_stats(gnnd_ctx* c, gnnd_iter_stats* out) {
 int step_sample(gnnd_ctx* c) {
   if (!c->has_graph) return fail(c, GNND_ESTATE, "no graph: call gnnd_init_random or gnnd_set_graph first");
   if (c->stage != 0) return fail(c, GNND_ESTATE, "stage order is sample, join, update");
-  // the counters only grow: keep their values from before this iteration
-  hipError_t e = launch_copy_u64(c->snap, c->ds.counters, (size_t)kStripes * C_SLOTS, c->stream);
-  if (e != hipSuccess) return hip_fail(c, e, "counter snapshot");
-  e = launch_sample(c->sh, c->ds, c->prm.seed, (uint32_t)(c->iter + 1), c->stream);
+  // (the counters only grow: the stage begins by keeping their values from before this iteration)
+  hipError_t e = launch_sample(c->sh, c->ds, c->prm.seed, (uint32_t)(c->iter + 1), c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "sampling kernels");
   c->stage = 1;
   return GNND_OK;

@@ -451,12 +451,6 @@ __global__ __launch_bounds__(kBlock) void k_zero_u32(uint32_t* p, size_t count) 
   if (i < count) p[i] = 0u;
 }
 
-__global__ __launch_bounds__(kBlock) void k_copy_u64(uint64_t* dst, const uint64_t* src,
-                                                     size_t count) {
-  const size_t i = (size_t)block_linear() * kBlock + threadIdx.x;
-  if (i < count) dst[i] = src[i];
-}
-
 // ---------------------------------------------------------------------------
 // GGM, Alg. 3 "Divide" + "Append": keep the first ceil(k/2) entries (OLD), set
 // the rest aside, refill with floor(k/2) random objects of the other set (NEW)
@@ -531,8 +525,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_final(int64_t n, MergeIds mi, 
 }
 
 // ---------------------------------------------------------------------------
-// Exclusive scan, three passes: per-block scan of 1024 elements, scan of the
-// block sums by one block, add-back.
+// Exclusive scan: per-block scan of 1024 elements, scan of the block sums, add-back.
 constexpr int kScanPerThread = 4;
 constexpr int kScanPerBlock = kBlock * kScanPerThread;
 
@@ -593,10 +586,21 @@ __global__ __launch_bounds__(kBlock) void k_scan_bsum(uint64_t* bsum, int64_t nb
   }
 }
 
+// SUM: bsum holds the block sums themselves, and every block adds up those before its own
+// (for up to kScanSumBlocks blocks cheaper than a launch of k_scan_bsum); otherwise their scan.
+constexpr int64_t kScanSumBlocks = 2048;
+template <bool SUM>
 __global__ __launch_bounds__(kBlock) void k_scan_add(uint64_t* out, uint64_t* packed,
                                                      const uint64_t* bsum, int64_t count) {
   const int64_t i0 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * kScanPerThread;
-  const uint64_t add = bsum[blockIdx.x];
+  uint64_t add;
+  if (SUM) {
+    uint64_t mine = 0;
+    for (unsigned b = threadIdx.x; b < blockIdx.x; b += kBlock) mine += bsum[b];
+    (void)block_exclusive_scan(mine, &add);
+  } else {
+    add = bsum[blockIdx.x];
+  }
 #pragma unroll
   for (int j = 0; j < kScanPerThread; ++j)
     if (i0 + j <= count) {
@@ -613,8 +617,12 @@ hipError_t launch_scan(const uint32_t* in, const uint32_t* in2, uint64_t* out, u
                        uint64_t* counters, uint64_t* tmp, int64_t count, hipStream_t st) {
   const int64_t nb = (count + 1 + kScanPerBlock - 1) / kScanPerBlock;
   k_scan_local<<<(unsigned)nb, kBlock, 0, st>>>(in, in2, out, tmp, counters, count);
-  k_scan_bsum<<<1, kBlock, 0, st>>>(tmp, nb);
-  k_scan_add<<<(unsigned)nb, kBlock, 0, st>>>(out, packed, tmp, count);
+  if (nb <= kScanSumBlocks) {
+    k_scan_add<true><<<(unsigned)nb, kBlock, 0, st>>>(out, packed, tmp, count);
+  } else {
+    k_scan_bsum<<<1, kBlock, 0, st>>>(tmp, nb);
+    k_scan_add<false><<<(unsigned)nb, kBlock, 0, st>>>(out, packed, tmp, count);
+  }
   return hipGetLastError();
 }
 
@@ -626,15 +634,6 @@ static VecSrc vec_src(const Shape& sh) {
 hipError_t launch_zero_u32(uint32_t* p, size_t count, hipStream_t st) {
   if (count == 0) return hipSuccess;
   k_zero_u32<<<grid_blocks((int64_t)((count + kBlock - 1) / kBlock)), kBlock, 0, st>>>(p, count);
-  return hipGetLastError();
-}
-
-// A small copy inside the stream of kernels (the runtime's own copy leaves the GPU idle for
-// some 10 microseconds around it).
-hipError_t launch_copy_u64(uint64_t* dst, const uint64_t* src, size_t count, hipStream_t st) {
-  if (count == 0) return hipSuccess;
-  k_copy_u64<<<grid_blocks((int64_t)((count + kBlock - 1) / kBlock)), kBlock, 0, st>>>(dst, src,
-                                                                                      count);
   return hipGetLastError();
 }
 

@@ -506,46 +506,17 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
   if (do_nn) tally.evals += (uint64_t)nn * (nn - 1) / 2;
 }
 
-// The nodes that have something to evaluate, listed by class (list c at nodes + c n, its
-// length in count[c]; the order inside a list is of no consequence).  A workgroup takes
-// kClassifyNodes consecutive nodes, numbers those of each class in LDS and reserves their
-// places with one addition per class.
-constexpr int kClassifyPerThread = 16;
-constexpr int kClassifyNodes = 256 * kClassifyPerThread;
+// The nodes that have something to evaluate, listed by class.
+template <int PER>
 __global__ __launch_bounds__(256) void k_gram_classify(int64_t n, int merge_mode,
                                                        const int32_t* __restrict__ cnew,
                                                        const int32_t* __restrict__ cold,
                                                        int32_t* nodes, uint32_t* count) {
-  __shared__ uint32_t here[kGramClasses], base[kGramClasses];
-  const int64_t first = block_linear() * kClassifyNodes;
-  if (threadIdx.x < kGramClasses) here[threadIdx.x] = 0u;
-  __syncthreads();
-  int32_t place[kClassifyPerThread];  // class + kGramClasses x (number within the workgroup)
-#pragma unroll
-  for (int j = 0; j < kClassifyPerThread; ++j) {
-    const int64_t s = first + j * 256 + threadIdx.x;
-    place[j] = -1;
-    if (s < n) {
-      const int nn = cnew[s], no = cold[s];
-      const bool do_nn = !merge_mode && nn > 1;
-      if (nn != 0 && (do_nn || no != 0)) {
-        const int cls = gram_class((nn + 15) >> 4, (no + 15) >> 4);
-        place[j] = cls + kGramClasses * (int32_t)atomicAdd(&here[cls], 1u);
-      }
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < kGramClasses && here[threadIdx.x] != 0u)
-    base[threadIdx.x] = atomicAdd(&count[threadIdx.x], here[threadIdx.x]);
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < kClassifyPerThread; ++j) {
-    if (place[j] >= 0) {
-      const int cls = place[j] % kGramClasses;
-      nodes[(int64_t)cls * n + base[cls] + place[j] / kGramClasses] =
-          (int32_t)(first + j * 256 + threadIdx.x);
-    }
-  }
+  list_nodes_by_class<kGramClasses, PER>(n, nodes, count, [&](int64_t s) {
+    const int nn = cnew[s], no = cold[s];
+    const bool do_nn = !merge_mode && nn > 1;
+    return nn != 0 && (do_nn || no != 0) ? gram_class((nn + 15) >> 4, (no + 15) >> 4) : -1;
+  });
 }
 
 // WHOLE: the dimension is a multiple of 16, every step reads 16 present dimensions.
@@ -621,26 +592,32 @@ hipError_t launch_join_gram(const Shape& sh, const DevState& ds, bool merge_mode
   VecSrc vs{sh.vec_a, sh.vec_b, sh.split, sh.d, sh.norms};
   const uint64_t slots = (uint64_t)sh.slots();
   const int mm = merge_mode ? 1 : 0;
-  // the nodes with work to do, by class
-  hipError_t e = launch_zero_u32(ds.cls_count, kGramClasses, st);
-  if (e != hipSuccess) return e;
-  k_gram_classify<<<grid_blocks((sh.n + kClassifyNodes - 1) / kClassifyNodes), 256, 0, st>>>(
-      sh.n, mm, ds.cnew, ds.cold, ds.cls_nodes, ds.cls_count);
+  // the nodes with work to do, by class (few nodes: fewer per workgroup, so that more of the
+  // chip lists them; many: fewer additions to the lists' lengths)
+  if (sh.n <= (1 << 20))
+    k_gram_classify<4><<<grid_blocks((sh.n + 1023) / 1024), 256, 0, st>>>(
+        sh.n, mm, ds.cnew, ds.cold, ds.cls_nodes, ds.cls_count);
+  else
+    k_gram_classify<16><<<grid_blocks((sh.n + 4095) / 4096), 256, 0, st>>>(
+        sh.n, mm, ds.cnew, ds.cold, ds.cls_nodes, ds.cls_count);
   // one build per class, each with about four sets of resident wavefronts (the lists' lengths
   // are known on the device only) and never more wavefronts than nodes
   const int64_t cap = (int64_t)64 * compute_units();
   const unsigned grid = (unsigned)(sh.n < cap ? sh.n : cap);
 #define GNND_GRAM_ARGS vs, sh.n, sh.p, mm, ds.snew, ds.sold, ds.cnew, ds.cold, ds.meta, ds.pslot, \
                        slots, ds.bins, ds.counters, ds.cls_nodes, ds.cls_count
-  // (in a merge no node without OLD samples has work to do)
-#define GNND_GRAM_CLASSES(M, W)                                                \
-  if (!merge_mode) k_join_gram<M, W, 0><<<grid, kWave, 0, st>>>(GNND_GRAM_ARGS); \
-  k_join_gram<M, W, 1><<<grid, kWave, 0, st>>>(GNND_GRAM_ARGS);                  \
-  k_join_gram<M, W, 2><<<grid, kWave, 0, st>>>(GNND_GRAM_ARGS);                  \
-  k_join_gram<M, W, 3><<<grid, kWave, 0, st>>>(GNND_GRAM_ARGS);                  \
-  k_join_gram<M, W, 4><<<grid, kWave, 0, st>>>(GNND_GRAM_ARGS);                  \
-  k_join_gram<M, W, 5><<<grid, kWave, 0, st>>>(GNND_GRAM_ARGS);                  \
-  k_join_gram<M, W, 6><<<grid, kWave, 0, st>>>(GNND_GRAM_ARGS);
+  // (in a merge no node without OLD samples has work to do; lists of up to 2p samples do not
+  // reach every class: a launch over an empty list still costs 3 to 4 microseconds)
+  bool reached[kGramClasses] = {false};
+  for (int rb = 1; rb <= (2 * sh.p + 15) / 16; ++rb)
+    for (int co = merge_mode ? 1 : 0; co <= (2 * sh.p + 15) / 16; ++co)
+      reached[gram_class(rb, co)] = true;
+#define GNND_GRAM_CLASS(M, W, C) \
+  if (reached[C]) k_join_gram<M, W, C><<<grid, kWave, 0, st>>>(GNND_GRAM_ARGS);
+#define GNND_GRAM_CLASSES(M, W)                                                            \
+  GNND_GRAM_CLASS(M, W, 0) GNND_GRAM_CLASS(M, W, 1) GNND_GRAM_CLASS(M, W, 2)               \
+  GNND_GRAM_CLASS(M, W, 3) GNND_GRAM_CLASS(M, W, 4) GNND_GRAM_CLASS(M, W, 5)               \
+  GNND_GRAM_CLASS(M, W, 6)
 #define GNND_GRAM_LAUNCH(M)                      \
   if (sh.d % kWC == 0) {                         \
     GNND_GRAM_CLASSES(M, true)                   \
@@ -655,6 +632,7 @@ hipError_t launch_join_gram(const Shape& sh, const DevState& ds, bool merge_mode
   }
 #undef GNND_GRAM_LAUNCH
 #undef GNND_GRAM_CLASSES
+#undef GNND_GRAM_CLASS
 #undef GNND_GRAM_ARGS
   return hipGetLastError();
 }

@@ -925,46 +925,16 @@ __global__ __launch_bounds__(kRcBlock) void k_result_csr(int64_t n, int tb,
   }
 }
 
-// The nodes that have something to evaluate, listed by shape (list c at nodes + c n, its
-// length in count[c]; the order inside a list is of no consequence).  A workgroup takes
-// kShapeNodes consecutive nodes, numbers those of each list in LDS and reserves their places
-// with one addition per list.
-constexpr int kShapePerThread = 16;
-constexpr int kShapeNodes = 256 * kShapePerThread;
+// The nodes that have something to evaluate, listed by shape.
 __global__ __launch_bounds__(256) void k_join_shapes(int64_t n, int merge_mode,
                                                      const int32_t* __restrict__ cnew,
                                                      const int32_t* __restrict__ cold,
                                                      int32_t* nodes, uint32_t* count) {
-  __shared__ uint32_t here[kJoinShapes], base[kJoinShapes];
-  const int64_t first = block_linear() * kShapeNodes;
-  if (threadIdx.x < kJoinShapes) here[threadIdx.x] = 0u;
-  __syncthreads();
-  int32_t place[kShapePerThread];  // list + kJoinShapes x (number within the workgroup)
-#pragma unroll
-  for (int j = 0; j < kShapePerThread; ++j) {
-    const int64_t s = first + j * 256 + threadIdx.x;
-    place[j] = -1;
-    if (s < n) {
-      const int nn = cnew[s], no = cold[s];
-      const bool do_nn = !merge_mode && nn > 1;
-      if (nn > 0 && (do_nn || no > 0)) {
-        const int c = join_list_of_shape(no <= 32 ? 1 : nn <= 32 ? 2 : 0);
-        place[j] = c + kJoinShapes * (int32_t)atomicAdd(&here[c], 1u);
-      }
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < kJoinShapes && here[threadIdx.x] != 0u)
-    base[threadIdx.x] = atomicAdd(&count[threadIdx.x], here[threadIdx.x]);
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < kShapePerThread; ++j) {
-    if (place[j] >= 0) {
-      const int c = place[j] % kJoinShapes;
-      nodes[(int64_t)c * n + base[c] + place[j] / kJoinShapes] =
-          (int32_t)(first + j * 256 + threadIdx.x);
-    }
-  }
+  list_nodes_by_class<kJoinShapes, 4>(n, nodes, count, [&](int64_t s) {
+    const int nn = cnew[s], no = cold[s];
+    const bool do_nn = !merge_mode && nn > 1;
+    return nn > 0 && (do_nn || no > 0) ? join_list_of_shape(no <= 32 ? 1 : nn <= 32 ? 2 : 0) : -1;
+  });
 }
 
 template <int KSTEPS, bool STAGED, bool LEAN = false, int SHAPE = 0>
@@ -1049,10 +1019,8 @@ hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode
   sa.nb = (int)((sh.n + ((int64_t)1 << sa.tb) - 1) >> sa.tb);
   // flush at half-full on average: few results find their bucket's places taken
   sa.threshold = (uint32_t)(sa.nb * (kStageSlots / 2));
-  e = launch_zero_u32(reinterpret_cast<uint32_t*>(ds.stg_cur), 2 * kStageBuckets, st);
-  if (e == hipSuccess) e = launch_zero_u32(ds.cls_count, kJoinShapes, st);
-  if (e != hipSuccess) return e;
-  k_join_shapes<<<grid_blocks((sh.n + kShapeNodes - 1) / kShapeNodes), 256, 0, st>>>(
+  // (the sampling stage has cleared the lists' lengths and the region cursors)
+  k_join_shapes<<<grid_blocks((sh.n + 1023) / 1024), 256, 0, st>>>(
       sh.n, merge_mode ? 1 : 0, ds.cnew, ds.cold, ds.cls_nodes, ds.cls_count);
   // persistent workgroups, one per CU (the staging area takes most of a CU's LDS); one launch
   // per shape, the common shapes first; all of them add to the same bucket regions
@@ -1066,10 +1034,10 @@ hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode
                                         ds, sa)                                                    \
            : launch_k<K, true, false, 1>(fcode, merge_mode, grid_slim, st, ds.shadow, ds.meta,     \
                                          dpad, sh, ds, sa);                                        \
-  if (e == hipSuccess)                                                                             \
+  if (e == hipSuccess && sh.p > 16) /* lists of up to 32 samples are all of the first shape */     \
     e = launch_k<K, true, false, 2>(fcode, merge_mode, grid_slim, st, ds.shadow, ds.meta, dpad,    \
                                     sh, ds, sa);                                                   \
-  if (e == hipSuccess)                                                                             \
+  if (e == hipSuccess && sh.p > 16)                                                                \
     e = launch_k<K, true, false, 0>(fcode, merge_mode, grid_full, st, ds.shadow, ds.meta, dpad,    \
                                     sh, ds, sa)
   switch (ksteps) {

@@ -50,10 +50,10 @@ struct DevState {
   uint64_t* bins;      // n*6p packed proposals, one segment per destination
   uint64_t* scan_tmp;  // block sums of the scans
   uint64_t* counters;  // kStripes * C_SLOTS
+  uint64_t* snap;      // the counters as the current iteration's sampling stage found them
   uint64_t* aside;     // merge only: n * floor(k/2) set-aside entries
   int8_t* shadow;      // matrix-core path: n rows of dpad int8 (value - 128), zero padded
   uint32_t* bk_cnt;    // 2 x 4096 bucket sizes of the bucketed reverse-candidate sort
-  uint64_t* bk_off;    // 2 x 4097 bucket offsets
   // staged hand-out of the matrix-core join (NULL when results are handed on one by one):
   // results leave the join grouped by bucket of destinations, then a second pass moves
   // them into the destinations' segments of `bins`
@@ -133,6 +133,8 @@ hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode
 hipError_t launch_pack_i8(const Shape& sh, const DevState& ds, int* bad_flag_dev, hipStream_t st);
 hipError_t launch_init_random_i8(const Shape& sh, const DevState& ds, uint64_t seed,
                                  hipStream_t st);
+// (also takes the snapshot of the counters and clears the joins' node list lengths and region
+// cursors: the first stage of an iteration)
 hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, hipStream_t st);
 // sample lists of 65..128 objects (p > 32): reverse selection and the join for long lists
 hipError_t launch_rev_select_long(const Shape& sh, const DevState& ds, uint64_t seed,
@@ -173,7 +175,6 @@ hipError_t launch_exact_knn(const void* vec, int64_t n, int32_t d, int32_t metri
                             const int32_t* queries, int64_t nq, int32_t K, int32_t* ids_out,
                             void* dist_out, hipStream_t st);
 hipError_t launch_zero_u32(uint32_t* p, size_t count, hipStream_t st);
-hipError_t launch_copy_u64(uint64_t* dst, const uint64_t* src, size_t count, hipStream_t st);
 
 // Exclusive scan of `count` uint32 into uint64 offsets out[0..count] (out[count] = total).
 // (in2 may be NULL; otherwise the scanned values are in[i] + in2[i])

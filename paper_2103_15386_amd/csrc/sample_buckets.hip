@@ -9,8 +9,9 @@
 //                      >> tb), kept as one column of a (bucket x workgroup)
 //                      matrix.
 //   2. k_wg_scan     - exclusive scan along the matrix rows: every workgroup's
-//                      run start inside every bucket, and the bucket sizes.
-//      k_bucket_scan - exclusive scan of the <= 4096 bucket sizes per kind.
+//                      run start inside every bucket, and the <= 4096 bucket sizes
+//                      per kind (the workgroups of 3. and 4. add those up for
+//                      themselves: a launch that did nothing else took 24 us).
 //   3. k_fwd_scatter_staged - every workgroup writes its (target, source)
 //                      edges into its runs, sorted by bucket in LDS first.
 //   4. k_bucket_csr  - one workgroup per bucket: LDS counters per target,
@@ -162,9 +163,20 @@ __global__ __launch_bounds__(kSB) void k_fwd_count(int64_t n, int k, int p, Buck
 // Exclusive scan along every row of the (bucket x workgroup) count matrix: the
 // entry of workgroup w becomes the start of w's run inside the bucket, the row
 // total the bucket's size.  One wavefront per row - no atomics, and the edge
-// order inside a bucket no longer depends on timing.
+// order inside a bucket no longer depends on timing.  One workgroup more than
+// the rows need keeps the counters' values from before this iteration and clears
+// what the cross-matching adds to.
 __global__ __launch_bounds__(kSB) void k_wg_scan(int W, int rows, uint32_t* wg_hist,
-                                                 uint32_t* bcnt) {
+                                                 uint32_t* bcnt, const uint64_t* counters,
+                                                 uint64_t* snap, uint32_t* cls_count,
+                                                 unsigned long long* stg_cur) {
+  if (blockIdx.x == gridDim.x - 1) {
+    for (int i = threadIdx.x; i < kStripes * C_SLOTS; i += kSB) snap[i] = counters[i];
+    if (cls_count && threadIdx.x < kNodeClassesMax) cls_count[threadIdx.x] = 0u;
+    if (stg_cur)
+      for (int i = threadIdx.x; i < kStageBuckets; i += kSB) stg_cur[i] = 0ull;
+    return;
+  }
   const int c = blockIdx.x * (kSB / kWave) + wave_id();
   if (c >= rows) return;
   const int lane = lane_id();
@@ -194,36 +206,27 @@ __global__ __launch_bounds__(kSB) void k_wg_scan(int W, int rows, uint32_t* wg_h
   if (lane == 0) bcnt[c] = carry;
 }
 
-// boff[kind][0..nb] = exclusive scan of the bucket sizes bcnt[kind][0..nb).
-__global__ __launch_bounds__(kCsrBlock) void k_bucket_scan(int nb, const uint32_t* bcnt,
-                                                           uint64_t* boff) {
-  __shared__ uint64_t part[kCsrBlock];
-  for (int kind = 0; kind < 2; ++kind) {
-    const uint32_t* c = bcnt + kind * nb;
-    uint64_t* o = boff + kind * (nb + 1);
-    const int per = (nb + kCsrBlock - 1) / kCsrBlock;
-    const int lo = threadIdx.x * per;
-    uint64_t sum = 0;
-    for (int i = lo; i < lo + per && i < nb; ++i) sum += c[i];
-    part[threadIdx.x] = sum;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      uint64_t run = 0;
-      for (int i = 0; i < kCsrBlock; ++i) {
-        uint64_t v = part[i];
-        part[i] = run;
-        run += v;
-      }
-      o[nb] = run;
-    }
-    __syncthreads();
-    uint64_t run = part[threadIdx.x];
-    for (int i = lo; i < lo + per && i < nb; ++i) {
-      o[i] = run;
-      run += c[i];
-    }
-    __syncthreads();
+// Sum of one value per thread over a workgroup of 1024 threads (`wsum`: 16 words of LDS),
+// and of those of the threads before this one.
+__device__ inline uint64_t block_sum_1024(uint64_t v, uint64_t* wsum, uint64_t* before) {
+  const int lane = lane_id(), wave = wave_id();
+  uint64_t inc = v;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const uint64_t o = __shfl_up(inc, off, kWave);
+    if (lane >= off) inc += o;
   }
+  __syncthreads();
+  if (lane == kWave - 1) wsum[wave] = inc;
+  __syncthreads();
+  uint64_t ahead = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < kCsrBlock / kWave; ++w) {
+    ahead += w < wave ? wsum[w] : 0ull;
+    total += wsum[w];
+  }
+  *before = ahead + inc - v;
+  return total;
 }
 
 // Scatter pass.  A workgroup of 1024 threads takes its rows in batches of 256,
@@ -241,7 +244,8 @@ constexpr int kStPasses = 8;                 // passes of kStBlock / PW rows mak
 template <int PW, bool PACKED>
 __global__ __launch_bounds__(kStBlock) void k_fwd_scatter_staged(
     int64_t n, int p, BucketGeom g, const int32_t* snew, const int32_t* sold,
-    const uint32_t* wg_hist, const uint64_t* boff, uint2* edges_new, uint2* edges_old) {
+    const uint32_t* wg_hist, const uint32_t* bcnt, uint2* edges_new, uint2* edges_old) {
+  __shared__ uint64_t scan_tmp[kStBlock / kWave];
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
   uint32_t* cursor = lds;               // 2 nb: where this workgroup writes next, per kind and bucket
   uint32_t* cnt = cursor + 2 * g.nb;    // nb: edges of the batch per bucket
@@ -249,9 +253,26 @@ __global__ __launch_bounds__(kStBlock) void k_fwd_scatter_staged(
   uint32_t* wsum = off + g.nb + 1;      // 16 wave totals of the scan
   uint2* stage = reinterpret_cast<uint2*>(lds + ((4 * g.nb + 17 + 3) & ~3));
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int i = tid; i < 2 * g.nb; i += kStBlock) {
-    const uint64_t bucket_start = i < g.nb ? boff[i] : boff[i + 1];
-    cursor[i] = (uint32_t)bucket_start + wg_hist[(size_t)i * gridDim.x + blockIdx.x];
+  // start of this workgroup's run in every bucket: the sizes of the buckets before it plus the
+  // run's start inside the bucket
+  for (int kind = 0; kind < 2; ++kind) {
+    uint32_t size[kMaxBuckets / kStBlock];
+    const int per_thread = (g.nb + kStBlock - 1) / kStBlock, b0 = tid * per_thread;
+    uint64_t sum = 0, at;
+#pragma unroll
+    for (int i = 0; i < kMaxBuckets / kStBlock; ++i) {
+      size[i] = i < per_thread && b0 + i < g.nb ? bcnt[kind * g.nb + b0 + i] : 0u;
+      sum += size[i];
+    }
+    block_sum_1024(sum, scan_tmp, &at);
+#pragma unroll
+    for (int i = 0; i < kMaxBuckets / kStBlock; ++i) {
+      if (i < per_thread && b0 + i < g.nb) {
+        const int c = kind * g.nb + b0 + i;
+        cursor[c] = (uint32_t)at + wg_hist[(size_t)c * gridDim.x + blockIdx.x];
+      }
+      at += size[i];
+    }
   }
   const int L = 2 * p;
   const int64_t row0 = (int64_t)blockIdx.x * g.rows_per_wg;
@@ -336,20 +357,23 @@ static size_t staged_lds_bytes(const BucketGeom& g) {
 // target.  LDS holds one counter per target of the bucket (dynamic size).
 template <bool PACKED>
 __global__ __launch_bounds__(kCsrBlock) void k_bucket_csr(int64_t n, BucketGeom g,
-                                                          const uint64_t* boff,
+                                                          const uint32_t* bcnt,
                                                           const uint2* edges_new,
                                                           const uint2* edges_old,
                                                           uint64_t* roff_new, uint64_t* roff_old,
                                                           int32_t* csr_new, int32_t* csr_old) {
   extern __shared__ uint32_t cnt[];  // 2^tb counters, then running offsets
   __shared__ uint32_t part[kCsrBlock];
+  __shared__ uint64_t scan_tmp[kCsrBlock / kWave];
   const int kind = blockIdx.y;
   const int b = blockIdx.x;
-  const uint64_t* bo = boff + kind * (g.nb + 1);
   const uint2* edges = kind ? edges_old : edges_new;
   uint64_t* roff = kind ? roff_old : roff_new;
   int32_t* csr = kind ? csr_old : csr_new;
-  const uint64_t beg = bo[b], end = bo[b + 1];
+  uint64_t before = 0, unused;  // the edges of the buckets before this one
+  for (int i = threadIdx.x; i < b; i += kCsrBlock) before += bcnt[kind * g.nb + i];
+  const uint64_t beg = block_sum_1024(before, scan_tmp, &unused);
+  const uint64_t end = beg + bcnt[kind * g.nb + b];
   const int T = 1 << g.tb;
   const uint32_t mask = (uint32_t)T - 1u;
   for (int i = threadIdx.x; i < T; i += kCsrBlock) cnt[i] = 0;
@@ -369,9 +393,10 @@ __global__ __launch_bounds__(kCsrBlock) void k_bucket_csr(int64_t n, BucketGeom 
       if (t[r] != 0xffffffffu) atomicAdd(&cnt[t[r]], 1u);
   }
   __syncthreads();
-  // exclusive scan over the T counters: T / 1024 consecutive counters per thread
-  const int per = T / kCsrBlock;  // T >= 4096
-  const int lo = threadIdx.x * per;
+  // exclusive scan over the T counters: T / 1024 consecutive counters per thread (fewer than
+  // 1024: one each)
+  const int lo = T > kCsrBlock ? (int)threadIdx.x * (T / kCsrBlock) : (int)threadIdx.x;
+  const int per = T > kCsrBlock ? T / kCsrBlock : (lo < T ? 1 : 0);
   uint32_t sum = 0;
   for (int i = 0; i < per; ++i) sum += cnt[lo + i];
   part[threadIdx.x] = sum;
@@ -401,7 +426,7 @@ __global__ __launch_bounds__(kCsrBlock) void k_bucket_csr(int64_t n, BucketGeom 
     if (first + lo + i < n) roff[first + lo + i] = beg + run;
     run += c;
   }
-  if (b == g.nb - 1 && threadIdx.x == 0) roff[n] = bo[g.nb];
+  if (b == g.nb - 1 && threadIdx.x == 0) roff[n] = end;
   __syncthreads();
   for (uint64_t e0 = beg + threadIdx.x; e0 < end; e0 += kAtOnce * kCsrBlock) {
     uint2 ed[kAtOnce];  // (target inside the bucket, source); target 0xffffffff: none
@@ -428,13 +453,23 @@ __global__ __launch_bounds__(kCsrBlock) void k_bucket_csr(int64_t n, BucketGeom 
   }
 }
 
-// The bucket layout for n <= 2^27 targets: at most 4096 buckets of 2^tb <= 2^15
-// targets (one workgroup's LDS counts a bucket's targets).
+// The bucket layout for n <= 2^27 targets: at most 4096 buckets of 2^tb <= 2^15 targets (one
+// workgroup's LDS counts a bucket's targets).  Small collections take smaller buckets and
+// fewer rows per workgroup, so that their passes still spread over the chip: buckets of 256
+// targets up to 2^18 nodes, of 1024 from 2^19 on, and up to 1024 workgroups of at least 32
+// rows (at 4096 nodes, 16 workgroups of 256 rows and 4 buckets: k_fwd_count 28 us, now 8).
 static BucketGeom bucket_geom(int64_t n) {
-  BucketGeom g{10, 0, 256};
-  while (((n + (1ll << g.tb) - 1) >> g.tb) > kMaxBuckets) ++g.tb;
-  g.nb = (int)((n + (1ll << g.tb) - 1) >> g.tb);
-  g.rows_per_wg = g.nb > 256 ? g.nb : 256;
+  BucketGeom g{8, 0, 32};
+  auto buckets = [&] { return (n + (1ll << g.tb) - 1) >> g.tb; };
+  while (g.tb < 10 && buckets() > 1024) ++g.tb;
+  while (buckets() > kMaxBuckets) ++g.tb;
+  g.nb = (int)buckets();
+  // the (bucket x workgroup) counts lie behind the edges in the proposal array, which leaves
+  // 8 words per node even for p = 1: two kinds x buckets x workgroups <= 8 n
+  while (g.rows_per_wg < 4096 &&
+         ((int64_t)g.rows_per_wg * 1024 < n ||
+          (n + g.rows_per_wg - 1) / g.rows_per_wg * g.nb > 4 * n))
+    g.rows_per_wg += 32;
   return g;
 }
 
@@ -451,7 +486,6 @@ hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, hipStream_
     attr_set = true;
   }
   uint32_t* bcnt = ds.bk_cnt;
-  uint64_t* boff = ds.bk_off;
   uint2* edges_new = reinterpret_cast<uint2*>(ds.bins);
   uint2* edges_old = edges_new + sh.n * sh.p;
   // per-workgroup bucket histograms, behind the edges in the same (still unused) array
@@ -463,9 +497,8 @@ hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, hipStream_
   else
     k_fwd_count<false><<<grid, kSB, 0, st>>>(sh.n, sh.k, sh.p, g, ds.G, ds.snew, ds.sold, ds.cnew,
                                              ds.cold, wg_hist);
-  k_wg_scan<<<(unsigned)((2 * g.nb + kSB / kWave - 1) / (kSB / kWave)), kSB, 0, st>>>(
-      (int)grid, 2 * g.nb, wg_hist, bcnt);
-  k_bucket_scan<<<1, kCsrBlock, 0, st>>>(g.nb, bcnt, boff);
+  k_wg_scan<<<(unsigned)((2 * g.nb + kSB / kWave - 1) / (kSB / kWave)) + 1, kSB, 0, st>>>(
+      (int)grid, 2 * g.nb, wg_hist, bcnt, ds.counters, ds.snap, ds.cls_count, ds.stg_cur);
   static bool staged_attr = false;
   if (!staged_attr) {
     hipError_t e = hipSuccess;
@@ -482,7 +515,7 @@ hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, hipStream_
   const bool packed = sh.n <= ((int64_t)1 << (32 - g.tb));
 #define GNND_SCATTER(PW, PK)                                                            \
   k_fwd_scatter_staged<PW, PK><<<grid, kStBlock, staged_lds_bytes(g), st>>>(            \
-      sh.n, sh.p, g, ds.snew, ds.sold, wg_hist, boff, edges_new, edges_old)
+      sh.n, sh.p, g, ds.snew, ds.sold, wg_hist, bcnt, edges_new, edges_old)
   if (sh.p <= 32) {
     if (packed) GNND_SCATTER(32, true);
     else GNND_SCATTER(32, false);
@@ -493,10 +526,10 @@ hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, hipStream_
 #undef GNND_SCATTER
   if (packed)
     k_bucket_csr<true><<<dim3((unsigned)g.nb, 2), kCsrBlock, (size_t)4 << g.tb, st>>>(
-        sh.n, g, boff, edges_new, edges_old, ds.roff_new, ds.roff_old, ds.csr_new, ds.csr_old);
+        sh.n, g, bcnt, edges_new, edges_old, ds.roff_new, ds.roff_old, ds.csr_new, ds.csr_old);
   else
     k_bucket_csr<false><<<dim3((unsigned)g.nb, 2), kCsrBlock, (size_t)4 << g.tb, st>>>(
-        sh.n, g, boff, edges_new, edges_old, ds.roff_new, ds.roff_old, ds.csr_new, ds.csr_old);
+        sh.n, g, bcnt, edges_new, edges_old, ds.roff_new, ds.roff_old, ds.csr_new, ds.csr_old);
   return hipGetLastError();
 }
 
