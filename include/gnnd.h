@@ -135,7 +135,11 @@ typedef struct gnnd_iter_stats {
 } gnnd_iter_stats;
 
 /* Device scratch needed for these parameters (pure host arithmetic; n, d, k, p,
- * metric are read).  Returns 0 when the parameters are invalid. */
+ * metric are read).  Returns 0 when the parameters are invalid.  Where the
+ * float32 matrix-core join applies and d >= 24 this includes room for a 16-bit
+ * copy of the vectors (2 bytes per dimension, padded to 32); a workspace that
+ * is smaller by that much is accepted as well and gives the same results,
+ * more slowly. */
 size_t gnnd_workspace_bytes(const gnnd_params* prm);
 
 /* Create a context over `vectors_dev`: n*d elements, row-major, float32 or

@@ -41,8 +41,11 @@ struct Layout {
   size_t off_G, off_kth, off_snew, off_sold, off_cnew, off_cold, off_ron,
       off_roo, off_csn, off_cso, off_capn, off_capo, off_pslot, off_poff, off_bins, off_scan,
       off_cnt, off_snap, off_aside, off_shadow, off_norms, off_flag, off_bkc, off_stg_ent,
-      off_stg_cur, off_cls_nodes, off_cls_count, total;
+      off_stg_cur, off_cls_nodes, off_cls_count, off_half, total;
+  bool half;  // has room for the 16-bit rows of the float32 matrix-core join
 };
+
+constexpr int kHalfMinDim = 24;
 
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -110,7 +113,13 @@ bool stage_possible(const gnnd_params* q) {
   return mfma_possible(q) && q->join_path != GNND_JOIN_MFMA_DIRECT && q->n <= kStageMaxNodes;
 }
 
-Layout make_layout(const gnnd_params* q, bool with_aside) {
+// 16-bit copies of the vectors for the first pass of the float32 matrix-core join: from 24
+// dimensions on (below, a row of them is no shorter than the float32 row).
+bool half_possible(const gnnd_params* q) { return gram_possible(q) && q->d >= kHalfMinDim; }
+
+// `half` = false: the layout without the 16-bit rows, for workspaces that have no room for them
+// (the join then reads the float32 rows twice; same results).
+Layout make_layout(const gnnd_params* q, bool with_aside, bool half = true) {
   Layout L;
   const size_t n = (size_t)q->n, k = (size_t)q->k, p = (size_t)q->p;
   size_t o = 0;
@@ -152,6 +161,8 @@ Layout make_layout(const gnnd_params* q, bool with_aside) {
   // (the float join lists its nodes in kGramClasses classes, the staged int8 join in three)
   L.off_cls_nodes = take(gram ? (size_t)kGramClasses * n * 4 : staged ? (size_t)3 * n * 4 : 0);
   L.off_cls_count = take(gram || staged ? 256 : 0);
+  L.half = half && half_possible(q);
+  L.off_half = take(L.half ? n * (size_t)half_row_elems(q->d) * 2 : 0);
   L.total = o;
   return L;
 }
@@ -227,6 +238,8 @@ void bind(gnnd_ctx* c, const Layout& L) {
   const bool gram = gram_possible(&c->prm);
   d.cls_nodes = gram || staged ? (int32_t*)(w + L.off_cls_nodes) : nullptr;
   d.cls_count = gram || staged ? (uint32_t*)(w + L.off_cls_count) : nullptr;
+  d.half_rows = L.half ? (void*)(w + L.off_half) : nullptr;
+  d.half_info = (uint32_t*)(w + L.off_flag) + 1;
 }
 
 // Fill in a default-constructed context (no allocation of any kind): layout,
@@ -258,13 +271,6 @@ int init_ctx(gnnd_ctx* c, const gnnd_params* prm, const Layout& L, const void* v
   if (e == hipSuccess)
     e = launch_zero_u32((uint32_t*)c->ds.counters, (size_t)kStripes * C_SLOTS * 2, c->stream);
   if (e != hipSuccess) return hip_fail(nullptr, e, "clearing workspace counters");
-  if (needs_norms(prm)) {  // the cosine distance divides by them, the float32 matrix-core
-                           // join turns inner products into distances with them
-    float* norms = reinterpret_cast<float*>(static_cast<char*>(prm->workspace_dev) + L.off_norms);
-    c->sh.norms = norms;
-    e = launch_row_norms(c->sh, norms, c->stream);
-    if (e != hipSuccess) return hip_fail(nullptr, e, "row norm kernel");
-  }
   // matrix-core path: build the int8 copy; float data qualifies only when every
   // value is an integer in 0..255 (then all distances are exact either way)
   c->use_mfma = false;
@@ -281,9 +287,20 @@ int init_ctx(gnnd_ctx* c, const gnnd_params* prm, const Layout& L, const void* v
     c->use_mfma = (bad == 0);
   }
   c->use_gram = gram_possible(prm) && !c->use_mfma;
-  if (c->use_gram) {
-    e = launch_gram_norms(c->sh, c->ds, c->stream);
-    if (e != hipSuccess) return hip_fail(nullptr, e, "row norm kernel");
+  // The cosine distance divides by the squared norms (summed in dimension order); the float32
+  // matrix-core join turns inner products into distances with them, and takes them from the
+  // pass that makes the 16-bit rows where that pass has summed its own.
+  const bool own_norms = c->use_gram && c->ds.half_rows && prm->metric != GNND_COSINE_F32;
+  if (prm->metric == GNND_COSINE_F32 || (c->use_gram && !own_norms)) {
+    float* norms = reinterpret_cast<float*>(static_cast<char*>(prm->workspace_dev) + L.off_norms);
+    c->sh.norms = norms;
+    e = launch_row_norms(c->sh, norms, c->stream);
+    if (e == hipSuccess && c->use_gram) e = launch_gram_norms(c->sh, c->ds, c->stream);
+    if (e != hipSuccess) return hip_fail(nullptr, e, "row norm kernels");
+  }
+  if (c->use_gram && c->ds.half_rows) {
+    e = launch_half_rows(c->sh, c->ds, c->stream);
+    if (e != hipSuccess) return hip_fail(nullptr, e, "16-bit row kernel");
   }
   if ((prm->join_path == GNND_JOIN_MFMA || prm->join_path == GNND_JOIN_MFMA_DIRECT) && !c->use_mfma)
     return fail(nullptr, GNND_EINVAL,
@@ -310,6 +327,7 @@ int create_impl(gnnd_ctx** out, const gnnd_params* prm, const void* vec_a, const
   if (const char* m = check_params(prm)) return fail(nullptr, GNND_EINVAL, m);
   if (const char* m = check_pointers(prm, vec_a, vec_b)) return fail(nullptr, GNND_EINVAL, m);
   Layout L = make_layout(prm, merge_mode);
+  if (prm->workspace_bytes < L.total) L = make_layout(prm, merge_mode, false);
   if (prm->workspace_bytes < L.total) {
     char buf[128];
     snprintf(buf, sizeof buf, "workspace too small: %zu bytes given, %zu needed",
@@ -490,7 +508,10 @@ struct ShardPlan {
       off_oids[2], off_odist[2], off_ws, ws_bytes, total;
 };
 
-const char* plan_shards(const gnnd_params* prm, int32_t shards, ShardPlan* pl) {
+// `arena`: the bytes at hand; an arena too small for workspaces with the 16-bit rows of the
+// float32 matrix-core join is planned without them.
+const char* plan_shards(const gnnd_params* prm, int32_t shards, ShardPlan* pl,
+                        size_t arena = SIZE_MAX) {
   if (!prm) return "params is NULL";
   if (prm->list_mode != GNND_LISTS_PLAIN) return "the shard driver works on plain lists (list_mode 0)";
   if (shards < 2 || shards > 1024) return "shards must be in [2, 1024]";
@@ -518,6 +539,7 @@ const char* plan_shards(const gnnd_params* prm, int32_t shards, ShardPlan* pl) {
     pl->off_odist[s] = take(2 * pl->graph_bytes);
   }
   pl->ws_bytes = make_layout(&q, true).total;
+  if (o + align_up(pl->ws_bytes) > arena) pl->ws_bytes = make_layout(&q, true, false).total;
   pl->off_ws = take(pl->ws_bytes);
   pl->total = o;
   return nullptr;
@@ -1108,7 +1130,8 @@ int gnnd_build_sharded(const gnnd_params* prm, const void* vectors_host, int32_t
                        int32_t build_iters, int32_t merge_iters, int32_t* ids_host,
                        void* dist_host, void* copy_stream, gnnd_shard_stats* stats) {
   ShardPlan pl;
-  if (const char* m = plan_shards(prm, shards, &pl)) return fail(nullptr, GNND_EINVAL, m);
+  if (const char* m = plan_shards(prm, shards, &pl, prm ? prm->workspace_bytes : 0))
+    return fail(nullptr, GNND_EINVAL, m);
   if (!vectors_host || !ids_host || !dist_host)
     return fail(nullptr, GNND_EINVAL, "NULL pointer argument");
   if (build_iters < 0 || merge_iters < 0) return fail(nullptr, GNND_EINVAL, "negative iteration count");
@@ -1129,7 +1152,8 @@ int gnnd_build_sharded_files(const gnnd_params* prm, const char* vectors_path, i
                              const char* dist_path, void* staging_host, size_t staging_bytes,
                              void* copy_stream, gnnd_shard_stats* stats) {
   ShardPlan pl;
-  if (const char* m = plan_shards(prm, shards, &pl)) return fail(nullptr, GNND_EINVAL, m);
+  if (const char* m = plan_shards(prm, shards, &pl, prm ? prm->workspace_bytes : 0))
+    return fail(nullptr, GNND_EINVAL, m);
   if (!vectors_path || !ids_path || !dist_path || !staging_host)
     return fail(nullptr, GNND_EINVAL, "NULL pointer argument");
   if (build_iters < 0 || merge_iters < 0) return fail(nullptr, GNND_EINVAL, "negative iteration count");
@@ -1171,7 +1195,8 @@ int gnnd_build_static(const gnnd_params* prm, const void* vectors_dev, int32_t m
   gnnd_params q = *prm;
   q.workspace_dev = nullptr;
   q.workspace_bytes = 0;
-  const Layout L = make_layout(&q, false);
+  Layout L = make_layout(&q, false);
+  if (L.total > kStaticScratchBytes) L = make_layout(&q, false, false);
   if (L.total > kStaticScratchBytes) {
     char buf[192];
     snprintf(buf, sizeof buf,

@@ -5,12 +5,15 @@
 //
 // One wavefront per node at a time, no barriers between wavefronts, four steps:
 //  1. The inner products of the block [NEW x (NEW | OLD)] of the node's <= 64 NEW
-//     and <= 64 OLD sample vectors are accumulated by v_mfma_f32_16x16x4_f32 in
-//     16 x 16 blocks, all of them in registers; only blocks that hold list
-//     entries are computed (lower block triangle of NEW x NEW).  The operands
-//     come straight from memory: four lanes read 64 consecutive bytes of a row,
-//     which is the matrix instruction's own operand layout, 16 dimensions per
-//     step, two steps (both halves of a 128-byte line) requested together.
+//     and <= 64 OLD sample vectors are accumulated on the matrix cores in 16 x 16
+//     blocks, all of them in registers; only blocks that hold list entries are
+//     computed (lower block triangle of NEW x NEW).  The operands come straight
+//     from memory: four lanes read 64 consecutive bytes of a row, which is the
+//     matrix instruction's own operand layout, two such steps (both halves of a
+//     128-byte line) requested together.  Two forms: HALF reads 16-bit copies of
+//     the vectors, each row divided by its norm (k_half_rows), 32 dimensions per
+//     v_mfma_f32_16x16x32_f16; the other reads the float32 vectors themselves,
+//     16 dimensions per four v_mfma_f32_16x16x4_f32.
 //  2. Inner product and squared norms give every pair an approximate distance
 //     whose difference from the canonical sum (one fused multiply-add per
 //     dimension, in dimension order) is bounded by eps(pair), see pair_bounds.
@@ -21,10 +24,20 @@
 //     beyond the threshold of the sample's list are dropped, for nothing at that
 //     distance is handed on.  One partner is left as a rule, seldom a few, often
 //     none.
-//  4. The vectors concerned are read once more, the same way, and pass through
-//     an LDS tile 16 dimensions at a time, where one lane per sample accumulates
-//     the canonical distances of the partners left; the smallest (distance, id)
-//     is the result.
+//  4. The pairs left are listed (a pair that serves both of its samples once) and
+//     dealt to the lanes; the vectors concerned are read once more, as float32,
+//     and pass through an LDS tile 16 dimensions at a time, where every lane
+//     accumulates the canonical distances of its pairs; the smallest
+//     (distance, id) of a sample is the result.
+//
+// Measured (builds of 12 iterations, k = p = 32, whole build): 150,000 x 960 squared L2 97.9 ->
+// 51.1 ms, 1.5 million x 96 angular 139.7 -> 116.7 ms, 100,000 x 75 cosine (p = 12, 8
+// iterations) 7.97 -> 5.66 ms, against float32 operands in step 1, bounds proportional to 6 d
+// and two partners per sample, direction and pass in step 4.  The tighter bounds and the pair
+// list were worth as much as the halved first reading: vector-ALU instructions per node fell
+// from 3600 to 2270 (62 rows of 96 dimensions).  What bounds it now: the gather (62 rows at
+// 192 + 384 bytes) and the returning atomics of the hand-out (92 million results in the first
+// iteration of the 1.5-million build at about 12 G/s, half of its 15.6 ms).
 // The nodes are listed by the number of blocks of 16 samples they fill
 // (k_gram_classify), and each class has its own build of the kernel, with the
 // registers and the LDS tile that its blocks need, run by persistent wavefronts
@@ -42,7 +55,7 @@ constexpr int kWC = 16;    // dimensions per step of the inner-product loop
 constexpr int kWLD = kWC + 4;  // row stride (floats) of the LDS tile of step 4: 16-byte aligned
                                // rows, and the 64 lanes of a 16-byte access spread evenly
                                // over the banks
-constexpr int kWCand = 2;  // canonical sums per lane and direction in one pass over the vectors
+constexpr int kWItems = 3;  // canonical sums per lane in one pass over the vectors
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -51,16 +64,30 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // "NEW sample towards OLD", 128..191 for "OLD sample towards NEW".
 struct GramLds {
   int32_t ids[128];
-  float norms[128];   // squared norms
+  // cosine: squared norms, for the canonical distance; otherwise with HALF: norm x 2^-kHalfBits
+  float norms[128];
   // what the approximate distance needs of a sample: its squared norm (cosine: one over its
-  // norm, 0 for a zero vector); NaN for the empty rows of a 16-row block, which makes every
+  // norm, 0 for a zero vector; HALF: 0); NaN for the empty rows of a 16-row block, which makes every
   // bound of their pairs NaN: never a minimum, never below a limit
   float weight[128];
   uint32_t kth[128];   // threshold of each sample's list
-  uint32_t upper[192];  // smallest upper bound of a partner's distance (order-preserving code)
-  float limit[192];     // what a partner's lower bound must not exceed
+  // smallest upper bound of a partner's distance (order-preserving code), and what a partner's
+  // lower bound must not exceed; step 4 keeps the smallest (distance, id) here instead
+  union {
+    struct {
+      uint32_t upper[192];
+      float limit[192];
+    };
+    unsigned long long best[192];
+  };
   unsigned long long cmask[192];  // the partners left (bit per partner)
 };
+// Step 4 keeps the pairs to be summed and the rows they need in place of the weights.
+struct PairList {
+  uint16_t pair[64 * kWItems];  // row a | row b << 7 | "also the nearest-object search of b" << 14
+  uint8_t wanted[128];
+};
+static_assert(sizeof(PairList) <= sizeof(GramLds::weight), "the pair list takes the weights' place");
 
 // The builds of the kernel: build c holds up to rbm blocks of 16 NEW and com blocks of 16 OLD
 // samples and is compiled for `waves` wavefronts per SIMD.  The shapes follow what a
@@ -92,13 +119,28 @@ __device__ constexpr int block_row(int q) {
   return q < RBM ? 16 * q : 64 + 16 * (q - RBM);
 }
 
+// The 16-bit copies (HALF): element i of row a is x_i / |a| x 2^kHalfBits, rounded to float16,
+// padded with zeros to whole steps of 32.  Elements below float16's normal range are made zero
+// (relative to the norm that is 2^-29), so that nothing depends on how the matrix unit treats
+// denormal operands.  `rho` bounds |a - copy of a| / |a| over all rows; rows whose norm is too
+// small to divide by are NaN in the copy, and all their pairs stay in the race.
+constexpr int kHalfBits = 15;
+struct HalfRows {
+  const _Float16* rows;
+  int32_t stride;           // elements per row, a multiple of 32
+  const float* rho;
+  const uint32_t* odd;      // number of rows that are NaN in the copy
+};
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
 // What a wavefront has counted over its nodes (the same in every lane).
 struct GramTally {
   uint64_t found = 0, passed = 0, overflow = 0, evals = 0;
 };
 
-template <int METRIC, bool WHOLE, int RBM, int COM>
-__device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc& vs, int64_t s,
+template <int METRIC, bool WHOLE, bool HALF, int RBM, int COM>
+__device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc& vs,
+                                          const HalfRows& hr, float rho, bool odd, int64_t s,
                                           int p, int merge_mode,
                                           const int32_t* __restrict__ snew,
                                           const int32_t* __restrict__ sold, int nn, int no,
@@ -145,7 +187,7 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
   // q.  An empty list place reads the node's first NEW sample instead: whatever stands in its
   // row or column of a block, the NaN weight of the place keeps it out of every result.
   const float* rows[NB];
-  {
+  if constexpr (!HALF) {
     const float* any_row = row_of(S.ids[0]) + g4;
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
@@ -183,7 +225,28 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
     }
   };
   float4 opa[NB], opb[NB];
-  fetch2(opa, opb, 0);
+  // HALF: the same with 32 dimensions of 16 bits per step
+  const _Float16* hrow[NB];
+  const int h_last = hr.stride - 32;
+  auto fetch_half2 = [&](int d0) {
+    const int d1 = d0 < h_last ? d0 + 32 : h_last;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      opa[q] = *reinterpret_cast<const float4*>(hrow[q] + d0);
+      opb[q] = *reinterpret_cast<const float4*>(hrow[q] + d1);
+    }
+  };
+  if constexpr (HALF) {
+    const _Float16* any_row = hr.rows + (int64_t)S.ids[0] * hr.stride + 2 * g4;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const int32_t id = S.ids[block_row<RBM>(q) + l16];
+      hrow[q] = id >= 0 ? hr.rows + (int64_t)id * hr.stride + 2 * g4 : any_row;
+    }
+    fetch_half2(0);
+  } else {
+    fetch2(opa, opb, 0);
+  }
 
   {
     // one 8-byte record per sample: the threshold of its list and its squared norm
@@ -194,11 +257,13 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
     const float nrmn = __uint_as_float(mn.y), nrmo = __uint_as_float(mo.y);
     auto weight_of = [&](int32_t id, float nrm) {
       float w = nrm;
-      if (METRIC == kCosineF32) w = nrm > 0.f ? 1.0f / sqrtf(nrm) : 0.f;
+      if (METRIC == kCosineF32)
+        w = HALF ? (nrm == nrm ? 0.f : kNaN) : nrm > 0.f ? 1.0f / sqrtf(nrm) : 0.f;
       return id >= 0 ? w : kNaN;
     };
-    S.norms[lane] = nrmn;
-    S.norms[64 + lane] = nrmo;
+    constexpr float kScale = 1.0f / (1 << kHalfBits);
+    S.norms[lane] = METRIC == kCosineF32 ? nrmn : HALF ? sqrtf(nrmn) * kScale : 0.f;
+    S.norms[64 + lane] = METRIC == kCosineF32 ? nrmo : HALF ? sqrtf(nrmo) * kScale : 0.f;
     S.kth[lane] = kthn;
     S.kth[64 + lane] = ktho;
     S.weight[lane] = weight_of(idn, nrmn);
@@ -232,6 +297,11 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
 #pragma unroll
   for (int t = 0; t < RBM * (RBM + 1) / 2; ++t) acc_nn[t] = f32x4{0.f, 0.f, 0.f, 0.f};
   auto mfma4 = [](f32x4& acc, const float4& a, const float4& b) {
+    if constexpr (HALF) {
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a),
+                                                   __builtin_bit_cast(f16x8, b), acc, 0, 0, 0);
+      return;
+    }
     acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b.z, acc, 0, 0, 0);
@@ -252,174 +322,310 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
     }
   };
   // steps 0, 2, 4, ... use opa, steps 1, 3, ... opb
+  constexpr int kStep = HALF ? 32 : kWC;
+  const int d_all = HALF ? hr.stride : d;
   for (int d0 = 0;;) {
     products(opa);
-    if (d0 + kWC < d) products(opb);
-    d0 += 2 * kWC;
-    if (d0 >= d) break;
-    fetch2(opa, opb, d0);
+    if (d0 + kStep < d_all) products(opb);
+    d0 += 2 * kStep;
+    if (d0 >= d_all) break;
+    if constexpr (HALF) fetch_half2(d0);
+    else fetch2(opa, opb, d0);
   }
 
   // ---- 2. + 3. partners that may be the nearest one --------------------------------------
-  // Bound eps of |approximate distance - canonical distance| (u = 2^-24, c0 = (6 d + 16) u):
-  // an inner product of d terms accumulated in float32 in any order and with any rounding of
-  // the partial sums is within 2 d u sum|a_i b_i| of the true one, the canonical sums within
-  // (d + 2) u of theirs, the norms within d u; sum|a_i b_i| <= sqrt(na nb) <= (na + nb) / 2.
-  // Squared L2, na + nb - 2 dot: the errors of na, nb, 2 dot and of the sum of differences
-  // add up to less than (5 d + 14) u (na + nb); c0 (na + nb) is used.  1 - dot: half of that
-  // plus the rounding of the subtraction (2^-22 covers both sides).  Cosine,
-  // 1 - dot / sqrt(na nb): the same relative to the denominator, plus the roundings of the
-  // reciprocal root and the products.
-  const float c0 = (float)(6 * d + 16) * 5.9604645e-8f;
+  // Bound eps of |approximate distance - canonical distance|, u = 2^-24, t = na + nb,
+  // P = |a| |b| <= t / 2, so that sum|a_i b_i| <= P:
+  //  - accumulating the inner product: a term passes through at most 32 + (steps) additions
+  //    (HALF; 4 + (instructions) otherwise), in whatever order the instruction adds its own
+  //    terms, each within 2 u of the partial sum of absolute values even if it truncates;
+  //    products of float16 numbers are exact in float32.  h P.
+  //  - HALF: the copies' inner product differs from that of a and b by at most
+  //    (2 rho + rho^2) P (|a - a'| <= rho |a|, Cauchy-Schwarz); the product with both norms
+  //    rounds four times.
+  //  - the canonical sums: (d + 2) u of squared L2 sums, d u P of inner products.
+  //  - the norms: HALF (d / 64 + 16) u of each, otherwise d u; the cosine divides by the very
+  //    same numbers on both sides.
+  // Squared L2, t - 2 dot: c1 t + c2 |value|.  1 - dot: half of c1 t and the rounding of the
+  // subtraction on both sides.  Cosine, 1 - dot / sqrt(na nb): the same relative to P.
+  constexpr float u = 5.9604645e-8f;
+  const float h = HALF ? (float)(2 * (32 + (hr.stride >> 5))) * u
+                       : (float)(2 * (4 + 4 * ((d + kWC - 1) / kWC))) * u;
+  const float dot_err = 1.01f * (h + (HALF ? (2.0f + rho) * rho : 0.f)) + 16.0f * u;
+  const float c1 = METRIC == kL2F32
+                       ? dot_err + (float)(HALF ? (d >> 6) + 24 : d + 8) * u
+                       : METRIC == kAngularF32 ? 0.5f * (dot_err + (float)(d + 8) * u)
+                                               : dot_err + (float)(d + 16) * u + 4.7683716e-7f;
+  const float c2 = METRIC == kL2F32 ? (float)(d + 4) * 1.02f * u : 0.f;
+  // Both bounds have the form base(row) + base(column) + dot factor(row) factor(column).  The
+  // c2 part of squared L2 is applied to the smallest upper bound and to the limit instead.
+  auto upper_base = [&](float w) {
+    if (METRIC == kL2F32) return __fmaf_rn(c1, w, w);
+    if (METRIC == kAngularF32) return __fmaf_rn(c1, w, 0.5f + 1.1920929e-7f);
+    return w * 0.f + (0.5f + 0.5f * c1);
+  };
+  auto lower_base = [&](float w) {
+    if (METRIC == kL2F32) return __fmaf_rn(-c1, w, w);
+    if (METRIC == kAngularF32) return __fmaf_rn(-c1, w, 0.5f - 1.1920929e-7f);
+    return w * 0.f + (0.5f - 0.5f * c1);
+  };
+  constexpr bool kFactors = METRIC == kCosineF32 ? !HALF : HALF;  // else the same for all pairs
+  const float* const factor = METRIC == kCosineF32 ? S.weight : S.norms;
+  constexpr float kOne = METRIC == kL2F32 ? -2.0f : -1.0f;
+  constexpr float kSame = HALF ? kOne / (1 << kHalfBits) / (1 << kHalfBits) : kOne;
+  auto bound = [&](float dot, float base, float fr, float fc, float unknown) {
+    float v = kFactors ? __fmaf_rn(dot, fr * fc, base) : __fmaf_rn(dot, kSame, base);
+    // A row that has no 16-bit copy: the pair stays in the race (`unknown`: the largest finite
+    // bounds).  Not where the sum of the norms is infinite under squared L2, nor with NaN
+    // anywhere: those have no distance to compare, here as in the other form.
+    if (HALF && odd && dot != dot)
+      v = (METRIC == kAngularF32 ? base == base : base * 0.f == 0.f) ? unknown : kNaN;
+    return v;
+  };
   const bool with_dups = !merge_mode && n_dup != 0;
+  auto four = [](const float* at) { return *reinterpret_cast<const float4*>(at); };
   // Pair (row R = arow + 4 g + r, column brow + l16) of a block: lane (l16, g) of the block's
-  // accumulator holds rows 4 g .. 4 g + 3 of column l16.
-  auto pair_bounds = [&](float dot, int arow, int brow, int r, float wc, int32_t idc, float& val,
-                         float& e) {
-    const int R = arow + g4 + r;
-    const float wr = S.weight[R];
-    if (METRIC == kCosineF32) {
-      val = 1.0f - dot * wr * wc;
-      e = c0 + 4.7683716e-7f;
-    } else {
-      const float t = wr + wc;
-      val = METRIC == kL2F32 ? t - 2.0f * dot : 1.0f - dot;
-      e = METRIC == kL2F32 ? c0 * t : c0 * t + 2.3841858e-7f;
-    }
-    if (brow == arow) {  // diagonal block of NEW x NEW: strict lower triangle, every pair once
-      if (l16 >= g4 + r) val = kNaN;
-    } else if (brow >= 64 && (with_dups || merge_mode)) {
-      const int32_t idr = S.ids[R];
-      if (merge_mode ? (((int64_t)idr < split) == ((int64_t)idc < split)) : idr == idc) val = kNaN;
-    }
+  // accumulator holds rows 4 g .. 4 g + 3 of column l16.  Whether the pair is one:
+  auto is_pair = [&](int arow, int brow, int r, int32_t idr, int32_t idc) {
+    if (brow == arow) return l16 < g4 + r;  // diagonal block of NEW x NEW: every pair once
+    if (brow >= 64 && (with_dups || merge_mode))
+      return merge_mode ? ((int64_t)idr < split) != ((int64_t)idc < split) : idr != idc;
+    return true;
   };
   // A pair of a NEW x OLD block serves the NEW sample's search among the OLD ones and the OLD
   // sample's among the NEW ones, a pair of a NEW x NEW block both of its samples.  First the
-  // smallest upper bound per sample and direction: along the rows through the 16 lanes of a
-  // lane row, along the columns inside the lane and over the four lane rows, then through LDS.
-  auto fold_upper = [&](const f32x4& acc, int arow, int brow) {
-    const bool nn_block = brow < 64;
-    const int col = brow + l16;
-    const float wc = S.weight[col];
-    const int32_t idc = S.ids[col];
-    float col_min = kInf;
+  // smallest upper bound per sample and direction: over a row's or a column's blocks inside
+  // the lane, then along a row through the 16 lanes of a lane row, along a column over the
+  // four lane rows, then through LDS.
+  auto code_of = [&](float bound_min) {
+    const float raised = METRIC == kL2F32 ? __fmaf_rn(c2, fabsf(bound_min), bound_min) : bound_min;
+    return bound_min < kInf ? ord_f32(raised) : kNone;
+  };
+  auto rows_min = [&](const float (&m)[4], int slot0) {
+    uint32_t v[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      float val, e;
-      pair_bounds(acc[r], arow, brow, r, wc, idc, val, e);
-      float row_min = fminf(val + e, kInf);
-      col_min = fminf(col_min, row_min);
-#pragma unroll
-      for (int j = 1; j < 16; j <<= 1)
-        row_min = fminf(row_min, __uint_as_float(xor_lanes(__float_as_uint(row_min), j, lane)));
-      if (l16 == 0 && row_min < kInf)
-        atomicMin(&S.upper[(nn_block ? 0 : 64) + arow + g4 + r], ord_f32(row_min));
+      v[r] = code_of(m[r]);
+      v[r] = vmin(v[r], (uint32_t)__builtin_amdgcn_mov_dpp((int)v[r], 0x128, 0xF, 0xF, true));  // row_ror:8
+      v[r] = vmin(v[r], (uint32_t)__builtin_amdgcn_mov_dpp((int)v[r], 0x124, 0xF, 0xF, true));  // row_ror:4
+      v[r] = vmin(v[r], (uint32_t)__builtin_amdgcn_mov_dpp((int)v[r], 0x122, 0xF, 0xF, true));  // row_ror:2
+      v[r] = vmin(v[r], (uint32_t)__builtin_amdgcn_mov_dpp((int)v[r], 0x121, 0xF, 0xF, true));  // row_ror:1
     }
-    col_min = fminf(col_min, __uint_as_float(xor_lanes(__float_as_uint(col_min), 16, lane)));
-    col_min = fminf(col_min, __uint_as_float(xor_lanes(__float_as_uint(col_min), 32, lane)));
-    if (g4 == 0 && col_min < kInf) atomicMin(&S.upper[nn_block ? col : 64 + col], ord_f32(col_min));
+    const uint32_t mine = l16 == 0 ? v[0] : l16 == 1 ? v[1] : l16 == 2 ? v[2] : v[3];
+    if (l16 < 4 && mine != kNone) atomicMin(&S.upper[slot0 + g4 + l16], mine);
   };
-  // Then every pair whose lower bound exceeds neither that nor the threshold of the sample's
-  // list is entered in the sample's set of partners.
-  auto fold_partners = [&](const f32x4& acc, int arow, int brow) {
-    const bool nn_block = brow < 64;
-    const int col = brow + l16;
-    const float wc = S.weight[col];
-    const int32_t idc = S.ids[col];
-    const int col_slot = nn_block ? col : 64 + col;
-    const float col_limit = S.limit[col_slot];
+  auto column_min = [&](float m, int slot) {
+    uint32_t v = code_of(m);
+    v = vmin(v, xor_lanes(v, 16, lane));
+    v = vmin(v, xor_lanes(v, 32, lane));
+    if (g4 == 0 && v != kNone) atomicMin(&S.upper[slot], v);
+  };
+  {
+    float col_nn[RBM], col_no[COM > 0 ? COM : 1];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      float val, e;
-      pair_bounds(acc[r], arow, brow, r, wc, idc, val, e);
-      const float lower = val - e;
-      const int R = arow + g4 + r;
-      const int row_slot = (nn_block ? 0 : 64) + R;
-      if (lower <= S.limit[row_slot]) atomicOr(&S.cmask[row_slot], 1ull << (col & 63));
-      if (lower <= col_limit) atomicOr(&S.cmask[col_slot], 1ull << R);
-    }
-  };
-  auto over_blocks = [&](auto fold) {
+    for (int cb = 0; cb < RBM; ++cb) col_nn[cb] = kInf;
+#pragma unroll
+    for (int cb = 0; cb < COM; ++cb) col_no[cb] = kInf;
 #pragma unroll
     for (int rb = 0; rb < RBM; ++rb) {
       if (rb < RB) {  // uniform
+        const int arow = 16 * rb;
+        float4 wr = four(&S.weight[arow + g4]), fr = wr;
+        if (kFactors) fr = four(&factor[arow + g4]);
+        const int4 idr = *reinterpret_cast<const int4*>(&S.ids[arow + g4]);
+        const float base_r[4] = {upper_base(wr.x), upper_base(wr.y), upper_base(wr.z),
+                                 upper_base(wr.w)};
+        const float fac_r[4] = {fr.x, fr.y, fr.z, fr.w};
+        const int32_t id_r[4] = {idr.x, idr.y, idr.z, idr.w};
+        auto fold = [&](const f32x4& acc, int brow, float (&row)[4], float& col_min) {
+          const int col = brow + l16;
+          const float base_c = upper_base(S.weight[col]);
+          const float fac_c = kFactors ? kOne * factor[col] : 0.f;
+          const int32_t idc = S.ids[col];
 #pragma unroll
-        for (int cb = 0; cb < COM; ++cb)
-          if (cb < CO) fold(acc_no[rb][cb], 16 * rb, 64 + 16 * cb);
+          for (int r = 0; r < 4; ++r) {
+            float v = bound(acc[r], base_r[r] + base_c, fac_r[r], fac_c, 3.4028235e38f);
+            v = is_pair(arow, brow, r, id_r[r], idc) ? v : kNaN;
+            row[r] = fminf(row[r], v);
+            col_min = fminf(col_min, v);
+          }
+        };
+        if (COM > 0 && CO > 0) {
+          float row[4] = {kInf, kInf, kInf, kInf};
+#pragma unroll
+          for (int cb = 0; cb < COM; ++cb)
+            if (cb < CO) fold(acc_no[rb][cb], 64 + 16 * cb, row, col_no[cb]);
+          rows_min(row, 64 + arow);
+        }
         if (do_nn) {
+          float row[4] = {kInf, kInf, kInf, kInf};
 #pragma unroll
-          for (int cb = 0; cb <= rb; ++cb) fold(acc_nn[rb * (rb + 1) / 2 + cb], 16 * rb, 16 * cb);
+          for (int cb = 0; cb <= rb; ++cb)
+            fold(acc_nn[rb * (rb + 1) / 2 + cb], 16 * cb, row, col_nn[cb]);
+          rows_min(row, arow);
         }
       }
     }
-  };
-  over_blocks(fold_upper);
-  __syncthreads();
+    if (do_nn) {
 #pragma unroll
-  for (int t = 0; t < 3; ++t)
-    S.limit[64 * t + lane] = unord_f32(vmin(S.upper[64 * t + lane], S.kth[t == 2 ? 64 + lane : lane]));
+      for (int cb = 0; cb < RBM; ++cb)
+        if (cb < RB) column_min(col_nn[cb], 16 * cb + l16);
+    }
+#pragma unroll
+    for (int cb = 0; cb < COM; ++cb)
+      if (cb < CO) column_min(col_no[cb], 128 + 16 * cb + l16);
+  }
   __syncthreads();
-  over_blocks(fold_partners);
-  __syncthreads();
-
-  // ---- 4. canonical distances of the partners left --------------------------------------
   // direction 0: NEW sample `lane` towards NEW, 1: NEW sample towards OLD, 2: OLD sample
   // towards NEW
-  uint64_t cand[3], best[3];
   bool found[3];
 #pragma unroll
   for (int t = 0; t < 3; ++t) {
-    const bool searching = (t == 2 ? ido : idn) >= 0 && (t != 0 || do_nn);
-    found[t] = searching && S.upper[64 * t + lane] != kNone;
-    cand[t] = searching ? S.cmask[64 * t + lane] : 0ull;
-    best[t] = kKeyMax;
+    const uint32_t up = S.upper[64 * t + lane];
+    found[t] = up != kNone;
+    const float lim = unord_f32(vmin(up, S.kth[t == 2 ? 64 + lane : lane]));
+    S.limit[64 * t + lane] = METRIC == kL2F32 ? __fmaf_rn(c2, fabsf(lim), lim) : lim;
   }
-  // The vectors concerned come the same way as in step 1 (two steps in flight, the others'
-  // places read the node's first NEW sample) and are laid out in LDS row by row, 16
-  // dimensions at a time; lane l then adds these 16 dimensions, in order, to the sums of its
-  // pairs.
-  while (__ballot((cand[0] | cand[1] | cand[2]) != 0ull) != 0ull) {
-    int crow[3][kWCand], c[3];
-    bool lanes_with[3][kWCand];  // some lane holds a partner number i in direction t
-    unsigned long long m0 = 0ull, m1 = 0ull;  // rows this lane reads: NEW rows, OLD rows
+  __syncthreads();
+  // Then every pair whose lower bound exceeds neither that nor the threshold of the sample's
+  // list is entered in the sample's set of partners.
 #pragma unroll
-    for (int t = 0; t < 3; ++t) {
-      c[t] = 0;
+  for (int rb = 0; rb < RBM; ++rb) {
+    if (rb < RB) {  // uniform
+      const int arow = 16 * rb;
+      float4 wr = four(&S.weight[arow + g4]), fr = wr;
+      if (kFactors) fr = four(&factor[arow + g4]);
+      const int4 idr = *reinterpret_cast<const int4*>(&S.ids[arow + g4]);
+      const float base_r[4] = {lower_base(wr.x), lower_base(wr.y), lower_base(wr.z),
+                               lower_base(wr.w)};
+      const float fac_r[4] = {fr.x, fr.y, fr.z, fr.w};
+      const int32_t id_r[4] = {idr.x, idr.y, idr.z, idr.w};
+      auto fold = [&](const f32x4& acc, int brow, const float4& row_limit) {
+        const bool nn_block = brow < 64;
+        const int col = brow + l16;
+        const float base_c = lower_base(S.weight[col]);
+        const float fac_c = kFactors ? kOne * factor[col] : 0.f;
+        const int32_t idc = S.ids[col];
+        const int col_slot = nn_block ? col : 64 + col;
+        const float col_limit = S.limit[col_slot];
+        const float lim[4] = {row_limit.x, row_limit.y, row_limit.z, row_limit.w};
 #pragma unroll
-      for (int i = 0; i < kWCand; ++i) {
-        crow[t][i] = 0;
-        if (cand[t] != 0ull) {
-          const int v = __ffsll((unsigned long long)cand[t]) - 1;
-          cand[t] &= cand[t] - 1;
-          crow[t][i] = t == 1 ? 64 + v : v;
-          (t == 1 ? m1 : m0) |= 1ull << v;
-          c[t] = i + 1;
+        for (int r = 0; r < 4; ++r) {
+          float v = bound(acc[r], base_r[r] + base_c, fac_r[r], fac_c, -3.4028235e38f);
+          v = is_pair(arow, brow, r, id_r[r], idc) ? v : kNaN;
+          const int R = arow + g4 + r;
+          if (v <= lim[r]) atomicOr(&S.cmask[(nn_block ? 0 : 64) + R], 1ull << (col & 63));
+          if (v <= col_limit) atomicOr(&S.cmask[col_slot], 1ull << R);
         }
-        lanes_with[t][i] = __ballot(c[t] > i) != 0ull;
-      }
-      if (c[t] > 0) (t == 2 ? m1 : m0) |= 1ull << lane;
-    }
-    // all lanes' rows: OR over the wavefront
+      };
+      if (COM > 0 && CO > 0) {
+        const float4 row_limit = four(&S.limit[64 + arow + g4]);
 #pragma unroll
-    for (int j = 1; j < 64; j <<= 1) {
-      m0 |= xor_lanes((uint64_t)m0, j, lane);
-      m1 |= xor_lanes((uint64_t)m1, j, lane);
+        for (int cb = 0; cb < COM; ++cb)
+          if (cb < CO) fold(acc_no[rb][cb], 64 + 16 * cb, row_limit);
+      }
+      if (do_nn) {
+        const float4 row_limit = four(&S.limit[arow + g4]);
+#pragma unroll
+        for (int cb = 0; cb <= rb; ++cb)
+          fold(acc_nn[rb * (rb + 1) / 2 + cb], 16 * cb, row_limit);
+      }
     }
+  }
+  __syncthreads();
+
+  // ---- 4. canonical distances of the partners left --------------------------------------
+  // The pairs of all samples and directions are listed, a pair that serves both of its samples
+  // once (by the one with the smaller number, or the NEW one), and dealt to the lanes,
+  // kWItems each in one pass over the vectors.
+  uint64_t todo[3] = {0ull, 0ull, S.cmask[128 + lane]};  // partners left to be listed, by direction
+  uint64_t mutual[2];
+  {
+    const uint64_t c_nn = S.cmask[lane], c_no = S.cmask[64 + lane];
+    mutual[0] = mutual[1] = 0ull;
+    for (uint64_t left = c_nn; __ballot(left != 0ull) != 0ull;) {
+      if (left != 0ull) {
+        const int v = __ffsll((unsigned long long)left) - 1;
+        left &= left - 1;
+        const bool both = ((S.cmask[v] >> lane) & 1ull) != 0ull;
+        if (both) mutual[0] |= 1ull << v;
+        if (!both || lane < v) todo[0] |= 1ull << v;
+      }
+    }
+    for (uint64_t left = c_no; __ballot(left != 0ull) != 0ull;) {
+      if (left != 0ull) {
+        const int v = __ffsll((unsigned long long)left) - 1;
+        left &= left - 1;
+        if (((S.cmask[128 + v] >> lane) & 1ull) != 0ull) mutual[1] |= 1ull << v;
+      }
+    }
+    todo[1] = c_no;
+    for (uint64_t left = todo[2]; __ballot(left != 0ull) != 0ull;) {
+      if (left != 0ull) {
+        const int v = __ffsll((unsigned long long)left) - 1;
+        left &= left - 1;
+        if (((S.cmask[64 + v] >> lane) & 1ull) != 0ull) todo[2] &= ~(1ull << v);
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 3; ++t) S.best[64 * t + lane] = kKeyMax;
+  PairList& list = *reinterpret_cast<PairList*>(S.weight);
+  for (;;) {
+    // places of this lane's pairs among all of them
+    const uint32_t count =
+        (uint32_t)(__popcll(todo[0]) + __popcll(todo[1]) + __popcll(todo[2]));
+    if (__ballot(count != 0u) == 0ull) break;
+    uint32_t inc = count;
+    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x111, 0xF, 0xF, false);  // row_shr:1
+    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x112, 0xF, 0xF, false);  // row_shr:2
+    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x114, 0xF, 0xF, false);  // row_shr:4
+    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x118, 0xF, 0xF, false);  // row_shr:8
+    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x142, 0xA, 0xF, false);  // row_bcast:15
+    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x143, 0xC, 0xF, false);  // row_bcast:31
+    const uint32_t all = __builtin_amdgcn_readlane(inc, 63);
+    const uint32_t here = all < 64u * kWItems ? all : 64u * kWItems;
+    __syncthreads();  // the weights, or the list before this one, are no longer needed
+    reinterpret_cast<uint16_t*>(list.wanted)[lane] = 0;
+    __syncthreads();
+    {
+      uint32_t at = inc - count;
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        while (todo[t] != 0ull && at < 64u * kWItems) {
+          const int v = __ffsll((unsigned long long)todo[t]) - 1;
+          todo[t] &= todo[t] - 1;
+          const int a = t == 2 ? 64 + lane : lane, b = t == 1 ? 64 + v : v;
+          const uint32_t both = t < 2 ? (uint32_t)((mutual[t < 2 ? t : 0] >> v) & 1ull) : 0u;
+          list.pair[at] = (uint16_t)(a | (b << 7) | (both << 14));
+          list.wanted[a] = list.wanted[b] = 1;
+          ++at;
+        }
+      }
+    }
+    __syncthreads();
+    // The vectors concerned come like the operands of the float32 form of step 1 (the others'
+    // places read the node's first NEW sample) and are laid out in LDS row by row, 16
+    // dimensions at a time; every lane then adds these 16 dimensions, in order, to the sums of
+    // its pairs.
     {
       const float* any_row = row_of(S.ids[0]) + g4;
 #pragma unroll
       for (int q = 0; q < NB; ++q) {
         const int row = block_row<RBM>(q) + l16;
-        const int32_t id = S.ids[row];
-        const bool wanted = (((row < 64 ? m0 : m1) >> (row & 63)) & 1ull) != 0;  // then id >= 0
-        rows[q] = wanted ? row_of(id) + g4 : any_row;
+        rows[q] = list.wanted[row] ? row_of(S.ids[row]) + g4 : any_row;  // (wanted: id >= 0)
       }
     }
-    float sum[3][kWCand];
+    uint32_t pair[kWItems];
+    const float *pa[kWItems], *pb[kWItems];
+    float sum[kWItems];
 #pragma unroll
-    for (int t = 0; t < 3; ++t)
-#pragma unroll
-      for (int i = 0; i < kWCand; ++i) sum[t][i] = 0.f;
+    for (int i = 0; i < kWItems; ++i) {
+      pair[i] = 64u * i + lane < here ? list.pair[64 * i + lane] : 0x8000u;  // bit 15: none
+      pa[i] = tile + tile_row((int)(pair[i] & 127u)) * kWLD;
+      pb[i] = tile + tile_row((int)((pair[i] >> 7) & 127u)) * kWLD;
+      sum[i] = 0.f;
+    }
     auto sums = [&](const float4* op, int d0) {
       __syncthreads();  // the tile has been read
 #pragma unroll
@@ -427,31 +633,23 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
         *reinterpret_cast<float4*>(tile + (16 * q + l16) * kWLD + g4) = op[q];
       __syncthreads();
       const int width = (d - d0) < kWC ? (d - d0) : kWC;
+      int j = 0;
+      for (; j + 3 < width; j += 4) {
 #pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        if (lanes_with[t][0]) {  // uniform
-          const float* pa = tile + tile_row(t == 2 ? 64 + lane : lane) * kWLD;
-          int j = 0;
-          for (; j + 3 < width; j += 4) {
-            const float4 va = *reinterpret_cast<const float4*>(pa + j);
-#pragma unroll
-            for (int i = 0; i < kWCand; ++i) {
-              if (lanes_with[t][i]) {
-                const float4 vb =
-                    *reinterpret_cast<const float4*>(tile + tile_row(crow[t][i]) * kWLD + j);
-                TR::step(va.x, vb.x, sum[t][i]);
-                TR::step(va.y, vb.y, sum[t][i]);
-                TR::step(va.z, vb.z, sum[t][i]);
-                TR::step(va.w, vb.w, sum[t][i]);
-              }
-            }
-          }
-          for (; j < width; ++j) {
-#pragma unroll
-            for (int i = 0; i < kWCand; ++i)
-              if (lanes_with[t][i]) TR::step(pa[j], tile[tile_row(crow[t][i]) * kWLD + j], sum[t][i]);
+        for (int i = 0; i < kWItems; ++i) {
+          if (64u * i < here) {  // uniform
+            const float4 va = four(pa[i] + j), vb = four(pb[i] + j);
+            TR::step(va.x, vb.x, sum[i]);
+            TR::step(va.y, vb.y, sum[i]);
+            TR::step(va.z, vb.z, sum[i]);
+            TR::step(va.w, vb.w, sum[i]);
           }
         }
+      }
+      for (; j < width; ++j) {
+#pragma unroll
+        for (int i = 0; i < kWItems; ++i)
+          if (64u * i < here) TR::step(pa[i][j], pb[i][j], sum[i]);
       }
     };
     fetch2(opa, opb, 0);
@@ -463,38 +661,59 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
       fetch2(opa, opb, d0);
     }
 #pragma unroll
-    for (int t = 0; t < 3; ++t) {
-#pragma unroll
-      for (int i = 0; i < kWCand; ++i) {
-        if (i < c[t]) {
-          const uint64_t code =
-              (uint64_t)TR::code(sum[t][i], S.norms[t == 2 ? 64 + lane : lane], S.norms[crow[t][i]]) << 32;
-          best[t] = vmin(best[t], code | (uint32_t)S.ids[crow[t][i]]);
-        }
+    for (int i = 0; i < kWItems; ++i) {
+      if (64u * i + lane < here) {
+        const int a = (int)(pair[i] & 127u), b = (int)((pair[i] >> 7) & 127u);
+        // (cosine: the norms; not used otherwise)
+        const uint64_t code = (uint64_t)TR::code(sum[i], S.norms[a], S.norms[b]) << 32;
+        // results for NEW towards NEW lie at 0..63, NEW towards OLD at 64.., OLD towards NEW
+        // at 128..
+        const int shift = (a | b) < 64 ? 0 : 64;
+        atomicMin(&S.best[a + shift], (unsigned long long)(code | (uint32_t)S.ids[b]));
+        if (pair[i] & 0x4000u)
+          atomicMin(&S.best[b + shift], (unsigned long long)(code | (uint32_t)S.ids[a]));
       }
     }
   }
+  __syncthreads();
+  uint64_t best[3];
+#pragma unroll
+  for (int t = 0; t < 3; ++t) best[t] = S.best[64 * t + lane];
 
   // ---- hand the results on --------------------------------------------------------------
   uint32_t n_found = 0, n_pass = 0, n_over = 0;
+  bool pass[3];
 #pragma unroll
   for (int t = 0; t < 3; ++t) {
-    const int32_t self = t == 2 ? ido : idn;
-    const uint32_t kth_self = S.kth[t == 2 ? 64 + lane : lane];
-    const bool pass = best[t] != kKeyMax && (uint32_t)(best[t] >> 32) <= kth_self;
-    bool over = false;
-    if (pass) {
-      // one returning add yields the start of the destination's segment of the proposal
-      // array and this result's place in it
-      const uint64_t w = atomicAdd(reinterpret_cast<unsigned long long*>(&pslot[self]), 1ull);
-      const uint64_t at = (w >> kSlotCountBits) + (w & kSlotCountMask);
-      if (at < slots) bins[at] = make_entry((uint32_t)(best[t] >> 32), (uint32_t)best[t], 3u);
-      else over = true;
-    }
+    pass[t] = best[t] != kKeyMax && (uint32_t)(best[t] >> 32) <= S.kth[t == 2 ? 64 + lane : lane];
     n_found += (uint32_t)__popcll(__ballot(found[t]));
-    n_pass += (uint32_t)__popcll(__ballot(pass));
-    n_over += (uint32_t)__popcll(__ballot(over));
+    n_pass += (uint32_t)__popcll(__ballot(pass[t]));
   }
+  // one returning add yields the start of the destination's segment of the proposal array and
+  // this result's place in it; the two results of a NEW sample share one
+  auto entry_of = [](uint64_t b) { return make_entry((uint32_t)(b >> 32), (uint32_t)b, 3u); };
+  auto reserve = [&](int32_t self, uint64_t results) {
+    const uint64_t w = atomicAdd(reinterpret_cast<unsigned long long*>(&pslot[self]),
+                                 (unsigned long long)results);
+    return (w >> kSlotCountBits) + (w & kSlotCountMask);
+  };
+  bool over = false;
+  if (pass[0] || pass[1]) {
+    const uint64_t both = pass[0] && pass[1] ? 1ull : 0ull;
+    const uint64_t at = reserve(idn, 1ull + both);
+    if (at + both < slots) {
+      bins[at] = entry_of(pass[0] ? best[0] : best[1]);
+      if (both) bins[at + 1] = entry_of(best[1]);
+    } else {
+      over = true;
+    }
+  }
+  if (pass[2]) {
+    const uint64_t at = reserve(ido, 1ull);
+    if (at < slots) bins[at] = entry_of(best[2]);
+    else over = true;
+  }
+  n_over = (uint32_t)__popcll(__ballot(over));
   tally.found += n_found;
   tally.passed += n_pass;
   tally.overflow += n_over;
@@ -524,10 +743,10 @@ __global__ __launch_bounds__(256) void k_gram_classify(int64_t n, int merge_mode
 // accumulators of all blocks and two sets of operands live in registers, and a build for
 // fewer blocks runs more wavefronts per SIMD and reads and multiplies fewer empty blocks.
 // Persistent wavefronts: wavefront w takes the list's places w, w + (number of wavefronts), ...
-template <int METRIC, bool WHOLE, int CLS>
+template <int METRIC, bool WHOLE, bool HALF, int CLS>
 __global__ __launch_bounds__(kWave)
 __attribute__((amdgpu_waves_per_eu(gram_shape(CLS).waves, gram_shape(CLS).waves))) void k_join_gram(
-    VecSrc vs, int64_t n, int p, int merge_mode, const int32_t* __restrict__ snew,
+    VecSrc vs, HalfRows hr, int64_t n, int p, int merge_mode, const int32_t* __restrict__ snew,
     const int32_t* __restrict__ sold, const int32_t* __restrict__ cnew,
     const int32_t* __restrict__ cold, const NodeMeta* __restrict__ meta, uint64_t* pslot,
     uint64_t slots, uint64_t* __restrict__ bins, uint64_t* counters,
@@ -541,10 +760,13 @@ __attribute__((amdgpu_waves_per_eu(gram_shape(CLS).waves, gram_shape(CLS).waves)
   const uint32_t mine = count[cls];
   const int32_t* const list = nodes + (int64_t)cls * n;
   GramTally tally;
+  const float rho = HALF ? *hr.rho : 0.f;
+  const bool odd = HALF && *hr.odd != 0u;
   for (uint32_t i = blockIdx.x; i < mine; i += gridDim.x) {
     const int64_t s = list[i];
-    gram_node<METRIC, WHOLE, RBM, COM>(S, tile, vs, s, p, merge_mode, snew, sold, cnew[s], cold[s],
-                                       meta, pslot, slots, bins, tally);
+    gram_node<METRIC, WHOLE, HALF, RBM, COM>(S, tile, vs, hr, rho, odd, s, p, merge_mode, snew,
+                                             sold, cnew[s], cold[s], meta, pslot, slots, bins,
+                                             tally);
     __syncthreads();  // the LDS arrays are taken over by the next node
   }
   if (threadIdx.x == 0) {
@@ -564,6 +786,73 @@ __global__ __launch_bounds__(256) void k_gram_norms(int64_t n, const float* __re
                                                     NodeMeta* meta) {
   const int64_t s = block_linear() * 256 + threadIdx.x;
   if (s < n) meta[s].norm = (int32_t)__float_as_uint(norms[s]);
+}
+
+// The 16-bit copies of the rows (see HalfRows): one wavefront per row.  A float16 quotient has
+// a relative error of at most 2^-11; what counts is the norm of all errors of a row together,
+// which is measured here (the largest over all rows goes to `rho`, as float bits).
+// OWN_NORMS: the metric does not need the norm that is summed in dimension order; the wavefront
+// adds up its own (64 partial sums, then a tree) and leaves it in the node's record.
+template <bool OWN_NORMS>
+__global__ __launch_bounds__(256) void k_half_rows(VecSrc vs, int64_t n, _Float16* out, int stride,
+                                                   NodeMeta* meta, uint32_t* rho, uint32_t* odd) {
+  __shared__ uint32_t largest, odd_here;
+  if (threadIdx.x == 0) largest = odd_here = 0u;
+  __syncthreads();
+  const int lane = lane_id();
+  constexpr int kRowsPerWave = 8;
+  const int64_t s0 = (block_linear() * 4 + wave_id()) * kRowsPerWave;
+  for (int i = 0; i < kRowsPerWave; ++i) {
+    const int64_t s = s0 + i;
+    if (s >= n) break;
+    const float* src = vs.row<float>((uint32_t)s);
+    float norm = 0.f;
+    if (OWN_NORMS) {
+      for (int j = lane; j < vs.d; j += kWave) norm = __fmaf_rn(src[j], src[j], norm);
+#pragma unroll
+      for (int o = 1; o < kWave; o <<= 1)
+        norm += __uint_as_float(xor_lanes(__float_as_uint(norm), o, lane));
+      if (lane == 0) meta[s].norm = (int32_t)__float_as_uint(norm);
+    } else {
+      norm = vs.norms[s];
+    }
+    const float root = sqrtf(norm);
+    const bool zero = norm == 0.f;
+    // no copy below 2^-90 (squares of elements come near the denormal range, and the product of
+    // two scaled norms as well), nor of infinite norms and NaN
+    const bool none = !zero && !(norm >= 8.0779357e-28f && norm < __uint_as_float(0x7f800000u));
+    const float scale = zero || none ? 0.f : (float)(1 << kHalfBits) / root;
+    const float back = root * (1.0f / (1 << kHalfBits));  // as the join multiplies it on again
+    _Float16* dst = out + s * stride;
+    float err = 0.f;
+    bool any = false;  // a norm of zero by underflow: elements that are not zero
+    for (int j = lane; j < stride; j += kWave) {
+      const float x = j < vs.d ? src[j] : 0.f;
+      _Float16 h = (_Float16)(x * scale);
+      if (fabsf((float)h) < 6.1035156e-5f) h = (_Float16)0.f;
+      if (zero) h = (_Float16)0.f;
+      const float diff = __fmaf_rn(-(float)h, back, x);
+      err = __fmaf_rn(diff, diff, err);
+      any |= x != 0.f;
+      if (none) h = (_Float16)__uint_as_float(0x7fc00000u);
+      dst[j] = h;
+    }
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) err += __uint_as_float(xor_lanes(__float_as_uint(err), o, lane));
+    const bool lost = norm == 0.f && __ballot(any) != 0ull;
+    if (lost)
+      for (int j = lane; j < stride; j += kWave) dst[j] = (_Float16)__uint_as_float(0x7fc00000u);
+    if (lane == 0) {
+      if (none || lost) atomicAdd(&odd_here, 1u);
+      // (0.2 % more than measured covers the roundings of the sums and of the norm)
+      else if (!zero) atomicMax(&largest, __float_as_uint(sqrtf(err / norm) * 1.002f));
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (largest) atomicMax(rho, largest);
+    if (odd_here) atomicAdd(odd, odd_here);
+  }
 }
 
 int compute_units() {
@@ -588,6 +877,17 @@ hipError_t launch_gram_norms(const Shape& sh, const DevState& ds, hipStream_t st
   return hipGetLastError();
 }
 
+hipError_t launch_half_rows(const Shape& sh, const DevState& ds, hipStream_t st) {
+  VecSrc vs{sh.vec_a, sh.vec_b, sh.split, sh.d, sh.norms};
+  hipError_t e = launch_zero_u32(ds.half_info, 2, st);
+  if (e != hipSuccess) return e;
+  auto* const kernel = sh.metric == kCosineF32 ? k_half_rows<false> : k_half_rows<true>;
+  kernel<<<grid_blocks((sh.n + 31) / 32), 256, 0, st>>>(
+      vs, sh.n, static_cast<_Float16*>(ds.half_rows), (int)half_row_elems(sh.d), ds.meta,
+      ds.half_info, ds.half_info + 1);
+  return hipGetLastError();
+}
+
 hipError_t launch_join_gram(const Shape& sh, const DevState& ds, bool merge_mode, hipStream_t st) {
   VecSrc vs{sh.vec_a, sh.vec_b, sh.split, sh.d, sh.norms};
   const uint64_t slots = (uint64_t)sh.slots();
@@ -604,7 +904,9 @@ hipError_t launch_join_gram(const Shape& sh, const DevState& ds, bool merge_mode
   // are known on the device only) and never more wavefronts than nodes
   const int64_t cap = (int64_t)64 * compute_units();
   const unsigned grid = (unsigned)(sh.n < cap ? sh.n : cap);
-#define GNND_GRAM_ARGS vs, sh.n, sh.p, mm, ds.snew, ds.sold, ds.cnew, ds.cold, ds.meta, ds.pslot, \
+  const HalfRows hr{static_cast<const _Float16*>(ds.half_rows), (int32_t)half_row_elems(sh.d),
+                    reinterpret_cast<const float*>(ds.half_info), ds.half_info + 1};
+#define GNND_GRAM_ARGS vs, hr, sh.n, sh.p, mm, ds.snew, ds.sold, ds.cnew, ds.cold, ds.meta, ds.pslot, \
                        slots, ds.bins, ds.counters, ds.cls_nodes, ds.cls_count
   // (in a merge no node without OLD samples has work to do; lists of up to 2p samples do not
   // reach every class: a launch over an empty list still costs 3 to 4 microseconds)
@@ -612,12 +914,18 @@ hipError_t launch_join_gram(const Shape& sh, const DevState& ds, bool merge_mode
   for (int rb = 1; rb <= (2 * sh.p + 15) / 16; ++rb)
     for (int co = merge_mode ? 1 : 0; co <= (2 * sh.p + 15) / 16; ++co)
       reached[gram_class(rb, co)] = true;
-#define GNND_GRAM_CLASS(M, W, C) \
-  if (reached[C]) k_join_gram<M, W, C><<<grid, kWave, 0, st>>>(GNND_GRAM_ARGS);
-#define GNND_GRAM_CLASSES(M, W)                                                            \
-  GNND_GRAM_CLASS(M, W, 0) GNND_GRAM_CLASS(M, W, 1) GNND_GRAM_CLASS(M, W, 2)               \
-  GNND_GRAM_CLASS(M, W, 3) GNND_GRAM_CLASS(M, W, 4) GNND_GRAM_CLASS(M, W, 5)               \
-  GNND_GRAM_CLASS(M, W, 6)
+#define GNND_GRAM_CLASS(M, W, H, C) \
+  if (reached[C]) k_join_gram<M, W, H, C><<<grid, kWave, 0, st>>>(GNND_GRAM_ARGS);
+#define GNND_GRAM_FORM(M, W, H)                                                            \
+  GNND_GRAM_CLASS(M, W, H, 0) GNND_GRAM_CLASS(M, W, H, 1) GNND_GRAM_CLASS(M, W, H, 2)      \
+  GNND_GRAM_CLASS(M, W, H, 3) GNND_GRAM_CLASS(M, W, H, 4) GNND_GRAM_CLASS(M, W, H, 5)      \
+  GNND_GRAM_CLASS(M, W, H, 6)
+#define GNND_GRAM_CLASSES(M, W)           \
+  if (ds.half_rows) {                     \
+    GNND_GRAM_FORM(M, W, true)            \
+  } else {                                \
+    GNND_GRAM_FORM(M, W, false)           \
+  }
 #define GNND_GRAM_LAUNCH(M)                      \
   if (sh.d % kWC == 0) {                         \
     GNND_GRAM_CLASSES(M, true)                   \
@@ -632,6 +940,7 @@ hipError_t launch_join_gram(const Shape& sh, const DevState& ds, bool merge_mode
   }
 #undef GNND_GRAM_LAUNCH
 #undef GNND_GRAM_CLASSES
+#undef GNND_GRAM_FORM
 #undef GNND_GRAM_CLASS
 #undef GNND_GRAM_ARGS
   return hipGetLastError();

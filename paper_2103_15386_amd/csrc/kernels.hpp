@@ -64,7 +64,14 @@ struct DevState {
   // which the float join uses kGramClasses and the int8 join three - and the lists' lengths
   int32_t* cls_nodes;
   uint32_t* cls_count;
+  // float32 matrix-core join: 16-bit copies of the rows divided by their norms (NULL: it reads
+  // the float32 rows twice instead), and what is known of them: the largest relative error
+  // (float bits), the number of rows without a copy
+  void* half_rows;
+  uint32_t* half_info;
 };
+// Elements per 16-bit row: whole steps of 32.
+inline int64_t half_row_elems(int32_t d) { return ((int64_t)d + 31) & ~(int64_t)31; }
 constexpr int kGramClasses = 7;
 constexpr int kNodeClassesMax = 7;
 
@@ -120,6 +127,9 @@ hipError_t launch_join(const Shape& sh, const DevState& ds, int path, bool merge
 // The float32 matrix-core join reads a sample's squared norm from its NodeMeta record (bits of
 // the float in `norm`): copied there from sh.norms once the join path is chosen.
 hipError_t launch_gram_norms(const Shape& sh, const DevState& ds, hipStream_t st);
+// The 16-bit copies of the rows into ds.half_rows, and (cosine: not; sh.norms must be set) the
+// squared norms in the NodeMeta records
+hipError_t launch_half_rows(const Shape& sh, const DevState& ds, hipStream_t st);
 // float32 vectors, metrics that are functions of an inner product and the norms (sh.norms
 // must be set): inner products on the matrix cores, canonical distances for the results
 hipError_t launch_join_gram(const Shape& sh, const DevState& ds, bool merge_mode, hipStream_t st);
