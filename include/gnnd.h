@@ -137,9 +137,10 @@ typedef struct gnnd_iter_stats {
 /* Device scratch needed for these parameters (pure host arithmetic; n, d, k, p,
  * metric are read).  Returns 0 when the parameters are invalid.  Where the
  * float32 matrix-core join applies and d >= 24 this includes room for a 16-bit
- * copy of the vectors (2 bytes per dimension, padded to 32); a workspace that
- * is smaller by that much is accepted as well and gives the same results,
- * more slowly. */
+ * copy of the vectors (2 bytes per dimension, padded to 32), and with p > 32 on
+ * uint8 or squared-L2 vectors of up to 128 dimensions for an int8 copy; a
+ * workspace that is smaller by that much is accepted as well and gives the same
+ * results, more slowly. */
 size_t gnnd_workspace_bytes(const gnnd_params* prm);
 
 /* Create a context over `vectors_dev`: n*d elements, row-major, float32 or
@@ -158,7 +159,9 @@ const char* gnnd_last_error(const gnnd_ctx* ctx);
  * L2, d <= 128, p <= 32, uint8 vectors or float32 vectors holding only integers
  * 0..255; other float32 vectors take GNND_JOIN_GRAM where it applies (squared
  * L2, angular, cosine; p <= 32; selective update); GNND_JOIN_VALU otherwise).
- * Negative on a NULL context. */
+ * Sample numbers beyond 32 report GNND_JOIN_VALU, also where GNND_JOIN_AUTO evaluates
+ * byte-valued data (d <= 128; float32 vectors in a context of gnnd_create's) on the int8
+ * matrix cores: the same integers.  Negative on a NULL context. */
 int gnnd_join_path(const gnnd_ctx* ctx);
 
 /* Stage timing without synchronising inside the loop.  gnnd_set_profiling(ctx,

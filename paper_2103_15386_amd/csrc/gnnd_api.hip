@@ -42,7 +42,8 @@ struct Layout {
       off_roo, off_csn, off_cso, off_capn, off_capo, off_pslot, off_poff, off_bins, off_scan,
       off_cnt, off_snap, off_aside, off_shadow, off_norms, off_flag, off_bkc, off_stg_ent,
       off_stg_cur, off_cls_nodes, off_cls_count, off_half, total;
-  bool half;  // has room for the 16-bit rows of the float32 matrix-core join
+  bool extra;  // has room for the 16-bit rows of the float32 matrix-core join, or the int8 rows
+               // of the long join
 };
 
 constexpr int kHalfMinDim = 24;
@@ -117,9 +118,17 @@ bool stage_possible(const gnnd_params* q) {
 // dimensions on (below, a row of them is no shorter than the float32 row).
 bool half_possible(const gnnd_params* q) { return gram_possible(q) && q->d >= kHalfMinDim; }
 
-// `half` = false: the layout without the 16-bit rows, for workspaces that have no room for them
-// (the join then reads the float32 rows twice; same results).
-Layout make_layout(const gnnd_params* q, bool with_aside, bool half = true) {
+// Sample lists beyond 64 on byte-valued data: the int8 matrix-core form of the long join, left
+// to itself only (GNND_JOIN_MFMA stays at p <= 32).
+bool long_i8_possible(const gnnd_params* q) {
+  return q->join_path == GNND_JOIN_AUTO && q->update_mode == GNND_UPDATE_SELECTIVE &&
+         q->d <= 128 && q->p > 32 && (q->metric == GNND_L2SQ_U8 || q->metric == GNND_L2SQ_F32);
+}
+
+// `extra` = false: the layout without the 16-bit rows (the join then reads the float32 rows
+// twice) and without the int8 rows of the long join, for workspaces that have no room for them.
+// Same results.
+Layout make_layout(const gnnd_params* q, bool with_aside, bool extra = true) {
   Layout L;
   const size_t n = (size_t)q->n, k = (size_t)q->k, p = (size_t)q->p;
   size_t o = 0;
@@ -149,7 +158,7 @@ Layout make_layout(const gnnd_params* q, bool with_aside, bool half = true) {
   L.off_cnt = take((size_t)kStripes * C_SLOTS * 8);
   L.off_snap = take((size_t)kStripes * C_SLOTS * 8);
   L.off_aside = take(with_aside ? n * (k / 2) * 8 : 0);
-  const bool shadow = mfma_possible(q);
+  const bool shadow = mfma_possible(q) || (extra && long_i8_possible(q));
   L.off_shadow = take(shadow ? n * (size_t)((q->d + 31) & ~31) : 0);
   L.off_norms = take(needs_norms(q) ? n * 4 : 0);  // squared norms
   L.off_flag = take(256);
@@ -161,8 +170,9 @@ Layout make_layout(const gnnd_params* q, bool with_aside, bool half = true) {
   // (the float join lists its nodes in kGramClasses classes, the staged int8 join in three)
   L.off_cls_nodes = take(gram ? (size_t)kGramClasses * n * 4 : staged ? (size_t)3 * n * 4 : 0);
   L.off_cls_count = take(gram || staged ? 256 : 0);
-  L.half = half && half_possible(q);
-  L.off_half = take(L.half ? n * (size_t)half_row_elems(q->d) * 2 : 0);
+  L.extra = extra;
+  const bool half = extra && half_possible(q);
+  L.off_half = take(half ? n * (size_t)half_row_elems(q->d) * 2 : 0);
   L.total = o;
   return L;
 }
@@ -184,6 +194,7 @@ struct gnnd_ctx {
   bool fresh_random;  // the graph is what gnnd_init_random left: no update has touched it yet
   bool merge_mode;
   bool use_mfma;
+  bool use_long_i8;   // sample lists beyond 64 on byte-valued data
   bool use_gram;
   int* flag_dev;
   hipEvent_t ev[5];
@@ -238,7 +249,7 @@ void bind(gnnd_ctx* c, const Layout& L) {
   const bool gram = gram_possible(&c->prm);
   d.cls_nodes = gram || staged ? (int32_t*)(w + L.off_cls_nodes) : nullptr;
   d.cls_count = gram || staged ? (uint32_t*)(w + L.off_cls_count) : nullptr;
-  d.half_rows = L.half ? (void*)(w + L.off_half) : nullptr;
+  d.half_rows = L.extra && half_possible(&c->prm) ? (void*)(w + L.off_half) : nullptr;
   d.half_info = (uint32_t*)(w + L.off_flag) + 1;
 }
 
@@ -247,8 +258,9 @@ void bind(gnnd_ctx* c, const Layout& L) {
 // a stream synchronisation: float32 data qualify for the matrix-core join only
 // after a device-side check whose verdict has to be read back; without it float
 // data take the general join (uint8 data always qualify, nothing is read back).
+// `own_context` = the caller's own gnnd_create.
 int init_ctx(gnnd_ctx* c, const gnnd_params* prm, const Layout& L, const void* vec_a,
-             const void* vec_b, int64_t split, bool merge_mode, bool may_sync) {
+             const void* vec_b, int64_t split, bool merge_mode, bool may_sync, bool own_context) {
   c->prm = *prm;
   c->stream = (hipStream_t)prm->stream;
   c->sh = Shape{prm->n, prm->d, prm->k, prm->p, prm->metric, split, vec_a, vec_b,
@@ -273,8 +285,12 @@ int init_ctx(gnnd_ctx* c, const gnnd_params* prm, const Layout& L, const void* v
   if (e != hipSuccess) return hip_fail(nullptr, e, "clearing workspace counters");
   // matrix-core path: build the int8 copy; float data qualifies only when every
   // value is an integer in 0..255 (then all distances are exact either way)
-  c->use_mfma = false;
-  if (mfma_possible(prm) && (may_sync || prm->metric == GNND_L2SQ_U8)) {
+  c->use_mfma = c->use_long_i8 = false;
+  // (the long join looks at float data only where it did not use to run before anything could
+  // wait for the verdict: in a context of the caller's own)
+  const bool long_i8 = L.extra && long_i8_possible(prm) &&
+                       (prm->metric == GNND_L2SQ_U8 || own_context);
+  if (long_i8 || (mfma_possible(prm) && (may_sync || prm->metric == GNND_L2SQ_U8))) {
     int bad = 0;
     e = launch_zero_u32((uint32_t*)c->flag_dev, 1, c->stream);
     if (e == hipSuccess) e = launch_pack_i8(c->sh, c->ds, c->flag_dev, c->stream);
@@ -284,7 +300,8 @@ int init_ctx(gnnd_ctx* c, const gnnd_params* prm, const Layout& L, const void* v
       if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     }
     if (e != hipSuccess) return hip_fail(nullptr, e, "packing vectors to int8");
-    c->use_mfma = (bad == 0);
+    c->use_long_i8 = long_i8 && bad == 0;
+    c->use_mfma = !long_i8 && bad == 0;
   }
   c->use_gram = gram_possible(prm) && !c->use_mfma;
   // The cosine distance divides by the squared norms (summed in dimension order); the float32
@@ -321,7 +338,7 @@ const char* check_pointers(const gnnd_params* prm, const void* vec_a, const void
 
 // Shared by gnnd_create and gnnd_merge.
 int create_impl(gnnd_ctx** out, const gnnd_params* prm, const void* vec_a, const void* vec_b,
-                int64_t split, bool merge_mode) {
+                int64_t split, bool merge_mode, bool own_context = false) {
   if (!out) return fail(nullptr, GNND_EINVAL, "out is NULL");
   *out = nullptr;
   if (const char* m = check_params(prm)) return fail(nullptr, GNND_EINVAL, m);
@@ -336,7 +353,7 @@ int create_impl(gnnd_ctx** out, const gnnd_params* prm, const void* vec_a, const
   }
   gnnd_ctx* c = new (std::nothrow) gnnd_ctx();
   if (!c) return fail(nullptr, GNND_EINVAL, "out of host memory");
-  const int rc = init_ctx(c, prm, L, vec_a, vec_b, split, merge_mode, true);
+  const int rc = init_ctx(c, prm, L, vec_a, vec_b, split, merge_mode, true, own_context);
   if (rc != GNND_OK) {
     delete c;
     return rc;
@@ -395,8 +412,9 @@ int step_join(gnnd_ctx* c, hipEvent_t after_join = nullptr) {
   if (c->use_mfma) {
     e = launch_join_mfma(c->sh, c->ds, c->merge_mode, c->fresh_random, c->stream, after_join);
   } else {
-    e = c->use_gram ? launch_join_gram(c->sh, c->ds, c->merge_mode, c->stream)
-                    : launch_join(c->sh, c->ds, c->prm.join_path, c->merge_mode, c->stream);
+    e = c->use_gram      ? launch_join_gram(c->sh, c->ds, c->merge_mode, c->stream)
+        : c->use_long_i8 ? launch_join_long_i8(c->sh, c->ds, c->merge_mode, c->stream)
+                         : launch_join(c->sh, c->ds, c->prm.join_path, c->merge_mode, c->stream);
     if (after_join) (void)hipEventRecord(after_join, c->stream);
   }
   if (e != hipSuccess) return hip_fail(c, e, "join kernel");
@@ -475,7 +493,7 @@ int merge_impl(const gnnd_params* prm, const void* vec1, int64_t n1, int64_t bas
   if (rc != GNND_OK) return rc;
   const MergeIds mi{n1, base1, n2, base2};
   hipError_t e =
-      c->use_mfma
+      c->use_mfma || c->use_long_i8
           ? launch_merge_init_i8(c->sh, c->ds, prm->seed, mi, ids1, dist1, ids2, dist2, c->stream)
           : launch_merge_init(c->sh, c->ds, prm->seed, mi, ids1, dist1, ids2, dist2, c->stream);
   if (e != hipSuccess) {
@@ -898,7 +916,7 @@ size_t gnnd_workspace_bytes(const gnnd_params* prm) {
 }
 
 int gnnd_create(gnnd_ctx** out, const gnnd_params* prm, const void* vectors_dev) {
-  return create_impl(out, prm, vectors_dev, nullptr, prm ? prm->n : 0, false);
+  return create_impl(out, prm, vectors_dev, nullptr, prm ? prm->n : 0, false, /*own_context=*/true);
 }
 
 void gnnd_destroy(gnnd_ctx* c) {
@@ -972,8 +990,9 @@ int gnnd_get_stage_ms(gnnd_ctx* c, int32_t* count, int32_t* missed, float* ms_sa
 int gnnd_init_random(gnnd_ctx* c) {
   if (!c) return fail(nullptr, GNND_EINVAL, "ctx is NULL");
   if (c->merge_mode) return fail(c, GNND_ESTATE, "context belongs to a merge");
-  hipError_t e = c->use_mfma ? launch_init_random_i8(c->sh, c->ds, c->prm.seed, c->stream)
-                             : launch_init_random(c->sh, c->ds, c->prm.seed, c->stream);
+  hipError_t e = c->use_mfma || c->use_long_i8
+                     ? launch_init_random_i8(c->sh, c->ds, c->prm.seed, c->stream)
+                     : launch_init_random(c->sh, c->ds, c->prm.seed, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "init kernel");
   c->has_graph = true;
   c->fresh_random = true;
@@ -1211,7 +1230,7 @@ int gnnd_build_static(const gnnd_params* prm, const void* vectors_dev, int32_t m
   q.workspace_bytes = kStaticScratchBytes;
   if (const char* m = check_pointers(&q, vectors_dev, nullptr)) return fail(nullptr, GNND_EINVAL, m);
   gnnd_ctx c;  // on the stack: nothing is allocated on the host either
-  int rc = init_ctx(&c, &q, L, vectors_dev, nullptr, q.n, false, /*may_sync=*/false);
+  int rc = init_ctx(&c, &q, L, vectors_dev, nullptr, q.n, false, /*may_sync=*/false, false);
   if (rc == GNND_OK) rc = gnnd_build(&c, max_iters, 0.f, nullptr);
   if (rc == GNND_OK) {
     hipError_t e = launch_get_graph(c.sh, c.ds, ids_out_dev, dist_out_dev, nullptr, 0, c.stream);

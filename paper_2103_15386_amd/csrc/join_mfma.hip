@@ -15,12 +15,10 @@
 #include <type_traits>
 
 #include "device_utils.hpp"
+#include "gram_i8.hpp"
 #include "kernels.hpp"
 
 namespace gnnd {
-
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int kMB = 256;  // 4 waves = 4 nodes in flight per workgroup
 constexpr int64_t kJoinGrid = 256 * 3 * 2;  // 256 CUs x 3 resident workgroups x 2
@@ -228,70 +226,8 @@ __global__ __launch_bounds__(256) void k_merge_init_i8(const int8_t* __restrict_
   if (lane == k - 1) meta[s].kth = entry_code(e);
 }
 
-// Best row per column of one 32x32 accumulator tile.  For row r the LDS array
-// holds negR = -((norm_r << 6) | position_r); then t = (G << 7) + negR is
-// -(((norm_r - 2 G) << 6) | position_r), so the maximum of t over the rows is
-// the row with the smallest (norm_r - 2 G), ties to the smallest position -
-// one shift-add and half a max3 per accumulator register.  Adding the column's
-// own norm to ((-t) >> 6) gives the squared distance; |.| stays below 2^31
-// because norms are below 2^22 (absent rows: 2^24 with G = 0).  Rows flagged
-// in `excl` are skipped.  Row of register r for this lane: 8*(r/4) + 4*half + r%4.
-constexpr int32_t kNone = (int32_t)0x80000000;
-
-template <bool MASKED>
-__device__ inline int32_t tile_col_best(const v16i& g, const int32_t* negr_lds, int half,
-                                        uint32_t excl) {
-  int32_t best = kNone;
-  const uint32_t ex = excl >> (4 * half);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int4 nr = *reinterpret_cast<const int4*>(negr_lds + 8 * q + 4 * half);
-    const int32_t negr[4] = {nr.x, nr.y, nr.z, nr.w};
-    int32_t t[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      t[i] = (int32_t)(((uint32_t)g[4 * q + i] << 7) + (uint32_t)negr[i]);
-      if (MASKED) t[i] = (ex & (1u << (8 * q + i))) ? kNone : t[i];
-    }
-    best = max(best, max(t[0], t[1]));
-    best = max(best, max(t[2], t[3]));
-  }
-  return best;
-}
-
-__device__ inline int32_t both_halves_max(int32_t x) {
-  auto sw = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
-  int32_t a = (int32_t)sw[0], b = (int32_t)sw[1];
-  return a > b ? a : b;
-}
-
 typedef uint64_t EntryPair __attribute__((ext_vector_type(2), aligned(8)));
 
-struct Operand {
-  v4i k[4];  // 4 steps of 32 dimensions, 16 bytes of this lane each
-};
-
-template <int KSTEPS>
-__device__ inline Operand load_block(const int8_t* shadow, int dpad, int32_t id, int half) {
-  Operand o;
-#pragma unroll
-  for (int s = 0; s < 4; ++s) o.k[s] = v4i{0, 0, 0, 0};
-  if (id >= 0) {
-    const int8_t* row = shadow + (int64_t)id * dpad + 16 * half;
-#pragma unroll
-    for (int s = 0; s < KSTEPS; ++s) o.k[s] = *reinterpret_cast<const v4i*>(row + 32 * s);
-  }
-  return o;
-}
-
-template <int KSTEPS>
-__device__ inline v16i gram(const Operand& rows, const Operand& cols) {
-  v16i acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-  for (int s = 0; s < KSTEPS; ++s)
-    acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(rows.k[s], cols.k[s], acc, 0, 0, 0);
-  return acc;
-}
 
 // FCODE: distances are reported as float32 codes (float input data) instead of
 // int32 codes.  MERGE: GGM mode - no NEW x NEW, only pairs from different sets.

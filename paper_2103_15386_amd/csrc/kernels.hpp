@@ -150,6 +150,9 @@ hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, hipStream_
 hipError_t launch_rev_select_long(const Shape& sh, const DevState& ds, uint64_t seed,
                                   uint32_t iter, hipStream_t st);
 hipError_t launch_join_long(const Shape& sh, const DevState& ds, bool merge_mode, hipStream_t st);
+// the same on byte-valued data of up to 128 dimensions (int8 rows in ds.shadow)
+hipError_t launch_join_long_i8(const Shape& sh, const DevState& ds, bool merge_mode,
+                               hipStream_t st);
 hipError_t launch_update(const Shape& sh, const DevState& ds, hipStream_t st);
 // lists of 65..128 entries (two per lane); the launchers above forward to these
 hipError_t launch_init_random_wide(const Shape& sh, const DevState& ds, uint64_t seed,
