@@ -6,13 +6,25 @@
 //
 // Layout: the node's <= 64 NEW and <= 64 OLD sample vectors are staged through
 // LDS in chunks of 64 dimensions (coalesced row reads from HBM); the 64 x 128
-// block of distances [NEW x (NEW | OLD)] is register-tiled 4 x 8 per thread
+// block of distances [NEW x (NEW | OLD)] is register-tiled 4 x 8 per thread (2 x 4 for lists of
+// up to 32 samples)
 // over a 16 x 16 thread grid with the rows/columns of a thread 16 apart, so
 // partially filled lists switch whole 16 x 16 sub-blocks off uniformly.  Only
 // the lower block triangle of NEW x NEW is evaluated.  Per sample the nearest
 // other NEW sample, the nearest OLD sample, and per OLD sample the nearest NEW
 // sample are reduced straight from the register tiles; three wavefronts, one
 // lane per sample, hand the results on.
+//
+// Chi-square: its terms are divided with correct rounding, some 20 issue slots per dimension and
+// pair.  All pairs are therefore summed with the reciprocal instruction first (8 slots); the
+// difference from the canonical sum is bounded relative to the sum, because no term is negative,
+// and the few pairs that can be a sample's nearest one within that bound (one per sample and
+// direction as a rule) are summed once more in the canonical arithmetic.  A node whose vectors
+// leave the range the bound is derived for, or with more such pairs than the list holds, is
+// evaluated in the canonical arithmetic throughout.  100,000 x 96, k = 20, p = 16,
+// 6 iterations: 21.7 -> 13.5 ms per build together with the smaller build for lists of up to 32
+// samples (at the registers and LDS of 64-sample lists the first pass alone gave 1 %: the
+// phases of three workgroups per CU did not overlap).  Bound: vector-ALU issue.
 #include "device_utils.hpp"
 #include "kernels.hpp"
 
@@ -62,10 +74,23 @@ __device__ inline void stage_row(ACC* dst, const uint8_t* src, int d, int d0, in
   *reinterpret_cast<int4*>(dst + part * 4) = v;
 }
 
+// Chi-square sums by the reciprocal instruction (at most 1 ulp off), which costs four issue
+// slots: one for two dimensions, x^2 / s + y^2 / t = (x^2 t + y^2 s) / (s t), 7 slots per
+// dimension.  Values are in [0, kChiMax], so nothing overflows, and staged with kChiTiny / 2
+// added, so that the sum of two zeros divides nothing by zero.
+constexpr float kChiMax = 1e9f, kChiTiny = 1e-15f;
+__device__ inline void chi2_two_approx(float a0, float a1, float b0, float b1, float& sum) {
+  const float x = a0 - b0, s = a0 + b0, y = a1 - b1, t = a1 + b1;
+  sum = __fmaf_rn(__fmaf_rn(y * y, s, (x * x) * t), __builtin_amdgcn_rcpf(s * t), sum);
+}
+constexpr int kChiPairs = 256;  // pairs of a node that are summed again: one per thread
+
 // ALL: every evaluated pair is proposed to both of its objects (the ablation
 // variant without the selective update of Sec. 4.3) instead of only the nearest
 // partner per sample.
-template <int METRIC, bool ALL>
+// RBM: sample lists of up to 16 RBM objects.  Lists of up to 32 (p <= 16) take half the
+// registers and LDS, so that twice as many wavefronts hide each other's phases.
+template <int METRIC, bool ALL, int RBM>
 __global__ __launch_bounds__(kJB) void k_join_valu(
     VecSrc vs, int64_t n, int p, int merge_mode, const int32_t* __restrict__ snew,
     const int32_t* __restrict__ sold, const int32_t* __restrict__ cnew,
@@ -74,14 +99,24 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
   using TR = JoinTraits<METRIC>;
   using T = typename TR::elem;
   using ACC = typename TR::acc;
-  __shared__ __attribute__((aligned(16))) ACC tile[128 * kLD];
+  constexpr int kRows = 16 * RBM;  // rows of the tile: NEW samples, then as many OLD ones
+  __shared__ __attribute__((aligned(16))) ACC tile[2 * kRows * kLD];
   __shared__ int32_t ids[128];
   // per sample the nearest partner: NEW towards NEW, NEW towards OLD, OLD towards NEW
   __shared__ uint64_t nearest[192];
   __shared__ uint32_t pair_count;
   __shared__ float norms_s[128];  // squared norms of the samples (cosine only)
+  constexpr bool kTwice = METRIC == kChi2F32 && !ALL;
+  // kTwice: smallest approximate distance per sample and direction (code), what a partner's
+  // lower bound must not exceed, the pairs to be summed again (row | column << 7 | for the row
+  // << 14 | for the column << 15) and their number (large: evaluate the node canonically)
+  __shared__ uint32_t min_s[kTwice ? 192 : 1];
+  __shared__ float limit_s[kTwice ? 192 : 1];
+  __shared__ uint32_t again_s[kTwice ? kChiPairs : 1];
+  __shared__ uint32_t again_count;
   constexpr bool kNorms = METRIC == kCosineF32;
-  static_assert(128 * kLD >= 64 * kDLD, "distance matrix must fit in the staging tile");
+  static_assert(!ALL || 2 * kRows * kLD >= 64 * kDLD,
+                "distance matrix must fit in the staging tile");
 
   const int64_t s = block_linear();
   if (s >= n) return;  // a folded grid may be longer than the node list
@@ -104,6 +139,10 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
   if (!ALL) {
     if (tid < 192) nearest[tid] = kKeyMax;
     if (tid == 0) pair_count = 0;
+    if (kTwice) {
+      if (tid < 192) min_s[tid] = 0xffffffffu;
+      if (tid == 0) again_count = 0;
+    }
   }
   const bool do_nn = !merge_mode && nn > 1;
   if (nn == 0 || (!do_nn && no == 0)) return;  // nothing to evaluate
@@ -115,118 +154,267 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
   const int d = vs.d;
   const bool aligned = (d & 3) == 0;
 
-  ACC acc[4][8];
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[r][c] = 0;
-
-  for (int d0 = 0; d0 < d; d0 += kDC) {
-    // stage: 16 threads per row, 16 rows per pass
+  ACC acc[RBM][2 * RBM];  // columns: NEW blocks, then OLD blocks
+  bool in_range = true;  // kTwice: all values this thread has staged are
+  // dimensions [d0, d0 + 64) of all vectors to LDS: 16 threads per row, 16 rows per pass
+  auto stage = [&](int d0, bool check) {
     const int part = tid & 15;
 #pragma unroll
-    for (int pass = 0; pass < 8; ++pass) {
+    for (int pass = 0; pass < 2 * RBM; ++pass) {
       const int row = pass * 16 + (tid >> 4);
-      const bool wanted = row < 64 ? (row < RB * 16) : (row - 64 < CO * 16);
+      const bool wanted = row < kRows ? (row < RB * 16) : (row - kRows < CO * 16);
       if (wanted) {
-        const int32_t id = ids[row];
+        const int32_t id = ids[row < kRows ? row : row - kRows + 64];
         const T* src = id >= 0 ? vs.row<T>((uint32_t)id) : nullptr;
         stage_row<ACC>(tile + row * kLD, src, d, d0, part, aligned);
+        if (kTwice && check) {
+          float4* const at = reinterpret_cast<float4*>(tile + row * kLD + part * 4);
+          float4 v = *at;
+          in_range &= v.x >= 0.f && v.x <= kChiMax && v.y >= 0.f && v.y <= kChiMax &&
+                      v.z >= 0.f && v.z <= kChiMax && v.w >= 0.f && v.w <= kChiMax;
+          v.x += 0.5f * kChiTiny;
+          v.y += 0.5f * kChiTiny;
+          v.z += 0.5f * kChiTiny;
+          v.w += 0.5f * kChiTiny;
+          *at = v;
+        }
       }
     }
     __syncthreads();
-    const int width = (d - d0) < kDC ? (d - d0) : kDC;
-    const int nsub = (width + 15) >> 4;
-    for (int sub = 0; sub < nsub; ++sub) {
-      ACC a[4][16];
+    return (d - d0) < kDC ? (d - d0) : kDC;
+  };
+  // the distances of all pairs of the tile, two dimensions per step
+  auto evaluate = [&](auto step, bool check) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if (r < RB) {
-          const ACC* src = tile + (ty + 16 * r) * kLD + sub * 16;
+    for (int r = 0; r < RBM; ++r)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int4 w = *reinterpret_cast<const int4*>(src + q * 4);
-            a[r][q * 4 + 0] = __builtin_bit_cast(ACC, w.x);
-            a[r][q * 4 + 1] = __builtin_bit_cast(ACC, w.y);
-            a[r][q * 4 + 2] = __builtin_bit_cast(ACC, w.z);
-            a[r][q * 4 + 3] = __builtin_bit_cast(ACC, w.w);
+      for (int c = 0; c < 2 * RBM; ++c) acc[r][c] = 0;
+    for (int d0 = 0; d0 < d; d0 += kDC) {
+      const int width = stage(d0, check);
+      const int nsub = (width + 15) >> 4;
+      for (int sub = 0; sub < nsub; ++sub) {
+        ACC a[RBM][16];
+#pragma unroll
+        for (int r = 0; r < RBM; ++r) {
+          if (r < RB) {
+            const ACC* src = tile + (ty + 16 * r) * kLD + sub * 16;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const int4 w = *reinterpret_cast<const int4*>(src + q * 4);
+              a[r][q * 4 + 0] = __builtin_bit_cast(ACC, w.x);
+              a[r][q * 4 + 1] = __builtin_bit_cast(ACC, w.y);
+              a[r][q * 4 + 2] = __builtin_bit_cast(ACC, w.z);
+              a[r][q * 4 + 3] = __builtin_bit_cast(ACC, w.w);
+            }
           }
         }
-      }
 #pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const bool col_on = c < 4 ? (do_nn && c < RB) : (c - 4 < CO);
-        if (col_on) {
-          const int crow = c < 4 ? (tx + 16 * c) : (64 + tx + 16 * (c - 4));
-          const ACC* src = tile + crow * kLD + sub * 16;
-          ACC b[16];
+        for (int c = 0; c < 2 * RBM; ++c) {
+          const bool col_on = c < RBM ? (do_nn && c < RB) : (c - RBM < CO);
+          if (col_on) {
+            const int crow = tx + 16 * c;
+            const ACC* src = tile + crow * kLD + sub * 16;
+            ACC b[16];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int4 w = *reinterpret_cast<const int4*>(src + q * 4);
-            b[q * 4 + 0] = __builtin_bit_cast(ACC, w.x);
-            b[q * 4 + 1] = __builtin_bit_cast(ACC, w.y);
-            b[q * 4 + 2] = __builtin_bit_cast(ACC, w.z);
-            b[q * 4 + 3] = __builtin_bit_cast(ACC, w.w);
-          }
+            for (int q = 0; q < 4; ++q) {
+              const int4 w = *reinterpret_cast<const int4*>(src + q * 4);
+              b[q * 4 + 0] = __builtin_bit_cast(ACC, w.x);
+              b[q * 4 + 1] = __builtin_bit_cast(ACC, w.y);
+              b[q * 4 + 2] = __builtin_bit_cast(ACC, w.z);
+              b[q * 4 + 3] = __builtin_bit_cast(ACC, w.w);
+            }
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            if (r < RB && (c >= 4 || c <= r)) {
+            for (int r = 0; r < RBM; ++r) {
+              if (r < RB && (c >= RBM || c <= r)) {
 #pragma unroll
-              for (int j = 0; j < 16; ++j) TR::step(a[r][j], b[j], acc[r][c]);
+                for (int j = 0; j < 16; j += 2) step(a[r][j], a[r][j + 1], b[j], b[j + 1], acc[r][c]);
+              }
             }
           }
         }
       }
+      __syncthreads();
+    }
+  };
+
+  const int64_t split = vs.split;
+  auto canonical = [](ACC a0, ACC a1, ACC b0, ACC b1, ACC& sum) {
+    TR::step(a0, b0, sum);
+    TR::step(a1, b1, sum);
+  };
+  uint32_t found = 0;      // kTwice: this sample has a partner
+  bool decided = false;    // kTwice: the pairs summed again have settled the node
+  if constexpr (kTwice) {
+    evaluate(chi2_two_approx, true);
+    if (!in_range) again_count = kChiPairs + 1;  // (any thread's word is enough)
+    // Both sums differ from the true one by at most (d + 12) u of it, u = 2^-24: a term takes
+    // five (canonical) to twelve roundings, all terms are non-negative.  The absolute part
+    // covers kChiTiny (values below 1e-8 are changed by it) and what is lost where squares of
+    // differences and their products underflow (differences or sums below 1e-15).
+    const float rel = (float)(2 * d + 48) * 5.9604645e-8f, abs_err = (float)d * 1e-14f;
+    // f(r, c, R, C): every pair of this thread's tile that is one (rows R: NEW; columns C: 0..63
+    // NEW, 64.. OLD)
+    auto over_pairs = [&](auto f) {
+#pragma unroll
+      for (int r = 0; r < RBM; ++r) {
+        if (r < RB) {
+          const int R = ty + 16 * r;
+          const int32_t idr = ids[R];
+#pragma unroll
+          for (int c = 0; c < 2 * RBM; ++c) {
+            if (!(c < RBM ? (do_nn && c <= r) : (c - RBM < CO))) continue;
+            const int C = c < RBM ? tx + 16 * c : 64 + tx + 16 * (c - RBM);
+            const int32_t idc = ids[C];
+            bool ok = idr >= 0 && idc >= 0;
+            if (c < RBM) {
+              ok = ok && (c < r || tx < ty);  // diagonal block: every pair once
+            } else {
+              ok = ok && idc != idr;
+              if (merge_mode) ok = ok && (((int64_t)idr < split) != ((int64_t)idc < split));
+            }
+            if (ok) f(r, c, R, C);
+          }
+        }
+      }
+    };
+    uint32_t row_nn[RBM], row_no[RBM], col[2 * RBM], pairs = 0;
+#pragma unroll
+    for (int r = 0; r < RBM; ++r) row_nn[r] = row_no[r] = 0xffffffffu;
+#pragma unroll
+    for (int c = 0; c < 2 * RBM; ++c) col[c] = 0xffffffffu;
+    over_pairs([&](int r, int c, int, int) {
+      const uint32_t code = ord_f32(acc[r][c]);
+      if (c < RBM) row_nn[r] = vmin(row_nn[r], code);
+      else row_no[r] = vmin(row_no[r], code);
+      col[c] = vmin(col[c], code);
+      pairs += c >= RBM ? 1u : 0u;
+    });
+#pragma unroll
+    for (int r = 0; r < RBM; ++r) {
+      if (r < RB) {
+#pragma unroll
+        for (int j = 1; j < 16; j <<= 1) {
+          row_nn[r] = vmin(row_nn[r], xor_lanes(row_nn[r], j, lane));
+          row_no[r] = vmin(row_no[r], xor_lanes(row_no[r], j, lane));
+        }
+        if (tx == 0) {
+          if (row_nn[r] != 0xffffffffu) atomicMin(&min_s[ty + 16 * r], row_nn[r]);
+          if (row_no[r] != 0xffffffffu) atomicMin(&min_s[64 + ty + 16 * r], row_no[r]);
+        }
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 2 * RBM; ++c) {
+      if (c < RBM ? (do_nn && c < RB) : (c - RBM < CO)) {
+        col[c] = vmin(col[c], xor_lanes(col[c], 16, lane));
+        col[c] = vmin(col[c], xor_lanes(col[c], 32, lane));
+        if (ty == (wave << 2) && col[c] != 0xffffffffu)
+          atomicMin(&min_s[c < RBM ? tx + 16 * c : 128 + tx + 16 * (c - RBM)], col[c]);
+      }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) pairs += __shfl_xor(pairs, off, kWave);
+    if (lane == 0 && pairs) atomicAdd(&pair_count, pairs);
+    __syncthreads();
+    if (wave < 3) {  // (thread 64 w + l answers for slot 64 w + l)
+      const uint32_t least = min_s[tid];
+      found = least != 0xffffffffu ? 1u : 0u;
+      // nothing beyond the threshold of the sample's list is handed on
+      uint32_t code = ord_f32(__fmaf_rn(rel, unord_f32(least), unord_f32(least)) + abs_err);
+      code = found ? vmin(code, kth_self) : 0u;
+      limit_s[tid] = found ? unord_f32(code) : -1.0f;
+    }
+    __syncthreads();
+    over_pairs([&](int r, int c, int R, int C) {
+      const float lower = __fmaf_rn(-rel, acc[r][c], acc[r][c]) - abs_err;
+      const bool for_row = lower <= limit_s[c < RBM ? R : 64 + R];
+      const bool for_col = lower <= limit_s[c < RBM ? C : 64 + C];
+      if (for_row || for_col) {
+        const uint32_t at = atomicAdd(&again_count, 1u);
+        if (at < (uint32_t)kChiPairs)
+          again_s[at] = (uint32_t)R | ((uint32_t)C << 7) | (for_row ? 1u << 14 : 0u) |
+                        (for_col ? 1u << 15 : 0u);
+      }
+    });
+    __syncthreads();
+    const uint32_t again = again_count;
+    decided = again <= (uint32_t)kChiPairs;
+    if (decided) {  // uniform
+      const uint32_t pair = (uint32_t)tid < again ? again_s[tid] : 0u;
+      const int R = (int)(pair & 127u), C = (int)((pair >> 7) & 127u);
+      const float *pa = tile + R * kLD, *pb = tile + (C < 64 ? C : C - 64 + kRows) * kLD;
+      float sum = 0.f;
+      for (int d0 = 0; d0 < d; d0 += kDC) {
+        const int width = stage(d0, false);
+        if (pair >> 14) {
+          int j = 0;
+          for (; j + 3 < width; j += 4) {
+            const float4 x = *reinterpret_cast<const float4*>(pa + j);
+            const float4 y = *reinterpret_cast<const float4*>(pb + j);
+            TR::step(x.x, y.x, sum);
+            TR::step(x.y, y.y, sum);
+            TR::step(x.z, y.z, sum);
+            TR::step(x.w, y.w, sum);
+          }
+          for (; j < width; ++j) TR::step(pa[j], pb[j], sum);
+        }
+        __syncthreads();
+      }
+      const unsigned long long code = (unsigned long long)TR::code(sum) << 32;
+      unsigned long long* const near = reinterpret_cast<unsigned long long*>(nearest);
+      if (pair & (1u << 14)) atomicMin(&near[C < 64 ? R : 64 + R], code | (uint32_t)ids[C]);
+      if (pair & (1u << 15)) atomicMin(&near[C < 64 ? C : 64 + C], code | (uint32_t)ids[R]);
+    } else if (tid == 0) {
+      pair_count = 0;  // (the canonical evaluation counts again)
     }
     __syncthreads();
   }
-
-  const int64_t split = vs.split;
+  if (!decided) evaluate(canonical, false);
   uint32_t* Dm = reinterpret_cast<uint32_t*>(tile);
   if constexpr (ALL) {
     // distances (as order-preserving codes) to LDS: Dm[row][col], col < 64 NEW, >= 64 OLD
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < RBM; ++r)
 #pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const bool on = r < RB && (c < 4 ? (do_nn && c <= r) : (c - 4 < CO));
+      for (int c = 0; c < 2 * RBM; ++c) {
+        const bool on = r < RB && (c < RBM ? (do_nn && c <= r) : (c - RBM < CO));
         if (on) {
-          const int col = c < 4 ? (tx + 16 * c) : (64 + tx + 16 * (c - 4));
+          const int col = c < RBM ? (tx + 16 * c) : (64 + tx + 16 * (c - RBM));
           Dm[(ty + 16 * r) * kDLD + col] =
               TR::code(acc[r][c], kNorms ? norms_s[ty + 16 * r] : 0.f, kNorms ? norms_s[col] : 0.f);
         }
       }
-  } else {
+  } else if (!decided) {
     // Nearest-object search straight from the register tiles.  A thread holds
     // rows R = ty + 16r and columns tx + 16c: the minimum along a row is
     // completed over the 16 lanes that share ty, the minimum along a column
     // over the lanes of the wavefront that share tx and then over the four
     // wavefronts through LDS.  Keys are (distance code, partner id), so equal
     // distances resolve to the smaller id whatever the order of reduction.
-    int32_t idc[8];
-    float normc[8];
+    int32_t idc[2 * RBM];
+    float normc[2 * RBM];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      idc[c] = ids[c < 4 ? (tx + 16 * c) : (64 + tx + 16 * (c - 4))];
-      normc[c] = kNorms ? norms_s[c < 4 ? (tx + 16 * c) : (64 + tx + 16 * (c - 4))] : 0.f;
+    for (int c = 0; c < 2 * RBM; ++c) {
+      idc[c] = ids[c < RBM ? (tx + 16 * c) : (64 + tx + 16 * (c - RBM))];
+      normc[c] = kNorms ? norms_s[c < RBM ? (tx + 16 * c) : (64 + tx + 16 * (c - RBM))] : 0.f;
     }
-    uint64_t down[8];  // per column: nearest row object seen by this thread
+    uint64_t down[2 * RBM];  // per column: nearest row object seen by this thread
 #pragma unroll
-    for (int c = 0; c < 8; ++c) down[c] = kKeyMax;
+    for (int c = 0; c < 2 * RBM; ++c) down[c] = kKeyMax;
     uint32_t pairs = 0;  // NEW x OLD pairs that count as evaluated
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int r = 0; r < RBM; ++r) {
       if (r < RB) {  // uniform over the workgroup
         const int R = ty + 16 * r;
         const int32_t idr = ids[R];
         uint64_t to_new = kKeyMax, to_old = kKeyMax;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          const bool on = c < 4 ? (do_nn && c <= r) : (c - 4 < CO);
+        for (int c = 0; c < 2 * RBM; ++c) {
+          const bool on = c < RBM ? (do_nn && c <= r) : (c - RBM < CO);
           if (!on) continue;
           const int32_t other = idc[c];
           bool ok = idr >= 0 && other >= 0;
-          if (c < 4) {
+          if (c < RBM) {
             ok = ok && (c < r || tx != ty);  // the diagonal block holds both orders of a pair
           } else {
             ok = ok && other != idr;
@@ -236,7 +424,7 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
           const uint64_t code = (uint64_t)TR::code(acc[r][c], kNorms ? norms_s[R] : 0.f,
                                                    kNorms ? normc[c] : 0.f) << 32;
           const uint64_t here = code | (uint32_t)other, there = code | (uint32_t)idr;
-          if (c < 4) {
+          if (c < RBM) {
             to_new = vmin(to_new, here);
             if (c < r) down[c] = vmin(down[c], there);
           } else {
@@ -258,15 +446,15 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
       }
     }
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const bool on = c < 4 ? (do_nn && c + 1 < RB) : (c - 4 < CO);
+    for (int c = 0; c < 2 * RBM; ++c) {
+      const bool on = c < RBM ? (do_nn && c + 1 < RB) : (c - RBM < CO);
       if (on) {  // uniform over the workgroup
         uint64_t v = down[c];
         v = vmin(v, xor_lanes(v, 16, lane));
         v = vmin(v, xor_lanes(v, 32, lane));
         if (ty == (wave << 2) && v != kKeyMax)
           atomicMin(reinterpret_cast<unsigned long long*>(
-                        &nearest[c < 4 ? (tx + 16 * c) : (128 + tx + 16 * (c - 4))]),
+                        &nearest[c < RBM ? (tx + 16 * c) : (128 + tx + 16 * (c - RBM))]),
                     (unsigned long long)v);
       }
     }
@@ -285,7 +473,7 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
   // hand a result to the destination's segment of the proposal array: one
   // returning add yields the segment start and this result's place in it
   auto hand_on = [&](uint64_t key) {
-    ++n_found;
+    if (!decided) ++n_found;
     if ((uint32_t)(key >> 32) > kth_self) return;  // dropped here already
     ++n_pass;
     const uint64_t w = atomicAdd(reinterpret_cast<unsigned long long*>(&pslot[self]), 1ull);
@@ -328,6 +516,7 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
     if (self >= 0) best = nearest[wave * 64 + lane];
     if (wave == 1 && lane == 0) evaluated = pair_count;
   }
+  if (decided && self >= 0) n_found = found;
   if (!ALL && best != kKeyMax) hand_on(best);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -352,7 +541,7 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
   }
 }
 
-template <bool ALL>
+template <bool ALL, int RBM>
 static void launch_join_as(const Shape& sh, const DevState& ds, bool merge_mode, hipStream_t st) {
   VecSrc vs{sh.vec_a, sh.vec_b, sh.split, sh.d, sh.norms};
   const dim3 grid = grid_blocks(sh.n);
@@ -361,11 +550,11 @@ static void launch_join_as(const Shape& sh, const DevState& ds, bool merge_mode,
 #define GNND_JOIN_ARGS vs, sh.n, sh.p, mm, ds.snew, ds.sold, ds.cnew, ds.cold, ds.meta, ds.pslot, \
                        slots, ds.bins, ds.counters
   switch (sh.metric) {
-    case kL2F32: k_join_valu<kL2F32, ALL><<<grid, kJB, 0, st>>>(GNND_JOIN_ARGS); break;
-    case kAngularF32: k_join_valu<kAngularF32, ALL><<<grid, kJB, 0, st>>>(GNND_JOIN_ARGS); break;
-    case kChi2F32: k_join_valu<kChi2F32, ALL><<<grid, kJB, 0, st>>>(GNND_JOIN_ARGS); break;
-    case kCosineF32: k_join_valu<kCosineF32, ALL><<<grid, kJB, 0, st>>>(GNND_JOIN_ARGS); break;
-    default: k_join_valu<kL2U8, ALL><<<grid, kJB, 0, st>>>(GNND_JOIN_ARGS);
+    case kL2F32: k_join_valu<kL2F32, ALL, RBM><<<grid, kJB, 0, st>>>(GNND_JOIN_ARGS); break;
+    case kAngularF32: k_join_valu<kAngularF32, ALL, RBM><<<grid, kJB, 0, st>>>(GNND_JOIN_ARGS); break;
+    case kChi2F32: k_join_valu<kChi2F32, ALL, RBM><<<grid, kJB, 0, st>>>(GNND_JOIN_ARGS); break;
+    case kCosineF32: k_join_valu<kCosineF32, ALL, RBM><<<grid, kJB, 0, st>>>(GNND_JOIN_ARGS); break;
+    default: k_join_valu<kL2U8, ALL, RBM><<<grid, kJB, 0, st>>>(GNND_JOIN_ARGS);
   }
 #undef GNND_JOIN_ARGS
 }
@@ -374,8 +563,9 @@ hipError_t launch_join(const Shape& sh, const DevState& ds, int path, bool merge
                        hipStream_t st) {
   (void)path;
   if (2 * sh.p > kWave) return launch_join_long(sh, ds, merge_mode, st);  // sample lists beyond 64
-  if (sh.all_pairs) launch_join_as<true>(sh, ds, merge_mode, st);
-  else launch_join_as<false>(sh, ds, merge_mode, st);
+  if (sh.all_pairs) launch_join_as<true, 4>(sh, ds, merge_mode, st);
+  else if (sh.p <= 16) launch_join_as<false, 2>(sh, ds, merge_mode, st);
+  else launch_join_as<false, 4>(sh, ds, merge_mode, st);
   return hipGetLastError();
 }
 
