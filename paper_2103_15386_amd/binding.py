@@ -414,8 +414,9 @@ def gnnd_build_sharded(vectors_host, shards, k, p, metric=L2SQ_F32, seed=42, bui
     arena = torch.empty(need, dtype=torch.uint8, device=dev)
     copy_stream = torch.cuda.Stream(device=dev)
     prm = make_params(n, d, k, p, metric, seed, join_path, _stream_ptr(dev), arena)
-    ids = torch.empty((n, k), dtype=torch.int32).pin_memory()
-    dist = torch.empty((n, k), dtype=dt).pin_memory()
+    # (allocated pinned: pin_memory() on a pageable tensor would copy it)
+    ids = torch.empty((n, k), dtype=torch.int32, pin_memory=True)
+    dist = torch.empty((n, k), dtype=dt, pin_memory=True)
     st = ShardStats()
     _check(lib.gnnd_build_sharded(C.byref(prm), vectors_host.data_ptr(), shards, build_iters,
                                   merge_iters, ids.data_ptr(), dist.data_ptr(),
@@ -441,7 +442,7 @@ def gnnd_build_sharded_files(vectors_path, n, d, shards, k, p, ids_path, dist_pa
                                           paths[1], paths[2], None, 0, None, None)
         raise GnndError(rc, _err())
     arena = torch.empty(need, dtype=torch.uint8, device=dev)
-    staging = torch.empty(int(staging_bytes), dtype=torch.uint8).pin_memory()
+    staging = torch.empty(int(staging_bytes), dtype=torch.uint8, pin_memory=True)
     copy_stream = torch.cuda.Stream(device=dev)
     prm = make_params(n, d, k, p, metric, seed, join_path, _stream_ptr(dev), arena)
     st = ShardStats()
