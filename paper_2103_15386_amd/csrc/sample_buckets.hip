@@ -456,8 +456,11 @@ __global__ __launch_bounds__(kCsrBlock) void k_bucket_csr(int64_t n, BucketGeom 
 // The bucket layout for n <= 2^27 targets: at most 4096 buckets of 2^tb <= 2^15 targets (one
 // workgroup's LDS counts a bucket's targets).  Small collections take smaller buckets and
 // fewer rows per workgroup, so that their passes still spread over the chip: buckets of 256
-// targets up to 2^18 nodes, of 1024 from 2^19 on, and up to 1024 workgroups of at least 32
-// rows (at 4096 nodes, 16 workgroups of 256 rows and 4 buckets: k_fwd_count 28 us, now 8).
+// targets up to 2^18 nodes, of 1024 from 2^19 on, and 512 workgroups (one round of the scatter
+// pass, two workgroups per CU) of at least 32 rows up to 2^19 nodes, 1024 beyond.  Sampling
+// stage in microseconds, this layout / buckets of 1024 and workgroups of at least 256 rows:
+// 4096 nodes 42 / 69, 30,000 nodes 90 / 119, 100,000 nodes 142 / 145; 512 / 1024 workgroups:
+// 100,000 nodes 142 / 155, 600,000 nodes 776 / 757, 10^6 nodes 1273 / 1212.
 static BucketGeom bucket_geom(int64_t n) {
   BucketGeom g{8, 0, 32};
   auto buckets = [&] { return (n + (1ll << g.tb) - 1) >> g.tb; };
@@ -466,8 +469,9 @@ static BucketGeom bucket_geom(int64_t n) {
   g.nb = (int)buckets();
   // the (bucket x workgroup) counts lie behind the edges in the proposal array, which leaves
   // 8 words per node even for p = 1: two kinds x buckets x workgroups <= 8 n
+  const int64_t workgroups = n <= (1 << 19) ? 512 : 1024;
   while (g.rows_per_wg < 4096 &&
-         ((int64_t)g.rows_per_wg * 1024 < n ||
+         (g.rows_per_wg * workgroups < n ||
           (n + g.rows_per_wg - 1) / g.rows_per_wg * g.nb > 4 * n))
     g.rows_per_wg += 32;
   return g;
