@@ -2,6 +2,7 @@
 // cores, and the nearest row of every column of a tile; shared by the joins on byte-valued data.
 #pragma once
 #include "device_utils.hpp"
+#include "kernels.hpp"
 
 namespace gnnd {
 
@@ -70,6 +71,71 @@ __device__ inline v16i gram(const Operand& rows, const Operand& cols) {
   for (int s = 0; s < KSTEPS; ++s)
     acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(rows.k[s], cols.k[s], acc, 0, 0, 0);
   return acc;
+}
+
+// Exact squared distances |a|^2 + |b|^2 - 2 a.b (four products per v_dot4) on
+// the int8 rows, from node s to one object per lane: `id` of lanes < count.
+// A row is C = dpad / 16 <= 8 chunks of 16 bytes; the C lanes of a group read
+// one object's row as one contiguous line (64 / C objects per load), multiply
+// it with the node's own chunk and add up across the group; the sums are then
+// handed to the lanes that hold the objects.  All 64 lanes call it together;
+// lanes >= count get 0.
+__device__ inline int32_t wave_distances_i8(const int8_t* __restrict__ shadow,
+                                            const NodeMeta* meta, int dpad, int64_t s, uint32_t id,
+                                            int count, int lane) {
+  const int C = dpad >> 4, per_load = kWave / C;
+  const int grp = lane / C, sub = lane - grp * C;
+  const bool lane_used = grp < per_load;  // C = 6 leaves four lanes without a group
+  const bool pow2 = (C & (C - 1)) == 0;
+  const v4i x = *reinterpret_cast<const v4i*>(shadow + s * dpad + 16 * sub);
+  const int32_t norm_s = meta[s].norm;
+  // (the objects' norms come from their rows, which are here anyway: a gather of the stored
+  // norm would be a second scattered access per object)
+  int32_t dot = 0, norm_id = 0;
+  for (int r0 = 0; r0 < count; r0 += per_load) {
+    const int j = r0 + grp;  // the object this group reads
+    const bool act = lane_used && j < count;
+    const uint32_t nid = __shfl(id, act ? j : 0, kWave);
+    int32_t part = 0, part_sq = 0;
+    if (act) {
+      const v4i y = *reinterpret_cast<const v4i*>(shadow + (int64_t)nid * dpad + 16 * sub);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        part = __builtin_amdgcn_sdot4(x[t], y[t], part, false);
+        part_sq = __builtin_amdgcn_sdot4(y[t], y[t], part_sq, false);
+      }
+    }
+    int32_t total = part, total_sq = part_sq;
+    if (pow2) {  // groups are aligned blocks of 2, 4 or 8 lanes: butterfly sum
+      if (C > 1) {
+        total += (int32_t)xor_lanes((uint32_t)total, 1, lane);
+        total_sq += (int32_t)xor_lanes((uint32_t)total_sq, 1, lane);
+      }
+      if (C > 2) {
+        total += (int32_t)xor_lanes((uint32_t)total, 2, lane);
+        total_sq += (int32_t)xor_lanes((uint32_t)total_sq, 2, lane);
+      }
+      if (C > 4) {
+        total += (int32_t)xor_lanes((uint32_t)total, 4, lane);
+        total_sq += (int32_t)xor_lanes((uint32_t)total_sq, 4, lane);
+      }
+    } else {
+      for (int off = 1; off < C; ++off) {
+        int o = sub + off;
+        o = o >= C ? o - C : o;
+        total += __shfl(part, (grp * C + o) & 63, kWave);
+        total_sq += __shfl(part_sq, (grp * C + o) & 63, kWave);
+      }
+    }
+    // object j = lane sits in group lane - r0
+    const int32_t got = __shfl(total, ((lane - r0) * C) & 63, kWave);
+    const int32_t got_sq = __shfl(total_sq, ((lane - r0) * C) & 63, kWave);
+    if (lane >= r0 && lane < r0 + per_load) {
+      dot = got;
+      norm_id = got_sq;
+    }
+  }
+  return lane < count ? norm_s + norm_id - 2 * dot : 0;
 }
 
 }  // namespace gnnd

@@ -89,71 +89,6 @@ __global__ __launch_bounds__(256) void k_pack_u8_wide(const uint8_t* vec_a, cons
   if (on && sub == 0) meta[row].norm = total;
 }
 
-// Exact squared distances |a|^2 + |b|^2 - 2 a.b (four products per v_dot4) on
-// the int8 rows, from node s to one object per lane: `id` of lanes < count.
-// A row is C = dpad / 16 <= 8 chunks of 16 bytes; the C lanes of a group read
-// one object's row as one contiguous line (64 / C objects per load), multiply
-// it with the node's own chunk and add up across the group; the sums are then
-// handed to the lanes that hold the objects.  All 64 lanes call it together;
-// lanes >= count get 0.
-__device__ inline int32_t wave_distances_i8(const int8_t* __restrict__ shadow,
-                                            const NodeMeta* meta, int dpad, int64_t s, uint32_t id,
-                                            int count, int lane) {
-  const int C = dpad >> 4, per_load = kWave / C;
-  const int grp = lane / C, sub = lane - grp * C;
-  const bool lane_used = grp < per_load;  // C = 6 leaves four lanes without a group
-  const bool pow2 = (C & (C - 1)) == 0;
-  const v4i x = *reinterpret_cast<const v4i*>(shadow + s * dpad + 16 * sub);
-  const int32_t norm_s = meta[s].norm;
-  // (the objects' norms come from their rows, which are here anyway: a gather of the stored
-  // norm would be a second scattered access per object)
-  int32_t dot = 0, norm_id = 0;
-  for (int r0 = 0; r0 < count; r0 += per_load) {
-    const int j = r0 + grp;  // the object this group reads
-    const bool act = lane_used && j < count;
-    const uint32_t nid = __shfl(id, act ? j : 0, kWave);
-    int32_t part = 0, part_sq = 0;
-    if (act) {
-      const v4i y = *reinterpret_cast<const v4i*>(shadow + (int64_t)nid * dpad + 16 * sub);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        part = __builtin_amdgcn_sdot4(x[t], y[t], part, false);
-        part_sq = __builtin_amdgcn_sdot4(y[t], y[t], part_sq, false);
-      }
-    }
-    int32_t total = part, total_sq = part_sq;
-    if (pow2) {  // groups are aligned blocks of 2, 4 or 8 lanes: butterfly sum
-      if (C > 1) {
-        total += (int32_t)xor_lanes((uint32_t)total, 1, lane);
-        total_sq += (int32_t)xor_lanes((uint32_t)total_sq, 1, lane);
-      }
-      if (C > 2) {
-        total += (int32_t)xor_lanes((uint32_t)total, 2, lane);
-        total_sq += (int32_t)xor_lanes((uint32_t)total_sq, 2, lane);
-      }
-      if (C > 4) {
-        total += (int32_t)xor_lanes((uint32_t)total, 4, lane);
-        total_sq += (int32_t)xor_lanes((uint32_t)total_sq, 4, lane);
-      }
-    } else {
-      for (int off = 1; off < C; ++off) {
-        int o = sub + off;
-        o = o >= C ? o - C : o;
-        total += __shfl(part, (grp * C + o) & 63, kWave);
-        total_sq += __shfl(part_sq, (grp * C + o) & 63, kWave);
-      }
-    }
-    // object j = lane sits in group lane - r0
-    const int32_t got = __shfl(total, ((lane - r0) * C) & 63, kWave);
-    const int32_t got_sq = __shfl(total_sq, ((lane - r0) * C) & 63, kWave);
-    if (lane >= r0 && lane < r0 + per_load) {
-      dot = got;
-      norm_id = got_sq;
-    }
-  }
-  return lane < count ? norm_s + norm_id - 2 * dot : 0;
-}
-
 // Alg. 1, first loop, on the int8 rows: k distinct random neighbours per node,
 // exact distances, sorted ascending by (distance, id), flagged NEW.  One
 // wavefront per node.
@@ -998,9 +933,9 @@ hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode
 
 hipError_t launch_init_random_i8(const Shape& sh, const DevState& ds, uint64_t seed,
                                  hipStream_t st) {
-  // long or segmented lists: the general kernels on the original vectors give the same integers
+  // segmented lists: the general kernel on the original vectors gives the same integers
   if (sh.segments > 1) return launch_init_random_segmented(sh, ds, seed, st);
-  if (sh.k > kWave) return launch_init_random_wide(sh, ds, seed, st);
+  if (sh.k > kWave) return launch_init_random_wide_i8(sh, ds, seed, st);
   const int dpad = (sh.d + 31) & ~31;
   const dim3 grid = grid_blocks((sh.n + 3) / 4);
   const uint64_t base = hash_base(seed, kTagInit);

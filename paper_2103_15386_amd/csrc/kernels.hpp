@@ -157,6 +157,9 @@ hipError_t launch_update(const Shape& sh, const DevState& ds, hipStream_t st);
 // lists of 65..128 entries (two per lane); the launchers above forward to these
 hipError_t launch_init_random_wide(const Shape& sh, const DevState& ds, uint64_t seed,
                                    hipStream_t st);
+// on the int8 rows (exact integers either way)
+hipError_t launch_init_random_wide_i8(const Shape& sh, const DevState& ds, uint64_t seed,
+                                      hipStream_t st);
 hipError_t launch_update_wide(const Shape& sh, const DevState& ds, hipStream_t st);
 // segmented lists (sh.segments > 1); the launchers above forward to these as well
 hipError_t launch_init_random_segmented(const Shape& sh, const DevState& ds, uint64_t seed,

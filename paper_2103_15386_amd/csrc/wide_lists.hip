@@ -6,6 +6,7 @@
 // against the first register and merging the larger half into the second
 // (sort128 / merge128).  The length of the sample lists is another matter (2p).
 #include "device_utils.hpp"
+#include "gram_i8.hpp"
 #include "kernels.hpp"
 
 namespace gnnd {
@@ -120,6 +121,47 @@ __global__ __launch_bounds__(kWB) void k_init_random_wide(VecSrc vs, int64_t n, 
   sort128(lo, hi, lane);
   G[s * k + lane] = lo;
   if (lane + kWave < k) G[s * k + kWave + lane] = hi;
+  if (lane + kWave == k - 1) meta[s].kth = entry_code(hi);
+}
+
+// The same on the int8 rows of byte-valued data (a quarter of the bytes of float rows, read as
+// whole lines by groups of lanes, v_dot4).  As in k_init_random_i8, whether the first attempts
+// of all slots are valid shows after the sort: equal ids have equal distances and end up next
+// to each other.  200,000 x 96 bytes, k = 96: build of 4 iterations 7.5 -> 6.3 ms (the general kernel
+// took 1.8 of it, waiting for rows that every lane walks through LDS on its own).
+template <bool FCODE>
+__global__ __launch_bounds__(kWB) void k_init_random_wide_i8(const int8_t* __restrict__ shadow,
+                                                             NodeMeta* meta, int dpad, int64_t n,
+                                                             int k, uint64_t base_hash,
+                                                             uint64_t* G) {
+  const int64_t s = wide_wave_index();
+  if (s >= n) return;
+  const int lane = lane_id();
+  const bool have1 = lane + kWave < k;
+  uint64_t lo, hi;
+  auto list_of = [&](uint32_t id0, uint32_t id1) {
+    const int32_t d0 = wave_distances_i8(shadow, meta, dpad, s, id0, kWave, lane);
+    const int32_t d1 = wave_distances_i8(shadow, meta, dpad, s, id1, k - kWave, lane);
+    lo = make_entry(FCODE ? ord_f32((float)d0) : ord_i32(d0), id0, 1u);
+    hi = have1 ? make_entry(FCODE ? ord_f32((float)d1) : ord_i32(d1), id1, 1u) : kKeyMax;
+    sort128(lo, hi, lane);
+  };
+  auto first = [&](int slot) {
+    return bounded(hash3(base_hash, (uint32_t)s, (uint32_t)slot, 0u), (uint32_t)n);
+  };
+  list_of(first(lane), first(lane + kWave));
+  const uint64_t before_lo = __shfl_up(lo, 1, kWave), last_lo = readlane64(lo, kWave - 1);
+  uint64_t before_hi = __shfl_up(hi, 1, kWave);
+  if (lane == 0) before_hi = last_lo;
+  const bool bad = entry_id(lo) == (uint32_t)s || (lane > 0 && entry_id(lo) == entry_id(before_lo)) ||
+                   (have1 && (entry_id(hi) == (uint32_t)s || entry_id(hi) == entry_id(before_hi)));
+  if (__ballot(bad) != 0ull) {
+    uint32_t id0, id1;
+    draw_distinct_wide(base_hash, (uint32_t)s, k, (uint32_t)n, 0u, (uint32_t)s, lane, id0, id1);
+    list_of(id0, id1);
+  }
+  G[s * k + lane] = lo;
+  if (have1) G[s * k + kWave + lane] = hi;
   if (lane + kWave == k - 1) meta[s].kth = entry_code(hi);
 }
 
@@ -270,6 +312,16 @@ hipError_t launch_init_random_wide(const Shape& sh, const DevState& ds, uint64_t
       k_init_random_wide<kL2U8><<<grid, kWB, 0, st>>>(wide_vec_src(sh), sh.n, sh.k, base, ds.G,
                                                       ds.meta);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_init_random_wide_i8(const Shape& sh, const DevState& ds, uint64_t seed,
+                                      hipStream_t st) {
+  const int dpad = (sh.d + 31) & ~31;
+  const uint64_t base = hash_base(seed, kTagInit);
+  auto* const kernel =
+      sh.metric != kL2U8 ? k_init_random_wide_i8<true> : k_init_random_wide_i8<false>;
+  kernel<<<wide_blocks(sh.n), kWB, 0, st>>>(ds.shadow, ds.meta, dpad, sh.n, sh.k, base, ds.G);
   return hipGetLastError();
 }
 
