@@ -70,7 +70,7 @@ enum {
                                destination list by itself (one device-wide atomic each);
                                GNND_JOIN_MFMA / AUTO collect the results per workgroup and
                                bucket of destinations first where the workspace for that is
-                               affordable (n <= 2^20) and use this form beyond.  Same lists */
+                               affordable (n <= 2^22) and use this form beyond.  Same lists */
   GNND_JOIN_GRAM = 4  /* float32 vectors of any dimension, squared L2 / angular / cosine,
                          p <= 32: inner products on the matrix cores pick, per sample, the
                          few partners that can be its nearest one; their distances are then
@@ -130,15 +130,16 @@ typedef struct gnnd_iter_stats {
   uint64_t passed;     /* results handed to the list update (after the early drop) */
   float ms_sample, ms_join, ms_update;
   float ms_handout;    /* between join and update: the pass that moves staged results into
-                          the destination lists' segments (matrix-core join, n <= 2^20);
+                          the destination lists' segments (matrix-core join, n <= 2^22);
                           ~0 where results are handed on inside the join itself        */
 } gnnd_iter_stats;
 
 /* Device scratch needed for these parameters (pure host arithmetic; n, d, k, p,
  * metric are read).  Returns 0 when the parameters are invalid.  Where the
  * float32 matrix-core join applies and d >= 24 this includes room for a 16-bit
- * copy of the vectors (2 bytes per dimension, padded to 32), and with p > 32 on
- * uint8 or squared-L2 vectors of up to 128 dimensions for an int8 copy; a
+ * copy of the vectors (2 bytes per dimension, padded to 32), with p > 32 on
+ * uint8 or squared-L2 vectors of up to 128 dimensions for an int8 copy, and with
+ * 2^20 < n <= 2^22 on such vectors for the results the int8 join stages; a
  * workspace that is smaller by that much is accepted as well and gives the same
  * results, more slowly. */
 size_t gnnd_workspace_bytes(const gnnd_params* prm);

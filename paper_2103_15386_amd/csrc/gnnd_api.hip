@@ -42,8 +42,8 @@ struct Layout {
       off_roo, off_csn, off_cso, off_capn, off_capo, off_pslot, off_poff, off_bins, off_scan,
       off_cnt, off_snap, off_aside, off_shadow, off_norms, off_flag, off_bkc, off_stg_ent,
       off_stg_cur, off_cls_nodes, off_cls_count, off_half, total;
-  bool extra;  // has room for the 16-bit rows of the float32 matrix-core join, or the int8 rows
-               // of the long join
+  bool extra;  // has room for the 16-bit rows of the float32 matrix-core join, the int8 rows of
+               // the long join, the staging array of the int8 join beyond 2^20 nodes
 };
 
 constexpr int kHalfMinDim = 24;
@@ -108,10 +108,12 @@ bool needs_norms(const gnnd_params* q) {
 }
 
 // The matrix-core join stages its results per bucket of destinations (instead of handing
-// them on one by one) for up to 2^20 nodes: a staged result then fits one 64-bit word, and
-// the staging array is as large again as the proposal array.
-bool stage_possible(const gnnd_params* q) {
-  return mfma_possible(q) && q->join_path != GNND_JOIN_MFMA_DIRECT && q->n <= kStageMaxNodes;
+// them on one by one) for up to 2^22 nodes: a staged result then fits one 64-bit word, and
+// the staging array is as large again as the proposal array.  Beyond 2^20 nodes only where
+// the workspace has room for it.
+bool stage_possible(const gnnd_params* q, bool extra) {
+  return mfma_possible(q) && q->join_path != GNND_JOIN_MFMA_DIRECT && q->n <= kStageMaxNodes &&
+         (extra || q->n <= ((int64_t)1 << 20));
 }
 
 // 16-bit copies of the vectors for the first pass of the float32 matrix-core join: from 24
@@ -126,8 +128,8 @@ bool long_i8_possible(const gnnd_params* q) {
 }
 
 // `extra` = false: the layout without the 16-bit rows (the join then reads the float32 rows
-// twice) and without the int8 rows of the long join, for workspaces that have no room for them.
-// Same results.
+// twice), the int8 rows of the long join and, beyond 2^20 nodes, the staging array (results are
+// handed on one by one), for workspaces that have no room for them.  Same results.
 Layout make_layout(const gnnd_params* q, bool with_aside, bool extra = true) {
   Layout L;
   const size_t n = (size_t)q->n, k = (size_t)q->k, p = (size_t)q->p;
@@ -163,7 +165,7 @@ Layout make_layout(const gnnd_params* q, bool with_aside, bool extra = true) {
   L.off_norms = take(needs_norms(q) ? n * 4 : 0);  // squared norms
   L.off_flag = take(256);
   L.off_bkc = take(2 * 4096 * 4);
-  const bool staged = stage_possible(q);
+  const bool staged = stage_possible(q, extra);
   L.off_stg_ent = take(staged ? n * slots_per_node * 8 : 0);
   L.off_stg_cur = take(staged ? (size_t)kStageBuckets * 8 : 0);
   const bool gram = gram_possible(q);
@@ -243,7 +245,7 @@ void bind(gnnd_ctx* c, const Layout& L) {
   d.shadow = (int8_t*)(w + L.off_shadow);
   c->flag_dev = (int*)(w + L.off_flag);
   d.bk_cnt = (uint32_t*)(w + L.off_bkc);
-  const bool staged = stage_possible(&c->prm);
+  const bool staged = stage_possible(&c->prm, L.extra);
   d.stg_ent = staged ? (uint64_t*)(w + L.off_stg_ent) : nullptr;
   d.stg_cur = staged ? (unsigned long long*)(w + L.off_stg_cur) : nullptr;
   const bool gram = gram_possible(&c->prm);

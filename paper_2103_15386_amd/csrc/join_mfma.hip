@@ -25,7 +25,7 @@ constexpr int64_t kJoinGrid = 256 * 3 * 2;  // 256 CUs x 3 resident workgroups x
 // staged hand-out: one workgroup of 8 waves per CU (2 per SIMD: the staging code needs the registers) shares the staging area
 constexpr int kStagedWaves = 8;       // four operand blocks: 2 wavefronts per SIMD
 constexpr int kStagedWavesSlim = 12;  // three operand blocks: 3 wavefronts per SIMD
-constexpr int kMBStaged = kStagedWaves * kWave;
+
 constexpr int32_t kFar = 1 << 24;  // "norm" of an absent row: above every real distance
 
 // Convert float32 rows holding integers 0..255 (or uint8 rows) to int8 rows
@@ -200,9 +200,12 @@ struct StageArgs {
 };
 constexpr size_t kStageLdsBytes = (size_t)kStageBuckets * kStageSlots * 8 + kStageBuckets * 20 + 16;
 // a staged result: distance code | destination inside its bucket | object id
+// a staged result without its destination, and with it
+__device__ inline uint64_t stage_entry(int32_t dist, uint32_t id) {
+  return ((uint64_t)(uint32_t)dist << kStageDistShift) | (uint64_t)id;
+}
 __device__ inline uint64_t stage_record(uint64_t entry, uint32_t dest, int tb) {
-  return (entry & 0xffffffff00000000ull) | ((uint64_t)(dest & ((1u << tb) - 1u)) << kStageIdBits) |
-         (uint64_t)entry_id(entry);
+  return entry | ((uint64_t)(dest & ((1u << tb) - 1u)) << kStageIdBits);
 }
 
 // Squared norm of the row this lane's sample stands for, from the operand registers: sample
@@ -269,7 +272,7 @@ __attribute__((amdgpu_waves_per_eu(STAGED && !SHAPE ? 2 : 3, STAGED && !SHAPE ? 
   uint32_t* const st_fill = st_cnt + kStageBuckets;  // [0] results staged, [1] waves out of nodes
   // (the wave index as a vector value: measured 3 % faster here than the scalar form)
   const int wave = threadIdx.x >> 6, lane = lane_id(), half = lane >> 5, col = lane & 31;
-  // (with lists n <= 2^20: places, node numbers and offsets into the sample lists fit 32 bits)
+  // (with lists n <= 2^22: places, node numbers and offsets into the sample lists fit 32 bits)
   using node_t = typename std::conditional<STAGED, int32_t, int64_t>::type;
   const node_t W = (node_t)gridDim.x * WAVES;
   // place `pos` of this build's list of nodes (staged) / of all nodes (direct)
@@ -523,7 +526,8 @@ __attribute__((amdgpu_waves_per_eu(STAGED && !SHAPE ? 2 : 3, STAGED && !SHAPE ? 
         // a result that cannot beat the last entry of the destination list is dropped
         // (LEAN: every result goes on, k_result_csr applies the threshold)
         pass[kind] = found && (LEAN || code <= cm.x);
-        entry[kind] = make_entry(code, (uint32_t)other, 3u);
+        entry[kind] = STAGED ? stage_entry(dist, (uint32_t)other)
+                             : make_entry(code, (uint32_t)other, 3u);
         found_total += (uint32_t)__popcll(__ballot(found));
       }
     } else {
@@ -658,15 +662,18 @@ constexpr int kRcBlock = 1024;
 // last entry of its destination's list is dropped here, and what is left is counted as passed.
 // Results per thread and tile: 12 (96 KB of LDS), 11 where the thresholds need room too.
 constexpr int rc_per_thread(bool filter) { return filter ? 11 : 12; }
-// LDS: the tile, then per destination of the bucket (at most 2^12) the number of results in
+// A bucket of more than 2^kRcBits destinations (more than 2^20 nodes) is worked on by several
+// workgroups, each of which reads all of the bucket's results and keeps those for its part.
+constexpr int kRcBits = 12;
+// LDS: the tile, then per destination of the bucket or part (at most 2^12) the number of results in
 // the tile / the start of its run, the next free place of its segment, the segment's end
 // (both relative to the region) and, with FILTER, the threshold of its list.
 static size_t result_csr_lds_bytes(int tb, bool filter) {
   return (size_t)kRcBlock * rc_per_thread(filter) * 8 + (((size_t)(filter ? 4 : 3) << tb) + 1) * 4;
 }
 
-template <bool FILTER>
-__global__ __launch_bounds__(kRcBlock) void k_result_csr(int64_t n, int tb,
+template <bool FILTER, bool FCODE>
+__global__ __launch_bounds__(kRcBlock) void k_result_csr(int64_t n, int bucket_tb,
                                                          const uint64_t* __restrict__ poff,
                                                          const unsigned long long* __restrict__ cur,
                                                          const uint64_t* __restrict__ ent,
@@ -679,24 +686,39 @@ __global__ __launch_bounds__(kRcBlock) void k_result_csr(int64_t n, int tb,
   extern __shared__ __attribute__((aligned(16))) uint64_t rc_lds[];
   __shared__ uint32_t part[kRcBlock / kWave];
   uint64_t* const tile = rc_lds;
+  const int tb = bucket_tb < kRcBits ? bucket_tb : kRcBits, parts = 1 << (bucket_tb - tb);
   const int T_max = 1 << tb;
   uint32_t* const run = reinterpret_cast<uint32_t*>(rc_lds + kRcTile);  // T_max + 1 entries
   uint32_t* const next = run + T_max + 1;
   uint32_t* const seg_end = next + T_max;
   uint32_t* const kth_s = seg_end + T_max;  // FILTER only
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t first = (int64_t)blockIdx.x << tb;
+  const int bucket = blockIdx.x / parts, part_of = blockIdx.x % parts;
+  const int64_t bucket_first = (int64_t)bucket << bucket_tb, first = bucket_first + part_of * T_max;
+  if (first >= n) return;
+  const int64_t bucket_end =
+      bucket_first + (1ll << bucket_tb) < n ? bucket_first + (1ll << bucket_tb) : n;
   const int T = (int)(n - first < (int64_t)T_max ? n - first : (int64_t)T_max);
-  const uint64_t region = poff[first], room = poff[first + T] - region;
+  const uint64_t region = poff[bucket_first], room = poff[bucket_end] - region;
+  // destination inside this part (T or more: none of this part's), and the distance's code
+  auto place_of = [&](uint64_t x) {
+    const uint32_t in_bucket =
+        (uint32_t)(x >> kStageIdBits) & ((1u << (kStageDistShift - kStageIdBits)) - 1u);
+    return in_bucket - (uint32_t)(part_of * T_max);
+  };
+  auto code_of = [](uint64_t x) {
+    const int32_t dist = (int32_t)(x >> kStageDistShift);
+    return FCODE ? ord_f32((float)dist) : ord_i32(dist);
+  };
   for (int t = tid; t < T_max; t += kRcBlock) {
     next[t] = t < T ? (uint32_t)(poff[first + t] - region) : (uint32_t)room;
     seg_end[t] = t < T ? (uint32_t)(poff[first + t + 1] - region) : (uint32_t)room;
     if (FILTER) kth_s[t] = t < T ? meta[first + t].kth : 0u;
   }
   uint32_t kept = 0;  // FILTER: results that pass
-  uint64_t count = cur[blockIdx.x];
+  uint64_t count = cur[bucket];
   if (count > room) {  // cannot happen: a region holds what its destinations can receive
-    if (tid == 0)
+    if (tid == 0 && part_of == 0)
       atomicAdd(reinterpret_cast<unsigned long long*>(counters + C_OVERFLOW),
                 (unsigned long long)(count - room));
     count = room;
@@ -715,8 +737,8 @@ __global__ __launch_bounds__(kRcBlock) void k_result_csr(int64_t n, int tb,
     }
 #pragma unroll
     for (int r = 0; r < kRcPerThread; ++r) {
-      const int t = (int)(((uint32_t)e[r] >> kStageIdBits) & (uint32_t)(T_max - 1));
-      if (e[r] == ~0ull || t >= T || (FILTER && (uint32_t)(e[r] >> 32) > kth_s[t])) {
+      const uint32_t t = place_of(e[r]);
+      if (e[r] == ~0ull || t >= (uint32_t)T || (FILTER && code_of(e[r]) > kth_s[t])) {
         e[r] = ~0ull;
       } else {
         rank[r] = atomicAdd(&run[t], 1u);
@@ -755,7 +777,7 @@ __global__ __launch_bounds__(kRcBlock) void k_result_csr(int64_t n, int tb,
 #pragma unroll
     for (int r = 0; r < kRcPerThread; ++r) {
       if (e[r] != ~0ull) {
-        const int t = (int)(((uint32_t)e[r] >> kStageIdBits) & (uint32_t)(T_max - 1));
+        const uint32_t t = place_of(e[r]);
         tile[run[t] + rank[r]] = e[r];
       }
     }
@@ -766,12 +788,12 @@ __global__ __launch_bounds__(kRcBlock) void k_result_csr(int64_t n, int tb,
       const uint32_t j = (uint32_t)r * kRcBlock + tid;
       if (j < in_tile) {
         const uint64_t x = tile[j];
-        const int t = (int)(((uint32_t)x >> kStageIdBits) & (uint32_t)(T_max - 1));
+        const uint32_t t = place_of(x);
         const uint32_t place = next[t] + (j - run[t]);
         // back to a list entry: distance code | object id | "admitted now" + NEW
         if (place < seg_end[t])
-          bins[region + place] = make_entry((uint32_t)(x >> 32),
-                                            (uint32_t)x & ((1u << kStageIdBits) - 1u), 3u);
+          bins[region + place] =
+              make_entry(code_of(x), (uint32_t)x & ((1u << kStageIdBits) - 1u), 3u);
       }
     }
     __syncthreads();
@@ -920,13 +942,16 @@ hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode
 #undef GNND_K
   if (after_join) (void)hipEventRecord(after_join, st);
   if (e != hipSuccess) return e;
-  // (a region is shorter than 2^32 slots: n <= 2^20, 6p <= 192 slots per node)
-  const size_t lds = result_csr_lds_bytes(sa.tb, lean);
-  auto* csr = lean ? &k_result_csr<true> : &k_result_csr<false>;
+  // (a region is shorter than 2^32 slots: n <= 2^22, 6p <= 192 slots per node)
+  const int part_tb = sa.tb < kRcBits ? sa.tb : kRcBits;
+  const size_t lds = result_csr_lds_bytes(part_tb, lean);
+  auto* csr = lean ? (fcode ? &k_result_csr<true, true> : &k_result_csr<true, false>)
+                   : (fcode ? &k_result_csr<false, true> : &k_result_csr<false, false>);
   e = hipFuncSetAttribute(reinterpret_cast<const void*>(csr),
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  csr<<<(unsigned)sa.nb, kRcBlock, lds, st>>>(sh.n, sa.tb, ds.poff, ds.stg_cur, ds.stg_ent, ds.bins,
+  const unsigned csr_grid = (unsigned)sa.nb << (sa.tb - part_tb);
+  csr<<<csr_grid, kRcBlock, lds, st>>>(sh.n, sa.tb, ds.poff, ds.stg_cur, ds.stg_ent, ds.bins,
                                              ds.pslot, ds.meta, ds.counters);
   return hipGetLastError();
 }

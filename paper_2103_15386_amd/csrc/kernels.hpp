@@ -77,11 +77,12 @@ constexpr int kNodeClassesMax = 7;
 
 // Staged hand-out: destinations are cut into at most kStageBuckets buckets of 2^tb
 // consecutive ids; a workgroup of the join keeps kStageSlots results per bucket in LDS.
-// A staged result is one 64-bit word: distance code (32) | destination inside its bucket
-// (12) | object id (20), which is what limits the staged form to 2^20 nodes.
+// A staged result is one 64-bit word: squared distance (23: at most 128 x 255^2) | destination
+// inside its bucket (19, of which at most 14 are in use) | object id (22), which is what limits
+// the staged form to 2^22 nodes.
 constexpr int kStageBuckets = 256;
 constexpr int kStageSlots = 64;
-constexpr int kStageIdBits = 20;
+constexpr int kStageIdBits = 22, kStageDistShift = 41;
 constexpr int64_t kStageMaxNodes = (int64_t)1 << kStageIdBits;
 inline int stage_bucket_bits(int64_t n) {
   int tb = 0;

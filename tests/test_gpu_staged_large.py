@@ -1,0 +1,51 @@
+"""The staged hand-out of the int8 join beyond 2^20 nodes, where a bucket of destinations is
+worked on by two or four workgroups: same graphs as the hand-out one by one, builds (the first
+iteration leaves the thresholds to the second pass) and merges, float codes and integer codes."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _vectors(n, d, dtype):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    c = torch.rand((64, d), generator=g, device="cuda") * 128
+    x = c[torch.randint(0, 64, (n,), generator=g, device="cuda")]
+    x = (x + 20 * torch.randn((n, d), generator=g, device="cuda")).clamp_(0, 255).round_()
+    return x.to(dtype)
+
+
+@pytest.mark.parametrize("n,d,k,p,dtype", [
+    ((1 << 20) + 1, 20, 8, 8, torch.uint8), ((1 << 20) + 333, 128, 20, 20, torch.float32),
+    ((1 << 21) + 5000, 16, 6, 6, torch.uint8), (1 << 22, 8, 4, 4, torch.uint8)])
+def test_staged_builds_equal_direct_ones(n, d, k, p, dtype):
+    import paper_2103_15386_amd as amd
+    x = _vectors(n, d, dtype)
+    metric = amd.L2SQ_U8 if dtype == torch.uint8 else amd.L2SQ_F32
+    graphs = []
+    for path in (amd.JOIN_MFMA, amd.JOIN_MFMA_DIRECT):
+        ctx = amd.Gnnd(x, k, p, metric, 42, path)
+        ctx.init_random()
+        stats = [ctx.iterate() for _ in range(3)]
+        counts = [[s[f] for f in ("inserts", "dist_evals", "proposals")] for s in stats]
+        # (the first iteration of a direct build hands on what cannot enter as well)
+        counts.append([s["passed"] for s in stats[1:]] + [s["dropped"] for s in stats])
+        graphs.append((*ctx.graph(with_flags=True), counts))
+        ctx.close()
+    assert all(torch.equal(a, b) for a, b in zip(graphs[0][:3], graphs[1][:3]))
+    assert graphs[0][3] == graphs[1][3]
+
+
+def test_staged_merge_equals_a_direct_one():
+    import paper_2103_15386_amd as amd
+    n1, n2, d, k, p = 700_002, 500_000, 24, 10, 10
+    x = _vectors(n1 + n2, d, torch.uint8)
+    a, b = x[:n1].contiguous(), x[n1:].contiguous()
+    ids1, dist1, c1 = amd.gnnd_build(a, k, p, amd.L2SQ_U8, 42, 4)
+    ids2, dist2, c2 = amd.gnnd_build(b, k, p, amd.L2SQ_U8, 43, 4)
+    ids2 = ids2 + n1
+    out = [amd.gnnd_merge(a, b, ids1, dist1, ids2, dist2, k, p, amd.L2SQ_U8, 42, 3, path)
+           for path in (amd.JOIN_MFMA, amd.JOIN_MFMA_DIRECT)]
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    c1.close()
+    c2.close()
