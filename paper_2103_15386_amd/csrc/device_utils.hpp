@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace gnnd {
 
 constexpr int kWave = 64;
@@ -387,34 +389,61 @@ __device__ inline uint32_t wave_distances(const VecSrc& vs, uint32_t s, uint32_t
   const int d = vs.d;
   const bool aligned = (d & 3) == 0;
   const int part = lane & 7, rsel = lane >> 3;
-  ACC acc = 0;
-  for (int d0 = 0; d0 < d; d0 += kEvalChunk) {
+  // the rows this lane helps to read: rows 0..63 are the lanes' objects, row 64 is s
+  constexpr int kRounds = 9;
+  const T* src[kRounds];
 #pragma unroll
-    for (int r0 = 0; r0 < 72; r0 += 8) {  // rows 0..63: the lanes' objects, row 64: s
-      const int r = r0 + rsel;
-      const uint32_t rid = __shfl(id, r & 63, kWave);
-      const int ron = __shfl((int)on, r & 63, kWave);
-      const bool want = r < 64 ? ron != 0 : r == 64;
-      if (want) {
-        const T* src = vs.row<T>(r < 64 ? rid : s);
-        const int j = d0 + part * 4;
-        ACC v[4] = {0, 0, 0, 0};
-        if (sizeof(T) == 4 && aligned && j + 3 < d) {
-          const float4 f = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(src) + j);
-          v[0] = (ACC)f.x; v[1] = (ACC)f.y; v[2] = (ACC)f.z; v[3] = (ACC)f.w;
-        } else if (sizeof(T) == 1 && aligned && j + 3 < d) {  // four bytes in one load
-          const uint32_t w = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(src) + j);
-          v[0] = (ACC)(w & 0xff); v[1] = (ACC)((w >> 8) & 0xff);
-          v[2] = (ACC)((w >> 16) & 0xff); v[3] = (ACC)(w >> 24);
-        } else {
+  for (int i = 0; i < kRounds; ++i) {
+    const int r = 8 * i + rsel;
+    const uint32_t rid = __shfl(id, r & 63, kWave);
+    const int ron = __shfl((int)on, r & 63, kWave);
+    const bool want = r < 64 ? ron != 0 : r == 64;
+    src[i] = want ? vs.row<T>(r < 64 ? rid : s) + part * 4 : nullptr;
+  }
+  // The next chunk is requested before this one is evaluated (four floats of a row, or its four
+  // bytes, per lane and round): with one chunk at a time the kernels waited for memory.  Random
+  // initial graphs, 1.5 million x 96 angular 5.3 -> 3.6 ms, 150,000 x 960 4.4 -> 2.8 ms (6.6 TB/s,
+  // the rate of a gather of random rows).
+  using Raw = typename std::conditional<sizeof(T) == 4, float4, uint32_t>::type;
+  Raw raw[kRounds];
+  auto fetch = [&](int d0) {
+    const int j = d0 + part * 4;
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (j + q < d) v[q] = (ACC)src[j + q];
-        }
+    for (int i = 0; i < kRounds; ++i) {
+      raw[i] = Raw{};
+      if (src[i] == nullptr) continue;
+      const T* at = src[i] + d0;
+      if (aligned && j + 3 < d) {
+        raw[i] = *reinterpret_cast<const Raw*>(at);
+      } else if constexpr (sizeof(T) == 4) {
+        if (j + 0 < d) raw[i].x = at[0];
+        if (j + 1 < d) raw[i].y = at[1];
+        if (j + 2 < d) raw[i].z = at[2];
+        if (j + 3 < d) raw[i].w = at[3];
+      } else {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) tile[r * kEvalStride + part * 4 + q] = v[q];
+        for (int q = 0; q < 4; ++q)
+          if (j + q < d) raw[i] |= (uint32_t)at[q] << (8 * q);
       }
     }
+  };
+  ACC acc = 0;
+  fetch(0);
+  for (int d0 = 0; d0 < d; d0 += kEvalChunk) {
+#pragma unroll
+    for (int i = 0; i < kRounds; ++i) {
+      const int r = 8 * i + rsel;
+      if (r <= 64) {
+        ACC* const to = tile + r * kEvalStride + part * 4;
+        if constexpr (sizeof(T) == 4) {
+          to[0] = raw[i].x; to[1] = raw[i].y; to[2] = raw[i].z; to[3] = raw[i].w;
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) to[q] = (ACC)((raw[i] >> (8 * q)) & 0xff);
+        }
+      }
+    }
+    if (d0 + kEvalChunk < d) fetch(d0 + kEvalChunk);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
