@@ -122,16 +122,24 @@ __device__ constexpr int block_row(int q) {
 // The 16-bit copies (HALF): element i of row a is x_i / |a| x 2^kHalfBits, rounded to float16,
 // padded with zeros to whole steps of 32.  Elements below float16's normal range are made zero
 // (relative to the norm that is 2^-29), so that nothing depends on how the matrix unit treats
-// denormal operands.  `rho` bounds |a - copy of a| / |a| over all rows; rows whose norm is too
-// small to divide by are NaN in the copy, and all their pairs stay in the race.
+// denormal operands.  `rho` bounds |a - copy of a| / |a| over all rows; rows whose squared norm
+// is outside [kHalfLeast, kNormMost] are NaN in the copy, and all their pairs stay in the race.
 constexpr int kHalfBits = 15;
 struct HalfRows {
   const _Float16* rows;
   int32_t stride;           // elements per row, a multiple of 32
   const float* rho;
-  const uint32_t* odd;      // number of rows that are NaN in the copy
 };
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+// Squared norms for which the bounds of step 2 hold.  Beyond 2^125 sums of them and of the inner
+// products may overflow; below 2^-90 the squares of a row's elements come near the denormal range,
+// and so does the product of two scaled norms.  The canonical cosine divides by the root of
+// fl(|a|^2 |b|^2): that product has to be a normal number too, which it is for every pair of
+// rows with squared norms in [2^-62, 2^62].
+constexpr float kNormMost = 4.2535296e37f, kHalfLeast = 8.0779357e-28f;
+constexpr float kCosineLeast = 2.1684043e-19f, kCosineMost = 4.6116860e18f;
+constexpr float kLeastNormal = 1.1754944e-38f, kMostFinite = 3.4028235e38f;
 
 // What a wavefront has counted over its nodes (the same in every lane).
 struct GramTally {
@@ -140,8 +148,8 @@ struct GramTally {
 
 template <int METRIC, bool WHOLE, bool HALF, int RBM, int COM>
 __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc& vs,
-                                          const HalfRows& hr, float rho, bool odd, int64_t s,
-                                          int p, int merge_mode,
+                                          const HalfRows& hr, float rho, int64_t s, int p,
+                                          int merge_mode,
                                           const int32_t* __restrict__ snew,
                                           const int32_t* __restrict__ sold, int nn, int no,
                                           const NodeMeta* __restrict__ meta, uint64_t* pslot,
@@ -248,6 +256,12 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
     fetch2(opa, opb, 0);
   }
 
+  // `special`: some sample's squared norm is outside the range in which the bounds of step 2
+  // hold for every pair (see pair_is_lost)
+  bool special;
+  // (the float32 form of squared L2: errors of up to 8 d 2^-149 where sums are denormal numbers,
+  // which the matrix unit keeps, have to be small against 24 u (na + nb))
+  const float least_sum = (float)d * kLeastNormal;
   {
     // one 8-byte record per sample: the threshold of its list and its squared norm
     // (launch_gram_norms put the float's bits where the int8 join keeps its integer norm)
@@ -258,9 +272,18 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
     auto weight_of = [&](int32_t id, float nrm) {
       float w = nrm;
       if (METRIC == kCosineF32)
-        w = HALF ? (nrm == nrm ? 0.f : kNaN) : nrm > 0.f ? 1.0f / sqrtf(nrm) : 0.f;
+        w = !HALF && nrm > 0.f ? 1.0f / sqrtf(nrm) : 0.f;
       return id >= 0 ? w : kNaN;
     };
+    auto is_special = [&](int32_t id, float nrm) {
+      const float least = METRIC == kCosineF32 ? kCosineLeast : HALF ? kHalfLeast : least_sum;
+      const float most = METRIC == kCosineF32 ? kCosineMost : kNormMost;
+      bool ok = nrm >= least && nrm <= most;
+      if (!HALF && METRIC == kCosineF32) ok = ok || nrm == 0.f;  // (weight 0: distance 1)
+      if (!HALF && METRIC == kAngularF32) ok = nrm <= most;
+      return id >= 0 && !ok;
+    };
+    special = __ballot(is_special(idn, nrmn) || is_special(ido, nrmo)) != 0ull;
     constexpr float kScale = 1.0f / (1 << kHalfBits);
     S.norms[lane] = METRIC == kCosineF32 ? nrmn : HALF ? sqrtf(nrmn) * kScale : 0.f;
     S.norms[64 + lane] = METRIC == kCosineF32 ? nrmo : HALF ? sqrtf(nrmo) * kScale : 0.f;
@@ -348,6 +371,7 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
   //    same numbers on both sides.
   // Squared L2, t - 2 dot: c1 t + c2 |value|.  1 - dot: half of c1 t and the rounding of the
   // subtraction on both sides.  Cosine, 1 - dot / sqrt(na nb): the same relative to P.
+  // All of this for squared norms inside the range of their form, see pair_is_lost.
   constexpr float u = 5.9604645e-8f;
   const float h = HALF ? (float)(2 * (32 + (hr.stride >> 5))) * u
                        : (float)(2 * (4 + 4 * ((d + kWC - 1) / kWC))) * u;
@@ -373,14 +397,8 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
   const float* const factor = METRIC == kCosineF32 ? S.weight : S.norms;
   constexpr float kOne = METRIC == kL2F32 ? -2.0f : -1.0f;
   constexpr float kSame = HALF ? kOne / (1 << kHalfBits) / (1 << kHalfBits) : kOne;
-  auto bound = [&](float dot, float base, float fr, float fc, float unknown) {
-    float v = kFactors ? __fmaf_rn(dot, fr * fc, base) : __fmaf_rn(dot, kSame, base);
-    // A row that has no 16-bit copy: the pair stays in the race (`unknown`: the largest finite
-    // bounds).  Not where the sum of the norms is infinite under squared L2, nor with NaN
-    // anywhere: those have no distance to compare, here as in the other form.
-    if (HALF && odd && dot != dot)
-      v = (METRIC == kAngularF32 ? base == base : base * 0.f == 0.f) ? unknown : kNaN;
-    return v;
+  auto bound = [&](float dot, float base, float fr, float fc) {
+    return kFactors ? __fmaf_rn(dot, fr * fc, base) : __fmaf_rn(dot, kSame, base);
   };
   const bool with_dups = !merge_mode && n_dup != 0;
   auto four = [](const float* at) { return *reinterpret_cast<const float4*>(at); };
@@ -392,6 +410,55 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
       return merge_mode ? ((int64_t)idr < split) != ((int64_t)idc < split) : idr != idc;
     return true;
   };
+  // Pairs whose approximate distance says nothing about the canonical one: a row without a
+  // 16-bit copy or with infinite elements (the product is NaN), and the ends of float32's range,
+  // where overflows and denormal numbers break the relative bounds.  Their products are made
+  // NaN, which keeps them out of the bounds below, and they are partners left in any case.  Not
+  // so empty list places and rows with NaN, whose weight is NaN (cosine: rows with NaN are at
+  // distance 1).  Only nodes with `special` samples look, in loops of their own.
+  auto pair_is_lost = [&](float dot, int R, int C) {
+    if (METRIC == kCosineF32) {
+      const float nr = S.norms[R], nc = S.norms[C], product = nr * nc;
+      if (nr == 0.f || nc == 0.f) return dot != dot;  // distance 1, as the weights have it
+      return dot != dot || !(product >= kLeastNormal && product <= kMostFinite &&
+                             fminf(nr, nc) >= kHalfLeast);
+    }
+    const float larger = fmaxf(S.weight[R], S.weight[C]);
+    return dot != dot || !(larger <= kNormMost) ||
+           (METRIC == kL2F32 && !HALF && larger < least_sum);
+  };
+  auto over_pairs = [&](auto f) {  // product = f(product, row, column) of all pairs that are one
+    auto block = [&](f32x4& acc, int arow, int brow) {
+      const int col = brow + l16;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int R = arow + g4 + r;
+        const float w = S.weight[R] + S.weight[col];
+        if (w == w && is_pair(arow, brow, r, S.ids[R], S.ids[col])) acc[r] = f(acc[r], R, col);
+      }
+    };
+#pragma unroll
+    for (int rb = 0; rb < RBM; ++rb) {
+      if (rb < RB) {  // uniform
+#pragma unroll
+        for (int cb = 0; cb < COM; ++cb)
+          if (cb < CO) block(acc_no[rb][cb], 16 * rb, 64 + 16 * cb);
+        if (do_nn) {
+#pragma unroll
+          for (int cb = 0; cb <= rb; ++cb)
+            block(acc_nn[rb * (rb + 1) / 2 + cb], 16 * rb, 16 * cb);
+        }
+      }
+    }
+  };
+  if (special)
+    over_pairs([&](float dot, int R, int C) {
+      if (!pair_is_lost(dot, R, C)) return dot;
+      const uint32_t some = ord_f32(kMostFinite);  // both samples have a partner
+      atomicMin(&S.upper[C < 64 ? R : 64 + R], some);
+      atomicMin(&S.upper[C < 64 ? C : 64 + C], some);
+      return kNaN;
+    });
   // A pair of a NEW x OLD block serves the NEW sample's search among the OLD ones and the OLD
   // sample's among the NEW ones, a pair of a NEW x NEW block both of its samples.  First the
   // smallest upper bound per sample and direction: over a row's or a column's blocks inside
@@ -444,7 +511,7 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
           const int32_t idc = S.ids[col];
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            float v = bound(acc[r], base_r[r] + base_c, fac_r[r], fac_c, 3.4028235e38f);
+            float v = bound(acc[r], base_r[r] + base_c, fac_r[r], fac_c);
             v = is_pair(arow, brow, r, id_r[r], idc) ? v : kNaN;
             row[r] = fminf(row[r], v);
             col_min = fminf(col_min, v);
@@ -511,7 +578,7 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
         const float lim[4] = {row_limit.x, row_limit.y, row_limit.z, row_limit.w};
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          float v = bound(acc[r], base_r[r] + base_c, fac_r[r], fac_c, -3.4028235e38f);
+          float v = bound(acc[r], base_r[r] + base_c, fac_r[r], fac_c);
           v = is_pair(arow, brow, r, id_r[r], idc) ? v : kNaN;
           const int R = arow + g4 + r;
           if (v <= lim[r]) atomicOr(&S.cmask[(nn_block ? 0 : 64) + R], 1ull << (col & 63));
@@ -532,6 +599,14 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
       }
     }
   }
+  if (special)
+    over_pairs([&](float dot, int R, int C) {
+      if (dot != dot) {
+        atomicOr(&S.cmask[C < 64 ? R : 64 + R], 1ull << (C & 63));
+        atomicOr(&S.cmask[C < 64 ? C : 64 + C], 1ull << R);
+      }
+      return dot;
+    });
   __syncthreads();
 
   // ---- 4. canonical distances of the partners left --------------------------------------
@@ -761,12 +836,10 @@ __attribute__((amdgpu_waves_per_eu(gram_shape(CLS).waves, gram_shape(CLS).waves)
   const int32_t* const list = nodes + (int64_t)cls * n;
   GramTally tally;
   const float rho = HALF ? *hr.rho : 0.f;
-  const bool odd = HALF && *hr.odd != 0u;
   for (uint32_t i = blockIdx.x; i < mine; i += gridDim.x) {
     const int64_t s = list[i];
-    gram_node<METRIC, WHOLE, HALF, RBM, COM>(S, tile, vs, hr, rho, odd, s, p, merge_mode, snew,
-                                             sold, cnew[s], cold[s], meta, pslot, slots, bins,
-                                             tally);
+    gram_node<METRIC, WHOLE, HALF, RBM, COM>(S, tile, vs, hr, rho, s, p, merge_mode, snew, sold,
+                                             cnew[s], cold[s], meta, pslot, slots, bins, tally);
     __syncthreads();  // the LDS arrays are taken over by the next node
   }
   if (threadIdx.x == 0) {
@@ -795,9 +868,9 @@ __global__ __launch_bounds__(256) void k_gram_norms(int64_t n, const float* __re
 // adds up its own (64 partial sums, then a tree) and leaves it in the node's record.
 template <bool OWN_NORMS>
 __global__ __launch_bounds__(256) void k_half_rows(VecSrc vs, int64_t n, _Float16* out, int stride,
-                                                   NodeMeta* meta, uint32_t* rho, uint32_t* odd) {
-  __shared__ uint32_t largest, odd_here;
-  if (threadIdx.x == 0) largest = odd_here = 0u;
+                                                   NodeMeta* meta, uint32_t* rho) {
+  __shared__ uint32_t largest;
+  if (threadIdx.x == 0) largest = 0u;
   __syncthreads();
   const int lane = lane_id();
   constexpr int kRowsPerWave = 8;
@@ -818,9 +891,7 @@ __global__ __launch_bounds__(256) void k_half_rows(VecSrc vs, int64_t n, _Float1
     }
     const float root = sqrtf(norm);
     const bool zero = norm == 0.f;
-    // no copy below 2^-90 (squares of elements come near the denormal range, and the product of
-    // two scaled norms as well), nor of infinite norms and NaN
-    const bool none = !zero && !(norm >= 8.0779357e-28f && norm < __uint_as_float(0x7f800000u));
+    const bool none = !zero && !(norm >= kHalfLeast && norm <= kNormMost);
     const float scale = zero || none ? 0.f : (float)(1 << kHalfBits) / root;
     const float back = root * (1.0f / (1 << kHalfBits));  // as the join multiplies it on again
     _Float16* dst = out + s * stride;
@@ -842,17 +913,12 @@ __global__ __launch_bounds__(256) void k_half_rows(VecSrc vs, int64_t n, _Float1
     const bool lost = norm == 0.f && __ballot(any) != 0ull;
     if (lost)
       for (int j = lane; j < stride; j += kWave) dst[j] = (_Float16)__uint_as_float(0x7fc00000u);
-    if (lane == 0) {
-      if (none || lost) atomicAdd(&odd_here, 1u);
-      // (0.2 % more than measured covers the roundings of the sums and of the norm)
-      else if (!zero) atomicMax(&largest, __float_as_uint(sqrtf(err / norm) * 1.002f));
-    }
+    // (0.2 % more than measured covers the roundings of the sums and of the norm)
+    if (lane == 0 && !none && !zero)
+      atomicMax(&largest, __float_as_uint(sqrtf(err / norm) * 1.002f));
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    if (largest) atomicMax(rho, largest);
-    if (odd_here) atomicAdd(odd, odd_here);
-  }
+  if (threadIdx.x == 0 && largest) atomicMax(rho, largest);
 }
 
 int compute_units() {
@@ -879,12 +945,12 @@ hipError_t launch_gram_norms(const Shape& sh, const DevState& ds, hipStream_t st
 
 hipError_t launch_half_rows(const Shape& sh, const DevState& ds, hipStream_t st) {
   VecSrc vs{sh.vec_a, sh.vec_b, sh.split, sh.d, sh.norms};
-  hipError_t e = launch_zero_u32(ds.half_info, 2, st);
+  hipError_t e = launch_zero_u32(ds.half_info, 1, st);
   if (e != hipSuccess) return e;
   auto* const kernel = sh.metric == kCosineF32 ? k_half_rows<false> : k_half_rows<true>;
   kernel<<<grid_blocks((sh.n + 31) / 32), 256, 0, st>>>(
       vs, sh.n, static_cast<_Float16*>(ds.half_rows), (int)half_row_elems(sh.d), ds.meta,
-      ds.half_info, ds.half_info + 1);
+      ds.half_info);
   return hipGetLastError();
 }
 
@@ -905,7 +971,7 @@ hipError_t launch_join_gram(const Shape& sh, const DevState& ds, bool merge_mode
   const int64_t cap = (int64_t)64 * compute_units();
   const unsigned grid = (unsigned)(sh.n < cap ? sh.n : cap);
   const HalfRows hr{static_cast<const _Float16*>(ds.half_rows), (int32_t)half_row_elems(sh.d),
-                    reinterpret_cast<const float*>(ds.half_info), ds.half_info + 1};
+                    reinterpret_cast<const float*>(ds.half_info)};
 #define GNND_GRAM_ARGS vs, hr, sh.n, sh.p, mm, ds.snew, ds.sold, ds.cnew, ds.cold, ds.meta, ds.pslot, \
                        slots, ds.bins, ds.counters, ds.cls_nodes, ds.cls_count
   // (in a merge no node without OLD samples has work to do; lists of up to 2p samples do not

@@ -65,8 +65,7 @@ struct DevState {
   int32_t* cls_nodes;
   uint32_t* cls_count;
   // float32 matrix-core join: 16-bit copies of the rows divided by their norms (NULL: it reads
-  // the float32 rows twice instead), and what is known of them: the largest relative error
-  // (float bits), the number of rows without a copy
+  // the float32 rows twice instead), and the largest relative error of a copy (float bits)
   void* half_rows;
   uint32_t* half_info;
 };
