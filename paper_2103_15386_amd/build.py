@@ -8,8 +8,10 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgnnd_hip.so")
-SOURCES = ["graph_kernels.hip", "wide_lists.hip", "long_samples.hip", "segmented_lists.hip", "join_valu.hip",
-           "join_mfma.hip", "join_gram.hip", "join_long_i8.hip", "sample_buckets.hip", "exact_knn.hip",
+# (the slowest to compile first)
+SOURCES = ["join_gram_l2.hip", "join_gram_cosine.hip", "join_gram_angular.hip", "join_mfma.hip",
+           "join_valu.hip", "exact_knn.hip", "graph_kernels.hip", "wide_lists.hip", "long_samples.hip",
+           "segmented_lists.hip", "join_gram.hip", "join_long_i8.hip", "sample_buckets.hip",
            "gnnd_api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-result",

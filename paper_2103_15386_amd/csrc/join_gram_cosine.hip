@@ -1,0 +1,6 @@
+// The builds of the float32 matrix-core join for the cosine distance.
+#include "join_gram.hpp"
+
+namespace gnnd {
+template void launch_gram_builds<kCosineF32>(const Shape&, const DevState&, int, unsigned, hipStream_t);
+}  // namespace gnnd
