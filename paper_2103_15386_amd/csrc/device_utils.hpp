@@ -505,6 +505,29 @@ __device__ inline void list_nodes_by_class(int64_t n, int32_t* nodes, uint32_t* 
           (int32_t)(first + j * 256 + threadIdx.x);
 }
 
+// Whether the faster first form of a join is worth trying for a node, by how that has gone so
+// far: nodes tried (upper half of a word) and nodes it was given up for (lower half).  Where that
+// was more than every third, it is tried for one node in 16 only.  What is counted decides on
+// time alone, never on results, so a sample is enough: one wavefront (or node) in 64 adds to the
+// word (with all of them the waves queued for it: 30,000 x 96, six iterations 2.18 -> 2.5 ms),
+// and the sampling stage makes the past count little against the coming iteration.
+struct FormTally {
+  uint64_t seen;  // as the word was when the wavefront began, and its own nodes
+  uint64_t own = 0;
+  __device__ explicit FormTally(uint64_t word) : seen(word) {}
+  __device__ bool promising(uint32_t node) const {
+    return 3 * (seen & 0xffffffffull) <= (seen >> 32) || (node & 15u) == 0u;
+  }
+  __device__ void count(bool given_up) {
+    const uint64_t one = (1ull << 32) | (given_up ? 1ull : 0ull);
+    seen += one;
+    own += one;
+  }
+  __device__ static uint64_t faded(uint64_t word) {
+    return word >> 37 << 32 | (word & 0xffffffffull) >> 5;
+  }
+};
+
 // Numbering inside one merge (Sec. 5.1 shards).  The two sets are the ranges
 // [base1, base1 + n1) and [base2, base2 + n2) of a larger collection; inside
 // the merge S1 is 0..n1-1, S2 is n1..n-1, and any other object (a list entry

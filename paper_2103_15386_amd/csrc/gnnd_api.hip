@@ -157,7 +157,7 @@ Layout make_layout(const gnnd_params* q, bool with_aside, bool extra = true) {
       q->update_mode == GNND_UPDATE_ALL_PAIRS ? 2 * p * (6 * p - 1) : 6 * p;
   L.off_bins = take(n * slots_per_node * 8);
   L.off_scan = take(scan_tmp_elems((int64_t)n) * 8);
-  L.off_cnt = take((size_t)kStripes * C_SLOTS * 8);
+  L.off_cnt = take((size_t)kStripes * C_SLOTS * 8 + 8);  // (and DevState::forms)
   L.off_snap = take((size_t)kStripes * C_SLOTS * 8);
   L.off_aside = take(with_aside ? n * (k / 2) * 8 : 0);
   const bool shadow = mfma_possible(q) || (extra && long_i8_possible(q));
@@ -242,6 +242,7 @@ void bind(gnnd_ctx* c, const Layout& L) {
   d.counters = (uint64_t*)(w + L.off_cnt);
   d.aside = (uint64_t*)(w + L.off_aside);
   d.snap = (uint64_t*)(w + L.off_snap);
+  d.forms = d.counters + (size_t)kStripes * C_SLOTS;
   d.shadow = (int8_t*)(w + L.off_shadow);
   c->flag_dev = (int*)(w + L.off_flag);
   d.bk_cnt = (uint32_t*)(w + L.off_bkc);
@@ -283,7 +284,7 @@ int init_ctx(gnnd_ctx* c, const gnnd_params* prm, const Layout& L, const void* v
   // first sampling stage writes them
   hipError_t e = launch_zero_u32((uint32_t*)c->ds.pslot, 2 * (size_t)prm->n, c->stream);
   if (e == hipSuccess)
-    e = launch_zero_u32((uint32_t*)c->ds.counters, (size_t)kStripes * C_SLOTS * 2, c->stream);
+    e = launch_zero_u32((uint32_t*)c->ds.counters, ((size_t)kStripes * C_SLOTS + 1) * 2, c->stream);
   if (e != hipSuccess) return hip_fail(nullptr, e, "clearing workspace counters");
   // matrix-core path: build the int8 copy; float data qualifies only when every
   // value is an integer in 0..255 (then all distances are exact either way)

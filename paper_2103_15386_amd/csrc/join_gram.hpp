@@ -147,8 +147,10 @@ struct GramTally {
   uint64_t found = 0, passed = 0, overflow = 0, evals = 0;
 };
 
-template <int METRIC, bool WHOLE, bool HALF, int RBM, int COM>
-__device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc& vs,
+// Returns false where the 16-bit form has been given up (HALF only): nothing has been handed on
+// or counted then.  FORM: see k_join_gram.
+template <int METRIC, int FORM, bool HALF, int RBM, int COM>
+__device__ __forceinline__ bool gram_node(GramLds& S, float* tile, const VecSrc& vs,
                                           const HalfRows& hr, float rho, int64_t s, int p,
                                           int merge_mode,
                                           const int32_t* __restrict__ snew,
@@ -211,8 +213,9 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
   // so that the number of loads in flight is known where the products wait for them; where
   // the vector ends after the first of the two steps, the second reads that step once more.
   const int d_last = ((d - 1) / kWC) * kWC;
+  // every step reads 16 present dimensions (FORM 2: the builds with both forms look at it here)
+  const bool whole = FORM == 1 || (FORM == 2 && d % kWC == 0);
   auto fetch_one = [&](const float* src, int j) {
-    if (WHOLE) return *reinterpret_cast<const float4*>(src);
     // dimensions beyond the last one count as zeros
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     if (aligned && j + 3 < d) {
@@ -227,10 +230,18 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
   };
   auto fetch2 = [&](float4* fa, float4* fb, int d0) {
     const int d1 = d0 + kWC < d_last ? d0 + kWC : d_last;
+    if (whole) {  // uniform
 #pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      fa[q] = fetch_one(rows[q] + d0, d0 + g4);
-      fb[q] = fetch_one(rows[q] + d1, d1 + g4);
+      for (int q = 0; q < NB; ++q) {
+        fa[q] = *reinterpret_cast<const float4*>(rows[q] + d0);
+        fb[q] = *reinterpret_cast<const float4*>(rows[q] + d1);
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < NB; ++q) {
+        fa[q] = fetch_one(rows[q] + d0, d0 + g4);
+        fb[q] = fetch_one(rows[q] + d1, d1 + g4);
+      }
     }
   };
   float4 opa[NB], opb[NB];
@@ -647,7 +658,7 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
 #pragma unroll
   for (int t = 0; t < 3; ++t) S.best[64 * t + lane] = kKeyMax;
   PairList& list = *reinterpret_cast<PairList*>(S.weight);
-  for (;;) {
+  for (bool first = true;; first = false) {
     // places of this lane's pairs among all of them
     const uint32_t count =
         (uint32_t)(__popcll(todo[0]) + __popcll(todo[1]) + __popcll(todo[2]));
@@ -660,6 +671,8 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
     inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x142, 0xA, 0xF, false);  // row_bcast:15
     inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x143, 0xC, 0xF, false);  // row_bcast:31
     const uint32_t all = __builtin_amdgcn_readlane(inc, 63);
+    // (three passes and more; two cost less than the float32 form's first reading)
+    if (HALF && first && all > 2u * 64u * kWItems) return false;
     const uint32_t here = all < 64u * kWItems ? all : 64u * kWItems;
     __syncthreads();  // the weights, or the list before this one, are no longer needed
     reinterpret_cast<uint16_t*>(list.wanted)[lane] = 0;
@@ -799,21 +812,31 @@ __device__ __forceinline__ void gram_node(GramLds& S, float* tile, const VecSrc&
   tally.evals += merge_mode ? fa * ((uint64_t)no - fb) + ((uint64_t)nn - fa) * fb
                             : (uint64_t)nn * no - n_dup;
   if (do_nn) tally.evals += (uint64_t)nn * (nn - 1) / 2;
+  return true;
 }
 
-// WHOLE: the dimension is a multiple of 16, every step reads 16 present dimensions.
 // CLS: the build (gram_shape); it takes the nodes of its class from that class's list.  The
 // accumulators of all blocks and two sets of operands live in registers, and a build for
 // fewer blocks runs more wavefronts per SIMD and reads and multiplies fewer empty blocks.
 // Persistent wavefronts: wavefront w takes the list's places w, w + (number of wavefronts), ...
-template <int METRIC, bool WHOLE, bool HALF, int CLS>
+// FORM: 0, 1 - there are no 16-bit copies (1: the dimension is a multiple of 16); 2 - there are.
+//
+// The error of the 16-bit copies is relative to the rows' norms.  Where the distances are small
+// against those (vectors far from the origin, directions close to each other) it leaves too many
+// partners; such a node is worked on once more in the float32 form, and where that happens often
+// the 16-bit form is hardly tried any more (FormTally).
+// Builds of 200,000 x 96 Gaussian vectors, k = p = 32, six iterations, squared L2, offset from the
+// origin 0 / 10 / 30 standard deviations: 11.0 / 13.4 / 17.9 ms; with the 16-bit form for all nodes
+// 11.1 / 13.4 / 44.1, with the float32 form for all of them in the build made for it alone 14.7 /
+// 15.5 / 21.6 (measured before steps 2 and 4 took their present form).
+template <int METRIC, int FORM, int CLS>
 __global__ __launch_bounds__(kWave)
 __attribute__((amdgpu_waves_per_eu(gram_shape(CLS).waves, gram_shape(CLS).waves))) void k_join_gram(
     VecSrc vs, HalfRows hr, int64_t n, int p, int merge_mode, const int32_t* __restrict__ snew,
     const int32_t* __restrict__ sold, const int32_t* __restrict__ cnew,
     const int32_t* __restrict__ cold, const NodeMeta* __restrict__ meta, uint64_t* pslot,
     uint64_t slots, uint64_t* __restrict__ bins, uint64_t* counters,
-    const int32_t* __restrict__ nodes, const uint32_t* __restrict__ count) {
+    uint64_t* forms, const int32_t* __restrict__ nodes, const uint32_t* __restrict__ count) {
   constexpr int RBM = gram_shape(CLS).rbm, COM = gram_shape(CLS).com;
   constexpr int NB = RBM + COM;
   constexpr int cls = CLS;
@@ -823,12 +846,27 @@ __attribute__((amdgpu_waves_per_eu(gram_shape(CLS).waves, gram_shape(CLS).waves)
   const uint32_t mine = count[cls];
   const int32_t* const list = nodes + (int64_t)cls * n;
   GramTally tally;
-  const float rho = HALF ? *hr.rho : 0.f;
+  constexpr bool kCopies = FORM == 2;
+  const float rho = kCopies ? *hr.rho : 0.f;
+  FormTally first_form(kCopies ? *forms : 0ull);
   for (uint32_t i = blockIdx.x; i < mine; i += gridDim.x) {
     const int64_t s = list[i];
-    gram_node<METRIC, WHOLE, HALF, RBM, COM>(S, tile, vs, hr, rho, s, p, merge_mode, snew, sold,
-                                             cnew[s], cold[s], meta, pslot, slots, bins, tally);
-    __syncthreads();  // the LDS arrays are taken over by the next node
+    const int nn = cnew[s], no = cold[s];
+    bool done = false;
+    if constexpr (kCopies) {
+      if (first_form.promising((uint32_t)s)) {
+        done = gram_node<METRIC, FORM, true, RBM, COM>(S, tile, vs, hr, rho, s, p, merge_mode,
+                                                       snew, sold, nn, no, meta, pslot, slots,
+                                                       bins, tally);
+        first_form.count(!done);
+        __syncthreads();  // the LDS arrays are taken over by the next node (or form)
+      }
+    }
+    if (!done) {
+      gram_node<METRIC, FORM, false, RBM, COM>(S, tile, vs, hr, rho, s, p, merge_mode, snew, sold,
+                                               nn, no, meta, pslot, slots, bins, tally);
+      __syncthreads();
+    }
   }
   if (threadIdx.x == 0) {
     uint64_t* cs = counters + (blockIdx.x & (kStripes - 1)) * C_SLOTS;
@@ -840,6 +878,8 @@ __attribute__((amdgpu_waves_per_eu(gram_shape(CLS).waves, gram_shape(CLS).waves)
                                (unsigned long long)tally.found);
     if (tally.evals) atomicAdd(reinterpret_cast<unsigned long long*>(cs + C_EVALS),
                                (unsigned long long)tally.evals);
+    if (kCopies && first_form.own != 0ull && blockIdx.x % 64 == 0)
+      atomicAdd(reinterpret_cast<unsigned long long*>(forms), (unsigned long long)first_form.own);
   }
 }
 
@@ -859,14 +899,14 @@ void launch_gram_builds(const Shape& sh, const DevState& ds, int mm, unsigned gr
   for (int rb = 1; rb <= (2 * sh.p + 15) / 16; ++rb)
     for (int co = mm ? 1 : 0; co <= (2 * sh.p + 15) / 16; ++co)
       reached[gram_class(rb, co)] = true;
-  auto form = [&](auto whole, auto half) {
-    constexpr bool W = decltype(whole)::value, H = decltype(half)::value;
+  auto builds = [&](auto form) {
+    constexpr int F = decltype(form)::value;
     auto build = [&](auto cls) {
       constexpr int C = decltype(cls)::value;
       if (reached[C])
-        k_join_gram<METRIC, W, H, C><<<grid, kWave, 0, st>>>(
+        k_join_gram<METRIC, F, C><<<grid, kWave, 0, st>>>(
             vs, hr, sh.n, sh.p, mm, ds.snew, ds.sold, ds.cnew, ds.cold, ds.meta, ds.pslot, slots,
-            ds.bins, ds.counters, ds.cls_nodes, ds.cls_count);
+            ds.bins, ds.counters, ds.forms, ds.cls_nodes, ds.cls_count);
     };
     build(std::integral_constant<int, 0>{});
     build(std::integral_constant<int, 1>{});
@@ -876,15 +916,9 @@ void launch_gram_builds(const Shape& sh, const DevState& ds, int mm, unsigned gr
     build(std::integral_constant<int, 5>{});
     build(std::integral_constant<int, 6>{});
   };
-  using Yes = std::true_type;
-  using No = std::false_type;
-  if (sh.d % kWC == 0) {
-    if (ds.half_rows) form(Yes{}, Yes{});
-    else form(Yes{}, No{});
-  } else {
-    if (ds.half_rows) form(No{}, Yes{});
-    else form(No{}, No{});
-  }
+  if (ds.half_rows) builds(std::integral_constant<int, 2>{});
+  else if (sh.d % kWC == 0) builds(std::integral_constant<int, 1>{});
+  else builds(std::integral_constant<int, 0>{});
 }
 
 }  // namespace gnnd

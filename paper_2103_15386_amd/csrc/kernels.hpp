@@ -51,6 +51,7 @@ struct DevState {
   uint64_t* scan_tmp;  // block sums of the scans
   uint64_t* counters;  // kStripes * C_SLOTS
   uint64_t* snap;      // the counters as the current iteration's sampling stage found them
+  uint64_t* forms;     // joins with a faster first form: how it has gone so far (see FormTally)
   uint64_t* aside;     // merge only: n * floor(k/2) set-aside entries
   int8_t* shadow;      // matrix-core path: n rows of dpad int8 (value - 128), zero padded
   uint32_t* bk_cnt;    // 2 x 4096 bucket sizes of the bucketed reverse-candidate sort

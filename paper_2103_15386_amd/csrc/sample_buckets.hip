@@ -168,10 +168,12 @@ __global__ __launch_bounds__(kSB) void k_fwd_count(int64_t n, int k, int p, Buck
 // what the cross-matching adds to.
 __global__ __launch_bounds__(kSB) void k_wg_scan(int W, int rows, uint32_t* wg_hist,
                                                  uint32_t* bcnt, const uint64_t* counters,
-                                                 uint64_t* snap, uint32_t* cls_count,
+                                                 uint64_t* snap, uint64_t* forms,
+                                                 uint32_t* cls_count,
                                                  unsigned long long* stg_cur) {
   if (blockIdx.x == gridDim.x - 1) {
     for (int i = threadIdx.x; i < kStripes * C_SLOTS; i += kSB) snap[i] = counters[i];
+    if (threadIdx.x == 0) *forms = FormTally::faded(*forms);
     if (cls_count && threadIdx.x < kNodeClassesMax) cls_count[threadIdx.x] = 0u;
     if (stg_cur)
       for (int i = threadIdx.x; i < kStageBuckets; i += kSB) stg_cur[i] = 0ull;
@@ -502,7 +504,8 @@ hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, hipStream_
     k_fwd_count<false><<<grid, kSB, 0, st>>>(sh.n, sh.k, sh.p, g, ds.G, ds.snew, ds.sold, ds.cnew,
                                              ds.cold, wg_hist);
   k_wg_scan<<<(unsigned)((2 * g.nb + kSB / kWave - 1) / (kSB / kWave)) + 1, kSB, 0, st>>>(
-      (int)grid, 2 * g.nb, wg_hist, bcnt, ds.counters, ds.snap, ds.cls_count, ds.stg_cur);
+      (int)grid, 2 * g.nb, wg_hist, bcnt, ds.counters, ds.snap, ds.forms,
+      ds.cls_count, ds.stg_cur);
   static bool staged_attr = false;
   if (!staged_attr) {
     hipError_t e = hipSuccess;
