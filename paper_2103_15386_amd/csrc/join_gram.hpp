@@ -878,7 +878,7 @@ __attribute__((amdgpu_waves_per_eu(gram_shape(CLS).waves, gram_shape(CLS).waves)
                                (unsigned long long)tally.found);
     if (tally.evals) atomicAdd(reinterpret_cast<unsigned long long*>(cs + C_EVALS),
                                (unsigned long long)tally.evals);
-    if (kCopies && first_form.own != 0ull && blockIdx.x % 64 == 0)
+    if (kCopies && first_form.own != 0ull && FormTally::in_64(blockIdx.x))
       atomicAdd(reinterpret_cast<unsigned long long*>(forms), (unsigned long long)first_form.own);
   }
 }

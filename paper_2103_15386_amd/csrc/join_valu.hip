@@ -21,10 +21,14 @@
 // and the few pairs that can be a sample's nearest one within that bound (one per sample and
 // direction as a rule) are summed once more in the canonical arithmetic.  A node whose vectors
 // leave the range the bound is derived for, or with more such pairs than the list holds, is
-// evaluated in the canonical arithmetic throughout.  100,000 x 96, k = 20, p = 16,
-// 6 iterations: 21.7 -> 13.5 ms per build together with the smaller build for lists of up to 32
-// samples (at the registers and LDS of 64-sample lists the first pass alone gave 1 %: the
-// phases of three workgroups per CU did not overlap).  Bound: vector-ALU issue.
+// evaluated in the canonical arithmetic throughout; where that was more than every third node
+// (negative values, ties en masse) the others are hardly tried any more (FormTally).
+// 100,000 x 96, k = 20, p = 16, 6 iterations: 21.7 -> 12.3 ms per build together with the smaller
+// build for lists of up to 32 samples (at the registers and LDS of 64-sample lists the first pass
+// alone gave 1 %: the phases of three workgroups per CU did not overlap; with 128 registers, four
+// workgroups, 60,000 x 96, k = p = 32 takes 13.8 ms instead of 23.3 with the canonical sums alone).
+// Where values are negative throughout: 19.7 ms, against 19.3 with the canonical sums alone and
+// 30.9 with both for every node.  Bound: vector-ALU issue.
 #include "device_utils.hpp"
 #include "kernels.hpp"
 
@@ -95,7 +99,7 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
     VecSrc vs, int64_t n, int p, int merge_mode, const int32_t* __restrict__ snew,
     const int32_t* __restrict__ sold, const int32_t* __restrict__ cnew,
     const int32_t* __restrict__ cold, const NodeMeta* __restrict__ meta, uint64_t* pslot,
-    uint64_t slots, uint64_t* __restrict__ bins, uint64_t* counters) {
+    uint64_t slots, uint64_t* __restrict__ bins, uint64_t* counters, uint64_t* forms) {
   using TR = JoinTraits<METRIC>;
   using T = typename TR::elem;
   using ACC = typename TR::acc;
@@ -114,6 +118,7 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
   __shared__ float limit_s[kTwice ? 192 : 1];
   __shared__ uint32_t again_s[kTwice ? kChiPairs : 1];
   __shared__ uint32_t again_count;
+  __shared__ bool twice_s;  // kTwice: this node is worth the two passes
   constexpr bool kNorms = METRIC == kCosineF32;
   static_assert(!ALL || 2 * kRows * kLD >= 64 * kDLD,
                 "distance matrix must fit in the staging tile");
@@ -141,7 +146,12 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
     if (tid == 0) pair_count = 0;
     if (kTwice) {
       if (tid < 192) min_s[tid] = 0xffffffffu;
-      if (tid == 0) again_count = 0;
+      if (tid == 0) {
+        again_count = 0;
+        // (as the workgroups on all parts of the chip have left it, not as this part's cache has it)
+        const uint64_t so_far = __hip_atomic_load(forms, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        twice_s = FormTally(so_far).promising((uint32_t)s);
+      }
     }
   }
   const bool do_nn = !merge_mode && nn > 1;
@@ -192,6 +202,7 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
     for (int d0 = 0; d0 < d; d0 += kDC) {
       const int width = stage(d0, check);
       const int nsub = (width + 15) >> 4;
+#pragma unroll 1
       for (int sub = 0; sub < nsub; ++sub) {
         ACC a[RBM][16];
 #pragma unroll
@@ -244,7 +255,8 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
   };
   uint32_t found = 0;      // kTwice: this sample has a partner
   bool decided = false;    // kTwice: the pairs summed again have settled the node
-  if constexpr (kTwice) {
+  const bool twice = kTwice && __builtin_amdgcn_readfirstlane((int)twice_s) != 0;
+  if constexpr (kTwice) if (twice) {
     evaluate(chi2_two_approx, true);
     if (!in_range) again_count = kChiPairs + 1;  // (any thread's word is enough)
     // Both sums differ from the true one by at most (d + 12) u of it, u = 2^-24: a term takes
@@ -337,8 +349,12 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
       }
     });
     __syncthreads();
-    const uint32_t again = again_count;
+    const uint32_t again = __builtin_amdgcn_readfirstlane(again_count);
     decided = again <= (uint32_t)kChiPairs;
+    // (of the nodes that are tried in any case: a fair sample)
+    if (tid == 0 && FormTally::in_64((uint32_t)s))
+      atomicAdd(reinterpret_cast<unsigned long long*>(forms),
+                (1ull << 32) | (decided ? 0ull : 1ull));
     if (decided) {  // uniform
       const uint32_t pair = (uint32_t)tid < again ? again_s[tid] : 0u;
       const int R = (int)(pair & 127u), C = (int)((pair >> 7) & 127u);
@@ -604,7 +620,7 @@ static void launch_join_as(const Shape& sh, const DevState& ds, bool merge_mode,
   const uint64_t slots = (uint64_t)sh.slots();  // size of the proposal array
   const int mm = merge_mode ? 1 : 0;
 #define GNND_JOIN_ARGS vs, sh.n, sh.p, mm, ds.snew, ds.sold, ds.cnew, ds.cold, ds.meta, ds.pslot, \
-                       slots, ds.bins, ds.counters
+                       slots, ds.bins, ds.counters, ds.forms
   switch (sh.metric) {
     case kL2F32: k_join_valu<kL2F32, ALL, RBM><<<grid, kJB, 0, st>>>(GNND_JOIN_ARGS); break;
     case kAngularF32: k_join_valu<kAngularF32, ALL, RBM><<<grid, kJB, 0, st>>>(GNND_JOIN_ARGS); break;

@@ -25,10 +25,15 @@ def _vectors(kind, n, d):
         x[:5] = 0.0
     elif kind == "negative":  # the distance skips dimensions with a + b <= 0
         x[3::11, 0] = -0.5
+    elif kind == "signed":  # every node leaves the range: hardly one is tried in two passes
+        x -= np.float32(x.mean())
+    elif kind == "last_negative":  # seen in the last chunk of dimensions only
+        x[:, d - 1] = -1.0
     return x
 
 
-@pytest.mark.parametrize("kind", ["plain", "copies", "small", "large", "zeros", "negative"])
+@pytest.mark.parametrize("kind", ["plain", "copies", "small", "large", "zeros", "negative",
+                                  "signed", "last_negative"])
 @pytest.mark.parametrize("d,k,p", [(64, 32, 32), (65, 20, 16), (130, 24, 20), (3, 10, 8)])
 def test_chi2_join_matches_oracle(kind, d, k, p):
     import paper_2103_15386_amd as amd
