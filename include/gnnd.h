@@ -146,7 +146,10 @@ size_t gnnd_workspace_bytes(const gnnd_params* prm);
 
 /* Create a context over `vectors_dev`: n*d elements, row-major, float32 or
  * uint8 according to the metric, 16-byte aligned.  Validates everything, lays
- * the workspace out and clears its counters (enqueued on the stream). */
+ * the workspace out and clears its counters (enqueued on the stream).  Squared-L2
+ * float32 vectors of up to 128 dimensions are looked at (are they byte valued?),
+ * which synchronises the stream: with p <= 32 under GNND_JOIN_AUTO and the MFMA forms, with
+ * p > 32 under GNND_JOIN_AUTO unless the stream is capturing a graph. */
 int gnnd_create(gnnd_ctx** out, const gnnd_params* prm, const void* vectors_dev);
 void gnnd_destroy(gnnd_ctx* ctx);
 
@@ -161,8 +164,8 @@ const char* gnnd_last_error(const gnnd_ctx* ctx);
  * 0..255; other float32 vectors take GNND_JOIN_GRAM where it applies (squared
  * L2, angular, cosine; p <= 32; selective update); GNND_JOIN_VALU otherwise).
  * Sample numbers beyond 32 report GNND_JOIN_VALU, also where GNND_JOIN_AUTO evaluates
- * byte-valued data (d <= 128; float32 vectors in a context of gnnd_create's) on the int8
- * matrix cores: the same integers.  Negative on a NULL context. */
+ * byte-valued data (d <= 128; float32 vectors in a context of gnnd_create's that was not
+ * created under capture) on the int8 matrix cores: the same integers.  Negative on a NULL context. */
 int gnnd_join_path(const gnnd_ctx* ctx);
 
 /* Stage timing without synchronising inside the loop.  gnnd_set_profiling(ctx,

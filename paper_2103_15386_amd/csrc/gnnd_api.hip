@@ -256,6 +256,16 @@ void bind(gnnd_ctx* c, const Layout& L) {
   d.half_info = (uint32_t*)(w + L.off_flag) + 1;
 }
 
+// Whether a graph is being captured on the stream (where nothing can be read back).  Asking
+// about the default stream while another one captures is itself an error: taken as yes.
+bool is_capturing(hipStream_t stream) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &status) == hipSuccess)
+    return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // Fill in a default-constructed context (no allocation of any kind): layout,
 // cleared counters, per-vector norms, int8 copy.  `may_sync` = the caller allows
 // a stream synchronisation: float32 data qualify for the matrix-core join only
@@ -289,10 +299,10 @@ int init_ctx(gnnd_ctx* c, const gnnd_params* prm, const Layout& L, const void* v
   // matrix-core path: build the int8 copy; float data qualifies only when every
   // value is an integer in 0..255 (then all distances are exact either way)
   c->use_mfma = c->use_long_i8 = false;
-  // (the long join looks at float data only where it did not use to run before anything could
-  // wait for the verdict: in a context of the caller's own)
+  // (the long join looks at float data only in a context of the caller's own, and not where one is
+  // created in a captured graph: appends, merges and captured builds with p > 32 read nothing back)
   const bool long_i8 = L.extra && long_i8_possible(prm) &&
-                       (prm->metric == GNND_L2SQ_U8 || own_context);
+                       (prm->metric == GNND_L2SQ_U8 || (own_context && !is_capturing(c->stream)));
   if (long_i8 || (mfma_possible(prm) && (may_sync || prm->metric == GNND_L2SQ_U8))) {
     int bad = 0;
     e = launch_zero_u32((uint32_t*)c->flag_dev, 1, c->stream);
