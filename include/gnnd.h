@@ -110,7 +110,7 @@ typedef struct gnnd_params {
   uint64_t seed;  /* seed of all random draws                                       */
   void* stream;   /* hipStream_t; NULL = the default stream                         */
   void* workspace_dev;    /* device scratch, 256-byte aligned, caller-owned         */
-  size_t workspace_bytes; /* its size, >= gnnd_workspace_bytes()                    */
+  size_t workspace_bytes; /* its size, >= gnnd_workspace_bytes_min()                */
   int32_t join_path;      /* GNND_JOIN_*                                            */
   int32_t update_mode;    /* GNND_UPDATE_*; 0 = the method as published             */
   int32_t list_mode;      /* GNND_LISTS_*; 0 = plain lists                          */
@@ -139,10 +139,11 @@ typedef struct gnnd_iter_stats {
  * float32 matrix-core join applies and d >= 24 this includes room for a 16-bit
  * copy of the vectors (2 bytes per dimension, padded to 32), with p > 32 on
  * uint8 or squared-L2 vectors of up to 128 dimensions for an int8 copy, and with
- * 2^20 < n <= 2^22 on such vectors for the results the int8 join stages; a
- * workspace that is smaller by that much is accepted as well and gives the same
- * results, more slowly. */
+ * 2^20 < n <= 2^22 on such vectors for the results the int8 join stages.  A
+ * workspace without that room, of gnnd_workspace_bytes_min() bytes or more, is
+ * accepted as well and gives the same results, more slowly. */
 size_t gnnd_workspace_bytes(const gnnd_params* prm);
+size_t gnnd_workspace_bytes_min(const gnnd_params* prm);
 
 /* Create a context over `vectors_dev`: n*d elements, row-major, float32 or
  * uint8 according to the metric, 16-byte aligned.  Validates everything, lays
@@ -293,6 +294,8 @@ typedef struct gnnd_shard_stats {
   float reserved;
 } gnnd_shard_stats;
 size_t gnnd_sharded_arena_bytes(const gnnd_params* prm, int32_t shards);
+/* ... and the smallest arena: the same graph, more slowly (see gnnd_workspace_bytes) */
+size_t gnnd_sharded_arena_bytes_min(const gnnd_params* prm, int32_t shards);
 int gnnd_build_sharded(const gnnd_params* prm, const void* vectors_host, int32_t shards,
                        int32_t build_iters, int32_t merge_iters, int32_t* ids_host,
                        void* dist_host, void* copy_stream, gnnd_shard_stats* stats_host);

@@ -19,11 +19,13 @@ _LIB_PATH = os.path.join(_HERE, "libgnnd_hip.so")
 _lib = None
 
 EXPORTS = [
-    "gnnd_workspace_bytes", "gnnd_create", "gnnd_destroy", "gnnd_last_error", "gnnd_init_random",
+    "gnnd_workspace_bytes", "gnnd_workspace_bytes_min", "gnnd_create", "gnnd_destroy",
+    "gnnd_last_error", "gnnd_init_random",
     "gnnd_iterate", "gnnd_step_sample", "gnnd_step_join", "gnnd_step_update", "gnnd_build",
     "gnnd_get_graph", "gnnd_set_graph", "gnnd_get_samples", "gnnd_get_proposals", "gnnd_merge",
     "gnnd_exact_knn", "gnnd_join_path", "gnnd_set_profiling", "gnnd_get_stage_ms",
-    "gnnd_sharded_arena_bytes", "gnnd_build_sharded", "gnnd_build_sharded_files", "gnnd_append",
+    "gnnd_sharded_arena_bytes", "gnnd_sharded_arena_bytes_min", "gnnd_build_sharded",
+    "gnnd_build_sharded_files", "gnnd_append",
     "gnnd_build_static",
 ]
 
@@ -74,8 +76,9 @@ def load_library():
     vp, i32, i64 = C.c_void_p, C.c_int32, C.c_int64
     PP = C.POINTER(Params)
     SP = C.POINTER(IterStats)
-    lib.gnnd_workspace_bytes.restype = C.c_size_t
-    lib.gnnd_workspace_bytes.argtypes = [PP]
+    for name in ("gnnd_workspace_bytes", "gnnd_workspace_bytes_min"):
+        getattr(lib, name).restype = C.c_size_t
+        getattr(lib, name).argtypes = [PP]
     lib.gnnd_create.restype = C.c_int
     lib.gnnd_create.argtypes = [C.POINTER(vp), PP, vp]
     lib.gnnd_destroy.restype = None
@@ -103,8 +106,9 @@ def load_library():
     lib.gnnd_merge.argtypes = [PP, vp, i64, i64, vp, i64, i64, i64, vp, vp, vp, vp, i32, vp, vp, SP]
     lib.gnnd_append.restype = C.c_int
     lib.gnnd_append.argtypes = [PP, vp, i64, vp, vp, vp, i64, i32, i32, vp, vp]
-    lib.gnnd_sharded_arena_bytes.restype = C.c_size_t
-    lib.gnnd_sharded_arena_bytes.argtypes = [PP, i32]
+    for name in ("gnnd_sharded_arena_bytes", "gnnd_sharded_arena_bytes_min"):
+        getattr(lib, name).restype = C.c_size_t
+        getattr(lib, name).argtypes = [PP, i32]
     lib.gnnd_build_sharded.restype = C.c_int
     lib.gnnd_build_sharded.argtypes = [PP, vp, i32, i32, i32, vp, vp, vp, C.POINTER(ShardStats)]
     lib.gnnd_build_sharded_files.restype = C.c_int
@@ -178,6 +182,30 @@ def workspace_bytes(n, d, k, p, metric, update_mode=UPDATE_SELECTIVE, list_mode=
     return int(load_library().gnnd_workspace_bytes(C.byref(prm)))
 
 
+def _scratch(full, least, dev):
+    """Device scratch of `full` bytes; of least() bytes where memory is short: what lies between
+    only makes a call faster, and whatever fits without it has to go on fitting.  More than 1 GiB of
+    it is taken only if an eighth of the card stays free for what the program allocates next."""
+    if (full > 1 << 30 and full - least() > 1 << 30
+            and not torch.cuda.is_current_stream_capturing()):
+        free, total = torch.cuda.mem_get_info(dev)
+        free += torch.cuda.memory_reserved(dev) - torch.cuda.memory_allocated(dev)
+        if free - full < total // 8:
+            full = least()
+    try:
+        return torch.empty(full, dtype=torch.uint8, device=dev)
+    except torch.cuda.OutOfMemoryError:
+        if full == least():
+            raise
+    return torch.empty(least(), dtype=torch.uint8, device=dev)
+
+
+def _workspace(prm, dev):
+    lib = load_library()
+    return _scratch(max(int(lib.gnnd_workspace_bytes(C.byref(prm))), 256),
+                    lambda: max(int(lib.gnnd_workspace_bytes_min(C.byref(prm))), 256), dev)
+
+
 class Gnnd:
     """One GNND context over a resident vector tensor (n x d, float32 or uint8)."""
 
@@ -188,14 +216,13 @@ class Gnnd:
         self.n, self.d = vectors.shape
         self.k, self.p, self.metric, self.seed = k, p, metric, seed
         self.update_mode = update_mode
-        need = workspace_bytes(self.n, self.d, k, p, metric, update_mode, list_mode, join_path)
-        if need == 0:
-            prm = make_params(self.n, self.d, k, p, metric, seed, join_path,
-                              update_mode=update_mode, list_mode=list_mode)
+        prm = make_params(self.n, self.d, k, p, metric, seed, join_path,
+                          update_mode=update_mode, list_mode=list_mode)
+        if lib.gnnd_workspace_bytes(C.byref(prm)) == 0:
             ctx = C.c_void_p()
             rc = lib.gnnd_create(C.byref(ctx), C.byref(prm), vectors.data_ptr())
             raise GnndError(rc, _err())
-        self.workspace = torch.empty(need, dtype=torch.uint8, device=vectors.device)
+        self.workspace = _workspace(prm, vectors.device)
         self.prm = make_params(self.n, self.d, k, p, metric, seed, join_path,
                                _stream_ptr(vectors.device), self.workspace, update_mode, list_mode)
         self._ctx = C.c_void_p()
@@ -347,9 +374,8 @@ def gnnd_merge(vec1, vec2, ids1, dist1, ids2, dist2, k, p, metric=L2SQ_F32, seed
     n = n1 + n2
     base2 = n1 if base2 is None else base2
     id_space = max(base1 + n1, base2 + n2) if id_space is None else id_space
-    need = workspace_bytes(n, d, k, p, metric, join_path=join_path)
     dev = vec1.device
-    ws = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
+    ws = _workspace(make_params(n, d, k, p, metric, join_path=join_path), dev)
     prm = make_params(n, d, k, p, metric, seed, join_path, _stream_ptr(dev), ws)
     ids = torch.empty((n, k), dtype=torch.int32, device=dev)
     dist = torch.empty((n, k), dtype=dt, device=dev)
@@ -380,8 +406,7 @@ def gnnd_append(vec1, ids1, dist1, vec2, k, p, metric=L2SQ_F32, seed=42, build_i
     n2 = vec2.shape[0]
     n = n1 + n2
     dev = vec1.device
-    ws = torch.empty(max(workspace_bytes(n, d, k, p, metric, join_path=join_path), 256),
-                     dtype=torch.uint8, device=dev)
+    ws = _workspace(make_params(n, d, k, p, metric, join_path=join_path), dev)
     prm = make_params(n, d, k, p, metric, seed, join_path, _stream_ptr(dev), ws)
     ids = torch.empty((n, k), dtype=torch.int32, device=dev)
     dist = torch.empty((n, k), dtype=dt, device=dev)
@@ -411,7 +436,7 @@ def gnnd_build_sharded(vectors_host, shards, k, p, metric=L2SQ_F32, seed=42, bui
         rc = lib.gnnd_build_sharded(C.byref(prm), vectors_host.data_ptr(), shards, build_iters,
                                     merge_iters, None, None, None, None)
         raise GnndError(rc, _err())
-    arena = torch.empty(need, dtype=torch.uint8, device=dev)
+    arena = _scratch(need, lambda: int(lib.gnnd_sharded_arena_bytes_min(C.byref(prm), shards)), dev)
     copy_stream = torch.cuda.Stream(device=dev)
     prm = make_params(n, d, k, p, metric, seed, join_path, _stream_ptr(dev), arena)
     # (allocated pinned: pin_memory() on a pageable tensor would copy it)
@@ -441,7 +466,7 @@ def gnnd_build_sharded_files(vectors_path, n, d, shards, k, p, ids_path, dist_pa
         rc = lib.gnnd_build_sharded_files(C.byref(prm), paths[0], shards, build_iters, merge_iters,
                                           paths[1], paths[2], None, 0, None, None)
         raise GnndError(rc, _err())
-    arena = torch.empty(need, dtype=torch.uint8, device=dev)
+    arena = _scratch(need, lambda: int(lib.gnnd_sharded_arena_bytes_min(C.byref(prm), shards)), dev)
     staging = torch.empty(int(staging_bytes), dtype=torch.uint8, pin_memory=True)
     copy_stream = torch.cuda.Stream(device=dev)
     prm = make_params(n, d, k, p, metric, seed, join_path, _stream_ptr(dev), arena)

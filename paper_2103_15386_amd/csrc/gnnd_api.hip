@@ -103,9 +103,6 @@ bool gram_possible(const gnnd_params* q) {
          (q->metric == GNND_L2SQ_F32 || q->metric == GNND_ANGULAR_F32 ||
           q->metric == GNND_COSINE_F32);
 }
-bool needs_norms(const gnnd_params* q) {
-  return q->metric == GNND_COSINE_F32 || gram_possible(q);
-}
 
 // The matrix-core join stages its results per bucket of destinations (instead of handing
 // them on one by one) for up to 2^22 nodes: a staged result then fits one 64-bit word, and
@@ -162,19 +159,20 @@ Layout make_layout(const gnnd_params* q, bool with_aside, bool extra = true) {
   L.off_aside = take(with_aside ? n * (k / 2) * 8 : 0);
   const bool shadow = mfma_possible(q) || (extra && long_i8_possible(q));
   L.off_shadow = take(shadow ? n * (size_t)((q->d + 31) & ~31) : 0);
-  L.off_norms = take(needs_norms(q) ? n * 4 : 0);  // squared norms
+  const bool gram = gram_possible(q), half = extra && half_possible(q);
+  L.off_norms = take(q->metric == GNND_COSINE_F32 || gram ? n * 4 : 0);  // squared norms
   L.off_flag = take(256);
   L.off_bkc = take(2 * 4096 * 4);
   const bool staged = stage_possible(q, extra);
-  L.off_stg_ent = take(staged ? n * slots_per_node * 8 : 0);
+  // the results the int8 join stages, or the 16-bit rows: a context has one of the two joins
+  const size_t stage_bytes = staged ? n * slots_per_node * 8 : 0;
+  const size_t half_bytes = half ? n * (size_t)half_row_elems(q->d) * 2 : 0;
+  L.off_stg_ent = L.off_half = take(stage_bytes > half_bytes ? stage_bytes : half_bytes);
   L.off_stg_cur = take(staged ? (size_t)kStageBuckets * 8 : 0);
-  const bool gram = gram_possible(q);
   // (the float join lists its nodes in kGramClasses classes, the staged int8 join in three)
   L.off_cls_nodes = take(gram ? (size_t)kGramClasses * n * 4 : staged ? (size_t)3 * n * 4 : 0);
   L.off_cls_count = take(gram || staged ? 256 : 0);
   L.extra = extra;
-  const bool half = extra && half_possible(q);
-  L.off_half = take(half ? n * (size_t)half_row_elems(q->d) * 2 : 0);
   L.total = o;
   return L;
 }
@@ -928,6 +926,11 @@ size_t gnnd_workspace_bytes(const gnnd_params* prm) {
   return make_layout(prm, true).total;
 }
 
+size_t gnnd_workspace_bytes_min(const gnnd_params* prm) {
+  if (check_params(prm)) return 0;
+  return make_layout(prm, true, false).total;
+}
+
 int gnnd_create(gnnd_ctx** out, const gnnd_params* prm, const void* vectors_dev) {
   return create_impl(out, prm, vectors_dev, nullptr, prm ? prm->n : 0, false, /*own_context=*/true);
 }
@@ -1155,6 +1158,12 @@ int gnnd_append(const gnnd_params* prm, const void* vec1, int64_t n1, const int3
 size_t gnnd_sharded_arena_bytes(const gnnd_params* prm, int32_t shards) {
   ShardPlan pl;
   if (plan_shards(prm, shards, &pl)) return 0;
+  return pl.total;
+}
+
+size_t gnnd_sharded_arena_bytes_min(const gnnd_params* prm, int32_t shards) {
+  ShardPlan pl;
+  if (plan_shards(prm, shards, &pl, 0)) return 0;
   return pl.total;
 }
 
