@@ -199,8 +199,7 @@ struct StageArgs {
   bool count_passed;        // false when the pass behind the join counts what passes
 };
 constexpr size_t kStageLdsBytes = (size_t)kStageBuckets * kStageSlots * 8 + kStageBuckets * 20 + 16;
-// a staged result: distance code | destination inside its bucket | object id
-// a staged result without its destination, and with it
+// a staged result (see kStageDistShift) without its destination, and with it
 __device__ inline uint64_t stage_entry(int32_t dist, uint32_t id) {
   return ((uint64_t)(uint32_t)dist << kStageDistShift) | (uint64_t)id;
 }

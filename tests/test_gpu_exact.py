@@ -1,7 +1,8 @@
 """Exhaustive search against the oracle's, element by element: every number of queries per
-workgroup (1, 2, 4, 8, chosen by the number of queries), row counts around the tile of 64 and
-the round of 1024 rows, dimensions around the chunk of 32 floats (16 words of bytes) and of
-every alignment, the shortest and longest result lists."""
+workgroup (1, 2, 4, 8, chosen by the number of queries), row counts around the tile of 128 rows (two
+per lane; the last tile is moved back) and the round of 2048 rows (a wavefront's second tile),
+dimensions around the chunk of 16 words (16 floats, 64 bytes) and of every alignment, the shortest
+and longest result lists."""
 import numpy as np
 import pytest
 import torch
@@ -25,6 +26,9 @@ GEN = {
     (2, 1, 2, 1), (3, 4, 3, 64), (64, 33, 64, 64), (65, 32, 5, 10), (1023, 31, 40, 64),
     (1025, 36, 257, 10), (2100, 20, 300, 64), (1300, 66, 600, 7), (1090, 13, 1030, 10),
     (5000, 64, 1100, 33), (4097, 128, 1, 64),
+    (127, 16, 30, 64), (128, 15, 20, 64), (128, 16, 128, 10), (129, 17, 129, 10), (129, 64, 5, 64),
+    (2047, 64, 100, 10), (2048, 60, 300, 33), (2048, 16, 1030, 10), (2049, 65, 40, 64),
+    (2049, 64, 600, 10), (2177, 68, 1100, 10),
 ])
 def test_exact_knn_equals_brute_force(metric, n, d, nq, K):
     import paper_2103_15386_amd as amd
