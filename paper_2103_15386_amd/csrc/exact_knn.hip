@@ -155,6 +155,8 @@ __global__ __launch_bounds__(kEBlock) void k_exact_knn(const void* vec, int64_t 
       uint32_t v = 0u;
       if (!kBytes || (d & 3) == 0) {
         v = reinterpret_cast<const uint32_t*>(src)[w];
+      } else if (4 * w + 3 < d) {
+        __builtin_memcpy(&v, src + 4 * (int64_t)w, 4);  // (rows of odd length: not aligned)
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -284,7 +286,8 @@ __global__ __launch_bounds__(kEBlock) void k_exact_knn(const void* vec, int64_t 
     }
   }
 
-  // the wavefronts' lists of query q, merged by wavefront q
+  // the wavefronts' lists of query q, merged by wavefront q (few rows: of those that had a tile)
+  const int filled = n < step ? (int)((n + kTile - 1) / kTile) : kEWaves;
   __syncthreads();  // the tiles are no longer in use
   uint64_t* const lists = reinterpret_cast<uint64_t*>(lds);  // [Q][kEWaves][64]
 #pragma unroll
@@ -292,7 +295,7 @@ __global__ __launch_bounds__(kEBlock) void k_exact_knn(const void* vec, int64_t 
   __syncthreads();
   if (wave >= Q || q0 + wave >= nq) return;
   uint64_t all = lists[wave * kEWaves * kWave + lane];
-  for (int w = 1; w < kEWaves; ++w)
+  for (int w = 1; w < filled; ++w)
     all = wave_merge_smallest(all, lists[(wave * kEWaves + w) * kWave + lane], lane);
   if (lane < K) {
     const bool have = (int64_t)(uint32_t)queries[q0 + wave] < n && all != kKeyMax;
