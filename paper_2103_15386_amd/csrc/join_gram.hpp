@@ -31,8 +31,8 @@
 //     (distance, id) of a sample is the result.
 //
 // Measured (builds of 12 iterations, k = p = 32, whole build): 150,000 x 960 squared L2 97.9 ->
-// 51.1 ms, 1.5 million x 96 angular 139.7 -> 116.7 ms, 100,000 x 75 cosine (p = 12, 8
-// iterations) 7.97 -> 5.66 ms, against float32 operands in step 1, bounds proportional to 6 d
+// 49.8 ms, 1.5 million x 96 angular 139.7 -> 113.3 ms, 100,000 x 75 cosine (p = 12, 8
+// iterations) 7.97 -> 5.49 ms, against float32 operands in step 1, bounds proportional to 6 d
 // and two partners per sample, direction and pass in step 4.  The tighter bounds and the pair
 // list were worth as much as the halved first reading: vector-ALU instructions per node fell
 // from 3600 to 2270 (62 rows of 96 dimensions).  What bounds it now: the gather (62 rows at
