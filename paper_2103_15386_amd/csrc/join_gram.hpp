@@ -277,8 +277,10 @@ __device__ __forceinline__ bool gram_node(GramLds& S, float* tile, const VecSrc&
   {
     // one 8-byte record per sample: the threshold of its list and its squared norm
     // (launch_gram_norms put the float's bits where the int8 join keeps its integer norm)
-    const uint2 mn = idn >= 0 ? *reinterpret_cast<const uint2*>(&meta[idn]) : make_uint2(0u, 0u);
-    const uint2 mo = ido >= 0 ? *reinterpret_cast<const uint2*>(&meta[ido]) : make_uint2(0u, 0u);
+    // (an empty list place: a norm of 1, which is not special)
+    const uint2 none = make_uint2(0u, 0x3f800000u);
+    const uint2 mn = idn >= 0 ? *reinterpret_cast<const uint2*>(&meta[idn]) : none;
+    const uint2 mo = ido >= 0 ? *reinterpret_cast<const uint2*>(&meta[ido]) : none;
     const uint32_t kthn = mn.x, ktho = mo.x;
     const float nrmn = __uint_as_float(mn.y), nrmo = __uint_as_float(mo.y);
     auto weight_of = [&](int32_t id, float nrm) {
@@ -287,15 +289,18 @@ __device__ __forceinline__ bool gram_node(GramLds& S, float* tile, const VecSrc&
         w = !HALF && nrm > 0.f ? 1.0f / sqrtf(nrm) : 0.f;
       return id >= 0 ? w : kNaN;
     };
-    auto is_special = [&](int32_t id, float nrm) {
-      const float least = METRIC == kCosineF32 ? kCosineLeast : HALF ? kHalfLeast : least_sum;
-      const float most = METRIC == kCosineF32 ? kCosineMost : kNormMost;
-      bool ok = nrm >= least && nrm <= most;
-      if (!HALF && METRIC == kCosineF32) ok = ok || nrm == 0.f;  // (weight 0: distance 1)
-      if (!HALF && METRIC == kAngularF32) ok = nrm <= most;
-      return id >= 0 && !ok;
+    // (norms are not negative, so their bits compare as they do; NaN lies above all of them)
+    const uint32_t least = METRIC == kCosineF32              ? __float_as_uint(kCosineLeast)
+                           : HALF                            ? __float_as_uint(kHalfLeast)
+                           : METRIC == kL2F32                ? __float_as_uint(least_sum)
+                                                             : 0u;
+    const uint32_t span =
+        __float_as_uint(METRIC == kCosineF32 ? kCosineMost : kNormMost) - least;
+    auto is_special = [&](uint32_t bits) {
+      if (!HALF && METRIC == kCosineF32) bits = bits ? bits : least;  // (weight 0: distance 1)
+      return bits - least > span;
     };
-    special = __ballot(is_special(idn, nrmn) || is_special(ido, nrmo)) != 0ull;
+    special = (__ballot(is_special(mn.y)) | __ballot(is_special(mo.y))) != 0ull;
     constexpr float kScale = 1.0f / (1 << kHalfBits);
     S.norms[lane] = METRIC == kCosineF32 ? nrmn : HALF ? sqrtf(nrmn) * kScale : 0.f;
     S.norms[64 + lane] = METRIC == kCosineF32 ? nrmo : HALF ? sqrtf(nrmo) * kScale : 0.f;
