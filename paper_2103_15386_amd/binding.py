@@ -26,7 +26,7 @@ EXPORTS = [
     "gnnd_exact_knn", "gnnd_join_path", "gnnd_set_profiling", "gnnd_get_stage_ms",
     "gnnd_sharded_arena_bytes", "gnnd_sharded_arena_bytes_min", "gnnd_build_sharded",
     "gnnd_build_sharded_files", "gnnd_append",
-    "gnnd_build_static",
+    "gnnd_build_static", "gnnd_exact_knn_workspace_bytes", "gnnd_exact_knn_ws",
 ]
 
 
@@ -126,6 +126,10 @@ def load_library():
     lib.gnnd_build_static.argtypes = [PP, vp, i32, vp, vp]
     lib.gnnd_exact_knn.restype = C.c_int
     lib.gnnd_exact_knn.argtypes = [vp, i64, i32, i32, vp, i64, i32, vp, vp, vp]
+    lib.gnnd_exact_knn_workspace_bytes.restype = C.c_size_t
+    lib.gnnd_exact_knn_workspace_bytes.argtypes = [i64, i32, i32, i64, i32]
+    lib.gnnd_exact_knn_ws.restype = C.c_int
+    lib.gnnd_exact_knn_ws.argtypes = [vp, i64, i32, i32, vp, i64, i32, vp, vp, vp, C.c_size_t, vp]
     _lib = lib
     return lib
 
@@ -486,8 +490,13 @@ def exact_knn(vectors, queries, K, metric=L2SQ_F32):
     nq = queries.numel()
     ids = torch.empty((nq, K), dtype=torch.int32, device=vectors.device)
     dist = torch.empty((nq, K), dtype=_dist_dtype(metric), device=vectors.device)
-    _check(lib.gnnd_exact_knn(vectors.data_ptr(), n, d, metric, queries.data_ptr(), nq, K,
-                              ids.data_ptr(), dist.data_ptr(), _stream_ptr(vectors.device)))
+    # (freed when this returns: the allocator hands it on in the order of this stream's work)
+    need = int(lib.gnnd_exact_knn_workspace_bytes(n, d, metric, nq, K))
+    ws = _scratch(need, lambda: 0, vectors.device) if need else None
+    _check(lib.gnnd_exact_knn_ws(vectors.data_ptr(), n, d, metric, queries.data_ptr(), nq, K,
+                                 ids.data_ptr(), dist.data_ptr(),
+                                 ws.data_ptr() if need else None, ws.numel() if need else 0,
+                                 _stream_ptr(vectors.device)))
     return ids, dist
 
 

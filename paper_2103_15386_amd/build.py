@@ -10,7 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgnnd_hip.so")
 # (the slowest to compile first)
 SOURCES = ["join_gram_l2.hip", "join_gram_cosine.hip", "join_gram_angular.hip", "join_mfma.hip",
-           "join_valu.hip", "exact_knn.hip", "graph_kernels.hip", "wide_lists.hip", "long_samples.hip",
+           "join_valu.hip", "exact_scan.hip", "exact_knn.hip", "graph_kernels.hip", "wide_lists.hip", "long_samples.hip",
            "segmented_lists.hip", "join_gram.hip", "join_long_i8.hip", "sample_buckets.hip",
            "gnnd_api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

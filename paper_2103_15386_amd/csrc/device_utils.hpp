@@ -375,13 +375,15 @@ struct JoinTraits<kL2U8> {
 // tile in chunks of kEvalChunk dimensions with coalesced reads (8 lanes per row
 // chunk), then every lane accumulates its own pair in dimension order: the
 // canonical arithmetic, without 64 lanes each walking a row of its own through HBM.  All 64 lanes must call it together.
+// wave_sums gives the running sums, wave_distances the codes of the distances.
 constexpr int kEvalChunk = 32;
 constexpr int kEvalStride = kEvalChunk + 1;  // odd stride: lanes walk their rows free of bank conflicts
 constexpr int kEvalTileWords = 65 * kEvalStride;
 
 template <int METRIC>
-__device__ inline uint32_t wave_distances(const VecSrc& vs, uint32_t s, uint32_t id, bool on,
-                                          uint32_t* tile_raw, int lane) {
+__device__ inline typename JoinTraits<METRIC>::acc wave_sums(const VecSrc& vs, uint32_t s,
+                                                             uint32_t id, bool on,
+                                                             uint32_t* tile_raw, int lane) {
   using TR = JoinTraits<METRIC>;
   using T = typename TR::elem;
   using ACC = typename TR::acc;
@@ -455,8 +457,15 @@ __device__ inline uint32_t wave_distances(const VecSrc& vs, uint32_t s, uint32_t
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  if constexpr (METRIC == kCosineF32) return TR::code(acc, vs.norms[s], on ? vs.norms[id] : 0.f);
-  else return TR::code(acc);
+  return acc;
+}
+template <int METRIC>
+__device__ inline uint32_t wave_distances(const VecSrc& vs, uint32_t s, uint32_t id, bool on,
+                                          uint32_t* tile_raw, int lane) {
+  const auto acc = wave_sums<METRIC>(vs, s, id, on, tile_raw, lane);
+  if constexpr (METRIC == kCosineF32)
+    return JoinTraits<METRIC>::code(acc, vs.norms[s], on ? vs.norms[id] : 0.f);
+  else return JoinTraits<METRIC>::code(acc);
 }
 
 // The nodes with work to do, listed by class: list c at nodes + c n, its length in count[c]

@@ -79,13 +79,19 @@ __device__ inline void take_keys(uint64_t& best, uint64_t key, uint64_t* shared_
 template <int METRIC, int Q, bool ALIGNED>
 __global__ __launch_bounds__(kEBlock) void k_exact_knn(const void* vec, int64_t n, int d,
                                                        const int32_t* queries, int64_t nq, int K,
-                                                       int32_t* ids_out, void* dist_out) {
+                                                       int32_t* ids_out, void* dist_out,
+                                                       const uint8_t* only) {
   constexpr bool kBytes = METRIC == kL2U8;
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
   __shared__ uint64_t last_of[8];
   const int lane = lane_id(), wave = wave_id();
   uint32_t* const tile = lds + wave * ((kTile + Q) * kChunk);
   const int64_t q0 = (int64_t)blockIdx.x * Q;
+  if (only) {  // uniform
+    bool any = false;
+    for (int q = 0; q < Q; ++q) any = any || (q0 + q < nq && only[q0 + q] == 1);
+    if (!any) return;
+  }
   if (threadIdx.x < 8) last_of[threadIdx.x] = kKeyMax;
   __syncthreads();
   const int words = kBytes ? (d + 3) >> 2 : d;  // words per row
@@ -293,7 +299,7 @@ __global__ __launch_bounds__(kEBlock) void k_exact_knn(const void* vec, int64_t 
 #pragma unroll
   for (int q = 0; q < Q; ++q) lists[(q * kEWaves + wave) * kWave + lane] = best[q];
   __syncthreads();
-  if (wave >= Q || q0 + wave >= nq) return;
+  if (wave >= Q || q0 + wave >= nq || (only && only[q0 + wave] != 1)) return;
   uint64_t all = lists[wave * kEWaves * kWave + lane];
   for (int w = 1; w < filled; ++w)
     all = wave_merge_smallest(all, lists[(wave * kEWaves + w) * kWave + lane], lane);
@@ -312,7 +318,8 @@ __global__ __launch_bounds__(kEBlock) void k_exact_knn(const void* vec, int64_t 
 
 template <int METRIC, int Q>
 hipError_t launch(const void* vec, int64_t n, int32_t d, const int32_t* queries, int64_t nq,
-                  int32_t K, int32_t* ids_out, void* dist_out, hipStream_t st) {
+                  int32_t K, int32_t* ids_out, void* dist_out, hipStream_t st,
+                  const uint8_t* only) {
   constexpr size_t tiles = (size_t)kEWaves * (kTile + Q) * kChunk * 4;
   constexpr size_t lists = (size_t)Q * kEBlock * 8;
   constexpr size_t bytes = tiles > lists ? tiles : lists;
@@ -324,7 +331,7 @@ hipError_t launch(const void* vec, int64_t n, int32_t d, const int32_t* queries,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   if (e != hipSuccess) return e;
   kernel<<<(unsigned)((nq + Q - 1) / Q), kEBlock, bytes, st>>>(vec, n, d, queries, nq, K, ids_out,
-                                                               dist_out);
+                                                               dist_out, only);
   return hipGetLastError();
 }
 
@@ -333,7 +340,8 @@ hipError_t launch(const void* vec, int64_t n, int32_t d, const int32_t* queries,
 // moving the row through LDS, about as much as two.
 template <int METRIC>
 hipError_t launch_metric(const void* vec, int64_t n, int32_t d, const int32_t* queries, int64_t nq,
-                         int32_t K, int32_t* ids_out, void* dist_out, hipStream_t st) {
+                         int32_t K, int32_t* ids_out, void* dist_out, hipStream_t st,
+                         const uint8_t* only) {
   int q = 1;
   int64_t least = INT64_MAX;
   for (int c = 1; c <= 8; c *= 2) {
@@ -344,10 +352,10 @@ hipError_t launch_metric(const void* vec, int64_t n, int32_t d, const int32_t* q
     }
   }
   switch (q) {
-    case 1: return launch<METRIC, 1>(vec, n, d, queries, nq, K, ids_out, dist_out, st);
-    case 2: return launch<METRIC, 2>(vec, n, d, queries, nq, K, ids_out, dist_out, st);
-    case 4: return launch<METRIC, 4>(vec, n, d, queries, nq, K, ids_out, dist_out, st);
-    default: return launch<METRIC, 8>(vec, n, d, queries, nq, K, ids_out, dist_out, st);
+    case 1: return launch<METRIC, 1>(vec, n, d, queries, nq, K, ids_out, dist_out, st, only);
+    case 2: return launch<METRIC, 2>(vec, n, d, queries, nq, K, ids_out, dist_out, st, only);
+    case 4: return launch<METRIC, 4>(vec, n, d, queries, nq, K, ids_out, dist_out, st, only);
+    default: return launch<METRIC, 8>(vec, n, d, queries, nq, K, ids_out, dist_out, st, only);
   }
 }
 
@@ -355,16 +363,17 @@ hipError_t launch_metric(const void* vec, int64_t n, int32_t d, const int32_t* q
 
 hipError_t launch_exact_knn(const void* vec, int64_t n, int32_t d, int32_t metric,
                             const int32_t* queries, int64_t nq, int32_t K, int32_t* ids_out,
-                            void* dist_out, hipStream_t st) {
+                            void* dist_out, hipStream_t st, const uint8_t* only) {
   if (nq == 0) return hipSuccess;
   switch (metric) {
-    case kL2F32: return launch_metric<kL2F32>(vec, n, d, queries, nq, K, ids_out, dist_out, st);
-    case kAngularF32:
-      return launch_metric<kAngularF32>(vec, n, d, queries, nq, K, ids_out, dist_out, st);
-    case kChi2F32: return launch_metric<kChi2F32>(vec, n, d, queries, nq, K, ids_out, dist_out, st);
-    case kCosineF32:
-      return launch_metric<kCosineF32>(vec, n, d, queries, nq, K, ids_out, dist_out, st);
-    default: return launch_metric<kL2U8>(vec, n, d, queries, nq, K, ids_out, dist_out, st);
+#define GNND_EXACT(M) \
+  return launch_metric<M>(vec, n, d, queries, nq, K, ids_out, dist_out, st, only)
+    case kL2F32: GNND_EXACT(kL2F32);
+    case kAngularF32: GNND_EXACT(kAngularF32);
+    case kChi2F32: GNND_EXACT(kChi2F32);
+    case kCosineF32: GNND_EXACT(kCosineF32);
+    default: GNND_EXACT(kL2U8);
+#undef GNND_EXACT
   }
 }
 

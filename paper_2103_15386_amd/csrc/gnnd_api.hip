@@ -1263,8 +1263,17 @@ int gnnd_build_static(const gnnd_params* prm, const void* vectors_dev, int32_t m
   return rc;
 }
 
-int gnnd_exact_knn(const void* vec, int64_t n, int32_t d, int32_t metric, const int32_t* queries,
-                   int64_t nq, int32_t K, int32_t* ids_out, void* dist_out, void* stream) {
+size_t gnnd_exact_knn_workspace_bytes(int64_t n, int32_t d, int32_t metric, int64_t nq,
+                                      int32_t K) {
+  if (metric < GNND_L2SQ_F32 || metric > GNND_COSINE_F32 || n < 2 || n > ((int64_t)1 << 30) ||
+      d < 1 || nq < 0 || K < 1 || K > 64)
+    return 0;
+  return exact_scan_bytes(n, d, metric, nq);
+}
+
+int gnnd_exact_knn_ws(const void* vec, int64_t n, int32_t d, int32_t metric,
+                      const int32_t* queries, int64_t nq, int32_t K, int32_t* ids_out,
+                      void* dist_out, void* workspace, size_t workspace_bytes, void* stream) {
   if (!vec || !queries || !ids_out || !dist_out)
     return fail(nullptr, GNND_EINVAL, "NULL pointer argument");
   if (metric < GNND_L2SQ_F32 || metric > GNND_COSINE_F32)
@@ -1272,9 +1281,20 @@ int gnnd_exact_knn(const void* vec, int64_t n, int32_t d, int32_t metric, const 
   if (n < 2 || n > ((int64_t)1 << 30) || d < 1 || nq < 0 || K < 1 || K > 64)
     return fail(nullptr, GNND_EINVAL, "need 2 <= n <= 2^30, d >= 1, nq >= 0, 1 <= K <= 64");
   if ((uintptr_t)vec & 15) return fail(nullptr, GNND_EINVAL, "vectors must be 16-byte aligned");
-  hipError_t e = launch_exact_knn(vec, n, d, metric, queries, nq, K, ids_out, dist_out,
-                                  (hipStream_t)stream);
-  return e == hipSuccess ? GNND_OK : hip_fail(nullptr, e, "exact_knn kernel");
+  if ((uintptr_t)workspace & 255)
+    return fail(nullptr, GNND_EINVAL, "workspace must be 256-byte aligned");
+  const size_t need = exact_scan_bytes(n, d, metric, nq);
+  const bool scan = need != 0 && workspace && workspace_bytes >= need;
+  hipError_t e = scan ? launch_exact_scan(vec, n, d, metric, queries, nq, K, ids_out, dist_out,
+                                          workspace, (hipStream_t)stream)
+                      : launch_exact_knn(vec, n, d, metric, queries, nq, K, ids_out, dist_out,
+                                         (hipStream_t)stream);
+  return e == hipSuccess ? GNND_OK : hip_fail(nullptr, e, "exact_knn kernels");
+}
+
+int gnnd_exact_knn(const void* vec, int64_t n, int32_t d, int32_t metric, const int32_t* queries,
+                   int64_t nq, int32_t K, int32_t* ids_out, void* dist_out, void* stream) {
+  return gnnd_exact_knn_ws(vec, n, d, metric, queries, nq, K, ids_out, dist_out, nullptr, 0, stream);
 }
 
 }  // extern "C"

@@ -190,7 +190,14 @@ hipError_t launch_merge_final_wide(const Shape& sh, const DevState& ds, const Me
                                    int32_t* ids_out, void* dist_out, hipStream_t st);
 hipError_t launch_exact_knn(const void* vec, int64_t n, int32_t d, int32_t metric,
                             const int32_t* queries, int64_t nq, int32_t K, int32_t* ids_out,
-                            void* dist_out, hipStream_t st);
+                            void* dist_out, hipStream_t st, const uint8_t* only = nullptr);
+// The same results with the matrix cores turning rows away (exact_scan.hip), in a workspace of
+// exact_scan_bytes() bytes; 0: this form does not take such a call.  (launch_exact_knn answers the
+// queries it leaves over: those with only[q] == 1.)
+size_t exact_scan_bytes(int64_t n, int32_t d, int32_t metric, int64_t nq);
+hipError_t launch_exact_scan(const void* vec, int64_t n, int32_t d, int32_t metric,
+                             const int32_t* queries, int64_t nq, int32_t K, int32_t* ids_out,
+                             void* dist_out, void* workspace, hipStream_t st);
 hipError_t launch_zero_u32(uint32_t* p, size_t count, hipStream_t st);
 
 // Exclusive scan of `count` uint32 into uint64 offsets out[0..count] (out[count] = total).

@@ -1,0 +1,105 @@
+"""Exhaustive search with a workspace (matrix cores turn rows away) against the oracle and, on data
+outside its bounds' range, against the form without one, bit for bit: row counts around the tile of 64,
+dimensions around the 64-byte pieces of a copy, query counts around the group of 256 and the slice of
+4096, rows and queries without a usable copy, lists that run over."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as og
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+GEN = {
+    og.L2SQ_F32: lambda n, d: W.uniform_f32(n, d, seed=411),
+    og.ANGULAR_F32: lambda n, d: W.deep_like_f32(n, d, seed=412, n_comp=5),
+    og.L2SQ_U8: lambda n, d: W.sift_like_u8(n, d, seed=413, n_comp=4),
+    og.COSINE_F32: lambda n, d: W.scaled_directions_f32(n, d, seed=415, n_comp=5, zero_rows=1),
+}
+
+
+def _both(x, q, K, metric):
+    """(ids, distances) of the form with and of the form without a workspace."""
+    import paper_2103_15386_amd as amd
+    lib = amd.load_library()
+    (n, d), nq = x.shape, q.numel()
+    need = int(lib.gnnd_exact_knn_workspace_bytes(n, d, metric, nq, K))
+    assert need > 0
+    with_ws = amd.exact_knn(x, q, K, metric)
+    ids, dist = torch.empty_like(with_ws[0]), torch.empty_like(with_ws[1])
+    assert lib.gnnd_exact_knn(x.data_ptr(), n, d, metric, q.data_ptr(), nq, K, ids.data_ptr(),
+                              dist.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+    return with_ws, (ids, dist)
+
+
+@pytest.mark.parametrize("metric", list(GEN))
+@pytest.mark.parametrize("n,d,nq,K", [
+    (6016, 128, 600, 10), (6017, 97, 700, 1), (6079, 96, 769, 64), (6080, 65, 1023, 10),
+    (6081, 64, 1025, 33), (7000, 63, 900, 10), (9000, 33, 1000, 7), (9001, 32, 1000, 10),
+    (9000, 31, 1000, 64), (20000, 127, 257, 10), (20001, 76, 256, 64), (40000, 20, 300, 5),
+    (20000, 4, 4100, 10), (16400, 128, 3, 10),
+])
+def test_scan_equals_brute_force(metric, n, d, nq, K):
+    x = GEN[metric](n, d)
+    x[n // 2:n // 2 + 40] = x[:40]  # equal distances: the id decides
+    q = W.sample_nodes(n, nq, seed=3)
+    (ids, dist), general = _both(torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda(), K, metric)
+    assert torch.equal(ids, general[0]) and torch.equal(dist, general[1])
+    some = np.r_[0:min(nq, 40), max(0, nq - 40):nq]
+    oi, od = og.bruteforce(x, metric, q[some], K)
+    assert (ids.cpu().numpy()[some] == oi).all()
+    assert (dist.cpu().numpy().astype(np.float64)[some] == od).all()
+
+
+def _hard(name, x):
+    if name == "offset":
+        x += 30
+    elif name == "copies":  # more candidates than a list holds
+        x[100:3000] = x[0]
+    elif name == "lengths":
+        x *= torch.exp(8 * torch.randn((len(x), 1), device=x.device,
+                                       generator=torch.Generator(x.device).manual_seed(1)))
+    elif name == "zeros":
+        x[::3] = 0
+    elif name == "ends":  # no usable copy: infinite, huge, tiny
+        x[7], x[11], x[800], x[1200], x[1300] = float("inf"), 1e30, 1e25, 1e-25, 1e-38
+    elif name == "nan":
+        x[9, 3] = x[400, 2] = float("nan")
+    return x
+
+
+@pytest.mark.parametrize("metric", [og.L2SQ_F32, og.ANGULAR_F32, og.COSINE_F32])
+@pytest.mark.parametrize("name", ["offset", "copies", "lengths", "zeros", "ends", "nan"])
+def test_scan_on_data_its_bounds_do_not_suit(metric, name):
+    x = _hard(name, torch.from_numpy(W.deep_like_f32(16000, 48, seed=416, n_comp=40)).cuda())
+    q = torch.arange(0, 16000, 25, dtype=torch.int32, device="cuda")
+    got, want = _both(x, q, 10, metric)
+    assert torch.equal(got[0], want[0])
+    assert torch.equal(got[1].view(torch.int32), want[1].view(torch.int32))
+
+
+def test_scan_query_ids():
+    x = torch.from_numpy(W.uniform_f32(16000, 48, seed=417)).cuda()
+    q = torch.arange(0, 16000, 25, dtype=torch.int32, device="cuda")
+    q[5], q[6], q[7], q[8] = -1, 16000, 15999, 15999
+    got, want = _both(x, q, 64, og.L2SQ_F32)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    assert (got[0][5] == -1).all() and torch.equal(got[0][7], got[0][8])
+
+
+def test_scan_under_capture():
+    x = torch.from_numpy(W.uniform_f32(16000, 48, seed=418)).cuda()
+    q = torch.arange(0, 16000, 25, dtype=torch.int32, device="cuda")
+    import paper_2103_15386_amd as amd
+    want = amd.exact_knn(x, q, 10)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ids, dist = amd.exact_knn(x, q, 10)
+    for _ in range(3):
+        ids.fill_(-7)
+        graph.replay()
+        again = amd.exact_knn(x, q, 10)
+        torch.cuda.synchronize()
+        assert torch.equal(ids, want[0]) and torch.equal(dist, want[1])
+        assert torch.equal(again[0], want[0])
