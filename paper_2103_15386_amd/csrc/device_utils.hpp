@@ -104,10 +104,9 @@ __device__ inline uint32_t xor_lanes(uint32_t v, int j, int lane) {
     case 1: return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);  // quad_perm:[1,0,3,2]
     case 2: return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);  // quad_perm:[2,3,0,1]
     case 4: {
-      // lanes 0-3 and 8-11 of a row read 4 lanes up (row_shl:4), the others 4 lanes down (row_shr:4)
-      int r = __builtin_amdgcn_update_dpp(0, (int)v, 0x104, 0xF, 0x5, false);
-      r = __builtin_amdgcn_update_dpp(r, (int)v, 0x114, 0xF, 0xA, false);
-      return (uint32_t)r;
+      // mirrored inside 8 lanes (lane ^ 7), then inside quads (lane ^ 3)
+      const int r = __builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, true);
+      return (uint32_t)__builtin_amdgcn_mov_dpp(r, 0x1B, 0xF, 0xF, true);
     }
     case 8: return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, true);  // row_ror:8
     case 16: {
@@ -139,49 +138,87 @@ __device__ inline uint64_t reverse_lanes(uint64_t v, int lane) {
   return ((uint64_t)hi << 32) | lo;
 }
 
-// One compare-exchange of a sorting network: this lane keeps the smaller of
-// its value and its partner's when keep_min, else the larger.  (Equal values:
-// either.)  One comparison; the lane pattern keep_min folds into the mask.
-template <typename T>
-__device__ inline T exchange(T v, T o, bool keep_min) {
+// Values of the lanes without and with bit j (16 or 32) of this lane's pair, in both of its lanes.
+__device__ inline void pair_lanes(uint32_t v, int j, uint32_t& lower, uint32_t& upper) {
+  if (j == 16) {
+    auto sw = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    lower = sw[0];
+    upper = sw[1];
+  } else {
+    auto sw = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    lower = sw[0];
+    upper = sw[1];
+  }
+}
+
+// One compare-exchange of a sorting network between lanes `lane` and lane ^ j: this lane keeps
+// the smaller of its value and its partner's when keep_min, else the larger.  (Equal values:
+// either.)  One comparison; the lane pattern keep_min folds into the mask.  Across rows and halves
+// both values are at hand in both lanes, so nothing has to be picked before the comparison.
+__device__ inline uint64_t exchange_step(uint64_t v, int j, int lane, bool keep_min) {
+  if (j >= 16) {
+    uint32_t lo0, lo1, hi0, hi1;
+    pair_lanes((uint32_t)v, j, lo0, lo1);
+    pair_lanes((uint32_t)(v >> 32), j, hi0, hi1);
+    const uint64_t a = ((uint64_t)hi0 << 32) | lo0, b = ((uint64_t)hi1 << 32) | lo1;
+    return ((b < a) == keep_min) ? b : a;
+  }
+  const uint64_t o = xor_lanes(v, j, lane);
   return ((o < v) == keep_min) ? o : v;
 }
-// 32-bit values: min and max can take the partner straight from the lane
-// permutation (no separate move), then one select on the lane pattern.
-__device__ inline uint32_t exchange(uint32_t v, uint32_t o, bool keep_min) {
-  const uint32_t lo = v < o ? v : o, hi = v < o ? o : v;
-  return keep_min ? lo : hi;
-}
 
-// Full ascending sort of 64 lane values (bitonic network, 21 exchange stages).
-template <typename T>
-__device__ inline T wave_sort(T v, int lane) {
-#pragma unroll
-  for (int k = 2; k <= kWave; k <<= 1) {
-#pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      const T o = xor_lanes(v, j, lane);
-      v = exchange(v, o, ((lane & j) == 0) == ((lane & k) == 0));
-    }
+// 32-bit values: the median of both values and 0 is the smaller, of both and 2^32 - 1 the larger
+// one, so a limit per lane (lane_limit) makes an exchange one instruction.
+__device__ inline uint32_t median(uint32_t a, uint32_t b, uint32_t c) {
+  return vmax(vmin(a, b), vmin(vmax(a, b), c));
+}
+// all ones in the lanes with bit j, 0 in the others (kept opaque: the median is to stay one)
+__device__ inline uint32_t lane_limit(int lane, int j) {
+  uint32_t m = (lane & j) ? 0xffffffffu : 0u;
+  asm("" : "+v"(m));
+  return m;
+}
+// lanes without bit j keep the smaller, lanes with it the larger value
+__device__ inline uint32_t exchange_step(uint32_t v, int j, int lane) {
+  if (j >= 16) {
+    uint32_t a, b;
+    pair_lanes(v, j, a, b);
+    return median(a, b, lane_limit(lane, j));
   }
-  return v;
+  return median(v, xor_lanes(v, j, lane), lane_limit(lane, j));
 }
 
-// Ascending sort when only the first `count` lanes hold real values and all
-// other lanes hold the maximum: the network over the next power of two is
-// enough (short lists are the common case), the tail is in place already.
-template <int N, typename T>
-__device__ inline T wave_sort_first(T v, int lane) {
+// Ascending sort when only the first `N` lanes hold real values and all other lanes hold the
+// maximum: the bitonic network over N lanes (short lists are the common case), every group of N
+// lanes for itself.
+// 32-bit values are complemented in the groups that a phase sorts downwards, so that all groups
+// of all phases sort upwards.
+template <int N>
+__device__ inline uint64_t wave_sort_first(uint64_t v, int lane) {
 #pragma unroll
   for (int k = 2; k <= N; k <<= 1) {
 #pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      const T o = xor_lanes(v, j, lane);
-      v = exchange(v, o, ((lane & j) == 0) == ((lane & k) == 0));
-    }
+    for (int j = k >> 1; j > 0; j >>= 1)
+      v = exchange_step(v, j, lane, ((lane & j) == 0) == ((lane & k) == 0));
   }
   return v;
 }
+template <int N>
+__device__ inline uint32_t wave_sort_first(uint32_t v, int lane) {
+#pragma unroll
+  for (int k = 2; k <= N; k <<= 1) {
+    if (k < N) v ^= lane_limit(lane, k);
+#pragma unroll
+    for (int j = k >> 1; j > 0; j >>= 1) v = exchange_step(v, j, lane);
+    if (k < N) v ^= lane_limit(lane, k);
+  }
+  return v;
+}
+// Full ascending sort of 64 lane values (21 exchange stages).
+template <typename T>
+__device__ inline T wave_sort(T v, int lane) { return wave_sort_first<kWave>(v, lane); }
+
+// Ascending sort of the first `count` lanes' values, the maximum in all others.
 template <typename T>
 __device__ inline T wave_sort_upto(T v, int lane, int count) {
   if (count <= 1) return v;
@@ -195,13 +232,14 @@ __device__ inline T wave_sort_upto(T v, int lane, int count) {
 
 // Lanes hold a bitonic sequence (ascending then descending, or an element-wise
 // min of an ascending and a reversed ascending one): 6 stages sort it ascending.
-template <typename T>
-__device__ inline T wave_bitonic_merge(T v, int lane) {
+__device__ inline uint64_t wave_bitonic_merge(uint64_t v, int lane) {
 #pragma unroll
-  for (int j = kWave >> 1; j > 0; j >>= 1) {
-    const T o = xor_lanes(v, j, lane);
-    v = exchange(v, o, (lane & j) == 0);
-  }
+  for (int j = kWave >> 1; j > 0; j >>= 1) v = exchange_step(v, j, lane, (lane & j) == 0);
+  return v;
+}
+__device__ inline uint32_t wave_bitonic_merge(uint32_t v, int lane) {
+#pragma unroll
+  for (int j = kWave >> 1; j > 0; j >>= 1) v = exchange_step(v, j, lane);
   return v;
 }
 
@@ -233,6 +271,53 @@ __device__ inline void merge128(T& lo, T& hi, T c, int lane) {
   lo = wave_bitonic_merge(a, lane);
   const T spill = wave_bitonic_merge(b, lane);  // the 64 largest of lo and c, ascending
   hi = wave_merge_smallest(hi, spill, lane);
+}
+
+// Value of the lane before this one; lane 0: `first`.
+__device__ inline uint32_t lane_before(uint32_t v, uint32_t first) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138, 0xF, 0xF, false);  // wave_shr:1
+}
+__device__ inline uint64_t lane_before(uint64_t v, uint64_t first) {
+  const uint32_t lo = lane_before((uint32_t)v, (uint32_t)first);
+  const uint32_t hi = lane_before((uint32_t)(v >> 32), (uint32_t)(first >> 32));
+  return ((uint64_t)hi << 32) | lo;
+}
+// Bits of `mask` below this lane's.
+__device__ inline int rank_in(uint64_t mask) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                        __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// Of up to 64 R candidates (lane's candidate r exists where bit `lane` of have[r] is set), `room`
+// < their number are to be chosen: those with the smallest hashes h[r].  A value t is searched that
+// exactly `room` of them do not exceed - each try costs one comparison, the rest is scalar work -
+// and win[r] is where those are.  The hashes are evenly spread, so the tries follow the number
+// that is missing for a while, and halve the range then: four or five tries as a rule, where a
+// sorting network of (hash, id) pairs took 15 to 21 stages of six vector instructions.  False
+// where equal hashes leave no such t.
+template <int R>
+__device__ inline bool choose_smallest(const uint32_t (&h)[R], const uint64_t (&have)[R], int count,
+                                       int room, uint64_t (&win)[R]) {
+  const uint32_t step = (uint32_t)__builtin_amdgcn_readfirstlane(
+      (int)(uint32_t)(4294967040.f * __builtin_amdgcn_rcpf((float)count)));
+  uint32_t lo = 0u, hi = 0xffffffffu, t = step * (uint32_t)room;
+  for (int tries = 0;; ++tries) {
+    int c = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      win[r] = __ballot(h[r] <= t) & have[r];
+      c += __popcll(win[r]);
+    }
+    if (c == room) return true;
+    if (c < room) lo = t + 1u;  // (t < hi)
+    else hi = t;
+    if (lo >= hi) return false;
+    t = lo + ((hi - lo) >> 1);
+    if (tries < 4) {
+      const uint32_t jump = step * (uint32_t)(c < room ? room - c : c - room);
+      if (jump < hi - lo) t = c < room ? lo + jump : hi - jump;
+    }
+  }
 }
 
 // Stable compaction of the lanes with keep == true to the front; the other
@@ -273,8 +358,8 @@ __device__ inline uint64_t filter_candidates(uint64_t pk, uint64_t row, int k, i
   // survivors to the front, then a sorting network just wide enough for them
   pk = wave_compact(pk, pk != kKeyMax, kKeyMax, lane);
   pk = wave_sort_upto(pk, lane, __popcll(left));
-  const uint64_t prev = __shfl_up(pk, 1, kWave);
-  const bool rep = lane > 0 && pk != kKeyMax && entry_key(pk) == entry_key(prev);
+  const uint64_t prev = lane_before(pk, kKeyMax);
+  const bool rep = pk != kKeyMax && entry_key(pk) == entry_key(prev);
   if (__ballot(rep) != 0ull) pk = wave_compact(pk, !rep, kKeyMax, lane);
   return pk;
 }

@@ -39,7 +39,7 @@ thread_local std::string g_last_error = "";
 
 struct Layout {
   size_t off_G, off_kth, off_snew, off_sold, off_cnew, off_cold, off_ron,
-      off_roo, off_csn, off_cso, off_capn, off_capo, off_pslot, off_poff, off_bins, off_scan,
+      off_roo, off_csn, off_cso, off_fwd, off_grp, off_pslot, off_poff, off_bins,
       off_cnt, off_snap, off_aside, off_shadow, off_norms, off_flag, off_bkc, off_stg_ent,
       off_stg_cur, off_cls_nodes, off_cls_count, off_half, total;
   bool extra;  // has room for the 16-bit rows of the float32 matrix-core join, the int8 rows of
@@ -146,14 +146,13 @@ Layout make_layout(const gnnd_params* q, bool with_aside, bool extra = true) {
   L.off_roo = take((n + 1) * 8);
   L.off_csn = take(n * p * 4);
   L.off_cso = take(n * p * 4);
-  L.off_capn = take(n * 4);
-  L.off_capo = take(n * 4);
+  L.off_fwd = take(n * 4);
+  L.off_grp = take((n / 32 + 1) * 8);
   L.off_pslot = take(n * 8);
   L.off_poff = take((n + 1) * 8);
   const size_t slots_per_node =
       q->update_mode == GNND_UPDATE_ALL_PAIRS ? 2 * p * (6 * p - 1) : 6 * p;
   L.off_bins = take(n * slots_per_node * 8);
-  L.off_scan = take(scan_tmp_elems((int64_t)n) * 8);
   L.off_cnt = take((size_t)kStripes * C_SLOTS * 8 + 8);  // (and DevState::forms)
   L.off_snap = take((size_t)kStripes * C_SLOTS * 8);
   L.off_aside = take(with_aside ? n * (k / 2) * 8 : 0);
@@ -233,10 +232,9 @@ void bind(gnnd_ctx* c, const Layout& L) {
   d.csr_old = (int32_t*)(w + L.off_cso);
   d.pslot = (uint64_t*)(w + L.off_pslot);
   d.poff = (uint64_t*)(w + L.off_poff);
-  d.capn = (uint32_t*)(w + L.off_capn);
-  d.capo = (uint32_t*)(w + L.off_capo);
+  d.fwd_before = (uint32_t*)(w + L.off_fwd);
+  d.group_before = (uint64_t*)(w + L.off_grp);
   d.bins = (uint64_t*)(w + L.off_bins);
-  d.scan_tmp = (uint64_t*)(w + L.off_scan);
   d.counters = (uint64_t*)(w + L.off_cnt);
   d.aside = (uint64_t*)(w + L.off_aside);
   d.snap = (uint64_t*)(w + L.off_snap);

@@ -17,13 +17,6 @@ static inline dim3 blocks_for_waves(int64_t waves) {
   return grid_blocks((waves + kWavesPerBlock - 1) / kWavesPerBlock);
 }
 
-__device__ inline void counter_add(uint64_t* counters, int which, int64_t stripe_hint,
-                                   uint64_t v) {
-  atomicAdd(reinterpret_cast<unsigned long long*>(
-                counters + (stripe_hint & (kStripes - 1)) * C_SLOTS + which),
-            (unsigned long long)v);
-}
-
 // ---------------------------------------------------------------------------
 // Alg. 1, first loop: k distinct random neighbours per node, distances, sorted
 // ascending by (distance, id), flagged NEW.
@@ -50,34 +43,44 @@ __device__ inline uint64_t select_key(uint64_t base, int64_t v, uint32_t s, uint
   return ((hash3(base, (uint32_t)v, s, iter) >> 32) << 32) | (uint64_t)s;
 }
 
-// Sec. 4.1, reverse part and duplicate removal for one list.  `fwd_raw` is the
-// list row as loaded (its first nf entries are the forward samples), `first` the
-// first 64 reverse candidates (lane < deg).  Of the candidates the 2p - nf with
-// the smallest hash(seed, kind, v, s, iter) (ties by s) are appended - the
+// Sec. 4.1, reverse part and duplicate removal for one list.  `fwd` is the forward part (its nf
+// samples in the first lanes, kNoId in all others), `first` the first 64 of the deg reverse
+// candidates, candidate j in lane (nf + j) % 64 (kNoId where there is none).  Of the candidates the
+// 2p - nf with the smallest hash(seed, kind, v, s, iter) (ties by s) are appended - the
 // paper's "append until the list is full" with the winners chosen by a hash
 // instead of by thread timing.  The list is then sorted by id, duplicates are
 // dropped and it is written back with -1 behind its end.  Returns its size.
-__device__ __forceinline__ int select_list(int64_t v, int p, uint64_t base, uint32_t iter, int32_t* list,
-                                  uint32_t fwd_raw, int nf, const int32_t* csr, uint64_t beg,
-                                  uint32_t deg, uint32_t first, int lane) {
-  const uint32_t fwd = lane < nf ? fwd_raw : kIdMax;
+// (the list is sorted by id in any case, so only which candidates win has to be found out)
+constexpr uint32_t kNoId = 0xffffffffu;
+__device__ __forceinline__ int select_list(int64_t v, int p, uint64_t base, uint32_t iter,
+                                           int32_t* list, uint32_t fwd, int nf, const int32_t* csr,
+                                           uint64_t beg, uint32_t deg, uint32_t first, int lane) {
   const int room = 2 * p - nf;
-  uint32_t rev = kIdMax;
-  int m;
-  if (deg <= (uint32_t)room) {
-    m = (int)deg;
-    if (lane < m) rev = first;
+  uint32_t val;
+  int total = 2 * p;
+  auto hash_of = [&](uint32_t s) { return (uint32_t)(select_key(base, v, s, iter) >> 32); };
+  if (deg <= (uint32_t)room) {  // the candidates stand in the lanes behind the forward part
+    val = vmin(fwd, first);
+    total = nf + (int)deg;
   } else {
-    m = room;
-    uint64_t best = lane < deg ? select_key(base, v, first, iter) : kKeyMax;
-    if (room == kWave / 2 && deg <= (uint32_t)kWave) {
-      // The usual case (a full forward part, up to 64 candidates).  Which 32 candidates win
-      // is all that matters - the list is sorted by id below - so the network stops where
-      // the lower half of the lanes holds the 32 smallest keys: halves sorted up and down
-      // (15 stages), then one exchange across the halves, instead of 21 stages.
-      best = wave_sort_first<kWave / 2>(best, lane);
-      best = vmin(best, xor_lanes(best, kWave / 2, lane));
-    } else {
+    bool chosen = false;
+    if (deg <= (uint32_t)kWave) {
+      const uint32_t h[1] = {hash_of(first)};
+      const uint64_t have[1] = {__ballot(first != kNoId)};
+      uint64_t win[1];
+      chosen = choose_smallest(h, have, (int)deg, room, win);
+      if (chosen) {
+        // the winners move to the lanes behind the forward part, the others to all other lanes
+        const int before = rank_in(win[0]);
+        const bool mine = (win[0] >> lane) & 1ull;
+        const int dst = mine ? nf + before : 2 * p + lane - before;
+        const uint32_t moved =
+            (uint32_t)__builtin_amdgcn_ds_permute((dst & 63) << 2, (int)first);
+        val = lane < nf ? fwd : lane < 2 * p ? moved : kNoId;
+      }
+    }
+    if (!chosen) {
+      uint64_t best = first != kNoId ? select_key(base, v, first, iter) : kKeyMax;
       best = wave_sort(best, lane);
       for (uint32_t c = kWave; c < deg; c += kWave) {
         uint64_t key =
@@ -85,18 +88,17 @@ __device__ __forceinline__ int select_list(int64_t v, int p, uint64_t base, uint
         key = wave_sort(key, lane);
         best = wave_merge_smallest(best, key, lane);
       }
+      const int src = lane - nf;
+      const uint32_t r = __shfl((uint32_t)best, src < 0 ? 0 : src, kWave);
+      val = lane < nf ? fwd : src < room ? r : kNoId;
     }
-    if (lane < room) rev = (uint32_t)best;
   }
-  const int src = lane - nf;
-  const uint32_t r = __shfl(rev, src < 0 ? 0 : src, kWave);
-  uint32_t val = lane < nf ? fwd : (src < m ? r : kIdMax);
-  val = wave_sort_upto(val, lane, nf + m);
-  const uint32_t prev = __shfl_up(val, 1, kWave);
-  const bool keep = val != kIdMax && (lane == 0 || val != prev);
+  val = wave_sort_upto(val, lane, total);
+  const uint32_t prev = lane_before(val, kNoId);
+  const bool keep = val != prev && val != kNoId;
   const uint64_t mask = __ballot(keep);
   const int count = __popcll(mask);
-  if (keep) list[__popcll(mask & lanes_below(lane))] = (int32_t)val;
+  if (keep) list[rank_in(mask)] = (int32_t)val;
   if (lane >= count && lane < 2 * p) list[lane] = -1;
   return count;
 }
@@ -115,9 +117,8 @@ __global__ __launch_bounds__(kBlock) void k_rev_select(int64_t n, int p, uint64_
                                                        const uint64_t* roff_old,
                                                        const int32_t* csr_new,
                                                        const int32_t* csr_old,
-                                                       uint32_t* capn, uint32_t* capo,
-                                                       uint32_t per_new, uint32_t per_old,
-                                                       uint64_t* counters) {
+                                                       SegmentRule seg, uint64_t* poff,
+                                                       uint64_t* pslot, uint64_t* counters) {
   const int64_t v0 = wave_global_index() * kNodesPerWave;
   if (v0 >= n) return;
   const int lane = lane_id();
@@ -126,6 +127,20 @@ __global__ __launch_bounds__(kBlock) void k_rev_select(int64_t n, int p, uint64_
   uint64_t bn[kNodesPerWave], bo[kNodesPerWave];
   uint32_t dn[kNodesPerWave], dO[kNodesPerWave];  // a node's reverse degree is below 2^32
   uint32_t rown[kNodesPerWave], rowo[kNodesPerWave], firstn[kNodesPerWave], firsto[kNodesPerWave];
+  // (what the nodes' segments follow from: a lane per node)
+  uint64_t fwd_l = 0, bn_l = 0, bo_l = 0;
+  uint32_t dn_l = 0, do_l = 0;
+  int fn_l = 0, fo_l = 0;
+  if (lane < kNodesPerWave && v0 + lane < n) {
+    const int64_t v = v0 + lane;
+    fwd_l = seg.before(v);
+    fn_l = cnew[v];
+    fo_l = cold[v];
+    bn_l = roff_new[v];
+    dn_l = (uint32_t)(roff_new[v + 1] - bn_l);
+    bo_l = roff_old[v];
+    do_l = (uint32_t)(roff_old[v + 1] - bo_l);
+  }
 #pragma unroll
   for (int i = 0; i < kNodesPerWave; ++i) {
     const int64_t v = v0 + i < n ? v0 + i : n - 1;  // beyond the end: the last node again, unused
@@ -135,15 +150,18 @@ __global__ __launch_bounds__(kBlock) void k_rev_select(int64_t n, int p, uint64_
     dn[i] = (uint32_t)(roff_new[v + 1] - bn[i]);
     bo[i] = roff_old[v];
     dO[i] = (uint32_t)(roff_old[v + 1] - bo[i]);
-    rown[i] = lane < p ? (uint32_t)snew[v * L + lane] : kIdMax;  // the forward part
-    rowo[i] = lane < p ? (uint32_t)sold[v * L + lane] : kIdMax;
+    rown[i] = lane < p ? (uint32_t)snew[v * L + lane] : kNoId;  // the forward part, -1 behind it
+    rowo[i] = lane < p ? (uint32_t)sold[v * L + lane] : kNoId;
   }
 #pragma unroll
   for (int i = 0; i < kNodesPerWave; ++i) {
-    firstn[i] = (uint32_t)lane < dn[i] ? (uint32_t)csr_new[bn[i] + lane] : kIdMax;
-    firsto[i] = (uint32_t)lane < dO[i] ? (uint32_t)csr_old[bo[i] + lane] : kIdMax;
+    const uint32_t jn = (uint32_t)(lane - nfn[i]) & 63u, jo = (uint32_t)(lane - nfo[i]) & 63u;
+    firstn[i] = jn < dn[i] ? (uint32_t)csr_new[bn[i] + jn] : kNoId;
+    firsto[i] = jo < dO[i] ? (uint32_t)csr_old[bo[i] + jo] : kNoId;
   }
   uint64_t sum_new = 0, sum_old = 0;
+  // Lane i holds what is written for node i: its list sizes and its segment of the proposals.
+  int size_n = 0, size_o = 0;
 #pragma unroll
   for (int i = 0; i < kNodesPerWave; ++i) {
     const int64_t v = v0 + i;
@@ -154,18 +172,15 @@ __global__ __launch_bounds__(kBlock) void k_rev_select(int64_t n, int p, uint64_
                                  bo[i], dO[i], firsto[i], lane);
       sum_new += (uint64_t)cn;
       sum_old += (uint64_t)co;
-      if (lane == 0) {
-        cnew[v] = cn;
-        cold[v] = co;
-        // v can only sit in the sample list of a node that holds v as a forward
-        // sample (deg of them) or that v holds as one (nf): that bounds the number
-        // of joins v takes part in, hence the nearest-object results it can
-        // receive - two per join as a NEW sample, one as an OLD sample (per_new, per_old;
-        // when every pair is proposed: one per possible partner).
-        capn[v] = (uint32_t)(per_new * (dn[i] + (uint64_t)nfn[i]));
-        capo[v] = (uint32_t)(per_old * (dO[i] + (uint64_t)nfo[i]));
-      }
+      size_n = lane == i ? cn : size_n;
+      size_o = lane == i ? co : size_o;
     }
+  }
+  if (lane < kNodesPerWave && v0 + lane < n) {
+    const int64_t v = v0 + lane;
+    cnew[v] = size_n;
+    cold[v] = size_o;
+    seg.write(v, n, fwd_l, bn_l, dn_l, fn_l, bo_l, do_l, fo_l, poff, pslot, counters);
   }
   if (lane == 0) {
     counter_add(counters, C_SUMNEW, v0, sum_new);
@@ -239,8 +254,7 @@ __device__ inline uint64_t half_merge_smallest(uint64_t a_sorted, uint64_t b_sor
   uint64_t v = vmin(a_sorted, br);
 #pragma unroll
   for (int j = 16; j > 0; j >>= 1) {
-    const uint64_t o = xor_lanes(v, j, lane);
-    v = exchange(v, o, (lane & j) == 0);
+    v = exchange_step(v, j, lane, (lane & j) == 0);
   }
   return v;
 }
@@ -273,7 +287,7 @@ __device__ inline uint64_t half_sort_unique(uint64_t pk, int count, int lane) {
   else if (count > 4) pk = wave_sort_first<8>(pk, l32);
   else if (count > 2) pk = wave_sort_first<4>(pk, l32);
   else if (count > 1) pk = wave_sort_first<2>(pk, l32);
-  const uint64_t prev = __shfl_up(pk, 1, kWave);
+  const uint64_t prev = lane_before(pk, kKeyMax);
   const bool rep = l32 > 0 && pk != kKeyMax && entry_key(pk) == entry_key(prev);
   if (__ballot(rep) != 0ull) pk = half_compact(pk, !rep, kKeyMax, lane);
   return pk;
@@ -525,108 +539,6 @@ __global__ __launch_bounds__(kBlock) void k_merge_final(int64_t n, MergeIds mi, 
 }
 
 // ---------------------------------------------------------------------------
-// Exclusive scan: per-block scan of 1024 elements, scan of the block sums, add-back.
-constexpr int kScanPerThread = 4;
-constexpr int kScanPerBlock = kBlock * kScanPerThread;
-
-__device__ inline uint64_t block_exclusive_scan(uint64_t v, uint64_t* total) {
-  __shared__ uint64_t wsum[kWavesPerBlock];
-  const int lane = lane_id();
-  const int wave = wave_id();
-  uint64_t inc = v;
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    uint64_t o = __shfl_up(inc, off, kWave);
-    if (lane >= off) inc += o;
-  }
-  if (lane == kWave - 1) wsum[wave] = inc;
-  __syncthreads();
-  uint64_t before = 0, all = 0;
-  for (int w = 0; w < kWavesPerBlock; ++w) {
-    if (w < wave) before += wsum[w];
-    all += wsum[w];
-  }
-  __syncthreads();
-  *total = all;
-  return before + inc - v;
-}
-
-__global__ __launch_bounds__(kBlock) void k_scan_local(const uint32_t* in, const uint32_t* in2,
-                                                       uint64_t* out, uint64_t* bsum,
-                                                       uint64_t* counters, int64_t count) {
-  const int64_t i0 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * kScanPerThread;
-  uint32_t v[kScanPerThread];
-  uint64_t sum = 0;
-#pragma unroll
-  for (int j = 0; j < kScanPerThread; ++j) {
-    v[j] = (i0 + j < count) ? in[i0 + j] + (in2 ? in2[i0 + j] : 0u) : 0u;
-    sum += v[j];
-    // a segment longer than the count field of the slot word can hold is reported
-    if (counters && v[j] > kSlotCountMask) counter_add(counters, C_OVERFLOW, i0 + j, v[j]);
-  }
-  uint64_t total;
-  uint64_t run = block_exclusive_scan(sum, &total);
-#pragma unroll
-  for (int j = 0; j < kScanPerThread; ++j) {
-    if (i0 + j <= count) out[i0 + j] = run;
-    run += v[j];
-  }
-  if (threadIdx.x == 0) bsum[blockIdx.x] = total;
-}
-
-__global__ __launch_bounds__(kBlock) void k_scan_bsum(uint64_t* bsum, int64_t nb) {
-  uint64_t carry = 0;
-  for (int64_t c = 0; c < nb; c += kBlock) {
-    const int64_t i = c + threadIdx.x;
-    uint64_t v = i < nb ? bsum[i] : 0;
-    uint64_t total;
-    uint64_t ex = block_exclusive_scan(v, &total);
-    if (i < nb) bsum[i] = carry + ex;
-    carry += total;
-  }
-}
-
-// SUM: bsum holds the block sums themselves, and every block adds up those before its own
-// (for up to kScanSumBlocks blocks cheaper than a launch of k_scan_bsum); otherwise their scan.
-constexpr int64_t kScanSumBlocks = 2048;
-template <bool SUM>
-__global__ __launch_bounds__(kBlock) void k_scan_add(uint64_t* out, uint64_t* packed,
-                                                     const uint64_t* bsum, int64_t count) {
-  const int64_t i0 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * kScanPerThread;
-  uint64_t add;
-  if (SUM) {
-    uint64_t mine = 0;
-    for (unsigned b = threadIdx.x; b < blockIdx.x; b += kBlock) mine += bsum[b];
-    (void)block_exclusive_scan(mine, &add);
-  } else {
-    add = bsum[blockIdx.x];
-  }
-#pragma unroll
-  for (int j = 0; j < kScanPerThread; ++j)
-    if (i0 + j <= count) {
-      const uint64_t v = out[i0 + j] + add;
-      out[i0 + j] = v;
-      // slot word of element i0 + j: its offset, nothing received yet
-      if (packed && i0 + j < count) packed[i0 + j] = v << kSlotCountBits;
-    }
-}
-
-size_t scan_tmp_elems(int64_t count) { return (size_t)((count + 1 + kScanPerBlock - 1) / kScanPerBlock); }
-
-hipError_t launch_scan(const uint32_t* in, const uint32_t* in2, uint64_t* out, uint64_t* packed,
-                       uint64_t* counters, uint64_t* tmp, int64_t count, hipStream_t st) {
-  const int64_t nb = (count + 1 + kScanPerBlock - 1) / kScanPerBlock;
-  k_scan_local<<<(unsigned)nb, kBlock, 0, st>>>(in, in2, out, tmp, counters, count);
-  if (nb <= kScanSumBlocks) {
-    k_scan_add<true><<<(unsigned)nb, kBlock, 0, st>>>(out, packed, tmp, count);
-  } else {
-    k_scan_bsum<<<1, kBlock, 0, st>>>(tmp, nb);
-    k_scan_add<false><<<(unsigned)nb, kBlock, 0, st>>>(out, packed, tmp, count);
-  }
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
 static VecSrc vec_src(const Shape& sh) {
   return VecSrc{sh.vec_a, sh.vec_b, sh.split, sh.d, sh.norms};
 }
@@ -716,20 +628,16 @@ hipError_t launch_init_random(const Shape& sh, const DevState& ds, uint64_t seed
 hipError_t launch_sample(const Shape& sh, const DevState& ds, uint64_t seed, uint32_t iter,
                          hipStream_t st) {
   // forward sampling, and the reverse candidates grouped by target (two-level counting sort)
-  hipError_t e = launch_sample_buckets(sh, ds, st);
+  int group_rows = 0;
+  hipError_t e = launch_sample_buckets(sh, ds, &group_rows, st);
   if (e != hipSuccess) return e;
-  if (2 * sh.p > kWave) {  // two list entries per lane
-    e = launch_rev_select_long(sh, ds, seed, iter, st);
-    if (e != hipSuccess) return e;
-    return launch_scan(ds.capn, ds.capo, ds.poff, ds.pslot, ds.counters, ds.scan_tmp, sh.n, st);
-  }
+  if (2 * sh.p > kWave)  // two list entries per lane
+    return launch_rev_select_long(sh, ds, seed, iter, group_rows, st);
   k_rev_select<<<blocks_for_waves((sh.n + kNodesPerWave - 1) / kNodesPerWave), kBlock, 0, st>>>(
       sh.n, sh.p, hash_base(seed, kTagRevNew), hash_base(seed, kTagRevOld), iter, ds.snew,
-      ds.sold, ds.cnew, ds.cold, ds.roff_new, ds.roff_old, ds.csr_new, ds.csr_old, ds.capn,
-      ds.capo, (uint32_t)sh.slots_new_per_appearance(), (uint32_t)sh.slots_old_per_appearance(),
-      ds.counters);
-  // one segment of the proposal array per destination, sized by its bound
-  return launch_scan(ds.capn, ds.capo, ds.poff, ds.pslot, ds.counters, ds.scan_tmp, sh.n, st);
+      ds.sold, ds.cnew, ds.cold, ds.roff_new, ds.roff_old, ds.csr_new, ds.csr_old,
+      SegmentRule(sh, ds, group_rows), ds.poff, ds.pslot, ds.counters);
+  return hipGetLastError();
 }
 
 hipError_t launch_update(const Shape& sh, const DevState& ds, hipStream_t st) {

@@ -43,12 +43,11 @@ struct DevState {
   uint64_t* roff_old;  // n+1
   int32_t* csr_new;    // n*p reverse candidates grouped by target
   int32_t* csr_old;    // n*p
-  uint32_t* capn;      // n: upper bound of the proposals a node can receive as a NEW sample
-  uint32_t* capo;      // n: ... as an OLD sample
   uint64_t* pslot;     // n: (segment start << 24) | proposals received; rewritten by every sampling
-  uint64_t* poff;      // n+1 segment offsets into bins (exclusive scan of capn + capo)
+  uint64_t* poff;      // n+1 segment offsets into bins (see SegmentRule)
+  uint32_t* fwd_before;    // n: see SegmentRule
+  uint64_t* group_before;  // n / 32 + 1: one per workgroup of the forward sampling
   uint64_t* bins;      // n*6p packed proposals, one segment per destination
-  uint64_t* scan_tmp;  // block sums of the scans
   uint64_t* counters;  // kStripes * C_SLOTS
   uint64_t* snap;      // the counters as the current iteration's sampling stage found them
   uint64_t* forms;     // joins with a faster first form: how it has gone so far (see FormTally)
@@ -110,6 +109,63 @@ struct Shape {
   }
 };
 
+__device__ inline void counter_add(uint64_t* counters, int which, int64_t stripe_hint,
+                                   uint64_t v) {
+  atomicAdd(reinterpret_cast<unsigned long long*>(
+                counters + (stripe_hint & (kStripes - 1)) * C_SLOTS + which),
+            (unsigned long long)v);
+}
+
+// One segment of the proposal array per destination, one behind the other.  Node v can only sit in
+// the sample list of a node that holds v as a forward sample (its reverse degree of them) or that v
+// holds as one, which bounds the number of joins it takes part in and with them the results it can
+// receive: per_new per join as a NEW sample, per_old per join as an OLD one.  Where a segment
+// starts follows from v's places in the two candidate arrays (the reverse degrees of all nodes
+// before it) and from the forward samples of the nodes before it.  Two launches of a scan over the
+// bounds stood here before: 7 us per iteration at 4096 nodes, 19 at 10^6.
+// Up to kRoomForAll nodes p forward samples are counted for every node, which needs no sums (all
+// segments together then fill the array); beyond, the forward sampling adds up the actual numbers
+// per workgroup (k_fwd_count, k_wg_scan), because longer segments cost the passes over the
+// proposals more than the sums cost.
+constexpr int64_t kRoomForAll = 1 << 18;
+struct SegmentRule {
+  uint32_t per_new, per_old;
+  uint32_t per_node;            // slots for p forward samples of either kind; 0: the actual number
+  uint32_t inverse;             // see group_of
+  const uint32_t* fwd_before;   // slots for the forward samples of the nodes before v in its group
+  const uint64_t* group_before; // ... of the groups before this one
+  SegmentRule(const Shape& sh, const DevState& ds, int group_rows)
+      : per_new((uint32_t)sh.slots_new_per_appearance()),
+        per_old((uint32_t)sh.slots_old_per_appearance()),
+        per_node(sh.n <= kRoomForAll ? (uint32_t)sh.p * (per_new + per_old) : 0u),
+        inverse((uint32_t)((((uint64_t)1 << 32) + (group_rows >> 5) - 1) / (group_rows >> 5))),
+        fwd_before(ds.fwd_before), group_before(ds.group_before) {}
+  // v / group_rows: a group is a multiple of 32 rows, at most 4096, and v below 2^27, so that the
+  // product with the reciprocal, rounded up, is exact (groups of 32: the reciprocal is 2^32)
+  __device__ uint32_t group_of(int64_t v) const {
+    const uint32_t v32 = (uint32_t)(v >> 5);
+    return inverse ? __umulhi(v32, inverse) : v32;
+  }
+  // Slots for the forward samples of the nodes before v.
+  __device__ uint64_t before(int64_t v) const {
+    return per_node ? (uint64_t)v * per_node : fwd_before[v] + group_before[group_of(v)];
+  }
+  // Node v's offset and its slot word (nothing received yet); `fwd` = before(v), `beg_*`, `deg_*`:
+  // its reverse candidates, `fwd_*`: its forward samples.  The last node closes the offsets.
+  __device__ void write(int64_t v, int64_t n, uint64_t fwd, uint64_t beg_new, uint32_t deg_new,
+                        int fwd_new, uint64_t beg_old, uint32_t deg_old, int fwd_old,
+                        uint64_t* poff, uint64_t* pslot, uint64_t* counters) const {
+    const uint64_t at = per_new * beg_new + per_old * beg_old + fwd;
+    const uint64_t rev = (uint64_t)per_new * deg_new + (uint64_t)per_old * deg_old;
+    const uint64_t size = rev + per_new * (uint32_t)fwd_new + per_old * (uint32_t)fwd_old;
+    poff[v] = at;
+    pslot[v] = at << kSlotCountBits;
+    if (v == n - 1) poff[n] = at + (per_node ? rev + per_node : size);
+    // more results than the count field of the slot word can hold: reported
+    if (size > kSlotCountMask) counter_add(counters, C_OVERFLOW, v, size);
+  }
+};
+
 // Grid of `blocks` workgroups, folded into two dimensions beyond 2^22 (device side:
 // block_linear()); the fold may add up to 2^22 - 1 workgroups past the end.
 inline dim3 grid_blocks(int64_t blocks) {
@@ -145,11 +201,13 @@ hipError_t launch_pack_i8(const Shape& sh, const DevState& ds, int* bad_flag_dev
 hipError_t launch_init_random_i8(const Shape& sh, const DevState& ds, uint64_t seed,
                                  hipStream_t st);
 // (also takes the snapshot of the counters and clears the joins' node list lengths and region
-// cursors: the first stage of an iteration)
-hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, hipStream_t st);
+// cursors: the first stage of an iteration).  `group_rows`: rows per workgroup of the forward
+// sampling (see SegmentRule).
+hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, int* group_rows,
+                                 hipStream_t st);
 // sample lists of 65..128 objects (p > 32): reverse selection and the join for long lists
 hipError_t launch_rev_select_long(const Shape& sh, const DevState& ds, uint64_t seed,
-                                  uint32_t iter, hipStream_t st);
+                                  uint32_t iter, int group_rows, hipStream_t st);
 hipError_t launch_join_long(const Shape& sh, const DevState& ds, bool merge_mode, hipStream_t st);
 // the same on byte-valued data of up to 128 dimensions (int8 rows in ds.shadow)
 hipError_t launch_join_long_i8(const Shape& sh, const DevState& ds, bool merge_mode,
@@ -199,12 +257,5 @@ hipError_t launch_exact_scan(const void* vec, int64_t n, int32_t d, int32_t metr
                              const int32_t* queries, int64_t nq, int32_t K, int32_t* ids_out,
                              void* dist_out, void* workspace, hipStream_t st);
 hipError_t launch_zero_u32(uint32_t* p, size_t count, hipStream_t st);
-
-// Exclusive scan of `count` uint32 into uint64 offsets out[0..count] (out[count] = total).
-// (in2 may be NULL; otherwise the scanned values are in[i] + in2[i])
-hipError_t launch_scan(const uint32_t* in, const uint32_t* in2, uint64_t* out, uint64_t* packed,
-                       uint64_t* counters, uint64_t* tmp,
-                       int64_t count, hipStream_t st);
-size_t scan_tmp_elems(int64_t count);
 
 }  // namespace gnnd

@@ -18,64 +18,76 @@ namespace {
 constexpr int kLB = 256;
 constexpr int kWavesPerLB = kLB / kWave;
 
-__device__ inline void counter_add_long(uint64_t* counters, int which, int64_t stripe_hint,
-                                        uint64_t v) {
-  atomicAdd(reinterpret_cast<unsigned long long*>(
-                counters + (stripe_hint & (kStripes - 1)) * C_SLOTS + which),
-            (unsigned long long)v);
-}
-
-// One sample list of up to 128 objects.  `fwd_raw` holds the forward samples (lane <
-// nf <= 64); of the `deg` reverse candidates csr[beg..] the 2p - nf with the smallest
-// hash(seed, kind, v, s, iter) (ties by s) join them, all of them when they fit.  The
+// One sample list of up to 128 objects.  `fwd` holds the forward samples (lane < nf <= 64); of the
+// `deg` reverse candidates csr[beg..] the 2p - nf with the smallest hash(seed, kind, v, s, iter)
+// (ties by s) join them, all of them when they fit; `first` holds the first 128 of them.  The
 // list is then sorted by id, duplicates are dropped, and it is written back with -1
 // behind its end.  Returns its size.
 __device__ inline int select_list_long(int64_t v, int p, uint64_t base, uint32_t iter,
-                                       int32_t* list, uint32_t fwd_raw, int nf,
-                                       const int32_t* csr, uint64_t beg, uint64_t deg, int lane) {
+                                       int32_t* list, uint32_t fwd, int nf, const int32_t* csr,
+                                       uint64_t beg, uint64_t deg, const uint32_t (&first)[2],
+                                       int lane) {
   const int room = 2 * p - nf;  // 1..128
-  uint32_t rev0 = kIdMax, rev1 = kIdMax;
-  int m;
+  const int m = deg <= (uint64_t)room ? (int)deg : room;
+  // the chosen ones stand in the lanes `win` of two registers; the forward samples come first and
+  // the chosen ones behind them, object i of that sequence in lane i % 64 of register i / 64
+  uint32_t rev[2] = {first[0], first[1]};
+  uint64_t win[2];
+  bool chosen = true;
   if (deg <= (uint64_t)room) {
-    m = (int)deg;
-    if (lane < m) rev0 = (uint32_t)csr[beg + lane];
-    if (lane + kWave < m) rev1 = (uint32_t)csr[beg + kWave + lane];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) win[r] = __ballot((uint64_t)(lane + r * kWave) < deg);
   } else {
-    m = room;
-    uint64_t best0 = kKeyMax, best1 = kKeyMax;  // the 128 smallest keys so far, ascending
-    for (uint64_t c = 0; c < deg; c += kWave) {
-      uint64_t key = kKeyMax;
-      if (c + lane < deg) {
-        const uint32_t s = (uint32_t)csr[beg + c + lane];
-        key = ((hash3(base, (uint32_t)v, s, iter) >> 32) << 32) | (uint64_t)s;
+    chosen = deg <= (uint64_t)(2 * kWave);
+    if (chosen) {
+      uint32_t h[2];
+      uint64_t have[2];
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        h[r] = (uint32_t)(hash3(base, (uint32_t)v, first[r], iter) >> 32);
+        have[r] = __ballot((uint64_t)(lane + r * kWave) < deg);
       }
-      key = wave_sort(key, lane);
-      merge128(best0, best1, key, lane);
+      chosen = choose_smallest(h, have, (int)deg, room, win);
     }
-    if (lane < room) rev0 = (uint32_t)best0;
-    if (lane + kWave < room) rev1 = (uint32_t)best1;
+    if (!chosen) {
+      uint64_t best0 = kKeyMax, best1 = kKeyMax;  // the 128 smallest keys so far, ascending
+      for (uint64_t c = 0; c < deg; c += kWave) {
+        uint64_t key = kKeyMax;
+        if (c + lane < deg) {
+          const uint32_t s = (uint32_t)csr[beg + c + lane];
+          key = ((hash3(base, (uint32_t)v, s, iter) >> 32) << 32) | (uint64_t)s;
+        }
+        key = wave_sort(key, lane);
+        merge128(best0, best1, key, lane);
+      }
+      rev[0] = (uint32_t)best0;
+      rev[1] = (uint32_t)best1;
+#pragma unroll
+      for (int r = 0; r < 2; ++r) win[r] = __ballot(lane + r * kWave < room);
+    }
   }
-  // forward samples first, the chosen candidates behind them: object i of that
-  // sequence in lane i % 64 of register i / 64
   const int total = nf + m;  // <= 2p <= 128
-  const int j0 = lane - nf, j1 = lane + kWave - nf;  // positions among the candidates
-  const uint32_t a0 = __shfl(rev0, j0 < 0 ? 0 : j0, kWave);
-  const uint32_t b0 = __shfl(rev0, j1 & 63, kWave), b1 = __shfl(rev1, j1 & 63, kWave);
-  uint32_t v0 = lane < nf ? fwd_raw : a0;
-  uint32_t v1 = j1 < kWave ? b0 : b1;
-  if (lane >= total) v0 = kIdMax;
-  if (lane + kWave >= total) v1 = kIdMax;
+  const int mid = nf + __popcll(win[0]);  // objects of the second register start here
+  uint32_t moved[2];
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const int at = r ? mid : nf, behind = r ? total : mid;
+    const int before = rank_in(win[r]);
+    const int dst = (win[r] >> lane) & 1ull ? at + before : behind + lane - before;
+    moved[r] = (uint32_t)__builtin_amdgcn_ds_permute((dst & 63) << 2, (int)rev[r]);
+  }
+  uint32_t v0 = lane < nf ? fwd : lane < mid ? moved[0] : lane < total ? moved[1] : kIdMax;
+  const int i1 = lane + kWave;
+  uint32_t v1 = i1 < mid ? moved[0] : i1 < total ? moved[1] : kIdMax;
   sort128(v0, v1, lane);
-  const uint32_t p0 = __shfl_up(v0, 1, kWave);
-  const uint32_t last0 = __shfl(v0, kWave - 1, kWave);
-  uint32_t p1 = __shfl_up(v1, 1, kWave);
-  if (lane == 0) p1 = last0;
-  const bool keep0 = v0 != kIdMax && (lane == 0 || v0 != p0);
+  const uint32_t p0 = lane_before(v0, kIdMax);
+  const uint32_t p1 = lane_before(v1, (uint32_t)__builtin_amdgcn_readlane((int)v0, kWave - 1));
+  const bool keep0 = v0 != kIdMax && v0 != p0;
   const bool keep1 = v1 != kIdMax && v1 != p1;
   const uint64_t m0 = __ballot(keep0), m1 = __ballot(keep1);
   const int c0 = __popcll(m0), count = c0 + __popcll(m1);
-  if (keep0) list[__popcll(m0 & lanes_below(lane))] = (int32_t)v0;
-  if (keep1) list[c0 + __popcll(m1 & lanes_below(lane))] = (int32_t)v1;
+  if (keep0) list[rank_in(m0)] = (int32_t)v0;
+  if (keep1) list[c0 + rank_in(m1)] = (int32_t)v1;
   if (lane >= count && lane < 2 * p) list[lane] = -1;
   if (lane + kWave >= count && lane + kWave < 2 * p) list[lane + kWave] = -1;
   return count;
@@ -85,8 +97,8 @@ __device__ inline int select_list_long(int64_t v, int p, uint64_t base, uint32_t
 __global__ __launch_bounds__(kLB) void k_rev_select_long(
     int64_t n, int p, uint64_t base_new, uint64_t base_old, uint32_t iter, int32_t* snew,
     int32_t* sold, int32_t* cnew, int32_t* cold, const uint64_t* roff_new,
-    const uint64_t* roff_old, const int32_t* csr_new, const int32_t* csr_old, uint32_t* capn,
-    uint32_t* capo, uint32_t per_new, uint32_t per_old, uint64_t* counters) {
+    const uint64_t* roff_old, const int32_t* csr_new, const int32_t* csr_old, SegmentRule seg,
+    uint64_t* poff, uint64_t* pslot, uint64_t* counters) {
   const int64_t v = block_linear() * kWavesPerLB + wave_id();
   if (v >= n) return;
   const int lane = lane_id();
@@ -98,17 +110,22 @@ __global__ __launch_bounds__(kLB) void k_rev_select_long(
   const uint64_t bo = roff_old[v], dO = roff_old[v + 1] - bo;
   const uint32_t rown = lane < nfn ? (uint32_t)list_n[lane] : kIdMax;
   const uint32_t rowo = lane < nfo ? (uint32_t)list_o[lane] : kIdMax;
-  const int cn = select_list_long(v, p, base_new, iter, list_n, rown, nfn, csr_new, bn, dn, lane);
-  const int co = select_list_long(v, p, base_old, iter, list_o, rowo, nfo, csr_old, bo, dO, lane);
+  uint32_t fn[2], fo[2];
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    fn[r] = (uint64_t)(lane + r * kWave) < dn ? (uint32_t)csr_new[bn + lane + r * kWave] : kIdMax;
+    fo[r] = (uint64_t)(lane + r * kWave) < dO ? (uint32_t)csr_old[bo + lane + r * kWave] : kIdMax;
+  }
+  const int cn = select_list_long(v, p, base_new, iter, list_n, rown, nfn, csr_new, bn, dn, fn,
+                                  lane);
+  const int co = select_list_long(v, p, base_old, iter, list_o, rowo, nfo, csr_old, bo, dO, fo,
+                                  lane);
   if (lane == 0) {
     cnew[v] = cn;
     cold[v] = co;
-    counter_add_long(counters, C_SUMNEW, v, (uint64_t)cn);
-    counter_add_long(counters, C_SUMOLD, v, (uint64_t)co);
-    // bound of the results v can receive: per join it takes part in, two as a NEW sample
-    // and one as an OLD sample; it takes part in at most (candidates + forward samples) joins
-    capn[v] = (uint32_t)(per_new * (dn + (uint64_t)nfn));
-    capo[v] = (uint32_t)(per_old * (dO + (uint64_t)nfo));
+    counter_add(counters, C_SUMNEW, v, (uint64_t)cn);
+    counter_add(counters, C_SUMOLD, v, (uint64_t)co);
+    seg.write(v, n, seg.before(v), bn, (uint32_t)dn, nfn, bo, (uint32_t)dO, nfo, poff, pslot, counters);
   }
 }
 
@@ -336,12 +353,12 @@ __global__ __launch_bounds__(kLB) void k_join_long(
     n_over += __shfl_xor(n_over, off, kWave);
   }
   if (lane == 0) {
-    if (n_pass) counter_add_long(counters, C_PASSED, s, n_pass);
-    if (n_over) counter_add_long(counters, C_OVERFLOW, s, n_over);
-    if (n_found) counter_add_long(counters, C_PROPS, s, n_found);
+    if (n_pass) counter_add(counters, C_PASSED, s, n_pass);
+    if (n_over) counter_add(counters, C_OVERFLOW, s, n_over);
+    if (n_found) counter_add(counters, C_PROPS, s, n_found);
     if (tid == 0) {
       const uint64_t ev = (uint64_t)pair_count + (do_nn ? (uint64_t)nn * (nn - 1) / 2 : 0);
-      if (ev) counter_add_long(counters, C_EVALS, s, ev);
+      if (ev) counter_add(counters, C_EVALS, s, ev);
     }
   }
 }
@@ -349,13 +366,12 @@ __global__ __launch_bounds__(kLB) void k_join_long(
 }  // namespace
 
 hipError_t launch_rev_select_long(const Shape& sh, const DevState& ds, uint64_t seed,
-                                  uint32_t iter, hipStream_t st) {
+                                  uint32_t iter, int group_rows, hipStream_t st) {
   const dim3 grid = grid_blocks((sh.n + kWavesPerLB - 1) / kWavesPerLB);
   k_rev_select_long<<<grid, kLB, 0, st>>>(
       sh.n, sh.p, hash_base(seed, kTagRevNew), hash_base(seed, kTagRevOld), iter, ds.snew, ds.sold,
-      ds.cnew, ds.cold, ds.roff_new, ds.roff_old, ds.csr_new, ds.csr_old, ds.capn, ds.capo,
-      (uint32_t)sh.slots_new_per_appearance(), (uint32_t)sh.slots_old_per_appearance(),
-      ds.counters);
+      ds.cnew, ds.cold, ds.roff_new, ds.roff_old, ds.csr_new, ds.csr_old, SegmentRule(sh, ds, group_rows),
+      ds.poff, ds.pslot, ds.counters);
   return hipGetLastError();
 }
 

@@ -40,7 +40,7 @@ struct BucketGeom {
 __device__ inline void forward_sample_row(int64_t s, int64_t n, int k, int p, uint64_t* G,
                                           int32_t* snew, int32_t* sold, int32_t* cnew,
                                           int32_t* cold, int lane, uint64_t e, int32_t& v_new,
-                                          int32_t& v_old) {
+                                          int32_t& v_old, int& cn, int& co) {
   // e = this lane's entry of the row (lanes >= k: anything)
   // entries numbered beyond n are frozen leftovers of an earlier merge: not sampled
   const bool valid = lane < k && (int64_t)entry_id(e) < n;
@@ -60,7 +60,8 @@ __device__ inline void forward_sample_row(int64_t s, int64_t n, int k, int p, ui
     sold[s * L + ro] = id;
     v_old = id;
   }
-  const int cn = __popcll(mn) < p ? __popcll(mn) : p, co = __popcll(mo) < p ? __popcll(mo) : p;
+  cn = __popcll(mn) < p ? __popcll(mn) : p;
+  co = __popcll(mo) < p ? __popcll(mo) : p;
   // the rest of the forward part reads "nothing", so that the scatter pass needs no counts
   if (lane >= cn && lane < p) snew[s * L + lane] = -1;
   if (lane >= co && lane < p) sold[s * L + lane] = -1;
@@ -75,7 +76,8 @@ __device__ inline void forward_sample_row(int64_t s, int64_t n, int k, int p, ui
 __device__ inline void forward_sample_row_wide(int64_t s, int64_t n, int k, int p, uint64_t* G,
                                                int32_t* snew, int32_t* sold, int32_t* cnew,
                                                int32_t* cold, int lane, uint64_t e0, uint64_t e1,
-                                               int32_t (&v_new)[2], int32_t (&v_old)[2]) {
+                                               int32_t (&v_new)[2], int32_t (&v_old)[2], int& cn,
+                                               int& co) {
   const uint64_t e[2] = {e0, e1};
   uint64_t mn[2], mo[2];
   bool isnew[2], isold[2];
@@ -105,7 +107,8 @@ __device__ inline void forward_sample_row_wide(int64_t s, int64_t n, int k, int 
     }
   }
   const int tn = __popcll(mn[0]) + __popcll(mn[1]), to = __popcll(mo[0]) + __popcll(mo[1]);
-  const int cn = tn < p ? tn : p, co = to < p ? to : p;
+  cn = tn < p ? tn : p;
+  co = to < p ? to : p;
   if (lane >= cn && lane < p) snew[s * L + lane] = -1;
   if (lane >= co && lane < p) sold[s * L + lane] = -1;
   if (lane == 0) {
@@ -114,12 +117,17 @@ __device__ inline void forward_sample_row_wide(int64_t s, int64_t n, int k, int 
   }
 }
 
-template <bool WIDE>
+// SUMS: also the proposal slots of the forward samples (see SegmentRule).
+template <bool WIDE, bool SUMS>
 __global__ __launch_bounds__(kSB) void k_fwd_count(int64_t n, int k, int p, BucketGeom g,
                                                    uint64_t* G, int32_t* snew, int32_t* sold,
                                                    int32_t* cnew, int32_t* cold,
-                                                   uint32_t* wg_hist) {
-  __shared__ uint32_t hist[2 * kMaxBuckets];
+                                                   uint32_t* wg_hist, uint32_t per_new,
+                                                   uint32_t per_old, uint32_t* fwd_before,
+                                                   uint64_t* group_before) {
+  extern __shared__ uint32_t hist[];  // 2 nb, then the proposal slots of every row's samples
+  __shared__ uint32_t wsum[kSB / kWave];
+  uint32_t* const row_slots = hist + 2 * g.nb;
   for (int i = threadIdx.x; i < 2 * g.nb; i += kSB) hist[i] = 0;
   __syncthreads();
   const int lane = lane_id(), wave = wave_id();
@@ -139,9 +147,11 @@ __global__ __launch_bounds__(kSB) void k_fwd_count(int64_t n, int k, int p, Buck
     for (int r = 0; r < kRowsAtOnce; ++r) {
       const int64_t s = s0 + r * (kSB / kWave);
       if (s >= row1) break;
+      int cn, co;
       if (WIDE) {
         int32_t vn[2], vo[2];
-        forward_sample_row_wide(s, n, k, p, G, snew, sold, cnew, cold, lane, e[r], e1[r], vn, vo);
+        forward_sample_row_wide(s, n, k, p, G, snew, sold, cnew, cold, lane, e[r], e1[r], vn, vo,
+                                cn, co);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
           if (vn[q] >= 0) atomicAdd(&hist[vn[q] >> g.tb], 1u);
@@ -149,13 +159,40 @@ __global__ __launch_bounds__(kSB) void k_fwd_count(int64_t n, int k, int p, Buck
         }
       } else {
         int32_t vn, vo;
-        forward_sample_row(s, n, k, p, G, snew, sold, cnew, cold, lane, e[r], vn, vo);
+        forward_sample_row(s, n, k, p, G, snew, sold, cnew, cold, lane, e[r], vn, vo, cn, co);
         if (vn >= 0) atomicAdd(&hist[vn >> g.tb], 1u);
         if (vo >= 0) atomicAdd(&hist[g.nb + (vo >> g.tb)], 1u);
       }
+      if (SUMS && lane == 0) row_slots[s - row0] = per_new * (uint32_t)cn + per_old * (uint32_t)co;
     }
   }
   __syncthreads();
+  // slots of the forward samples of the rows before each one: rows tid * per .. of this workgroup
+  if (SUMS) {
+    const int rows = (int)(row1 - row0), per = (g.rows_per_wg + kSB - 1) / kSB;
+    const int r0 = threadIdx.x * per;
+    uint32_t sum = 0;
+    for (int i = 0; i < per; ++i) sum += r0 + i < rows ? row_slots[r0 + i] : 0u;
+    uint32_t inc = sum;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+      const uint32_t o = __shfl_up(inc, off, kWave);
+      if (lane >= off) inc += o;
+    }
+    if (lane == kWave - 1) wsum[wave] = inc;
+    __syncthreads();
+    uint32_t at = inc - sum;
+    for (int w = 0; w < wave; ++w) at += wsum[w];
+    for (int i = 0; i < per; ++i)
+      if (r0 + i < rows) {
+        const uint32_t own = row_slots[r0 + i];
+        row_slots[r0 + i] = at;
+        at += own;
+      }
+    if (threadIdx.x == kSB - 1) group_before[blockIdx.x] = at;
+    __syncthreads();
+    for (int i = threadIdx.x; i < rows; i += kSB) fwd_before[row0 + i] = row_slots[i];
+  }
   // column blockIdx.x of the (bucket x workgroup) count matrix
   for (int i = threadIdx.x; i < 2 * g.nb; i += kSB) wg_hist[(size_t)i * gridDim.x + blockIdx.x] = hist[i];
 }
@@ -164,14 +201,30 @@ __global__ __launch_bounds__(kSB) void k_fwd_count(int64_t n, int k, int p, Buck
 // entry of workgroup w becomes the start of w's run inside the bucket, the row
 // total the bucket's size.  One wavefront per row - no atomics, and the edge
 // order inside a bucket no longer depends on timing.  One workgroup more than
-// the rows need keeps the counters' values from before this iteration and clears
-// what the cross-matching adds to.
+// the rows need keeps the counters' values from before this iteration, clears
+// what the cross-matching adds to, and scans the workgroups' proposal slots.
 __global__ __launch_bounds__(kSB) void k_wg_scan(int W, int rows, uint32_t* wg_hist,
                                                  uint32_t* bcnt, const uint64_t* counters,
                                                  uint64_t* snap, uint64_t* forms,
                                                  uint32_t* cls_count,
-                                                 unsigned long long* stg_cur) {
+                                                 unsigned long long* stg_cur,
+                                                 uint64_t* group_before) {
   if (blockIdx.x == gridDim.x - 1) {
+    if (group_before && wave_id() == kSB / kWave - 1) {
+      const int lane = lane_id();
+      uint64_t carry = 0;
+      for (int w0 = 0; w0 < W; w0 += kWave) {
+        const uint64_t v = w0 + lane < W ? group_before[w0 + lane] : 0ull;
+        uint64_t inc = v;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+          const uint64_t o = __shfl_up(inc, off, kWave);
+          if (lane >= off) inc += o;
+        }
+        if (w0 + lane < W) group_before[w0 + lane] = carry + inc - v;
+        carry += __shfl(inc, kWave - 1, kWave);
+      }
+    }
     for (int i = threadIdx.x; i < kStripes * C_SLOTS; i += kSB) snap[i] = counters[i];
     if (threadIdx.x == 0) *forms = FormTally::faded(*forms);
     if (cls_count && threadIdx.x < kNodeClassesMax) cls_count[threadIdx.x] = 0u;
@@ -479,8 +532,10 @@ static BucketGeom bucket_geom(int64_t n) {
   return g;
 }
 
-hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, hipStream_t st) {
+hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, int* group_rows,
+                                 hipStream_t st) {
   const BucketGeom g = bucket_geom(sh.n);
+  *group_rows = g.rows_per_wg;
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_bucket_csr<false>),
@@ -497,15 +552,24 @@ hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, hipStream_
   // per-workgroup bucket histograms, behind the edges in the same (still unused) array
   uint32_t* wg_hist = reinterpret_cast<uint32_t*>(edges_old + sh.n * sh.p);
   const unsigned grid = (unsigned)((sh.n + g.rows_per_wg - 1) / g.rows_per_wg);
-  if (sh.k > kWave)
-    k_fwd_count<true><<<grid, kSB, 0, st>>>(sh.n, sh.k, sh.p, g, ds.G, ds.snew, ds.sold, ds.cnew,
-                                            ds.cold, wg_hist);
-  else
-    k_fwd_count<false><<<grid, kSB, 0, st>>>(sh.n, sh.k, sh.p, g, ds.G, ds.snew, ds.sold, ds.cnew,
-                                             ds.cold, wg_hist);
+  const bool sums = sh.n > kRoomForAll;
+  const size_t lds = (size_t)(2 * g.nb + (sums ? g.rows_per_wg : 0)) * 4;
+#define GNND_FWD(WIDE, SUMS)                                                                    \
+  k_fwd_count<WIDE, SUMS><<<grid, kSB, lds, st>>>(                                              \
+      sh.n, sh.k, sh.p, g, ds.G, ds.snew, ds.sold, ds.cnew, ds.cold, wg_hist,                   \
+      (uint32_t)sh.slots_new_per_appearance(), (uint32_t)sh.slots_old_per_appearance(),         \
+      ds.fwd_before, ds.group_before)
+  if (sh.k > kWave) {
+    if (sums) GNND_FWD(true, true);
+    else GNND_FWD(true, false);
+  } else {
+    if (sums) GNND_FWD(false, true);
+    else GNND_FWD(false, false);
+  }
+#undef GNND_FWD
   k_wg_scan<<<(unsigned)((2 * g.nb + kSB / kWave - 1) / (kSB / kWave)) + 1, kSB, 0, st>>>(
       (int)grid, 2 * g.nb, wg_hist, bcnt, ds.counters, ds.snap, ds.forms,
-      ds.cls_count, ds.stg_cur);
+      ds.cls_count, ds.stg_cur, sums ? ds.group_before : nullptr);
   static bool staged_attr = false;
   if (!staged_attr) {
     hipError_t e = hipSuccess;

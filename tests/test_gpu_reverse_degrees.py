@@ -1,0 +1,80 @@
+"""The reverse part of the sample lists where its kernels change their way of working: as many
+candidates as there is room for and one more or less, up to 64, up to 128 and beyond; and the
+proposal segments on both sides of the size from which the forward samples are added up."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as og
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+SEED = W.ALGO_SEED
+
+
+def _graph_with_degrees(n, k, p, rng):
+    """Random lists (k = p: every entry is sampled) in which chosen nodes are entries of as many
+    other lists, flagged NEW or OLD, as the comment above names."""
+    isnew = (rng.random((n, k)) < rng.random((n, 1))).astype(np.uint8)
+    free = [list(rng.permutation(k)) for _ in range(n)]
+    ids = np.full((n, k), -1, np.int64)
+    special = 0
+    for kind in (1, 0):
+        for want in range(13):
+            v = special
+            special += 1
+            room = 2 * p - int((isnew[v] == kind).sum())
+            deg = [0, 1, room - 1, room, room + 1, 63, 64, 65, 127, 128, 129, 193, 300][want]
+            for s in rng.permutation(n):
+                if deg <= 0:
+                    break
+                slots = [j for j in free[s] if isnew[s, j] == kind]
+                if s == v or not slots or len(free[s]) <= k // 2:
+                    continue
+                ids[s, slots[0]] = v
+                free[s].remove(slots[0])
+                deg -= 1
+    for s in range(n):
+        fill = rng.choice(n - special, k + 1, replace=False) + special
+        fill = [v for v in fill if v != s][:len(free[s])]
+        ids[s, free[s]] = fill
+    dist = np.broadcast_to(np.arange(1, k + 1, dtype=np.float64), (n, k)).copy()
+    return ids.astype(np.int32), dist, isnew
+
+
+@pytest.mark.parametrize("p", [5, 8, 31, 32, 33, 42, 64])
+@pytest.mark.parametrize("seed", [1, 2])
+def test_samples_match_the_oracle_at_chosen_reverse_degrees(p, seed):
+    import paper_2103_15386_amd as amd
+    n, k = 1100, p
+    rng = np.random.default_rng(100 * p + seed)
+    x = rng.random((n, 4), dtype=np.float32)
+    g = og.init_random(x, k, og.L2SQ_F32, SEED)
+    ids, dist, isnew = _graph_with_degrees(n, k, p, rng)
+    g.ids[:], g.dist[:], g.isnew[:] = ids, dist, isnew
+    ctx = amd.Gnnd(torch.from_numpy(x).cuda(), k, p, amd.L2SQ_F32, SEED)
+    ctx.set_graph(torch.from_numpy(ids).cuda(), torch.from_numpy(dist.astype(np.float32)).cuda(),
+                  torch.from_numpy(isnew).cuda(), 2)
+    ctx.step_sample()
+    got = [t.cpu().numpy() for t in ctx.samples()]
+    snew, cnew, sold, cold = og.sample(g, p, SEED, 3)
+    for a, b in zip(got, (snew, cnew, sold, cold)):
+        assert (a == b).all()
+    ctx.close()
+
+
+@pytest.mark.parametrize("n", [(1 << 18) - 1, 1 << 18, (1 << 18) + 1, (1 << 18) + 4099])
+@pytest.mark.parametrize("metric", [og.L2SQ_F32, og.L2SQ_U8])
+def test_builds_match_the_oracle_around_the_segment_rule(n, metric):
+    import paper_2103_15386_amd as amd
+    x = W.uniform_f32(n, 4, seed=3)
+    if metric == og.L2SQ_U8:
+        x = (x * 255).astype(np.uint8)
+    g, _ = og.build(x, 6, 5, metric, SEED, 2)
+    ctx = amd.Gnnd(torch.from_numpy(x).cuda(), 6, 5, metric, SEED)
+    st = ctx.build(2)
+    ids, dist = ctx.graph()
+    assert st["dropped"] == 0
+    assert (ids.cpu().numpy() == g.ids).all() and (dist.cpu().numpy() == g.dist).all()
+    ctx.close()
