@@ -323,35 +323,49 @@ __device__ inline bool choose_smallest(const uint32_t (&h)[R], const uint64_t (&
 // Stable compaction of the lanes with keep == true to the front; the other
 // lanes end up behind them holding `fill`.
 __device__ inline uint64_t wave_compact(uint64_t v, bool keep, uint64_t fill, int lane) {
-  uint64_t mask = __ballot(keep);
-  int nkeep = __popcll(mask);
-  int before = __popcll(mask & lanes_below(lane));
-  int dst = keep ? before : nkeep + (lane - before);
+  const uint64_t mask = __ballot(keep);
+  const int before = rank_in(mask);
+  const int dst = keep ? before : __popcll(mask) + (lane - before);
   uint64_t x = keep ? v : fill;
   uint32_t lo = __builtin_amdgcn_ds_permute(dst << 2, (int)(uint32_t)x);
   uint32_t hi = __builtin_amdgcn_ds_permute(dst << 2, (int)(uint32_t)(x >> 32));
   return ((uint64_t)hi << 32) | lo;
 }
 
+// What a wavefront's lanes have written to LDS before this is read by the others after it.
+__device__ inline void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Whether the N entries at `row` in LDS (ascending, unused ones the maximum, N a power of two)
+// hold the (distance, id) of e.  The updates are bound by vector-instruction issue: a step of the
+// search is one read, one comparison and one addition, where a row kept in registers took two
+// lane permutations and the key shifted out of every entry.  An entry below the key with its flags
+// cleared has a smaller key, whatever its own flags are.
+template <int N>
+__device__ inline bool list_holds(const uint64_t* row, uint64_t e) {
+  const uint64_t key = e & ~3ull;
+  const uint64_t* at = row;
+#pragma unroll
+  for (int step = N / 2; step > 0; step >>= 1) at = at[step - 1] < key ? at + step : at;
+  return ((*at ^ e) >> 2) == 0ull;
+}
+
 // Drop from `pk` (one candidate per lane, kKeyMax = none) what cannot enter the
 // ascending list `row` of k entries: not closer than its last entry, already
-// in it, or a repeat of another candidate.  Returns the survivors ascending.
+// in it, or a repeat of another candidate.  Returns the survivors ascending.  `lds`: 64 words of
+// the wavefront's own.
 __device__ inline uint64_t filter_candidates(uint64_t pk, uint64_t row, int k, int lane,
-                                             bool& any) {
-  const uint64_t last = readlane64(row, k - 1);
-  if (pk != kKeyMax && entry_key(pk) >= entry_key(last)) pk = kKeyMax;
+                                             uint64_t* lds, bool& any) {
+  if (pk >= (readlane64(row, k - 1) & ~3ull)) pk = kKeyMax;
   any = __ballot(pk != kKeyMax) != 0ull;
   if (!any) return pk;
-  // already in the list?  The 64 lanes of `row` ascend (unused lanes hold the
-  // maximum), so each candidate finds its lower bound in six halving steps.
-  const uint64_t kk = entry_key(pk);
-  int pos = 0;
-#pragma unroll
-  for (int step = kWave / 2; step > 0; step >>= 1) {
-    const uint64_t r = __shfl(row, pos + step - 1, kWave);
-    pos += (entry_key(r) < kk) ? step : 0;
-  }
-  if (entry_key(__shfl(row, pos, kWave)) == kk) pk = kKeyMax;
+  lds[lane] = row;
+  wave_lds_fence();
+  if (list_holds<kWave>(lds, pk)) pk = kKeyMax;
+  wave_lds_fence();  // (the next row may be written)
   const uint64_t left = __ballot(pk != kKeyMax);
   any = left != 0ull;
   if (!any) return pk;

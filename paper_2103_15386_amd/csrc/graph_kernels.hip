@@ -196,6 +196,7 @@ __global__ __launch_bounds__(kBlock) void k_rev_select(int64_t n, int p, uint64_
 __global__ __launch_bounds__(kBlock) void k_update(int64_t n, int k, uint64_t* G, NodeMeta* meta,
                                                    const uint64_t* pslot, const uint64_t* poff,
                                                    const uint64_t* bins, uint64_t* counters) {
+  __shared__ uint64_t lds[kWavesPerBlock][kWave];
   const int64_t u = wave_global_index();
   if (u >= n) return;
   const int lane = lane_id();
@@ -213,7 +214,7 @@ __global__ __launch_bounds__(kBlock) void k_update(int64_t n, int k, uint64_t* G
   for (uint64_t c = 0; c < cnt; c += kWave) {
     uint64_t pk = (c + lane < cnt) ? bins[beg + c + lane] : kKeyMax;
     bool any;
-    pk = filter_candidates(pk, row, k, lane, any);
+    pk = filter_candidates(pk, row, k, lane, lds[wave_id()], any);
     if (!any) continue;
     row = wave_merge_smallest(row, pk, lane);
     if (lane >= k) row = kKeyMax;
@@ -235,10 +236,10 @@ __device__ inline uint64_t half_lanes(int lane) {
 }
 // stable compaction inside each half (see wave_compact)
 __device__ inline uint64_t half_compact(uint64_t v, bool keep, uint64_t fill, int lane) {
-  const uint64_t mask = __ballot(keep) & half_lanes(lane);
-  const int nkeep = __popcll(mask);
-  const int before = __popcll(mask & lanes_below(lane));
-  const int dst = (lane & 32) | (keep ? before : nkeep + ((lane & 31) - before));
+  const uint64_t all = __ballot(keep);
+  const uint32_t mask = (lane & 32) ? (uint32_t)(all >> 32) : (uint32_t)all;
+  const int before = __popc(mask & ((1u << (lane & 31)) - 1u));
+  const int dst = (lane & 32) | (keep ? before : __popc(mask) + ((lane & 31) - before));
   const uint64_t x = keep ? v : fill;
   const uint32_t lo = __builtin_amdgcn_ds_permute(dst << 2, (int)(uint32_t)x);
   const uint32_t hi = __builtin_amdgcn_ds_permute(dst << 2, (int)(uint32_t)(x >> 32));
@@ -258,23 +259,13 @@ __device__ inline uint64_t half_merge_smallest(uint64_t a_sorted, uint64_t b_sor
   }
   return v;
 }
-// filter_candidates on 32 lanes, in two parts; `row` holds k <= 32 ascending entries per half.
-// First part: what is not closer than the list's last entry or already in the list becomes
-// kKeyMax (where it stands).
-__device__ inline uint64_t half_drop_known(uint64_t pk, uint64_t row, int k, int lane) {
-  const int base = lane & 32;
-  const uint64_t last = __shfl(row, base | (k - 1), kWave);
-  if (pk != kKeyMax && entry_key(pk) >= entry_key(last)) pk = kKeyMax;
+// filter_candidates on 32 lanes, in two parts; `row` is the half's ascending list in LDS, 32
+// entries of which k are used.  First part: what is not closer than the list's last entry or
+// already in the list becomes kKeyMax (where it stands).
+__device__ inline uint64_t half_drop_known(uint64_t pk, const uint64_t* row, int k) {
+  if (pk >= (row[k - 1] & ~3ull)) pk = kKeyMax;
   if (__ballot(pk != kKeyMax) == 0ull) return pk;
-  const uint64_t kk = entry_key(pk);
-  int pos = 0;
-#pragma unroll
-  for (int step = 16; step > 0; step >>= 1) {
-    const uint64_t r = __shfl(row, base | (pos + step - 1), kWave);
-    pos += (entry_key(r) < kk) ? step : 0;
-  }
-  if (entry_key(__shfl(row, base | pos, kWave)) == kk) pk = kKeyMax;
-  return pk;
+  return list_holds<32>(row, pk) ? kKeyMax : pk;
 }
 // Second part: the survivors, already at the front of their half (`count` = the larger
 // number of them in the two halves), ascending and without repeats.
@@ -298,8 +289,9 @@ __device__ inline uint64_t half_sort_unique(uint64_t pk, int count, int lane) {
 __device__ inline void update_pair(int64_t u, bool live, int k, uint64_t cnt, uint64_t beg,
                                    uint64_t row, uint64_t pa, uint64_t pb, uint64_t* G,
                                    NodeMeta* meta, const uint64_t* bins, uint64_t* counters,
-                                   int lane) {
+                                   uint64_t* lds, int lane) {
   const int l32 = lane & 31;
+  const uint64_t* const list = lds + (lane & 32);  // the half's row, for the tests
   if (__ballot(cnt != 0) == 0ull) return;
   const uint64_t cnt_other = __shfl(cnt, lane ^ 32, kWave);
   const uint64_t rounds = cnt > cnt_other ? cnt : cnt_other;
@@ -321,8 +313,11 @@ __device__ inline void update_pair(int64_t u, bool live, int k, uint64_t cnt, ui
       pa = (c + l32 < cnt) ? bins[beg + c + l32] : kKeyMax;
       pb = (c + 32 + l32 < cnt) ? bins[beg + c + 32 + l32] : kKeyMax;
     }
-    pa = half_drop_known(pa, row, k, lane);
-    pb = half_drop_known(pb, row, k, lane);
+    lds[lane] = row;
+    wave_lds_fence();
+    pa = half_drop_known(pa, list, k);
+    pb = half_drop_known(pb, list, k);
+    wave_lds_fence();
     const uint64_t left_a = __ballot(pa != kKeyMax), left_b = __ballot(pb != kKeyMax);
     if ((left_a | left_b) == 0ull) continue;
     const int na = __popcll(left_a & mine_mask), nb = __popcll(left_b & mine_mask);
@@ -340,7 +335,10 @@ __device__ inline void update_pair(int64_t u, bool live, int k, uint64_t cnt, ui
     } else {
       if (left_a != 0ull) admit(pa, na_max);
       // the list has changed: the second register takes the cheap tests again
-      pb = half_drop_known(pb, row, k, lane);
+      lds[lane] = row;
+      wave_lds_fence();
+      pb = half_drop_known(pb, list, k);
+      wave_lds_fence();
       const uint64_t left = __ballot(pb != kKeyMax);
       if (left != 0ull) {
         pb = half_compact(pb, pb != kKeyMax, kKeyMax, lane);
@@ -364,6 +362,7 @@ __global__ __launch_bounds__(kBlock) void k_update_pairs(int64_t n, int k, uint6
                                                          NodeMeta* meta, const uint64_t* pslot,
                                                          const uint64_t* poff,
                                                          const uint64_t* bins, uint64_t* counters) {
+  __shared__ uint64_t lds[kWavesPerBlock][kWave];
   const int lane = lane_id(), l32 = lane & 31;
   const int64_t u0 = wave_global_index() * (2 * kPairsPerWave) + (lane >> 5);
   if (u0 - (lane >> 5) >= n) return;  // the whole wavefront lies beyond the last node
@@ -392,7 +391,7 @@ __global__ __launch_bounds__(kBlock) void k_update_pairs(int64_t n, int k, uint6
 #pragma unroll
   for (int j = 0; j < kPairsPerWave; ++j)
     update_pair(u[j], live[j], k, cnt[j], beg[j], row[j], pa[j], pb[j], G, meta, bins, counters,
-                lane);
+                lds[wave_id()], lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -514,6 +513,7 @@ template <bool FLOAT>
 __global__ __launch_bounds__(kBlock) void k_merge_final(int64_t n, MergeIds mi, int k,
                                                         const uint64_t* G, const uint64_t* aside,
                                                         int32_t* ids_out, void* dist_out) {
+  __shared__ uint64_t lds[kWavesPerBlock][kWave];
   const int64_t s = wave_global_index();
   if (s >= n) return;
   const int lane = lane_id();
@@ -523,7 +523,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_final(int64_t n, MergeIds mi, 
   // the set-aside entries may tie with the list's last entry: compare on the
   // full (distance, id) key, which filter_candidates does
   bool any;
-  pk = filter_candidates(pk, row, k, lane, any);
+  pk = filter_candidates(pk, row, k, lane, lds[wave_id()], any);
   if (any) {
     row = wave_merge_smallest(row, pk, lane);
   }

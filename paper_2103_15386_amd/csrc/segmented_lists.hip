@@ -124,6 +124,7 @@ __global__ __launch_bounds__(kSGB) void k_update_segmented(int64_t n, int k, uin
                                                            const uint64_t* poff,
                                                            const uint64_t* bins,
                                                            uint64_t* counters) {
+  __shared__ uint64_t lds[kSGB / kWave][kWave];
   const int64_t u = seg_wave_index();
   if (u >= n) return;
   const int lane = lane_id();
@@ -163,7 +164,7 @@ __global__ __launch_bounds__(kSGB) void k_update_segmented(int64_t n, int k, uin
       if (r < m) {  // uniform
         uint64_t mine = (pk != kKeyMax && entry_id(pk) % m == r) ? pk : kKeyMax;
         bool any;
-        mine = filter_candidates(mine, seg[r], kSeg, lane, any);
+        mine = filter_candidates(mine, seg[r], kSeg, lane, lds[wave_id()], any);
         if (any) {
           seg[r] = wave_merge_smallest(seg[r], mine, lane);
           if (lane >= kSeg) seg[r] = kKeyMax;

@@ -23,38 +23,26 @@ inline dim3 wide_blocks(int64_t waves) {
   return grid_blocks((waves + kWavesPerWB - 1) / kWavesPerWB);
 }
 
-// lower bound of key kk among the 64 ascending entries of `row`, compared on (distance, id)
-__device__ inline bool holds_key(uint64_t row, uint64_t kk) {
-  int pos = 0;
-#pragma unroll
-  for (int step = kWave / 2; step > 0; step >>= 1) {
-    const uint64_t r = __shfl(row, pos + step - 1, kWave);
-    pos += (entry_key(r) < kk) ? step : 0;
-  }
-  return entry_key(__shfl(row, pos, kWave)) == kk;
-}
-
 // The wide form of the candidate filter of the update: drop what is not closer
 // than the list's last entry, what the list already holds, and repeats; the
-// survivors come back ascending.
+// survivors come back ascending.  `lds`: 128 words of the wavefront's own.
 __device__ inline uint64_t filter_candidates_wide(uint64_t pk, uint64_t lo, uint64_t hi, int k,
-                                                  int lane, bool& any) {
-  const uint64_t last = readlane64(hi, k - 1 - kWave);
-  if (pk != kKeyMax && entry_key(pk) >= entry_key(last)) pk = kKeyMax;
+                                                  int lane, uint64_t* lds, bool& any) {
+  if (pk >= (readlane64(hi, k - 1 - kWave) & ~3ull)) pk = kKeyMax;
   any = __ballot(pk != kKeyMax) != 0ull;
   if (!any) return pk;
-  const uint64_t kk = entry_key(pk);
-  // both searches by all lanes: they read each other's registers
-  const bool in_lo = holds_key(lo, kk);
-  const bool in_hi = holds_key(hi, kk);
-  if (in_lo || in_hi) pk = kKeyMax;
+  lds[lane] = lo;
+  lds[kWave + lane] = hi;
+  wave_lds_fence();
+  if (list_holds<2 * kWave>(lds, pk)) pk = kKeyMax;
+  wave_lds_fence();
   const uint64_t left = __ballot(pk != kKeyMax);
   any = left != 0ull;
   if (!any) return pk;
   pk = wave_compact(pk, pk != kKeyMax, kKeyMax, lane);
   pk = wave_sort_upto(pk, lane, __popcll(left));
-  const uint64_t prev = __shfl_up(pk, 1, kWave);
-  const bool rep = lane > 0 && pk != kKeyMax && entry_key(pk) == entry_key(prev);
+  const uint64_t prev = lane_before(pk, kKeyMax);
+  const bool rep = pk != kKeyMax && entry_key(pk) == entry_key(prev);
   if (__ballot(rep) != 0ull) pk = wave_compact(pk, !rep, kKeyMax, lane);
   return pk;
 }
@@ -170,6 +158,7 @@ __global__ __launch_bounds__(kWB) void k_init_random_wide_i8(const int8_t* __res
 __global__ __launch_bounds__(kWB) void k_update_wide(int64_t n, int k, uint64_t* G, NodeMeta* meta,
                                                      const uint64_t* pslot, const uint64_t* poff,
                                                      const uint64_t* bins, uint64_t* counters) {
+  __shared__ uint64_t lds[kWavesPerWB][2 * kWave];
   const int64_t u = wide_wave_index();
   if (u >= n) return;
   const int lane = lane_id();
@@ -188,7 +177,7 @@ __global__ __launch_bounds__(kWB) void k_update_wide(int64_t n, int k, uint64_t*
   for (uint64_t c = 0; c < cnt; c += kWave) {
     uint64_t pk = (c + lane < cnt) ? bins[beg + c + lane] : kKeyMax;
     bool any;
-    pk = filter_candidates_wide(pk, lo, hi, k, lane, any);
+    pk = filter_candidates_wide(pk, lo, hi, k, lane, lds[wave_id()], any);
     if (!any) continue;
     merge128(lo, hi, pk, lane);
     if (lane + kWave >= k) hi = kKeyMax;
@@ -254,6 +243,7 @@ template <bool FLOAT>
 __global__ __launch_bounds__(kWB) void k_merge_final_wide(int64_t n, MergeIds mi, int k,
                                                           const uint64_t* G, const uint64_t* aside,
                                                           int32_t* ids_out, void* dist_out) {
+  __shared__ uint64_t lds[kWavesPerWB][2 * kWave];
   const int64_t s = wide_wave_index();
   if (s >= n) return;
   const int lane = lane_id();
@@ -262,7 +252,7 @@ __global__ __launch_bounds__(kWB) void k_merge_final_wide(int64_t n, MergeIds mi
   uint64_t hi = lane + kWave < k ? G[s * k + kWave + lane] : kKeyMax;
   uint64_t pk = lane < fill ? aside[s * fill + lane] : kKeyMax;
   bool any;
-  pk = filter_candidates_wide(pk, lo, hi, k, lane, any);
+  pk = filter_candidates_wide(pk, lo, hi, k, lane, lds[wave_id()], any);
   if (any) {
     merge128(lo, hi, pk, lane);
     if (lane + kWave >= k) hi = kKeyMax;
