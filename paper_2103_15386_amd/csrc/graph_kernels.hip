@@ -103,11 +103,12 @@ __device__ __forceinline__ int select_list(int64_t v, int p, uint64_t base, uint
   return count;
 }
 
-// One wavefront finishes both sample lists of kNodesPerWave nodes.  The kernel is bound by
-// the latency of its two dependent rounds of reads (sizes, offsets and list rows, then the
-// candidate segments), not by its arithmetic, and it needs few registers: so a wavefront
-// requests everything of the first round for all its nodes at once, then everything of the
-// second round, and only then works the lists off one node after the other.
+// One wavefront finishes both sample lists of kNodesPerWave nodes.  It requests everything of
+// the two dependent rounds of reads (sizes, offsets and list rows, then the candidate segments)
+// for all its nodes at once and then works the lists off; from there on the kernel is bound by
+// vector-instruction issue.  The values of list t (node t / 2, kind t % 2) that are the same for
+// all lanes stand in lane t, and the loop over the nodes is a loop: unrolled four times it was
+// 11,000 instructions with a hundred scalar registers spilled.
 constexpr int kNodesPerWave = 4;
 __global__ __launch_bounds__(kBlock) void k_rev_select(int64_t n, int p, uint64_t base_new,
                                                        uint64_t base_old, uint32_t iter,
@@ -123,69 +124,68 @@ __global__ __launch_bounds__(kBlock) void k_rev_select(int64_t n, int p, uint64_
   if (v0 >= n) return;
   const int lane = lane_id();
   const int L = 2 * p;
-  int nfn[kNodesPerWave], nfo[kNodesPerWave];
-  uint64_t bn[kNodesPerWave], bo[kNodesPerWave];
-  uint32_t dn[kNodesPerWave], dO[kNodesPerWave];  // a node's reverse degree is below 2^32
-  uint32_t rown[kNodesPerWave], rowo[kNodesPerWave], firstn[kNodesPerWave], firsto[kNodesPerWave];
-  // (what the nodes' segments follow from: a lane per node)
-  uint64_t fwd_l = 0, bn_l = 0, bo_l = 0;
-  uint32_t dn_l = 0, do_l = 0;
-  int fn_l = 0, fo_l = 0;
-  if (lane < kNodesPerWave && v0 + lane < n) {
-    const int64_t v = v0 + lane;
-    fwd_l = seg.before(v);
-    fn_l = cnew[v];
-    fo_l = cold[v];
-    bn_l = roff_new[v];
-    dn_l = (uint32_t)(roff_new[v + 1] - bn_l);
-    bo_l = roff_old[v];
-    do_l = (uint32_t)(roff_old[v + 1] - bo_l);
+  const int nodes = n - v0 < kNodesPerWave ? (int)(n - v0) : kNodesPerWave;
+  // lane t: forward samples, reverse degree (below 2^32) and first candidate of list t
+  const int64_t v_l = v0 + (lane >> 1);
+  const bool old_l = lane & 1, mine = lane < 2 * nodes;
+  int nf_l = 0;
+  uint32_t deg_l = 0;
+  uint64_t beg_l = 0, fwd_l = 0;
+  if (mine) {
+    const uint64_t* const roff = old_l ? roff_old : roff_new;
+    nf_l = (old_l ? cold : cnew)[v_l];
+    beg_l = roff[v_l];
+    deg_l = (uint32_t)(roff[v_l + 1] - beg_l);
+    fwd_l = seg.before(v_l);
   }
+  auto nf_of = [&](int t) { return __builtin_amdgcn_readlane(nf_l, t); };
+  auto deg_of = [&](int t) { return (uint32_t)__builtin_amdgcn_readlane((int)deg_l, t); };
+  uint32_t rown[kNodesPerWave], rowo[kNodesPerWave], firstn[kNodesPerWave], firsto[kNodesPerWave];
 #pragma unroll
   for (int i = 0; i < kNodesPerWave; ++i) {
     const int64_t v = v0 + i < n ? v0 + i : n - 1;  // beyond the end: the last node again, unused
-    nfn[i] = cnew[v];
-    nfo[i] = cold[v];
-    bn[i] = roff_new[v];
-    dn[i] = (uint32_t)(roff_new[v + 1] - bn[i]);
-    bo[i] = roff_old[v];
-    dO[i] = (uint32_t)(roff_old[v + 1] - bo[i]);
     rown[i] = lane < p ? (uint32_t)snew[v * L + lane] : kNoId;  // the forward part, -1 behind it
     rowo[i] = lane < p ? (uint32_t)sold[v * L + lane] : kNoId;
   }
 #pragma unroll
   for (int i = 0; i < kNodesPerWave; ++i) {
-    const uint32_t jn = (uint32_t)(lane - nfn[i]) & 63u, jo = (uint32_t)(lane - nfo[i]) & 63u;
-    firstn[i] = jn < dn[i] ? (uint32_t)csr_new[bn[i] + jn] : kNoId;
-    firsto[i] = jo < dO[i] ? (uint32_t)csr_old[bo[i] + jo] : kNoId;
+    const uint32_t jn = (uint32_t)(lane - nf_of(2 * i)) & 63u;
+    const uint32_t jo = (uint32_t)(lane - nf_of(2 * i + 1)) & 63u;
+    firstn[i] = jn < deg_of(2 * i) ? (uint32_t)csr_new[readlane64(beg_l, 2 * i) + jn] : kNoId;
+    firsto[i] =
+        jo < deg_of(2 * i + 1) ? (uint32_t)csr_old[readlane64(beg_l, 2 * i + 1) + jo] : kNoId;
   }
-  uint64_t sum_new = 0, sum_old = 0;
-  // Lane i holds what is written for node i: its list sizes and its segment of the proposals.
-  int size_n = 0, size_o = 0;
-#pragma unroll
-  for (int i = 0; i < kNodesPerWave; ++i) {
+  int size_l = 0;
+#pragma unroll 1
+  for (int i = 0; i < nodes; ++i) {
     const int64_t v = v0 + i;
-    if (v < n) {  // uniform
-      const int cn = select_list(v, p, base_new, iter, snew + v * L, rown[i], nfn[i], csr_new,
-                                 bn[i], dn[i], firstn[i], lane);
-      const int co = select_list(v, p, base_old, iter, sold + v * L, rowo[i], nfo[i], csr_old,
-                                 bo[i], dO[i], firsto[i], lane);
-      sum_new += (uint64_t)cn;
-      sum_old += (uint64_t)co;
-      size_n = lane == i ? cn : size_n;
-      size_o = lane == i ? co : size_o;
+    const int cn = select_list(v, p, base_new, iter, snew + v * L, rown[0], nf_of(2 * i), csr_new,
+                               readlane64(beg_l, 2 * i), deg_of(2 * i), firstn[0], lane);
+    size_l = lane == 2 * i ? cn : size_l;
+    const int co = select_list(v, p, base_old, iter, sold + v * L, rowo[0], nf_of(2 * i + 1),
+                               csr_old, readlane64(beg_l, 2 * i + 1), deg_of(2 * i + 1),
+                               firsto[0], lane);
+    size_l = lane == 2 * i + 1 ? co : size_l;
+#pragma unroll
+    for (int j = 0; j + 1 < kNodesPerWave; ++j) {
+      rown[j] = rown[j + 1];
+      rowo[j] = rowo[j + 1];
+      firstn[j] = firstn[j + 1];
+      firsto[j] = firsto[j + 1];
     }
   }
-  if (lane < kNodesPerWave && v0 + lane < n) {
-    const int64_t v = v0 + lane;
-    cnew[v] = size_n;
-    cold[v] = size_o;
-    seg.write(v, n, fwd_l, bn_l, dn_l, fn_l, bo_l, do_l, fo_l, poff, pslot, counters);
-  }
-  if (lane == 0) {
-    counter_add(counters, C_SUMNEW, v0, sum_new);
-    counter_add(counters, C_SUMOLD, v0, sum_old);
-  }
+  if (mine) (old_l ? cold : cnew)[v_l] = size_l;
+  // a node's segment of the proposals (both lists of a node stand side by side)
+  const uint32_t per = old_l ? seg.per_old : seg.per_new;
+  auto both = [&](uint64_t x) { return x + xor_lanes(x, 1, lane); };
+  const uint64_t at = both(per * beg_l) + fwd_l, rev = both((uint64_t)per * deg_l);
+  const uint64_t fwd = both((uint64_t)per * (uint32_t)nf_l);
+  if (mine && !old_l) seg.write(v_l, n, at, rev, fwd, poff, pslot, counters);
+  // (lanes without a list: 0)
+  uint32_t sum = (uint32_t)size_l;
+  sum += xor_lanes(sum, 2, lane);
+  sum += xor_lanes(sum, 4, lane);
+  if (lane < 2) counter_add(counters, lane ? C_SUMOLD : C_SUMNEW, v0, (uint64_t)sum);
 }
 
 // ---------------------------------------------------------------------------

@@ -150,14 +150,11 @@ struct SegmentRule {
   __device__ uint64_t before(int64_t v) const {
     return per_node ? (uint64_t)v * per_node : fwd_before[v] + group_before[group_of(v)];
   }
-  // Node v's offset and its slot word (nothing received yet); `fwd` = before(v), `beg_*`, `deg_*`:
-  // its reverse candidates, `fwd_*`: its forward samples.  The last node closes the offsets.
-  __device__ void write(int64_t v, int64_t n, uint64_t fwd, uint64_t beg_new, uint32_t deg_new,
-                        int fwd_new, uint64_t beg_old, uint32_t deg_old, int fwd_old,
+  // Node v's offset `at` and its slot word (nothing received yet); `rev`, `fwd`: slots for its
+  // reverse candidates and its forward samples.  The last node closes the offsets.
+  __device__ void write(int64_t v, int64_t n, uint64_t at, uint64_t rev, uint64_t fwd,
                         uint64_t* poff, uint64_t* pslot, uint64_t* counters) const {
-    const uint64_t at = per_new * beg_new + per_old * beg_old + fwd;
-    const uint64_t rev = (uint64_t)per_new * deg_new + (uint64_t)per_old * deg_old;
-    const uint64_t size = rev + per_new * (uint32_t)fwd_new + per_old * (uint32_t)fwd_old;
+    const uint64_t size = rev + fwd;
     poff[v] = at;
     pslot[v] = at << kSlotCountBits;
     if (v == n - 1) poff[n] = at + (per_node ? rev + per_node : size);

@@ -125,7 +125,9 @@ __global__ __launch_bounds__(kLB) void k_rev_select_long(
     cold[v] = co;
     counter_add(counters, C_SUMNEW, v, (uint64_t)cn);
     counter_add(counters, C_SUMOLD, v, (uint64_t)co);
-    seg.write(v, n, seg.before(v), bn, (uint32_t)dn, nfn, bo, (uint32_t)dO, nfo, poff, pslot, counters);
+    seg.write(v, n, seg.per_new * bn + seg.per_old * bo + seg.before(v),
+              seg.per_new * dn + seg.per_old * dO,
+              seg.per_new * (uint32_t)nfn + seg.per_old * (uint32_t)nfo, poff, pslot, counters);
   }
 }
 
