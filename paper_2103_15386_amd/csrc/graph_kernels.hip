@@ -109,7 +109,8 @@ __device__ __forceinline__ int select_list(int64_t v, int p, uint64_t base, uint
 // vector-instruction issue.  The values of list t (node t / 2, kind t % 2) that are the same for
 // all lanes stand in lane t, and the loop over the nodes is a loop: unrolled four times it was
 // 11,000 instructions with a hundred scalar registers spilled.
-constexpr int kNodesPerWave = 4;
+// kNodesPerWave is 4, and 1 where the chip has too few wavefronts that way: see launch_sample.
+template <int kNodesPerWave>
 __global__ __launch_bounds__(kBlock) void k_rev_select(int64_t n, int p, uint64_t base_new,
                                                        uint64_t base_old, uint32_t iter,
                                                        int32_t* snew, int32_t* sold,
@@ -625,6 +626,10 @@ hipError_t launch_init_random(const Shape& sh, const DevState& ds, uint64_t seed
   return hipGetLastError();
 }
 
+// Up to this many nodes a wavefront of the reverse selection takes one (16 wavefronts per CU): with
+// four, 4096 nodes are one wavefront per SIMD, and a build of 8 iterations takes 501 instead of 478
+// us.  Beyond, there are enough of them either way, and four nodes at a time hide their reads.
+constexpr int64_t kOneNodePerWave = 1 << 14;
 hipError_t launch_sample(const Shape& sh, const DevState& ds, uint64_t seed, uint32_t iter,
                          hipStream_t st) {
   // forward sampling, and the reverse candidates grouped by target (two-level counting sort)
@@ -633,10 +638,14 @@ hipError_t launch_sample(const Shape& sh, const DevState& ds, uint64_t seed, uin
   if (e != hipSuccess) return e;
   if (2 * sh.p > kWave)  // two list entries per lane
     return launch_rev_select_long(sh, ds, seed, iter, group_rows, st);
-  k_rev_select<<<blocks_for_waves((sh.n + kNodesPerWave - 1) / kNodesPerWave), kBlock, 0, st>>>(
-      sh.n, sh.p, hash_base(seed, kTagRevNew), hash_base(seed, kTagRevOld), iter, ds.snew,
-      ds.sold, ds.cnew, ds.cold, ds.roff_new, ds.roff_old, ds.csr_new, ds.csr_old,
-      SegmentRule(sh, ds, group_rows), ds.poff, ds.pslot, ds.counters);
+#define GNND_SELECT(NODES)                                                                       \
+  k_rev_select<NODES><<<blocks_for_waves((sh.n + NODES - 1) / NODES), kBlock, 0, st>>>(          \
+      sh.n, sh.p, hash_base(seed, kTagRevNew), hash_base(seed, kTagRevOld), iter, ds.snew,       \
+      ds.sold, ds.cnew, ds.cold, ds.roff_new, ds.roff_old, ds.csr_new, ds.csr_old,               \
+      SegmentRule(sh, ds, group_rows), ds.poff, ds.pslot, ds.counters)
+  if (sh.n <= kOneNodePerWave) GNND_SELECT(1);
+  else GNND_SELECT(4);
+#undef GNND_SELECT
   return hipGetLastError();
 }
 
