@@ -2,7 +2,11 @@
 // objects (p > 32) on byte-valued data of up to 128 dimensions: exact integer distances from
 // inner products on the matrix cores, the long-list form of k_join_mfma.
 //
-// One workgroup of four wavefronts per node.  Wavefront w brings blocks w (32 samples) of the
+// One workgroup of BLOCKS wavefronts per node: 3 for lists of up to 96 samples (p <= 48), 4 beyond.
+// (A fourth wavefront without samples of its own kept its place and a quarter of the LDS: with
+// three, 3.75 instead of 3 busy wavefronts per SIMD; 100,000 x 128, p = 42, whole build 3.70 ->
+// 3.39 ms.)
+// Wavefront w brings blocks w (32 samples) of the
 // NEW and of the OLD list, keeps them as column operands and leaves them in LDS as row operands
 // for all four; its columns then meet every block of rows they have partners in.  A tile's
 // epilogue keeps one column per lane (see tile_col_best), so nothing is reduced across lanes
@@ -10,7 +14,7 @@
 //
 // 100,000 x 128 byte-valued vectors, k = 64, p = 42: 0.61 ms per iteration where the general
 // long join (k_join_long, float32 sums on the vector units) takes 5.5; build of 4 iterations
-// 24.3 -> 4.2 ms.  Bound by the epilogue's vector instructions and the hand-out's atomics.
+// 24.3 -> 4.2 ms (3.4 with the three wavefronts and faster kernels around it).  Bound by the epilogue's vector instructions and the hand-out's atomics.
 #include "gram_i8.hpp"
 #include "kernels.hpp"
 
@@ -18,23 +22,23 @@ namespace gnnd {
 
 namespace {
 
-constexpr int kLongList = 128;         // longest sample list
 constexpr int kLongBits = 7;
 constexpr int32_t kFarLong = 3 << 22;  // "norm" of an absent row: above every real distance
 
-template <int KSTEPS, bool FCODE, bool MERGE>
-__global__ __launch_bounds__(256) void k_join_long_i8(
+template <int KSTEPS, int BLOCKS, bool FCODE, bool MERGE>
+__global__ __launch_bounds__(kWave* BLOCKS) void k_join_long_i8(
     const int8_t* __restrict__ shadow, const NodeMeta* __restrict__ meta, int64_t n, int p,
     int64_t split, const int32_t* __restrict__ snew, const int32_t* __restrict__ sold,
     const int32_t* __restrict__ cnew, const int32_t* __restrict__ cold, uint64_t* pslot,
     uint64_t slots, uint64_t* __restrict__ bins, uint64_t* counters) {
   constexpr int dpad = 32 * KSTEPS;
+  constexpr int kLongList = 32 * BLOCKS;  // longest sample list
   constexpr int kRow = dpad + 16;  // row stride in LDS: 8 lanes reading 16 bytes of 8
                                    // consecutive rows touch different banks
   __shared__ __attribute__((aligned(16))) int8_t rows[2 * kLongList * kRow];  // NEW, then OLD
   __shared__ __attribute__((aligned(16))) int32_t neg[2 * kLongList];  // see tile_col_best
   __shared__ int32_t ids[2 * kLongList];  // absent: INT_MAX, so that both lists stay ascending
-  __shared__ uint32_t second[8];          // MERGE: samples of the second set, per block of 32
+  __shared__ uint32_t second[2 * BLOCKS]; // MERGE: samples of the second set, per block of 32
   __shared__ uint32_t tally[4];           // duplicates, found, passed, overflow
   const int64_t s = block_linear();
   if (s >= n) return;
@@ -58,7 +62,7 @@ __global__ __launch_bounds__(256) void k_join_long_i8(
     const uint64_t m = __ballot(self >= 0 && (int64_t)self >= split);
     if (lane == 0) {
       second[wave] = (uint32_t)m;
-      second[4 + wave] = (uint32_t)(m >> 32);
+      second[BLOCKS + wave] = (uint32_t)(m >> 32);
     }
   }
 #pragma unroll
@@ -76,8 +80,8 @@ __global__ __launch_bounds__(256) void k_join_long_i8(
 #pragma unroll
     for (int step = 0; step < 8; ++step) {
       const bool go = lo < hi;
-      const int mid = (lo + hi) >> 1;  // <= 127 while lo < hi
-      const bool below = go && other[mid & (kLongList - 1)] < self;
+      const int mid = go ? (lo + hi) >> 1 : 0;  // < kLongList
+      const bool below = go && other[mid] < self;
       lo = below ? mid + 1 : lo;
       hi = (go && !below) ? mid : hi;
     }
@@ -112,10 +116,10 @@ __global__ __launch_bounds__(256) void k_join_long_i8(
                                          : tile_col_best<false, kLongBits>(g, neg + 32 * b, half, 0u));
       }
     for (int b = 0; b < nb_old; ++b) {
-      const v16i g = gram<KSTEPS>(row_block(4 + b), N);
+      const v16i g = gram<KSTEPS>(row_block(BLOCKS + b), N);
       const int32_t* at = neg + kLongList + 32 * b;
       near_no = max(near_no, masked ? tile_col_best<true, kLongBits>(
-                                          g, at, half, excluded(eq_n, b, MERGE ? second[4 + b] : 0u, id_n))
+                                          g, at, half, excluded(eq_n, b, MERGE ? second[BLOCKS + b] : 0u, id_n))
                                     : tile_col_best<false, kLongBits>(g, at, half, 0u));
     }
   }
@@ -145,7 +149,7 @@ __global__ __launch_bounds__(256) void k_join_long_i8(
     const int32_t dist = part + (int32_t)mine.y;
     const uint32_t code = FCODE ? ord_f32((float)dist) : ord_i32(dist);
     const int list = !half && t ? kLongList : 0;
-    const int32_t other = found[t] ? ids[list + (key & (kLongList - 1))] : 0;
+    const int32_t other = found[t] ? ids[list + (key & ((1 << kLongBits) - 1))] : 0;
     pass[t] = found[t] && code <= mine.x;  // what cannot enter the list is dropped
     entry[t] = make_entry(code, (uint32_t)other, 3u);
   }
@@ -176,9 +180,9 @@ __global__ __launch_bounds__(256) void k_join_long_i8(
     uint64_t ev;
     if (MERGE) {
       uint64_t n2 = 0, o2 = 0;  // samples of the second set
-      for (int b = 0; b < 4; ++b) {
+      for (int b = 0; b < BLOCKS; ++b) {
         n2 += (uint64_t)__popc(second[b]);
-        o2 += (uint64_t)__popc(second[4 + b]);
+        o2 += (uint64_t)__popc(second[BLOCKS + b]);
       }
       ev = n2 * ((uint64_t)no - o2) + ((uint64_t)nn - n2) * o2;
     } else {
@@ -193,17 +197,23 @@ __global__ __launch_bounds__(256) void k_join_long_i8(
   }
 }
 
-template <int KSTEPS>
+template <int KSTEPS, int BLOCKS>
 void launch(const Shape& sh, const DevState& ds, bool merge, hipStream_t st) {
   const dim3 grid = grid_blocks(sh.n);
   const uint64_t slots = (uint64_t)sh.slots();
   const bool fcode = sh.metric != kL2U8;
-  auto* const kernel = fcode ? (merge ? k_join_long_i8<KSTEPS, true, true>
-                                      : k_join_long_i8<KSTEPS, true, false>)
-                             : (merge ? k_join_long_i8<KSTEPS, false, true>
-                                      : k_join_long_i8<KSTEPS, false, false>);
-  kernel<<<grid, 256, 0, st>>>(ds.shadow, ds.meta, sh.n, sh.p, sh.split, ds.snew, ds.sold, ds.cnew,
-                               ds.cold, ds.pslot, slots, ds.bins, ds.counters);
+  auto* const kernel = fcode ? (merge ? k_join_long_i8<KSTEPS, BLOCKS, true, true>
+                                      : k_join_long_i8<KSTEPS, BLOCKS, true, false>)
+                             : (merge ? k_join_long_i8<KSTEPS, BLOCKS, false, true>
+                                      : k_join_long_i8<KSTEPS, BLOCKS, false, false>);
+  kernel<<<grid, kWave * BLOCKS, 0, st>>>(ds.shadow, ds.meta, sh.n, sh.p, sh.split, ds.snew,
+                                          ds.sold, ds.cnew, ds.cold, ds.pslot, slots, ds.bins,
+                                          ds.counters);
+}
+template <int KSTEPS>
+void launch(const Shape& sh, const DevState& ds, bool merge, hipStream_t st) {
+  if (2 * sh.p <= 96) launch<KSTEPS, 3>(sh, ds, merge, st);
+  else launch<KSTEPS, 4>(sh, ds, merge, st);
 }
 
 }  // namespace
