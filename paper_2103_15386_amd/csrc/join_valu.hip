@@ -26,7 +26,9 @@
 // 100,000 x 96, k = 20, p = 16, 6 iterations: 21.7 -> 12.3 ms per build together with the smaller
 // build for lists of up to 32 samples (at the registers and LDS of 64-sample lists the first pass
 // alone gave 1 %: the phases of three workgroups per CU did not overlap; with 128 registers, four
-// workgroups, 60,000 x 96, k = p = 32 takes 13.8 ms instead of 23.3 with the canonical sums alone).
+// workgroups, 60,000 x 96, k = p = 32 takes 13.8 ms instead of 23.3 with the canonical sums alone),
+// 10.9 ms with the pairs dealt one by one (kDealt) and the range looked at by one maximum over the
+// values' bits (13.8 -> 13.5 ms at k = p = 32).
 // Where values are negative throughout: 19.7 ms, against 19.3 with the canonical sums alone and
 // 30.9 with both for every node.  Bound: vector-ALU issue.
 #include "device_utils.hpp"
@@ -88,6 +90,13 @@ __device__ inline void chi2_two_approx(float a0, float a1, float b0, float b1, f
   sum = __fmaf_rn(__fmaf_rn(y * y, s, (x * x) * t), __builtin_amdgcn_rcpf(s * t), sum);
 }
 constexpr int kChiPairs = 256;  // pairs of a node that are summed again: one per thread
+// In the builds for lists of up to 32 samples the first pass deals a node's pairs to the threads
+// one by one, pair q 256 + tid to thread tid: the square blocks of the canonical evaluation hold
+// twice as many places as pairs where lists have 20 to 30 samples (100,000 x 96, k = 20, p = 16,
+// six iterations: 12.1 -> 10.9 ms).  Lists of up to 64 keep the blocks, which reuse their rows: 60,000 x 96,
+// k = p = 32, 13.8 ms with them and 14.1 with up to 2048 pairs dealt.
+constexpr int kDealt = 6;  // pairs per thread
+static_assert(32 * 31 / 2 + 32 * 32 <= kDealt * kJB, "all pairs are dealt");
 
 // ALL: every evaluated pair is proposed to both of its objects (the ablation
 // variant without the selective update of Sec. 4.3) instead of only the nearest
@@ -111,6 +120,7 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
   __shared__ uint32_t pair_count;
   __shared__ float norms_s[128];  // squared norms of the samples (cosine only)
   constexpr bool kTwice = METRIC == kChi2F32 && !ALL;
+  constexpr bool kDeal = kTwice && RBM == 2;
   // kTwice: smallest approximate distance per sample and direction (code), what a partner's
   // lower bound must not exceed, the pairs to be summed again (row | column << 7 | for the row
   // << 14 | for the column << 15) and their number (large: evaluate the node canonically)
@@ -165,7 +175,7 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
   const bool aligned = (d & 3) == 0;
 
   ACC acc[RBM][2 * RBM];  // columns: NEW blocks, then OLD blocks
-  bool in_range = true;  // kTwice: all values this thread has staged are
+  uint32_t largest = 0u;  // kTwice: of the bits of all values this thread has staged
   // dimensions [d0, d0 + 64) of all vectors to LDS: 16 threads per row, 16 rows per pass
   auto stage = [&](int d0, bool check) {
     const int part = tid & 15;
@@ -180,8 +190,9 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
         if (kTwice && check) {
           float4* const at = reinterpret_cast<float4*>(tile + row * kLD + part * 4);
           float4 v = *at;
-          in_range &= v.x >= 0.f && v.x <= kChiMax && v.y >= 0.f && v.y <= kChiMax &&
-                      v.z >= 0.f && v.z <= kChiMax && v.w >= 0.f && v.w <= kChiMax;
+          // (negative numbers and NaN have larger bits than kChiMax; adding 0 makes -0 one of 0)
+          auto bits = [](float x) { return __float_as_uint(x + 0.f); };
+          largest = vmax(largest, vmax(vmax(bits(v.x), bits(v.y)), vmax(bits(v.z), bits(v.w))));
           v.x += 0.5f * kChiTiny;
           v.y += 0.5f * kChiTiny;
           v.z += 0.5f * kChiTiny;
@@ -257,8 +268,74 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
   bool decided = false;    // kTwice: the pairs summed again have settled the node
   const bool twice = kTwice && __builtin_amdgcn_readfirstlane((int)twice_s) != 0;
   if constexpr (kTwice) if (twice) {
-    evaluate(chi2_two_approx, true);
-    if (!in_range) again_count = kChiPairs + 1;  // (any thread's word is enough)
+    const uint32_t pairs_nn = do_nn ? (uint32_t)(nn * (nn - 1) / 2) : 0u;
+    const uint32_t pairs_all = pairs_nn + (uint32_t)(nn * no);
+    // this thread's pairs - row | column << 7 (0..63 NEW, 64.. OLD) | "is a pair" << 14: objects in
+    // both lists are none - and their sums
+    uint32_t dealt_pair[kDealt];
+    float sum_of[kDealt];
+    auto row_of = [](uint32_t pair) { return (int)(pair & 127u); };
+    auto col_of = [](uint32_t pair) { return (int)((pair >> 7) & 127u); };
+    // pairs of this wavefront: rounds of 256
+    const int first_pair = wave * kWave;
+    const int rounds = (int)pairs_all > first_pair ? ((int)pairs_all - first_pair + kJB - 1) / kJB : 0;
+    if constexpr (kDeal) {
+      // NEW x NEW: samples i and (i + 1 + idx / nn) % nn, i = idx % nn, which is every pair once;
+      // lanes side by side have rows and columns side by side, and no bank conflicts
+      const float inv_nn = __builtin_amdgcn_rcpf((float)nn);
+      const float inv_no = __builtin_amdgcn_rcpf((float)(no > 0 ? no : 1));
+#pragma unroll
+      for (int q = 0; q < kDealt; ++q) {
+        const uint32_t idx = (uint32_t)(q * kJB + tid);
+        const bool nn_pair = idx < pairs_nn;
+        const int k = (int)(nn_pair ? idx : idx - pairs_nn), len = nn_pair ? nn : no;
+        // (k + 0.5) / len is at least 1 / 128 away from the next whole number
+        const int over = (int)(((float)k + 0.5f) * (nn_pair ? inv_nn : inv_no));
+        const int rest = k - over * len;
+        bool ok = idx < pairs_all;
+        int R = nn_pair ? rest : over, C = nn_pair ? rest + over + 1 : 64 + rest;
+        if (nn_pair && C >= nn) C -= nn;
+        R = ok ? R : 0;
+        C = ok ? C : 0;
+        if (C >= 64) {
+          const int32_t idr = ids[R], idc = ids[C];
+          ok = ok && idr != idc;
+          if (merge_mode) ok = ok && (((int64_t)idr < split) != ((int64_t)idc < split));
+        }
+        dealt_pair[q] = (uint32_t)(R | (C << 7) | (ok ? 1 << 14 : 0));
+        sum_of[q] = 0.f;
+      }
+      for (int d0 = 0; d0 < d; d0 += kDC) {
+        const int width = stage(d0, true);
+        const int nsub = (width + 15) >> 4;
+#pragma unroll 1
+        for (int sub = 0; sub < nsub; ++sub) {
+#pragma unroll
+          for (int q = 0; q < kDealt; ++q) {
+            if (q < rounds) {  // uniform
+              const int C = col_of(dealt_pair[q]);
+              const float* const pa = tile + row_of(dealt_pair[q]) * kLD + sub * 16;
+              const float* const pb = tile + (C < 64 ? C : C - 64 + kRows) * kLD + sub * 16;
+              float4 x[4], y[4];
+#pragma unroll
+              for (int j = 0; j < 4; ++j) {
+                x[j] = *reinterpret_cast<const float4*>(pa + 4 * j);
+                y[j] = *reinterpret_cast<const float4*>(pb + 4 * j);
+              }
+#pragma unroll
+              for (int j = 0; j < 4; ++j) {
+                chi2_two_approx(x[j].x, x[j].y, y[j].x, y[j].y, sum_of[q]);
+                chi2_two_approx(x[j].z, x[j].w, y[j].z, y[j].w, sum_of[q]);
+              }
+            }
+          }
+        }
+        __syncthreads();
+      }
+    } else {
+      evaluate(chi2_two_approx, true);
+    }
+    if (largest > __float_as_uint(kChiMax)) again_count = kChiPairs + 1;  // (any thread's word is enough)
     // Both sums differ from the true one by at most (d + 12) u of it, u = 2^-24: a term takes
     // five (canonical) to twelve roundings, all terms are non-negative.  The absolute part
     // covers kChiTiny (values below 1e-8 are changed by it) and what is lost where squares of
@@ -289,7 +366,20 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
         }
       }
     };
-    uint32_t row_nn[RBM], row_no[RBM], col[2 * RBM], pairs = 0;
+    uint32_t pairs = 0;
+    if constexpr (kDeal) {
+#pragma unroll
+      for (int q = 0; q < kDealt; ++q) {
+        if (q < rounds && (dealt_pair[q] >> 14)) {
+          const uint32_t code = ord_f32(sum_of[q]);
+          const int R = row_of(dealt_pair[q]), C = col_of(dealt_pair[q]), to = C < 64 ? 0 : 64;
+          atomicMin(&min_s[to + R], code);
+          atomicMin(&min_s[to + C], code);
+          pairs += to ? 1u : 0u;
+        }
+      }
+    } else {
+    uint32_t row_nn[RBM], row_no[RBM], col[2 * RBM];
 #pragma unroll
     for (int r = 0; r < RBM; ++r) row_nn[r] = row_no[r] = 0xffffffffu;
 #pragma unroll
@@ -324,6 +414,7 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
           atomicMin(&min_s[c < RBM ? tx + 16 * c : 128 + tx + 16 * (c - RBM)], col[c]);
       }
     }
+    }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) pairs += __shfl_xor(pairs, off, kWave);
     if (lane == 0 && pairs) atomicAdd(&pair_count, pairs);
@@ -337,17 +428,25 @@ __global__ __launch_bounds__(kJB) void k_join_valu(
       limit_s[tid] = found ? unord_f32(code) : -1.0f;
     }
     __syncthreads();
-    over_pairs([&](int r, int c, int R, int C) {
-      const float lower = __fmaf_rn(-rel, acc[r][c], acc[r][c]) - abs_err;
-      const bool for_row = lower <= limit_s[c < RBM ? R : 64 + R];
-      const bool for_col = lower <= limit_s[c < RBM ? C : 64 + C];
+    auto consider = [&](float sum, int R, int C) {
+      const float lower = __fmaf_rn(-rel, sum, sum) - abs_err;
+      const bool for_row = lower <= limit_s[C < 64 ? R : 64 + R];
+      const bool for_col = lower <= limit_s[C < 64 ? C : 64 + C];
       if (for_row || for_col) {
         const uint32_t at = atomicAdd(&again_count, 1u);
         if (at < (uint32_t)kChiPairs)
           again_s[at] = (uint32_t)R | ((uint32_t)C << 7) | (for_row ? 1u << 14 : 0u) |
                         (for_col ? 1u << 15 : 0u);
       }
-    });
+    };
+    if constexpr (kDeal) {
+#pragma unroll
+      for (int q = 0; q < kDealt; ++q)
+        if (q < rounds && (dealt_pair[q] >> 14))
+          consider(sum_of[q], row_of(dealt_pair[q]), col_of(dealt_pair[q]));
+    } else {
+      over_pairs([&](int r, int c, int R, int C) { consider(acc[r][c], R, C); });
+    }
     __syncthreads();
     const uint32_t again = __builtin_amdgcn_readfirstlane(again_count);
     decided = again <= (uint32_t)kChiPairs;
