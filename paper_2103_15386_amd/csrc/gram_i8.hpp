@@ -75,19 +75,22 @@ __device__ inline v16i gram(const Operand& rows, const Operand& cols) {
 
 // Exact squared distances |a|^2 + |b|^2 - 2 a.b (four products per v_dot4) on
 // the int8 rows, from node s to one object per lane: `id` of lanes < count.
-// A row is C = dpad / 16 <= 8 chunks of 16 bytes; the C lanes of a group read
-// one object's row as one contiguous line (64 / C objects per load), multiply
+// A row is C = dpad / 16 <= 8 chunks of 16 bytes; the lanes of a group of 2, 4 or 8 (C = 6: two
+// of 8 read nothing) read one object's row as one contiguous line, multiply
 // it with the node's own chunk and add up across the group; the sums are then
 // handed to the lanes that hold the objects.  All 64 lanes call it together;
-// lanes >= count get 0.
+// lanes >= count get 0.  (With groups of 6, ten objects per load, the sums took ten lane
+// permutations per load instead of three exchanges: 200,000 x 96 bytes, k = 96, whole build 5.95 ->
+// 5.87 ms.)
 __device__ inline int32_t wave_distances_i8(const int8_t* __restrict__ shadow,
                                             const NodeMeta* meta, int dpad, int64_t s, uint32_t id,
                                             int count, int lane) {
-  const int C = dpad >> 4, per_load = kWave / C;
-  const int grp = lane / C, sub = lane - grp * C;
-  const bool lane_used = grp < per_load;  // C = 6 leaves four lanes without a group
-  const bool pow2 = (C & (C - 1)) == 0;
-  const v4i x = *reinterpret_cast<const v4i*>(shadow + s * dpad + 16 * sub);
+  const int C = dpad >> 4, shift = C <= 2 ? 1 : C <= 4 ? 2 : 3;  // (C = 2, 4, 6, 8)
+  const int per_load = kWave >> shift;
+  const int grp = lane >> shift, sub = lane & ((1 << shift) - 1);
+  const bool lane_used = sub < C;
+  const v4i x = lane_used ? *reinterpret_cast<const v4i*>(shadow + s * dpad + 16 * sub)
+                          : v4i{0, 0, 0, 0};
   const int32_t norm_s = meta[s].norm;
   // (the objects' norms come from their rows, which are here anyway: a gather of the stored
   // norm would be a second scattered access per object)
@@ -106,30 +109,19 @@ __device__ inline int32_t wave_distances_i8(const int8_t* __restrict__ shadow,
       }
     }
     int32_t total = part, total_sq = part_sq;
-    if (pow2) {  // groups are aligned blocks of 2, 4 or 8 lanes: butterfly sum
-      if (C > 1) {
-        total += (int32_t)xor_lanes((uint32_t)total, 1, lane);
-        total_sq += (int32_t)xor_lanes((uint32_t)total_sq, 1, lane);
-      }
-      if (C > 2) {
-        total += (int32_t)xor_lanes((uint32_t)total, 2, lane);
-        total_sq += (int32_t)xor_lanes((uint32_t)total_sq, 2, lane);
-      }
-      if (C > 4) {
-        total += (int32_t)xor_lanes((uint32_t)total, 4, lane);
-        total_sq += (int32_t)xor_lanes((uint32_t)total_sq, 4, lane);
-      }
-    } else {
-      for (int off = 1; off < C; ++off) {
-        int o = sub + off;
-        o = o >= C ? o - C : o;
-        total += __shfl(part, (grp * C + o) & 63, kWave);
-        total_sq += __shfl(part_sq, (grp * C + o) & 63, kWave);
-      }
+    total += (int32_t)xor_lanes((uint32_t)total, 1, lane);
+    total_sq += (int32_t)xor_lanes((uint32_t)total_sq, 1, lane);
+    if (C > 2) {
+      total += (int32_t)xor_lanes((uint32_t)total, 2, lane);
+      total_sq += (int32_t)xor_lanes((uint32_t)total_sq, 2, lane);
+    }
+    if (C > 4) {
+      total += (int32_t)xor_lanes((uint32_t)total, 4, lane);
+      total_sq += (int32_t)xor_lanes((uint32_t)total_sq, 4, lane);
     }
     // object j = lane sits in group lane - r0
-    const int32_t got = __shfl(total, ((lane - r0) * C) & 63, kWave);
-    const int32_t got_sq = __shfl(total_sq, ((lane - r0) * C) & 63, kWave);
+    const int32_t got = __shfl(total, ((lane - r0) << shift) & 63, kWave);
+    const int32_t got_sq = __shfl(total_sq, ((lane - r0) << shift) & 63, kWave);
     if (lane >= r0 && lane < r0 + per_load) {
       dot = got;
       norm_id = got_sq;
