@@ -527,7 +527,10 @@ int merge_impl(const gnnd_params* prm, const void* vec1, int64_t n1, int64_t bas
 // live in (pinned) host memory; each is built on its own, then every pair of
 // shards is merged once and stored back as two sub-graphs.  Two device slots
 // alternate, so a copy stream moves the next step's data in and the previous
-// step's results out while the compute stream works.
+// step's results out while the compute stream works.  A sub-graph that the next merge needs is
+// read where the step before has left it on the GPU; on its way down and up again (8 bytes per
+// entry each way) the compute stream had nothing to do: 4 x 600,000 x 128 bytes, k = 32,
+// 238 -> 192 ms.
 struct ShardPlan {
   int shards;
   int64_t size, last, maxs;  // rows per shard, rows of the last shard, larger of the two
@@ -728,6 +731,50 @@ int run_sharded(const gnnd_params* prm, const ShardPlan& pl, ShardStore& store,
   hipEvent_t ev_up[2] = {nullptr, nullptr}, ev_done[2] = {nullptr, nullptr}, t0 = nullptr,
              t1 = nullptr, t2 = nullptr;
   const auto pairs = pair_schedule(pl.shards);
+  const int M = (int)pairs.size();
+  // Slots alternate through both phases: shard s is built in slot s % 2, merge m works in slot
+  // (shards + m) % 2 - not in the one that holds the graph of the step before it.
+  auto slot_of = [&](int m) { return (pl.shards + m) % 2; };
+  auto shard_of = [&](int m, int h) { return h ? pairs[m].second : pairs[m].first; };
+  // whether the step before merge m has worked on shard s (the last build comes before merge 0),
+  // and then where in that step's results the shard's rows begin
+  auto left_by_last = [&](int m, int s, size_t* rows_at) {
+    *rows_at = 0;
+    if (m == 0) return s == pl.shards - 1;
+    if (s == pairs[m - 1].second) *rows_at = (size_t)rows_of(pairs[m - 1].first) * row_g;
+    return s == pairs[m - 1].first || s == pairs[m - 1].second;
+  };
+  // What merge m needs from the host: the vectors, and the graphs that the step before it does
+  // not work on.  Its slot was last read by the step before that, whose results were fetched
+  // earlier in `copy`.
+  auto up_merge = [&](int m) {
+    const int slot = slot_of(m);
+    hipError_t e = hipSuccess;
+    for (int h = 0; h < 2 && e == hipSuccess; ++h) {
+      const int s = shard_of(m, h);
+      e = store.up(copy, arena + pl.off_vec[slot][h], ShardStore::kVec,
+                   (size_t)base_of(s) * row_vec, (size_t)rows_of(s) * row_vec);
+    }
+    for (int h = 0; h < 2 && e == hipSuccess; ++h) {
+      const int s = shard_of(m, h);
+      size_t unused;
+      if (left_by_last(m, s, &unused)) continue;
+      e = store.up(copy, arena + pl.off_ids[slot][h], ShardStore::kIds, (size_t)base_of(s) * row_g,
+                   (size_t)rows_of(s) * row_g);
+      if (e == hipSuccess)
+        e = store.up(copy, arena + pl.off_dist[slot][h], ShardStore::kDist,
+                     (size_t)base_of(s) * row_g, (size_t)rows_of(s) * row_g);
+    }
+    return e;
+  };
+  // the rows of shard s from a step's results to the host
+  auto down_graph = [&](int slot, int s, size_t rows_at) {
+    hipError_t e = store.down(copy, ShardStore::kIds, (size_t)base_of(s) * row_g,
+                              arena + pl.off_oids[slot] + rows_at, (size_t)rows_of(s) * row_g);
+    if (e != hipSuccess) return e;
+    return store.down(copy, ShardStore::kDist, (size_t)base_of(s) * row_g,
+                      arena + pl.off_odist[slot] + rows_at, (size_t)rows_of(s) * row_g);
+  };
   const auto wall0 = std::chrono::steady_clock::now();
   for (int i = 0; i < 2; ++i) {
     GNND_HIP(hipEventCreateWithFlags(&ev_up[i], hipEventDisableTiming), "hipEventCreate");
@@ -748,11 +795,11 @@ int run_sharded(const gnnd_params* prm, const ShardPlan& pl, ShardStore& store,
     GNND_HIP(hipEventRecord(ev_up[0], copy), "hipEventRecord");
     for (int s = 0; s < pl.shards; ++s) {
       const int slot = s % 2;
-      if (s + 1 < pl.shards) {  // next shard's vectors travel while this one is built
-        if (s >= 1) GNND_HIP(hipStreamWaitEvent(copy, ev_done[1 - slot], 0), "hipStreamWaitEvent");
-        GNND_HIP(upload(s + 1), "shard upload");
-        GNND_HIP(hipEventRecord(ev_up[1 - slot], copy), "hipEventRecord");
-      }
+      // what the next step needs travels while this shard is built
+      if (s >= 1) GNND_HIP(hipStreamWaitEvent(copy, ev_done[1 - slot], 0), "hipStreamWaitEvent");
+      if (s + 1 < pl.shards) GNND_HIP(upload(s + 1), "shard upload");
+      else GNND_HIP(up_merge(0), "merge upload");
+      GNND_HIP(hipEventRecord(ev_up[1 - slot], copy), "hipEventRecord");
       GNND_HIP(hipStreamWaitEvent(comp, ev_up[slot], 0), "hipStreamWaitEvent");
       gnnd_params q = *prm;
       q.n = rows_of(s);
@@ -775,88 +822,46 @@ int run_sharded(const gnnd_params* prm, const ShardPlan& pl, ShardStore& store,
       if (rc != GNND_OK) goto done;
       GNND_HIP(hipEventRecord(ev_done[slot], comp), "hipEventRecord");
       GNND_HIP(hipStreamWaitEvent(copy, ev_done[slot], 0), "hipStreamWaitEvent");
-      GNND_HIP(store.down(copy, ShardStore::kIds, (size_t)base_of(s) * row_g,
-                          arena + pl.off_oids[slot], (size_t)rows_of(s) * row_g), "graph download");
-      GNND_HIP(store.down(copy, ShardStore::kDist, (size_t)base_of(s) * row_g,
-                          arena + pl.off_odist[slot], (size_t)rows_of(s) * row_g), "graph download");
+      // (merge 0 reads the last shard's graph where it is, and writes that shard's rows)
+      if (s + 1 < pl.shards) GNND_HIP(down_graph(slot, s, 0), "graph download");
     }
   }
   GNND_HIP(hipEventRecord(t1, comp), "hipEventRecord");
 
   // ---- phase 2: every pair of shards merged once -------------------------------
-  {
-    // what of merge m can travel before merge m-1 has delivered: the vectors, and the
-    // graph of a shard that merge m-1 does not touch
-    auto up_vec = [&](int m) {
-      const int slot = m % 2;
-      const int sh[2] = {pairs[m].first, pairs[m].second};
-      for (int h = 0; h < 2; ++h) {
-        hipError_t e = store.up(copy, arena + pl.off_vec[slot][h], ShardStore::kVec,
-                                (size_t)base_of(sh[h]) * row_vec, (size_t)rows_of(sh[h]) * row_vec);
-        if (e != hipSuccess) return e;
-      }
-      return hipSuccess;
-    };
-    auto up_graph = [&](int m, int h) {
-      const int slot = m % 2;
-      const int s = h ? pairs[m].second : pairs[m].first;
-      hipError_t e = store.up(copy, arena + pl.off_ids[slot][h], ShardStore::kIds,
-                              (size_t)base_of(s) * row_g, (size_t)rows_of(s) * row_g);
-      if (e != hipSuccess) return e;
-      return store.up(copy, arena + pl.off_dist[slot][h], ShardStore::kDist,
-                      (size_t)base_of(s) * row_g, (size_t)rows_of(s) * row_g);
-    };
-    auto touches = [&](int m, int s) { return pairs[m].first == s || pairs[m].second == s; };
-    const int M = (int)pairs.size();
-    // merge 0: everything is on the host already (the downloads above are earlier in `copy`)
-    GNND_HIP(up_vec(0), "merge upload");
-    GNND_HIP(up_graph(0, 0), "merge upload");
-    GNND_HIP(up_graph(0, 1), "merge upload");
-    GNND_HIP(hipEventRecord(ev_up[0], copy), "hipEventRecord");
-    for (int m = 0; m < M; ++m) {
-      const int slot = m % 2;
-      const int sa = pairs[m].first, sb = pairs[m].second;
-      bool late[2] = {false, false};
-      if (m + 1 < M) {
-        // slot 1-slot was last read by merge m-1 and its results were fetched after
-        // ev_done[1-slot]; both are earlier in `copy` than what follows
-        GNND_HIP(up_vec(m + 1), "merge upload");
-        for (int h = 0; h < 2; ++h) {
-          const int s = h ? pairs[m + 1].second : pairs[m + 1].first;
-          late[h] = touches(m, s);
-          if (!late[h]) GNND_HIP(up_graph(m + 1, h), "merge upload");
-        }
-      }
-      GNND_HIP(hipStreamWaitEvent(comp, ev_up[slot], 0), "hipStreamWaitEvent");
-      gnnd_params q = *prm;
-      q.n = rows_of(sa) + rows_of(sb);
-      q.seed = prm->seed + 1000 + (uint64_t)m;
-      q.workspace_dev = arena + pl.off_ws;
-      q.workspace_bytes = pl.ws_bytes;
-      rc = merge_impl(&q, arena + pl.off_vec[slot][0], rows_of(sa), base_of(sa),
-                      arena + pl.off_vec[slot][1], rows_of(sb), base_of(sb), prm->n,
-                      (const int32_t*)(arena + pl.off_ids[slot][0]), arena + pl.off_dist[slot][0],
-                      (const int32_t*)(arena + pl.off_ids[slot][1]), arena + pl.off_dist[slot][1],
-                      merge_iters, (int32_t*)(arena + pl.off_oids[slot]),
-                      arena + pl.off_odist[slot], nullptr);
-      if (rc != GNND_OK) goto done;
-      GNND_HIP(hipEventRecord(ev_done[slot], comp), "hipEventRecord");
-      GNND_HIP(hipStreamWaitEvent(copy, ev_done[slot], 0), "hipStreamWaitEvent");
-      // results: rows of shard sa, then rows of shard sb
-      const size_t na = (size_t)rows_of(sa), nb = (size_t)rows_of(sb);
-      GNND_HIP(store.down(copy, ShardStore::kIds, (size_t)base_of(sa) * row_g,
-                          arena + pl.off_oids[slot], na * row_g), "merge download");
-      GNND_HIP(store.down(copy, ShardStore::kIds, (size_t)base_of(sb) * row_g,
-                          arena + pl.off_oids[slot] + na * row_g, nb * row_g), "merge download");
-      GNND_HIP(store.down(copy, ShardStore::kDist, (size_t)base_of(sa) * row_g,
-                          arena + pl.off_odist[slot], na * row_g), "merge download");
-      GNND_HIP(store.down(copy, ShardStore::kDist, (size_t)base_of(sb) * row_g,
-                          arena + pl.off_odist[slot] + na * row_g, nb * row_g), "merge download");
-      if (m + 1 < M) {
-        for (int h = 0; h < 2; ++h)
-          if (late[h]) GNND_HIP(up_graph(m + 1, h), "merge upload");
-        GNND_HIP(hipEventRecord(ev_up[1 - slot], copy), "hipEventRecord");
-      }
+  for (int m = 0; m < M; ++m) {
+    const int slot = slot_of(m);
+    const int sa = pairs[m].first, sb = pairs[m].second;
+    if (m + 1 < M) {
+      GNND_HIP(up_merge(m + 1), "merge upload");
+      GNND_HIP(hipEventRecord(ev_up[1 - slot], copy), "hipEventRecord");
+    }
+    GNND_HIP(hipStreamWaitEvent(comp, ev_up[slot], 0), "hipStreamWaitEvent");
+    const char *ids[2], *dist[2];
+    for (int h = 0; h < 2; ++h) {
+      size_t rows_at;
+      const bool here = left_by_last(m, shard_of(m, h), &rows_at);
+      ids[h] = arena + (here ? pl.off_oids[1 - slot] + rows_at : pl.off_ids[slot][h]);
+      dist[h] = arena + (here ? pl.off_odist[1 - slot] + rows_at : pl.off_dist[slot][h]);
+    }
+    gnnd_params q = *prm;
+    q.n = rows_of(sa) + rows_of(sb);
+    q.seed = prm->seed + 1000 + (uint64_t)m;
+    q.workspace_dev = arena + pl.off_ws;
+    q.workspace_bytes = pl.ws_bytes;
+    rc = merge_impl(&q, arena + pl.off_vec[slot][0], rows_of(sa), base_of(sa),
+                    arena + pl.off_vec[slot][1], rows_of(sb), base_of(sb), prm->n,
+                    (const int32_t*)ids[0], dist[0], (const int32_t*)ids[1], dist[1], merge_iters,
+                    (int32_t*)(arena + pl.off_oids[slot]), arena + pl.off_odist[slot], nullptr);
+    if (rc != GNND_OK) goto done;
+    GNND_HIP(hipEventRecord(ev_done[slot], comp), "hipEventRecord");
+    GNND_HIP(hipStreamWaitEvent(copy, ev_done[slot], 0), "hipStreamWaitEvent");
+    // results: rows of shard sa, then rows of shard sb; what the next merge works on stays here
+    // until that has written its own
+    for (int h = 0; h < 2; ++h) {
+      const int s = shard_of(m, h);
+      if (m + 1 < M && (s == pairs[m + 1].first || s == pairs[m + 1].second)) continue;
+      GNND_HIP(down_graph(slot, s, h ? (size_t)rows_of(sa) * row_g : 0), "merge download");
     }
   }
   GNND_HIP(hipEventRecord(t2, comp), "hipEventRecord");
