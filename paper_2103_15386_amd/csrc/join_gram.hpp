@@ -108,11 +108,15 @@ __host__ __device__ constexpr GramShape gram_shape(int cls) {
                     : GramShape{4, 4, 2};
 }
 // Which build takes a node with rb blocks of NEW and co blocks of OLD samples: the cheapest
-// one that holds them.
+// one that holds them.  (Up to 16 NEW samples: class 1 with and without OLD ones, so that lists of
+// up to 16 samples need one build, and no lists of nodes: see launch_join_gram.)
 __host__ __device__ constexpr int gram_class(int rb, int co) {
-  return co == 0 ? 0 : (rb <= 1 && co <= 2) ? 1 : (rb <= 3 && co <= 1) ? 2 : rb <= 1 ? 3
+  return co == 0 && rb > 1 ? 0 : (rb <= 1 && co <= 2) ? 1 : (rb <= 3 && co <= 1) ? 2 : rb <= 1 ? 3
          : rb <= 2 ? 4 : co <= 2 ? 5 : 6;
 }
+// Lists of up to 16 samples: all nodes are class 1.
+constexpr bool gram_one_class(int p) { return 2 * p <= 16; }
+static_assert(gram_class(1, 0) == 1 && gram_class(1, 1) == 1, "one build for p <= 8");
 static_assert(kGramClasses == 7, "gram_shape and gram_class list seven builds");
 // first LDS row of operand block q of a build with RBM blocks of NEW samples
 template <int RBM>
@@ -848,15 +852,17 @@ __attribute__((amdgpu_waves_per_eu(gram_shape(CLS).waves, gram_shape(CLS).waves)
   __shared__ __attribute__((aligned(16))) GramLds S;
   // step 4: 16 dimensions of every vector the build can hold, operand block after operand block
   __shared__ __attribute__((aligned(16))) float tile[NB * 16 * kWLD];
-  const uint32_t mine = count[cls];
+  // (count NULL: every node is this build's)
+  const uint32_t mine = count ? count[cls] : (uint32_t)n;
   const int32_t* const list = nodes + (int64_t)cls * n;
   GramTally tally;
   constexpr bool kCopies = FORM == 2;
   const float rho = kCopies ? *hr.rho : 0.f;
   FormTally first_form(kCopies ? *forms : 0ull);
   for (uint32_t i = blockIdx.x; i < mine; i += gridDim.x) {
-    const int64_t s = list[i];
+    const int64_t s = count ? list[i] : (int64_t)i;
     const int nn = cnew[s], no = cold[s];
+    if (!count && (nn == 0 || (no == 0 && (merge_mode || nn == 1)))) continue;  // nothing to do
     bool done = false;
     if constexpr (kCopies) {
       if (first_form.promising((uint32_t)s)) {
@@ -911,7 +917,8 @@ void launch_gram_builds(const Shape& sh, const DevState& ds, int mm, unsigned gr
       if (reached[C])
         k_join_gram<METRIC, F, C><<<grid, kWave, 0, st>>>(
             vs, hr, sh.n, sh.p, mm, ds.snew, ds.sold, ds.cnew, ds.cold, ds.meta, ds.pslot, slots,
-            ds.bins, ds.counters, ds.forms, ds.cls_nodes, ds.cls_count);
+            ds.bins, ds.counters, ds.forms, ds.cls_nodes,
+            gram_one_class(sh.p) ? nullptr : ds.cls_count);
     };
     build(std::integral_constant<int, 0>{});
     build(std::integral_constant<int, 1>{});
