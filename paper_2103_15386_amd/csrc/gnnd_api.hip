@@ -39,7 +39,7 @@ thread_local std::string g_last_error = "";
 
 struct Layout {
   size_t off_G, off_kth, off_snew, off_sold, off_cnew, off_cold, off_ron,
-      off_roo, off_csn, off_cso, off_fwd, off_grp, off_pslot, off_poff, off_bins,
+      off_roo, off_csn, off_cso, off_fwd, off_grp, off_pslot, off_deg, off_poff, off_bins,
       off_cnt, off_snap, off_aside, off_shadow, off_norms, off_flag, off_bkc, off_stg_ent,
       off_stg_cur, off_cls_nodes, off_cls_count, off_half, total;
   bool extra;  // has room for the 16-bit rows of the float32 matrix-core join, the int8 rows of
@@ -149,6 +149,7 @@ Layout make_layout(const gnnd_params* q, bool with_aside, bool extra = true) {
   L.off_fwd = take(n * 4);
   L.off_grp = take((n / 32 + 1) * 8);
   L.off_pslot = take(n * 8);
+  L.off_deg = take(sample_direct(q->n, q->p) ? n * 8 : 0);  // (cleared together with pslot)
   L.off_poff = take((n + 1) * 8);
   const size_t slots_per_node =
       q->update_mode == GNND_UPDATE_ALL_PAIRS ? 2 * p * (6 * p - 1) : 6 * p;
@@ -232,6 +233,7 @@ void bind(gnnd_ctx* c, const Layout& L) {
   d.csr_old = (int32_t*)(w + L.off_cso);
   d.pslot = (uint64_t*)(w + L.off_pslot);
   d.poff = (uint64_t*)(w + L.off_poff);
+  d.degree = (uint32_t*)(w + L.off_deg);
   d.fwd_before = (uint32_t*)(w + L.off_fwd);
   d.group_before = (uint64_t*)(w + L.off_grp);
   d.bins = (uint64_t*)(w + L.off_bins);
@@ -286,9 +288,12 @@ int init_ctx(gnnd_ctx* c, const gnnd_params* prm, const Layout& L, const void* v
   c->prof_count = 0;
   c->prof_missed = 0;
   bind(c, L);
-  // the statistics counters start at zero; the slot words read "nothing received" until the
-  // first sampling stage writes them
-  hipError_t e = launch_zero_u32((uint32_t*)c->ds.pslot, 2 * (size_t)prm->n, c->stream);
+  // the statistics counters start at zero, and so do the reverse degrees; the slot words read
+  // "nothing received" until the first sampling stage writes them
+  const size_t to_clear = sample_direct(prm->n, prm->p)
+                              ? (L.off_deg - L.off_pslot) / 4 + 2 * (size_t)prm->n
+                              : 2 * (size_t)prm->n;
+  hipError_t e = launch_zero_u32((uint32_t*)c->ds.pslot, to_clear, c->stream);
   if (e == hipSuccess)
     e = launch_zero_u32((uint32_t*)c->ds.counters, ((size_t)kStripes * C_SLOTS + 1) * 2, c->stream);
   if (e != hipSuccess) return hip_fail(nullptr, e, "clearing workspace counters");

@@ -120,7 +120,8 @@ __global__ __launch_bounds__(kBlock) void k_rev_select(int64_t n, int p, uint64_
                                                        const int32_t* csr_new,
                                                        const int32_t* csr_old,
                                                        SegmentRule seg, uint64_t* poff,
-                                                       uint64_t* pslot, uint64_t* counters) {
+                                                       uint64_t* pslot, uint64_t* counters,
+                                                       uint32_t* clear) {
   const int64_t v0 = wave_global_index() * kNodesPerWave;
   if (v0 >= n) return;
   const int lane = lane_id();
@@ -176,6 +177,7 @@ __global__ __launch_bounds__(kBlock) void k_rev_select(int64_t n, int p, uint64_
     }
   }
   if (mine) (old_l ? cold : cnew)[v_l] = size_l;
+  if (clear && mine) clear[(old_l ? n : 0) + v_l] = 0u;  // (DevState::degree)
   // a node's segment of the proposals (both lists of a node stand side by side)
   const uint32_t per = old_l ? seg.per_old : seg.per_new;
   auto both = [&](uint64_t x) { return x + xor_lanes(x, 1, lane); };
@@ -632,17 +634,20 @@ hipError_t launch_init_random(const Shape& sh, const DevState& ds, uint64_t seed
 constexpr int64_t kOneNodePerWave = 1 << 14;
 hipError_t launch_sample(const Shape& sh, const DevState& ds, uint64_t seed, uint32_t iter,
                          hipStream_t st) {
-  // forward sampling, and the reverse candidates grouped by target (two-level counting sort)
-  int group_rows = 0;
-  hipError_t e = launch_sample_buckets(sh, ds, &group_rows, st);
+  // forward sampling, and the reverse candidates grouped by target
+  const bool direct = sample_direct(sh.n, sh.p);
+  int group_rows = 32;
+  hipError_t e = direct ? launch_sample_direct(sh, ds, st)
+                        : launch_sample_buckets(sh, ds, &group_rows, st);
   if (e != hipSuccess) return e;
+  uint32_t* const clear = direct ? ds.degree : nullptr;
   if (2 * sh.p > kWave)  // two list entries per lane
-    return launch_rev_select_long(sh, ds, seed, iter, group_rows, st);
+    return launch_rev_select_long(sh, ds, seed, iter, group_rows, clear, st);
 #define GNND_SELECT(NODES)                                                                       \
   k_rev_select<NODES><<<blocks_for_waves((sh.n + NODES - 1) / NODES), kBlock, 0, st>>>(          \
       sh.n, sh.p, hash_base(seed, kTagRevNew), hash_base(seed, kTagRevOld), iter, ds.snew,       \
       ds.sold, ds.cnew, ds.cold, ds.roff_new, ds.roff_old, ds.csr_new, ds.csr_old,               \
-      SegmentRule(sh, ds, group_rows), ds.poff, ds.pslot, ds.counters)
+      SegmentRule(sh, ds, group_rows), ds.poff, ds.pslot, ds.counters, clear)
   if (sh.n <= kOneNodePerWave) GNND_SELECT(1);
   else GNND_SELECT(4);
 #undef GNND_SELECT

@@ -98,7 +98,7 @@ __global__ __launch_bounds__(kLB) void k_rev_select_long(
     int64_t n, int p, uint64_t base_new, uint64_t base_old, uint32_t iter, int32_t* snew,
     int32_t* sold, int32_t* cnew, int32_t* cold, const uint64_t* roff_new,
     const uint64_t* roff_old, const int32_t* csr_new, const int32_t* csr_old, SegmentRule seg,
-    uint64_t* poff, uint64_t* pslot, uint64_t* counters) {
+    uint64_t* poff, uint64_t* pslot, uint64_t* counters, uint32_t* clear) {
   const int64_t v = block_linear() * kWavesPerLB + wave_id();
   if (v >= n) return;
   const int lane = lane_id();
@@ -123,6 +123,7 @@ __global__ __launch_bounds__(kLB) void k_rev_select_long(
   if (lane == 0) {
     cnew[v] = cn;
     cold[v] = co;
+    if (clear) clear[v] = clear[n + v] = 0u;  // (DevState::degree)
     counter_add(counters, C_SUMNEW, v, (uint64_t)cn);
     counter_add(counters, C_SUMOLD, v, (uint64_t)co);
     seg.write(v, n, seg.per_new * bn + seg.per_old * bo + seg.before(v),
@@ -368,12 +369,13 @@ __global__ __launch_bounds__(kLB) void k_join_long(
 }  // namespace
 
 hipError_t launch_rev_select_long(const Shape& sh, const DevState& ds, uint64_t seed,
-                                  uint32_t iter, int group_rows, hipStream_t st) {
+                                  uint32_t iter, int group_rows, uint32_t* clear,
+                                  hipStream_t st) {
   const dim3 grid = grid_blocks((sh.n + kWavesPerLB - 1) / kWavesPerLB);
   k_rev_select_long<<<grid, kLB, 0, st>>>(
       sh.n, sh.p, hash_base(seed, kTagRevNew), hash_base(seed, kTagRevOld), iter, ds.snew, ds.sold,
       ds.cnew, ds.cold, ds.roff_new, ds.roff_old, ds.csr_new, ds.csr_old, SegmentRule(sh, ds, group_rows),
-      ds.poff, ds.pslot, ds.counters);
+      ds.poff, ds.pslot, ds.counters, clear);
   return hipGetLastError();
 }
 

@@ -197,6 +197,17 @@ __global__ __launch_bounds__(kSB) void k_fwd_count(int64_t n, int k, int p, Buck
   for (int i = threadIdx.x; i < 2 * g.nb; i += kSB) wg_hist[(size_t)i * gridDim.x + blockIdx.x] = hist[i];
 }
 
+// What the sampling stage keeps and clears before an iteration's cross-matching: the counters'
+// values, the joins' node list lengths and region cursors.  By one workgroup of 256.
+__device__ inline void begin_iteration(const uint64_t* counters, uint64_t* snap, uint64_t* forms,
+                                       uint32_t* cls_count, unsigned long long* stg_cur) {
+  for (int i = threadIdx.x; i < kStripes * C_SLOTS; i += kSB) snap[i] = counters[i];
+  if (threadIdx.x == 0) *forms = FormTally::faded(*forms);
+  if (cls_count && threadIdx.x < kNodeClassesMax) cls_count[threadIdx.x] = 0u;
+  if (stg_cur)
+    for (int i = threadIdx.x; i < kStageBuckets; i += kSB) stg_cur[i] = 0ull;
+}
+
 // Exclusive scan along every row of the (bucket x workgroup) count matrix: the
 // entry of workgroup w becomes the start of w's run inside the bucket, the row
 // total the bucket's size.  One wavefront per row - no atomics, and the edge
@@ -225,11 +236,7 @@ __global__ __launch_bounds__(kSB) void k_wg_scan(int W, int rows, uint32_t* wg_h
         carry += __shfl(inc, kWave - 1, kWave);
       }
     }
-    for (int i = threadIdx.x; i < kStripes * C_SLOTS; i += kSB) snap[i] = counters[i];
-    if (threadIdx.x == 0) *forms = FormTally::faded(*forms);
-    if (cls_count && threadIdx.x < kNodeClassesMax) cls_count[threadIdx.x] = 0u;
-    if (stg_cur)
-      for (int i = threadIdx.x; i < kStageBuckets; i += kSB) stg_cur[i] = 0ull;
+    begin_iteration(counters, snap, forms, cls_count, stg_cur);
     return;
   }
   const int c = blockIdx.x * (kSB / kWave) + wave_id();
@@ -506,6 +513,104 @@ __global__ __launch_bounds__(kCsrBlock) void k_bucket_csr(int64_t n, BucketGeom 
         csr[beg + pos] = (int32_t)ed[r].y;
       }
   }
+}
+
+// Small collections (sample_direct): forward sampling, a wavefront per row, and every sample's
+// rank among its target's candidates.  One workgroup more begins the iteration.
+template <bool WIDE>
+__global__ __launch_bounds__(kSB) void k_fwd_direct(int64_t n, int k, int p, uint64_t* G,
+                                                    int32_t* snew, int32_t* sold, int32_t* cnew,
+                                                    int32_t* cold, uint32_t* degree,
+                                                    uint32_t* rank, const uint64_t* counters,
+                                                    uint64_t* snap, uint64_t* forms,
+                                                    uint32_t* cls_count,
+                                                    unsigned long long* stg_cur) {
+  if (blockIdx.x == gridDim.x - 1) {
+    begin_iteration(counters, snap, forms, cls_count, stg_cur);
+    return;
+  }
+  const int64_t s = (int64_t)blockIdx.x * (kSB / kWave) + wave_id();
+  if (s >= n) return;
+  const int lane = lane_id();
+  const uint64_t e0 = lane < k ? G[s * k + lane] : 0ull;
+  int32_t v[2][2] = {{-1, -1}, {-1, -1}};  // kind, register
+  int cn, co;
+  if (WIDE) {
+    const uint64_t e1 = lane + kWave < k ? G[s * k + kWave + lane] : 0ull;
+    forward_sample_row_wide(s, n, k, p, G, snew, sold, cnew, cold, lane, e0, e1, v[0], v[1], cn, co);
+  } else {
+    forward_sample_row(s, n, k, p, G, snew, sold, cnew, cold, lane, e0, v[0][0], v[1][0], cn, co);
+  }
+  uint32_t r[2][2];
+#pragma unroll
+  for (int kind = 0; kind < 2; ++kind)
+#pragma unroll
+    for (int q = 0; q < (WIDE ? 2 : 1); ++q)
+      if (v[kind][q] >= 0) r[kind][q] = atomicAdd(&degree[kind * n + v[kind][q]], 1u);
+#pragma unroll
+  for (int kind = 0; kind < 2; ++kind) {
+    int at = 0;  // samples stand in the list in the order of their entries
+#pragma unroll
+    for (int q = 0; q < (WIDE ? 2 : 1); ++q) {
+      const uint64_t taken = __ballot(v[kind][q] >= 0);
+      if (v[kind][q] >= 0) rank[(kind * n + s) * p + at + rank_in(taken)] = r[kind][q];
+      at += __popcll(taken);
+    }
+  }
+}
+
+// The candidates of one kind (blockIdx.y) to their places.  Every workgroup scans all degrees for
+// itself (in LDS), then places its share of the samples.
+constexpr int kPlaceBlock = 1024;
+__global__ __launch_bounds__(kPlaceBlock) void k_place_direct(
+    int64_t n, int p, const int32_t* snew, const int32_t* sold, const uint32_t* degree,
+    const uint32_t* rank, uint64_t* roff_new, uint64_t* roff_old, int32_t* csr_new,
+    int32_t* csr_old) {
+  static_assert(kPlaceBlock == kCsrBlock, "block_sum_1024");
+  __shared__ uint32_t off[kDirectNodes];
+  __shared__ uint64_t scan_tmp[kPlaceBlock / kWave];
+  const int kind = blockIdx.y, N = (int)n;
+  const int32_t* list = kind ? sold : snew;
+  uint64_t* roff = kind ? roff_old : roff_new;
+  int32_t* csr = kind ? csr_old : csr_new;
+  degree += kind * n;
+  rank += kind * n * p;
+  for (int i = threadIdx.x; i < N; i += kPlaceBlock) off[i] = degree[i];
+  __syncthreads();
+  const int per = (N + kPlaceBlock - 1) / kPlaceBlock, first = threadIdx.x * per;
+  uint64_t sum = 0, before;
+  for (int i = first; i < first + per && i < N; ++i) sum += off[i];
+  const uint64_t all = block_sum_1024(sum, scan_tmp, &before);
+  uint32_t at = (uint32_t)before;
+  for (int i = first; i < first + per && i < N; ++i) {
+    const uint32_t own = off[i];
+    off[i] = at;
+    at += own;
+  }
+  __syncthreads();
+  const int step = gridDim.x * kPlaceBlock, own = blockIdx.x * kPlaceBlock + threadIdx.x;
+  for (int i = own; i < N; i += step) roff[i] = off[i];
+  if (own == 0) roff[N] = all;
+  const float inv_p = 1.0f / (float)p;  // ((e + 0.5) / p < 2^14 is 1 / 128 off the next number)
+  for (int e = own; e < N * p; e += step) {
+    const int s = (int)(((float)e + 0.5f) * inv_p);
+    const int32_t v = list[(int64_t)s * 2 * p + (e - s * p)];
+    if (v >= 0) csr[off[v] + rank[e]] = s;
+  }
+}
+
+hipError_t launch_sample_direct(const Shape& sh, const DevState& ds, hipStream_t st) {
+  // (the proposal array is not in use yet: 2 n p ranks in its 6 n p words or more)
+  uint32_t* rank = reinterpret_cast<uint32_t*>(ds.bins);
+  const unsigned grid = (unsigned)((sh.n + kSB / kWave - 1) / (kSB / kWave)) + 1;
+  auto* const fwd = sh.k > kWave ? k_fwd_direct<true> : k_fwd_direct<false>;
+  fwd<<<grid, kSB, 0, st>>>(sh.n, sh.k, sh.p, ds.G, ds.snew, ds.sold, ds.cnew, ds.cold, ds.degree,
+                            rank, ds.counters, ds.snap, ds.forms, ds.cls_count, ds.stg_cur);
+  const int64_t blocks = (sh.n * sh.p + kPlaceBlock - 1) / kPlaceBlock;
+  k_place_direct<<<dim3((unsigned)blocks, 2), kPlaceBlock, 0, st>>>(
+      sh.n, sh.p, ds.snew, ds.sold, ds.degree, rank, ds.roff_new, ds.roff_old, ds.csr_new,
+      ds.csr_old);
+  return hipGetLastError();
 }
 
 // The bucket layout for n <= 2^27 targets: at most 4096 buckets of 2^tb <= 2^15 targets (one

@@ -78,3 +78,19 @@ def test_builds_match_the_oracle_around_the_segment_rule(n, metric):
     assert st["dropped"] == 0
     assert (ids.cpu().numpy() == g.ids).all() and (dist.cpu().numpy() == g.dist).all()
     ctx.close()
+
+
+@pytest.mark.parametrize("n,k,p", [(12288, 10, 10), (12289, 10, 10), (12287, 11, 10),
+                                   (4096, 32, 32), (4097, 33, 32), (2048, 128, 64), (2049, 100, 64),
+                                   (1000, 70, 64), (65, 64, 40), (7, 5, 3)])
+def test_builds_match_the_oracle_where_small_collections_end(n, k, p):
+    import paper_2103_15386_amd as amd
+    x = W.uniform_f32(n, 8, seed=5)
+    g, _ = og.build(x, k, p, og.L2SQ_F32, SEED, 3)
+    ctx = amd.Gnnd(torch.from_numpy(x).cuda(), k, p, amd.L2SQ_F32, SEED)
+    for _ in range(2):  # (the second build finds what the first one has left)
+        st = ctx.build(3)
+        ids, dist = ctx.graph()
+        assert st["dropped"] == 0
+        assert (ids.cpu().numpy() == g.ids).all() and (dist.cpu().numpy() == g.dist).all()
+    ctx.close()
