@@ -23,8 +23,8 @@ namespace gnnd {
 constexpr int kMB = 256;  // 4 waves = 4 nodes in flight per workgroup
 constexpr int64_t kJoinGrid = 256 * 3 * 2;  // 256 CUs x 3 resident workgroups x 2
 // staged hand-out: one workgroup of 8 waves per CU (2 per SIMD: the staging code needs the registers) shares the staging area
-constexpr int kStagedWaves = 8;       // four operand blocks: 2 wavefronts per SIMD
-constexpr int kStagedWavesSlim = 12;  // three operand blocks: 3 wavefronts per SIMD
+constexpr int kStagedWaves = 8;       // four operand blocks of 128 bytes: 2 wavefronts per SIMD
+constexpr int kStagedWavesSlim = 12;  // three, or shorter rows: 3 wavefronts per SIMD
 
 constexpr int32_t kFar = 1 << 24;  // "norm" of an absent row: above every real distance
 
@@ -240,22 +240,28 @@ __device__ inline int32_t sample_norm(const Operand& b0, const Operand& b1, int 
 // most 32 NEW samples.  Most nodes are of shape 1 (early iterations: many NEW, few OLD) or 2
 // (late ones); without the fourth block's 16 registers the kernel fits 3 wavefronts per SIMD,
 // which hide the per-node chain wait -> evaluate -> hand on better than 2 do (6 to 12 % less
-// time per iteration).  k_join_shapes lists the nodes of each shape (those with nothing to
+// time per iteration).  Rows of up to 96 bytes leave room for the fourth block: 157 registers,
+// 200,000 x 96 bytes with full lists, whole build 5.87 -> 5.76 ms.  k_join_shapes lists the nodes of each shape (those with nothing to
 // evaluate are in no list) and every build runs over its own list.
 constexpr int kJoinShapes = 3;
 __host__ __device__ constexpr int join_list_of_shape(int shape) { return shape == 0 ? 2 : shape - 1; }
-__host__ __device__ constexpr int join_waves(bool staged, int shape) {
-  return staged ? (shape ? kStagedWavesSlim : kStagedWaves) : kMB / kWave;
+__host__ __device__ constexpr bool join_slim(int shape, int ksteps) { return shape || ksteps < 4; }
+__host__ __device__ constexpr int join_waves(bool staged, int shape, int ksteps) {
+  return !staged ? kMB / kWave : join_slim(shape, ksteps) ? kStagedWavesSlim : kStagedWaves;
+}
+__host__ __device__ constexpr int join_waves_per_simd(bool staged, int shape, int ksteps) {
+  return staged && !join_slim(shape, ksteps) ? 2 : 3;
 }
 
 template <int KSTEPS, bool FCODE, bool MERGE, bool STAGED, bool LEAN = false, int SHAPE = 0>
-__global__ __launch_bounds__(join_waves(STAGED, SHAPE) * kWave)
-__attribute__((amdgpu_waves_per_eu(STAGED && !SHAPE ? 2 : 3, STAGED && !SHAPE ? 2 : 3))) void k_join_mfma(
+__global__ __launch_bounds__(join_waves(STAGED, SHAPE, KSTEPS) * kWave)
+__attribute__((amdgpu_waves_per_eu(join_waves_per_simd(STAGED, SHAPE, KSTEPS),
+                                   join_waves_per_simd(STAGED, SHAPE, KSTEPS)))) void k_join_mfma(
     const int8_t* __restrict__ shadow, const NodeMeta* __restrict__ meta, int dpad, int64_t n,
     int p, int64_t split, const int32_t* __restrict__ snew, const int32_t* __restrict__ sold,
     uint64_t* pslot, uint64_t slots, uint64_t* __restrict__ bins, uint64_t* counters,
     StageArgs sa) {
-  constexpr int WAVES = join_waves(STAGED, SHAPE);
+  constexpr int WAVES = join_waves(STAGED, SHAPE, KSTEPS);
   constexpr bool kHasN1 = SHAPE != 2, kHasO1 = SHAPE != 1;
   static_assert(STAGED || SHAPE == 0, "shapes come with the node lists of the staged form");
   // per wave, for the 128 rows (NEW 0..63, OLD 64..127): -((norm << 6) | position), the ids
@@ -833,7 +839,7 @@ template <int KSTEPS, bool STAGED, bool LEAN = false, int SHAPE = 0>
 static hipError_t launch_k(bool fcode, bool merge, unsigned grid, hipStream_t st,
                            const int8_t* shadow, const NodeMeta* meta, int dpad, const Shape& sh,
                            const DevState& ds, const StageArgs& sa) {
-  constexpr int block = join_waves(STAGED, SHAPE) * kWave;
+  constexpr int block = join_waves(STAGED, SHAPE, KSTEPS) * kWave;
   const size_t lds = STAGED ? kStageLdsBytes : 0;
 #define GNND_ARGS shadow, meta, dpad, sh.n, sh.p, sh.split, ds.snew, ds.sold, \
                   ds.pslot, (uint64_t)sh.slots(), ds.bins, ds.counters, sa
@@ -920,7 +926,7 @@ hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode
     const int64_t want = (sh.n + waves - 1) / waves;
     return (unsigned)(want < compute_units() ? want : compute_units());
   };
-  const unsigned grid_slim = grid_for(kStagedWavesSlim), grid_full = grid_for(kStagedWaves);
+  const unsigned grid_slim = grid_for(kStagedWavesSlim);
 #define GNND_K(K)                                                                                  \
   e = lean ? launch_k<K, true, true, 1>(fcode, false, grid_slim, st, ds.shadow, ds.meta, dpad, sh, \
                                         ds, sa)                                                    \
@@ -930,8 +936,8 @@ hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode
     e = launch_k<K, true, false, 2>(fcode, merge_mode, grid_slim, st, ds.shadow, ds.meta, dpad,    \
                                     sh, ds, sa);                                                   \
   if (e == hipSuccess && sh.p > 16)                                                                \
-    e = launch_k<K, true, false, 0>(fcode, merge_mode, grid_full, st, ds.shadow, ds.meta, dpad,    \
-                                    sh, ds, sa)
+    e = launch_k<K, true, false, 0>(fcode, merge_mode, grid_for(join_waves(true, 0, K)), st,       \
+                                    ds.shadow, ds.meta, dpad, sh, ds, sa)
   switch (ksteps) {
     case 1: GNND_K(1); break;
     case 2: GNND_K(2); break;
