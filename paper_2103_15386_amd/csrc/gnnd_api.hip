@@ -47,6 +47,7 @@ struct Layout {
 };
 
 constexpr int kHalfMinDim = 24;
+constexpr int64_t kStageLeastNodes = 1 << 14;  // up to here results are not staged by themselves
 
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -113,6 +114,11 @@ bool stage_possible(const gnnd_params* q, bool extra) {
          (extra || q->n <= ((int64_t)1 << 20));
 }
 
+// Few nodes, and the library chooses: results are handed on one by one.
+bool stays_small(const gnnd_params* q) {
+  return q->join_path == GNND_JOIN_AUTO && q->n <= kStageLeastNodes;
+}
+
 // 16-bit copies of the vectors for the first pass of the float32 matrix-core join: from 24
 // dimensions on (below, a row of them is no shorter than the float32 row).
 bool half_possible(const gnnd_params* q) { return gram_possible(q) && q->d >= kHalfMinDim; }
@@ -146,8 +152,9 @@ Layout make_layout(const gnnd_params* q, bool with_aside, bool extra = true) {
   L.off_roo = take((n + 1) * 8);
   L.off_csn = take(n * p * 4);
   L.off_cso = take(n * p * 4);
-  L.off_fwd = take(n * 4);
-  L.off_grp = take((n / 32 + 1) * 8);
+  const bool sums = q->n > kRoomForAll;  // (see SegmentRule)
+  L.off_fwd = take(sums ? n * 4 : 0);
+  L.off_grp = take(sums ? (n / 32 + 1) * 8 : 0);
   L.off_pslot = take(n * 8);
   L.off_deg = take(sample_direct(q->n, q->p) ? n * 8 : 0);  // (cleared together with pslot)
   L.off_poff = take((n + 1) * 8);
@@ -244,7 +251,11 @@ void bind(gnnd_ctx* c, const Layout& L) {
   d.shadow = (int8_t*)(w + L.off_shadow);
   c->flag_dev = (int*)(w + L.off_flag);
   d.bk_cnt = (uint32_t*)(w + L.off_bkc);
-  const bool staged = stage_possible(&c->prm, L.extra);
+  // (few nodes: one by one is the faster way, unless asked for; the place is kept, so that the
+  // workspace is the same.  Six iterations, staged / one by one in microseconds: 2000 x 128, p = 32:
+  // 423 / 262; 5000 x 100, 32: 657 / 501; 10,000 x 128, 32: 729 / 626; 20,000 x 100, 32: 1132 /
+  // 1109; 20,000 x 64, 16: 710 / 716; 30,000 x 100, 32: 1366 / 1469)
+  const bool staged = stage_possible(&c->prm, L.extra) && !stays_small(&c->prm);
   d.stg_ent = staged ? (uint64_t*)(w + L.off_stg_ent) : nullptr;
   d.stg_cur = staged ? (unsigned long long*)(w + L.off_stg_cur) : nullptr;
   const bool gram = gram_possible(&c->prm);
@@ -424,7 +435,10 @@ int step_join(gnnd_ctx* c, hipEvent_t after_join = nullptr) {
   if (c->stage != 1) return fail(c, GNND_ESTATE, "stage order is sample, join, update");
   hipError_t e;
   if (c->use_mfma) {
-    e = launch_join_mfma(c->sh, c->ds, c->merge_mode, c->fresh_random, c->stream, after_join);
+    // (where small collections are not staged the thresholds decide in the join as ever: what it
+    // hands on is what the staged form does)
+    const bool first_look = c->fresh_random && !stays_small(&c->prm);
+    e = launch_join_mfma(c->sh, c->ds, c->merge_mode, first_look, c->stream, after_join);
   } else {
     e = c->use_gram      ? launch_join_gram(c->sh, c->ds, c->merge_mode, c->stream)
         : c->use_long_i8 ? launch_join_long_i8(c->sh, c->ds, c->merge_mode, c->stream)

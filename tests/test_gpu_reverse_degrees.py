@@ -94,3 +94,24 @@ def test_builds_match_the_oracle_where_small_collections_end(n, k, p):
         assert st["dropped"] == 0
         assert (ids.cpu().numpy() == g.ids).all() and (dist.cpu().numpy() == g.dist).all()
     ctx.close()
+
+
+@pytest.mark.parametrize("n,d,k,p", [(1 << 14, 20, 12, 10), ((1 << 14) + 1, 96, 20, 20),
+                                     (16000, 64, 33, 32), (16390, 128, 32, 32)])
+def test_hand_out_of_small_byte_collections(n, d, k, p):
+    """Results one by one up to 2^14 nodes, staged beyond: the oracle's graph, and the counters
+    of the staged form."""
+    import paper_2103_15386_amd as amd
+    x = torch.from_numpy(W.sift_like_u8(n, d, seed=9, n_comp=16)).cuda()
+    seen = []
+    for path in (amd.JOIN_AUTO, amd.JOIN_MFMA):
+        ctx = amd.Gnnd(x, k, p, amd.L2SQ_U8, SEED, path)
+        ctx.init_random()
+        stats = [ctx.iterate() for _ in range(3)]
+        seen.append(([{f: v for f, v in s.items() if not f.startswith("ms")} for s in stats],
+                     *[t.cpu().numpy() for t in ctx.graph()]))
+        ctx.close()
+    g, _ = og.build(x.cpu().numpy(), k, p, og.L2SQ_U8, SEED, 3)
+    assert seen[0][0] == seen[1][0]
+    for _, ids, dist in seen:
+        assert (ids == g.ids).all() and (dist == g.dist).all()
