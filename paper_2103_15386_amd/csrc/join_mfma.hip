@@ -253,6 +253,15 @@ __host__ __device__ constexpr int join_waves_per_simd(bool staged, int shape, in
   return staged && !join_slim(shape, ksteps) ? 2 : 3;
 }
 
+// Few nodes: all of them by the build for any shape, one launch that fills and empties a staging
+// area instead of three.  Six iterations, three launches / one, microseconds: 17,000 x 128 879 /
+// 819; 30,000 x 100 1357 / 1281; 60,000 x 128 1707 / 1730; with three wavefronts per SIMD in
+// that build: 30,000 x 64 1094 / 995; 60,000 x 96 1660 / 1571; 130,000 x 64 2955 / 2887; 400,000 x
+// 64 8857 / 8764; 900,000 x 96 22,625 / 22,557.
+__host__ __device__ constexpr int64_t one_shape_nodes(int ksteps) {
+  return join_slim(0, ksteps) ? 1 << 20 : 1 << 15;
+}
+
 template <int KSTEPS, bool FCODE, bool MERGE, bool STAGED, bool LEAN = false, int SHAPE = 0>
 __global__ __launch_bounds__(join_waves(STAGED, SHAPE, KSTEPS) * kWave)
 __attribute__((amdgpu_waves_per_eu(join_waves_per_simd(STAGED, SHAPE, KSTEPS),
@@ -824,14 +833,16 @@ __global__ __launch_bounds__(kRcBlock) void k_result_csr(int64_t n, int bucket_t
 }
 
 // The nodes that have something to evaluate, listed by shape.
-__global__ __launch_bounds__(256) void k_join_shapes(int64_t n, int merge_mode,
+// `one_shape`: all of them in the list of shape 0.
+__global__ __launch_bounds__(256) void k_join_shapes(int64_t n, int merge_mode, int one_shape,
                                                      const int32_t* __restrict__ cnew,
                                                      const int32_t* __restrict__ cold,
                                                      int32_t* nodes, uint32_t* count) {
   list_nodes_by_class<kJoinShapes, 4>(n, nodes, count, [&](int64_t s) {
     const int nn = cnew[s], no = cold[s];
     const bool do_nn = !merge_mode && nn > 1;
-    return nn > 0 && (do_nn || no > 0) ? join_list_of_shape(no <= 32 ? 1 : nn <= 32 ? 2 : 0) : -1;
+    const int shape = one_shape ? 0 : no <= 32 ? 1 : nn <= 32 ? 2 : 0;
+    return nn > 0 && (do_nn || no > 0) ? join_list_of_shape(shape) : -1;
   });
 }
 
@@ -918,8 +929,9 @@ hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode
   // flush at half-full on average: few results find their bucket's places taken
   sa.threshold = (uint32_t)(sa.nb * (kStageSlots / 2));
   // (the sampling stage has cleared the lists' lengths and the region cursors)
+  const bool one_shape = !lean && sh.p > 16 && sh.n <= one_shape_nodes(ksteps);
   k_join_shapes<<<grid_blocks((sh.n + 1023) / 1024), 256, 0, st>>>(
-      sh.n, merge_mode ? 1 : 0, ds.cnew, ds.cold, ds.cls_nodes, ds.cls_count);
+      sh.n, merge_mode ? 1 : 0, one_shape ? 1 : 0, ds.cnew, ds.cold, ds.cls_nodes, ds.cls_count);
   // persistent workgroups, one per CU (the staging area takes most of a CU's LDS); one launch
   // per shape, the common shapes first; all of them add to the same bucket regions
   auto grid_for = [&](int waves) {
@@ -928,11 +940,13 @@ hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode
   };
   const unsigned grid_slim = grid_for(kStagedWavesSlim);
 #define GNND_K(K)                                                                                  \
+  e = hipSuccess;                                                                                  \
+  if (!one_shape)                                                                                  \
   e = lean ? launch_k<K, true, true, 1>(fcode, false, grid_slim, st, ds.shadow, ds.meta, dpad, sh, \
                                         ds, sa)                                                    \
            : launch_k<K, true, false, 1>(fcode, merge_mode, grid_slim, st, ds.shadow, ds.meta,     \
                                          dpad, sh, ds, sa);                                        \
-  if (e == hipSuccess && sh.p > 16) /* lists of up to 32 samples are all of the first shape */     \
+  if (e == hipSuccess && sh.p > 16 && !one_shape) /* p <= 16: all nodes are of the first shape */  \
     e = launch_k<K, true, false, 2>(fcode, merge_mode, grid_slim, st, ds.shadow, ds.meta, dpad,    \
                                     sh, ds, sa);                                                   \
   if (e == hipSuccess && sh.p > 16)                                                                \
