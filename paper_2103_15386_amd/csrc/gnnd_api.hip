@@ -41,7 +41,7 @@ struct Layout {
   size_t off_G, off_kth, off_snew, off_sold, off_cnew, off_cold, off_ron,
       off_roo, off_csn, off_cso, off_fwd, off_grp, off_pslot, off_deg, off_poff, off_bins,
       off_cnt, off_snap, off_aside, off_shadow, off_norms, off_flag, off_bkc, off_stg_ent,
-      off_stg_cur, off_cls_nodes, off_cls_count, off_half, total;
+      off_stg_cur, off_cls_nodes, off_cls_count, off_half, clear_end, total;
   bool extra;  // has room for the 16-bit rows of the float32 matrix-core join, the int8 rows of
                // the long join, the staging array of the int8 join beyond 2^20 nodes
 };
@@ -156,19 +156,20 @@ Layout make_layout(const gnnd_params* q, bool with_aside, bool extra = true) {
   L.off_fwd = take(sums ? n * 4 : 0);
   L.off_grp = take(sums ? (n / 32 + 1) * 8 : 0);
   L.off_pslot = take(n * 8);
-  L.off_deg = take(sample_direct(q->n, q->p) ? n * 8 : 0);  // (cleared together with pslot)
+  L.off_deg = take(sample_direct(q->n, q->p) ? n * 8 : 0);
+  L.off_cnt = take((size_t)kStripes * C_SLOTS * 8 + 8);  // (and DevState::forms)
+  L.off_flag = take(256);
+  L.clear_end = o;  // (off_pslot .. here: cleared by one launch)
   L.off_poff = take((n + 1) * 8);
   const size_t slots_per_node =
       q->update_mode == GNND_UPDATE_ALL_PAIRS ? 2 * p * (6 * p - 1) : 6 * p;
   L.off_bins = take(n * slots_per_node * 8);
-  L.off_cnt = take((size_t)kStripes * C_SLOTS * 8 + 8);  // (and DevState::forms)
   L.off_snap = take((size_t)kStripes * C_SLOTS * 8);
   L.off_aside = take(with_aside ? n * (k / 2) * 8 : 0);
   const bool shadow = mfma_possible(q) || (extra && long_i8_possible(q));
   L.off_shadow = take(shadow ? n * (size_t)((q->d + 31) & ~31) : 0);
   const bool gram = gram_possible(q), half = extra && half_possible(q);
   L.off_norms = take(q->metric == GNND_COSINE_F32 || gram ? n * 4 : 0);  // squared norms
-  L.off_flag = take(256);
   L.off_bkc = take(2 * 4096 * 4);
   const bool staged = stage_possible(q, extra);
   // the results the int8 join stages, or the 16-bit rows: a context has one of the two joins
@@ -299,14 +300,9 @@ int init_ctx(gnnd_ctx* c, const gnnd_params* prm, const Layout& L, const void* v
   c->prof_count = 0;
   c->prof_missed = 0;
   bind(c, L);
-  // the statistics counters start at zero, and so do the reverse degrees; the slot words read
-  // "nothing received" until the first sampling stage writes them
-  const size_t to_clear = sample_direct(prm->n, prm->p)
-                              ? (L.off_deg - L.off_pslot) / 4 + 2 * (size_t)prm->n
-                              : 2 * (size_t)prm->n;
-  hipError_t e = launch_zero_u32((uint32_t*)c->ds.pslot, to_clear, c->stream);
-  if (e == hipSuccess)
-    e = launch_zero_u32((uint32_t*)c->ds.counters, ((size_t)kStripes * C_SLOTS + 1) * 2, c->stream);
+  // the statistics counters start at zero, and so do the reverse degrees and the flags; the slot
+  // words read "nothing received" until the first sampling stage writes them
+  hipError_t e = launch_zero_u32((uint32_t*)c->ds.pslot, (L.clear_end - L.off_pslot) / 4, c->stream);
   if (e != hipSuccess) return hip_fail(nullptr, e, "clearing workspace counters");
   // matrix-core path: build the int8 copy; float data qualifies only when every
   // value is an integer in 0..255 (then all distances are exact either way)
@@ -317,8 +313,7 @@ int init_ctx(gnnd_ctx* c, const gnnd_params* prm, const Layout& L, const void* v
                        (prm->metric == GNND_L2SQ_U8 || (own_context && !is_capturing(c->stream)));
   if (long_i8 || (mfma_possible(prm) && (may_sync || prm->metric == GNND_L2SQ_U8))) {
     int bad = 0;
-    e = launch_zero_u32((uint32_t*)c->flag_dev, 1, c->stream);
-    if (e == hipSuccess) e = launch_pack_i8(c->sh, c->ds, c->flag_dev, c->stream);
+    e = launch_pack_i8(c->sh, c->ds, c->flag_dev, c->stream);
     if (prm->metric != GNND_L2SQ_U8) {  // bytes always fit; floats have to be looked at
       if (e == hipSuccess)
         e = hipMemcpyAsync(&bad, c->flag_dev, sizeof bad, hipMemcpyDeviceToHost, c->stream);
@@ -336,8 +331,7 @@ int init_ctx(gnnd_ctx* c, const gnnd_params* prm, const Layout& L, const void* v
   if (prm->metric == GNND_COSINE_F32 || (c->use_gram && !own_norms)) {
     float* norms = reinterpret_cast<float*>(static_cast<char*>(prm->workspace_dev) + L.off_norms);
     c->sh.norms = norms;
-    e = launch_row_norms(c->sh, norms, c->stream);
-    if (e == hipSuccess && c->use_gram) e = launch_gram_norms(c->sh, c->ds, c->stream);
+    e = launch_row_norms(c->sh, norms, c->use_gram ? c->ds.meta : nullptr, c->stream);
     if (e != hipSuccess) return hip_fail(nullptr, e, "row norm kernels");
   }
   if (c->use_gram && c->ds.half_rows) {

@@ -556,7 +556,8 @@ hipError_t launch_zero_u32(uint32_t* p, size_t count, hipStream_t st) {
 // order (what the cosine distance divides by).  A wavefront takes 64 rows: chunks
 // of kEvalChunk dimensions go through LDS with coalesced reads (8 lanes per row
 // chunk), then each lane adds up its own row.
-__global__ __launch_bounds__(kBlock) void k_row_norms(VecSrc vs, int64_t n, float* norms) {
+__global__ __launch_bounds__(kBlock) void k_row_norms(VecSrc vs, int64_t n, float* norms,
+                                                      NodeMeta* meta) {
   __shared__ float tile[kWavesPerBlock][64 * kEvalStride];
   const int lane = lane_id();
   float* my = tile[wave_id()];
@@ -590,13 +591,16 @@ __global__ __launch_bounds__(kBlock) void k_row_norms(VecSrc vs, int64_t n, floa
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  if (row0 + lane < n) norms[row0 + lane] = acc;
+  if (row0 + lane < n) {
+    norms[row0 + lane] = acc;
+    if (meta) meta[row0 + lane].norm = (int32_t)__float_as_uint(acc);
+  }
 }
 
-hipError_t launch_row_norms(const Shape& sh, float* norms, hipStream_t st) {
+hipError_t launch_row_norms(const Shape& sh, float* norms, NodeMeta* meta, hipStream_t st) {
   const int64_t waves = (sh.n + 63) / 64;
   k_row_norms<<<grid_blocks((waves + kWavesPerBlock - 1) / kWavesPerBlock), kBlock, 0, st>>>(
-      vec_src(sh), sh.n, norms);
+      vec_src(sh), sh.n, norms, meta);
   return hipGetLastError();
 }
 

@@ -28,12 +28,6 @@ __global__ __launch_bounds__(256) void k_gram_classify(int64_t n, int merge_mode
   });
 }
 
-__global__ __launch_bounds__(256) void k_gram_norms(int64_t n, const float* __restrict__ norms,
-                                                    NodeMeta* meta) {
-  const int64_t s = block_linear() * 256 + threadIdx.x;
-  if (s < n) meta[s].norm = (int32_t)__float_as_uint(norms[s]);
-}
-
 // The 16-bit copies of the rows (see HalfRows): one wavefront per row.  A float16 quotient has
 // a relative error of at most 2^-11; what counts is the norm of all errors of a row together,
 // which is measured here (the largest over all rows goes to `rho`, as float bits).
@@ -109,17 +103,10 @@ int compute_units() {
 
 }  // namespace
 
-hipError_t launch_gram_norms(const Shape& sh, const DevState& ds, hipStream_t st) {
-  static_assert(sizeof(NodeMeta) == 8 && offsetof(NodeMeta, kth) == 0 && offsetof(NodeMeta, norm) == 4,
-                "k_join_gram reads a NodeMeta as (kth, norm bits)");
-  k_gram_norms<<<grid_blocks((sh.n + 255) / 256), 256, 0, st>>>(sh.n, sh.norms, ds.meta);
-  return hipGetLastError();
-}
-
 hipError_t launch_half_rows(const Shape& sh, const DevState& ds, hipStream_t st) {
   VecSrc vs{sh.vec_a, sh.vec_b, sh.split, sh.d, sh.norms};
-  hipError_t e = launch_zero_u32(ds.half_info, 1, st);
-  if (e != hipSuccess) return e;
+  static_assert(sizeof(NodeMeta) == 8 && offsetof(NodeMeta, kth) == 0 && offsetof(NodeMeta, norm) == 4,
+                "k_join_gram reads a NodeMeta as (kth, norm bits)");
   auto* const kernel = sh.metric == kCosineF32 ? k_half_rows<false> : k_half_rows<true>;
   kernel<<<grid_blocks((sh.n + 31) / 32), 256, 0, st>>>(
       vs, sh.n, static_cast<_Float16*>(ds.half_rows), (int)half_row_elems(sh.d), ds.meta,

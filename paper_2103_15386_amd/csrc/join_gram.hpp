@@ -280,7 +280,7 @@ __device__ __forceinline__ bool gram_node(GramLds& S, float* tile, const VecSrc&
   const float least_sum = (float)d * kLeastNormal;
   {
     // one 8-byte record per sample: the threshold of its list and its squared norm
-    // (launch_gram_norms put the float's bits where the int8 join keeps its integer norm)
+    // (k_row_norms or k_half_rows put the float's bits where the int8 join keeps its integer norm)
     // (an empty list place: a norm of 1, which is not special)
     const uint2 none = make_uint2(0u, 0x3f800000u);
     const uint2 mn = idn >= 0 ? *reinterpret_cast<const uint2*>(&meta[idn]) : none;

@@ -183,16 +183,15 @@ inline dim3 grid_blocks(int64_t blocks) {
 }
 
 hipError_t launch_init_random(const Shape& sh, const DevState& ds, uint64_t seed, hipStream_t st);
-// squared norms of all rows, one fused multiply-add per dimension in dimension order
-hipError_t launch_row_norms(const Shape& sh, float* norms, hipStream_t st);
+// squared norms of all rows, one fused multiply-add per dimension in dimension order; with `meta`
+// also into the nodes' records (the float's bits in `norm`), where the float32 matrix-core join
+// reads them
+hipError_t launch_row_norms(const Shape& sh, float* norms, NodeMeta* meta, hipStream_t st);
 hipError_t launch_sample(const Shape& sh, const DevState& ds, uint64_t seed, uint32_t iter,
                          hipStream_t st);
 hipError_t launch_join(const Shape& sh, const DevState& ds, int path, bool merge_mode,
                        hipStream_t st);
-// The float32 matrix-core join reads a sample's squared norm from its NodeMeta record (bits of
-// the float in `norm`): copied there from sh.norms once the join path is chosen.
-hipError_t launch_gram_norms(const Shape& sh, const DevState& ds, hipStream_t st);
-// The 16-bit copies of the rows into ds.half_rows, and (cosine: not; sh.norms must be set) the
+// The 16-bit copies of the rows into ds.half_rows (ds.half_info is 0 before), and (cosine: not; sh.norms must be set) the
 // squared norms in the NodeMeta records
 hipError_t launch_half_rows(const Shape& sh, const DevState& ds, hipStream_t st);
 // float32 vectors, metrics that are functions of an inner product and the norms (sh.norms
@@ -201,8 +200,8 @@ hipError_t launch_join_gram(const Shape& sh, const DevState& ds, bool merge_mode
 // results are staged per bucket when ds.stg_ent is set, handed on one by one otherwise;
 // `after_join` (may be NULL) is recorded behind the cross-matching kernel, in front of the
 // pass that moves staged results into the destinations' segments.  `first_look`: the graph is
-// a fresh random one (first iteration) - a hint that selects a form of the staged join that
-// leaves the lists' thresholds to the second pass; same results with or without it
+// a fresh random one (first iteration), so that no node has OLD samples; selects a form of the
+// staged join that leaves the lists' thresholds to the second pass; same results with or without it
 hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode, bool first_look,
                             hipStream_t st, hipEvent_t after_join = nullptr);
 hipError_t launch_pack_i8(const Shape& sh, const DevState& ds, int* bad_flag_dev, hipStream_t st);
