@@ -94,9 +94,12 @@ __device__ inline bool query_in_range(float norm) {
 }
 
 // Squared norms of the queries: the largest in range decides the common scale of the copies.
+// Whether a query is in range is decided here alone (`flags`, see k_pack): the rows' terms are
+// bounds only for queries whose norm is in the largest one, and k_pack's sum, in another order, may
+// fall on the other side of an end of the range.
 __global__ __launch_bounds__(256) void k_query_norms(const float* vec, int64_t n, int d,
                                                      const int32_t* queries, int64_t nq,
-                                                     SearchInfo* info) {
+                                                     SearchInfo* info, uint8_t* flags) {
   __shared__ uint32_t most;
   if (threadIdx.x == 0) most = 0u;
   __syncthreads();
@@ -109,7 +112,10 @@ __global__ __launch_bounds__(256) void k_query_norms(const float* vec, int64_t n
     for (int j = lane; j < d; j += kWave) s = __fmaf_rn(row[j], row[j], s);
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) s += __uint_as_float(xor_lanes(__float_as_uint(s), o, lane));
-    if (lane == 0 && query_in_range(s)) atomicMax(&most, __float_as_uint(s));
+    if (lane == 0) {
+      flags[q] = query_in_range(s) ? 0 : 1;
+      if (query_in_range(s)) atomicMax(&most, __float_as_uint(s));
+    }
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -159,8 +165,8 @@ __device__ inline float row_slack(float a, float ea, float b, float eb, float ha
 
 // Copies of 16 rows per wavefront.  Lane (r, g) = (lane % 16, lane / 16) holds bytes 16 g .. of
 // every 64-byte piece of row r's copy: 8 dimensions of 32 as float16, 16 of 64 as int8.
-// QUERY: the rows are those of queries[0..count); `flags` tells queries out of range (1) and ids
-// that are no node (2).
+// QUERY: the rows are those of queries[0..count); `flags` tells queries out of range (1; of float
+// vectors as k_query_norms has left it) and ids that are no node (2).
 template <int METRIC, int CH, bool QUERY>
 __global__ __launch_bounds__(256) void k_pack(const void* vec, int64_t n, int d,
                                               const int32_t* queries, int64_t count,
@@ -256,7 +262,7 @@ __global__ __launch_bounds__(256) void k_pack(const void* vec, int64_t n, int d,
       scale = usable ? kUnitScale / sqrtf(norm) : 0.f;
       lost = !usable && norm != 0.f;  // (norm 0: at distance 1 from everything, a score of 0)
     }
-    if (QUERY) lost = !query_in_range(norm);
+    if (QUERY) lost = lost || (have && flags[at] == 1);
     float err = 0.f;
     f16x8 h[CH];
     bool finite = true;
@@ -679,7 +685,7 @@ hipError_t search(const void* vec, int64_t n, int32_t d, const int32_t* queries,
   auto* const cand = reinterpret_cast<uint32_t*>(ws + L.off_cand);
   if (METRIC != kL2U8)
     k_query_norms<<<kNormParts, 256, 0, st>>>(static_cast<const float*>(vec), n, d, queries, nq,
-                                              info);
+                                              info, flags);
   const int64_t q_blocks = L.q_padded / 16, r_blocks = L.row_tiles * kRB;
   k_pack<METRIC, CH, true><<<(unsigned)((q_blocks + 3) / 4), 256, 0, st>>>(
       vec, n, d, queries, nq, q_blocks, qfrag, lower, upper, info, flags);

@@ -79,6 +79,62 @@ def test_scan_on_data_its_bounds_do_not_suit(metric, name):
     assert torch.equal(got[1].view(torch.int32), want[1].view(torch.int32))
 
 
+def _norm_in_parts(v, parts):
+    """Squared norm in float32: every part (a list of dimensions) by itself, one fused multiply-add
+    per dimension, then the parts' sums in pairs."""
+    sums = np.zeros((len(v), len(parts)), np.float32)
+    for i in range(len(parts[0])):
+        x = v[:, [p[i] for p in parts]].astype(np.float64)
+        sums = (x * x + sums).astype(np.float32)
+    while sums.shape[1] > 1:
+        sums = sums[:, 0::2] + sums[:, 1::2]
+    return sums[:, 0]
+
+
+def _at_the_end_of_the_range(rng):
+    """64 dimensions of 11 significant bits (exact as float16) whose squared norm is just above 2^60
+    or just not, as it is added up over the lanes of a wavefront or over groups of eight
+    dimensions."""
+    lanes = [[j] for j in range(64)]
+    groups = [[c * 32 + g * 8 + e for c in range(2) for e in range(8)] for g in range(4)]
+    while True:
+        a = 2048 + rng.integers(-150, 150, 64)
+        a = np.where(a > 2048, a & ~1, a)
+        for j in np.nonzero(a < 2000)[0]:
+            a[j] += np.clip(-((a * a).sum() - (1 << 28)) // (2 * a[j]), -40, 40)
+        low = np.nonzero(a < 2046)[0]
+        off = (a * a).sum() - (1 << 28)  # one up and one down moves it by twice their difference
+        pairs = np.argwhere(2 * (a[low][:, None] - a[low][None, :]) + 2 + off == rng.integers(1, 32))
+        if len(pairs) == 0 or pairs[0][0] == pairs[0][1]:
+            continue
+        a[low[pairs[0][0]]] += 1
+        a[low[pairs[0][1]]] -= 1
+        v = (a * 65536.0).astype(np.float32)[None]
+        if _norm_in_parts(v, lanes)[0] > 2.0 ** 60 >= _norm_in_parts(v, groups)[0]:
+            return v[0]
+
+
+@pytest.mark.parametrize("seed", [1, 2, 3, 4])
+def test_scan_query_at_the_end_of_the_range(seed):
+    """A query whose squared norm is in the bounds' range or not as it is summed, all others a
+    thousand times shorter: either it takes part and its length counts, or it does not.  Ten rows
+    lie a little nearer to it than two hundred others, but their copies are rounded the other way,
+    by all of their length."""
+    rng = np.random.default_rng(seed)
+    far = _at_the_end_of_the_range(rng)
+    x = rng.standard_normal((16000, 64)).astype(np.float32)
+    x *= 2.0 ** 19.5 / np.linalg.norm(x, axis=1, keepdims=True)
+    ulp = np.where(far < 2.0 ** 27, 65536.0, 131072.0).astype(np.float32)
+    x[400] = far
+    x[1001:1200] = far - (0.45 + 0.01 * rng.random((199, 1), np.float32)) * ulp
+    x[3001:3011] = far + (0.40 + 0.01 * rng.random((10, 1), np.float32)) * ulp
+    q = torch.arange(0, 16000, 25, dtype=torch.int32, device="cuda")
+    q[40:48] = q[60:68]  # (the rows around it are no queries: it is the only long one)
+    got, want = _both(torch.from_numpy(x).cuda(), q, 10, og.L2SQ_F32)
+    assert sorted(want[0][16].tolist()) == list(range(3001, 3011))
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
 def test_scan_query_ids():
     x = torch.from_numpy(W.uniform_f32(16000, 48, seed=417)).cuda()
     q = torch.arange(0, 16000, 25, dtype=torch.int32, device="cuda")
