@@ -135,6 +135,34 @@ def test_scan_query_at_the_end_of_the_range(seed):
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
 
 
+@pytest.mark.parametrize("metric,n,d,nq,K,by_class", [
+    (og.L2SQ_F32, 20000, 20, 4096, 64, False), (og.L2SQ_U8, 20000, 96, 4096, 64, False),
+    (og.ANGULAR_F32, 40000, 33, 5000, 64, False), (og.COSINE_F32, 17000, 8, 4097, 50, False),
+    (og.L2SQ_F32, 60000, 48, 600, 10, True), (og.L2SQ_U8, 60000, 96, 600, 32, True),
+])
+def test_scan_leaves_no_query_over(metric, n, d, nq, K, by_class):
+    """Many candidates per workgroup (thousands of queries, large K; rows in the order of their
+    components, queries side by side): only a query's own list is a limit."""
+    import paper_2103_15386_amd as amd
+    lib = amd.load_library()
+    x = W.uniform_f32(n, d, seed=421)
+    if by_class:
+        x = np.repeat(W.uniform_f32(n // 1000, d, seed=422), 1000, 0) + 0.2 * x
+    if metric == og.L2SQ_U8:
+        x = (x * 200).astype(np.uint8)
+    x = torch.from_numpy(x).cuda()
+    q = torch.arange(nq, dtype=torch.int32, device="cuda")
+    _, want = _both(x, q, K, metric)
+    ws = torch.empty(int(lib.gnnd_exact_knn_workspace_bytes(n, d, metric, nq, K)),
+                     dtype=torch.uint8, device="cuda")
+    ids, dist = torch.empty_like(want[0]), torch.empty_like(want[1])
+    assert lib.gnnd_exact_knn_ws(x.data_ptr(), n, d, metric, q.data_ptr(), nq, K, ids.data_ptr(),
+                                 dist.data_ptr(), ws.data_ptr(), ws.numel(),
+                                 torch.cuda.current_stream().cuda_stream) == 0
+    assert torch.equal(ids, want[0]) and torch.equal(dist, want[1])
+    assert int((ws[:nq] != 0).sum()) == 0  # (the workspace begins with a byte per query)
+
+
 def test_scan_query_ids():
     x = torch.from_numpy(W.uniform_f32(16000, 48, seed=417)).cuda()
     q = torch.arange(0, 16000, 25, dtype=torch.int32, device="cuda")
