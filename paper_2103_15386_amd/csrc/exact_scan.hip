@@ -31,6 +31,7 @@
 // not suit (distances small against the lengths, thousands of copies of a vector) cost the first
 // scan on top: 500 x 200,000 x 48, vectors 30 standard deviations off the origin, 0.69 -> 0.76 ms.
 #include <cfloat>
+#include <type_traits>
 
 #include "device_utils.hpp"
 #include "kernels.hpp"
@@ -63,6 +64,8 @@ constexpr float kUnitScale = 256.f;  // cosine: the length of a copy
 struct SearchInfo {
   uint32_t norm_max[kNormParts];  // largest squared norm of a query (float bits), in parts
   uint32_t query_err;             // largest error of a query's copy (float bits)
+  uint32_t no_number;             // a row holds a NaN: it is at no distance from any query, and what
+                                  // order that gives is for k_exact_knn to say, so nothing is scanned
 };
 
 template <int METRIC>
@@ -120,7 +123,7 @@ __global__ __launch_bounds__(256) void k_query_norms(const float* vec, int64_t n
   __syncthreads();
   if (threadIdx.x == 0) {
     info->norm_max[blockIdx.x] = most;
-    if (blockIdx.x == 0) info->query_err = 0u;
+    if (blockIdx.x == 0) info->query_err = info->no_number = 0u;
   }
 }
 
@@ -299,6 +302,7 @@ __global__ __launch_bounds__(256) void k_pack(const void* vec, int64_t n, int d,
       const float inf = __uint_as_float(0x7f800000u);
       float lo = -inf, hi = -inf;  // places behind the last row
       if (have) {
+        if (norm != norm) atomicOr(&info->no_number, 1u);
         const float ea = __uint_as_float(info->query_err);
         const float unit = METRIC == kCosineF32 ? kUnitScale : a0 * common;
         const float a = unit * 1.001f + ea;
@@ -336,7 +340,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     const uint4* __restrict__ rows, const typename ScoreOf<METRIC>::type* __restrict__ term,
     int64_t tiles, int step, int strips, int qgroups, int64_t n, const uint4* __restrict__ qfrag,
     const int32_t* __restrict__ queries, typename ScoreOf<METRIC>::type* bound, uint32_t* found,
-    uint32_t* cand) {
+    uint32_t* cand, const SearchInfo* __restrict__ info) {
+  if (METRIC != kL2U8 && !COLLECT && info->no_number) return;  // (the second scan: no query has a bound)
   using T = typename ScoreOf<METRIC>::type;
   using V = typename ScoreOf<METRIC>::vec;
   __shared__ uint4 tile[2][kRB * CH * kWave];
@@ -491,14 +496,18 @@ __global__ __launch_bounds__(256) void k_threshold(const T* __restrict__ best, i
                                                    const T* __restrict__ upper,
                                                    const uint8_t* __restrict__ flags, int64_t nq,
                                                    int64_t padded, int K, T* bound,
-                                                   uint32_t* found) {
+                                                   uint32_t* found,
+                                                   const SearchInfo* __restrict__ info) {
   const int64_t q = (int64_t)blockIdx.x * 4 + wave_id();
   if (q >= padded) return;
   const int lane = lane_id();
   const bool on = q < nq && flags[q] == 0;
   T result = score_never(T{});
   uint32_t given_up = 0u;
-  if (on) {
+  constexpr bool kFloat = std::is_same<T, float>::value;
+  if (kFloat && info->no_number) {  // (a query that is no node has no candidates: see k_pick)
+    given_up = on ? (uint32_t)kCap + 1u : 0u;
+  } else if (on) {
     const int groups = strips * 16;
     const uint32_t id = (uint32_t)queries[q], tile = id / kTileRows;
     const int own = tile % (uint32_t)step != 0u
@@ -711,15 +720,16 @@ hipError_t search(const void* vec, int64_t n, int32_t d, const int32_t* queries,
     const uint4* const qf = qfrag + s0 / 16 * CH * kWave;
     const int few = first_strips(tiles, groups);
     k_scan<METRIC, CH, false><<<(unsigned)((few + 7) / 8 * 8 * groups), 256, 0, st>>>(
-        rows, lower, tiles, step, few, groups, n, qf, queries + s0, best, found, cand);
+        rows, lower, tiles, step, few, groups, n, qf, queries + s0, best, found, cand, info);
     k_threshold<T, typename ScoreOf<METRIC>::vec><<<(unsigned)((padded + 3) / 4), 256, 0, st>>>(
-        best, few, step, queries + s0, lower, upper, flags + s0, here, padded, K, bound, found);
+        best, few, step, queries + s0, lower, upper, flags + s0, here, padded, K, bound, found,
+        info);
     int64_t strips = 1024 / groups & ~7;
     strips = strips < 8 ? 8 : strips;
     strips = strips < L.row_tiles ? strips : L.row_tiles;
     k_scan<METRIC, CH, true><<<(unsigned)((strips + 7) / 8 * 8 * groups), 256, 0, st>>>(
         rows, upper, L.row_tiles, 1, (int)strips, groups, n, qf, queries + s0, bound, found,
-        cand);
+        cand, info);
     k_pick<METRIC><<<(unsigned)here, 256, 0, st>>>(
         vec, n, d, queries + s0, flags + s0, found, cand, K, ids_out + s0 * K,
         static_cast<char*>(dist_out) + s0 * K * 4);

@@ -170,6 +170,10 @@ def test_scan_query_ids():
     got, want = _both(x, q, 64, og.L2SQ_F32)
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
     assert (got[0][5] == -1).all() and torch.equal(got[0][7], got[0][8])
+    x[15998, 47] = float("nan")  # (its order among the others is the general form's to decide)
+    got, want = _both(x, q, 64, og.L2SQ_F32)
+    assert torch.equal(got[0], want[0]) and (got[0][5:7] == -1).all()
+    assert torch.equal(got[1].view(torch.int32), want[1].view(torch.int32))
 
 
 def test_scan_under_capture():
