@@ -362,8 +362,8 @@ int gnnd_exact_knn(const void* vectors_dev, int64_t n, int32_t d, int32_t metric
  * 16 bits (bytes: 8) and the matrix cores turn most pairs away, the distances of
  * the rest are evaluated as above.  gnnd_exact_knn_workspace_bytes() = the bytes
  * it takes for such a call; 0 where the form above is the faster one or the only
- * one (few rows or queries, more than 128 dimensions, the chi-square distance,
- * arguments out of range).  workspace_dev: device memory, 256-byte aligned, free
+ * one (few rows, or few queries or a small K among few rows; more than 128
+ * dimensions, the chi-square distance, arguments out of range).  workspace_dev: device memory, 256-byte aligned, free
  * again once the work enqueued on `stream` is done; with NULL or fewer bytes this
  * is gnnd_exact_knn. */
 size_t gnnd_exact_knn_workspace_bytes(int64_t n, int32_t d, int32_t metric, int64_t nq,

@@ -335,23 +335,11 @@ hipError_t launch(const void* vec, int64_t n, int32_t d, const int32_t* queries,
   return hipGetLastError();
 }
 
-// Queries per workgroup: one workgroup fills a CU and reads all rows once, so the time is the
-// number of rounds of 256 workgroups times what a round takes - Q distances per row plus
-// moving the row through LDS, about as much as two.
 template <int METRIC>
 hipError_t launch_metric(const void* vec, int64_t n, int32_t d, const int32_t* queries, int64_t nq,
                          int32_t K, int32_t* ids_out, void* dist_out, hipStream_t st,
                          const uint8_t* only) {
-  int q = 1;
-  int64_t least = INT64_MAX;
-  for (int c = 1; c <= 8; c *= 2) {
-    const int64_t rounds = ((nq + c - 1) / c + 255) / 256, cost = rounds * (c + 2);
-    if (cost < least) {
-      least = cost;
-      q = c;
-    }
-  }
-  switch (q) {
+  switch (exact_queries(nq)) {
     case 1: return launch<METRIC, 1>(vec, n, d, queries, nq, K, ids_out, dist_out, st, only);
     case 2: return launch<METRIC, 2>(vec, n, d, queries, nq, K, ids_out, dist_out, st, only);
     case 4: return launch<METRIC, 4>(vec, n, d, queries, nq, K, ids_out, dist_out, st, only);

@@ -759,16 +759,27 @@ hipError_t search_metric(const void* vec, int64_t n, int32_t d, const int32_t* q
 
 }  // namespace
 
-// The line between the two forms: this one takes about 60 us for its nine launches however small
-// the call, k_exact_knn a time in proportion to rows x dimensions (few queries: a workgroup each)
-// or to queries x rows x dimensions.  In microseconds, this form / k_exact_knn: 12,000 x 20, 1000
-// queries 76 / 110, 300 queries 81 / 68; 25,000 x 20, 100 queries 76 / 66; 25,000 x 96, 16 queries
-// 67 / 164; 6000 x 96, 2000 queries 88 / 104; 3000 x 96, 2000 queries 88 / 72.
-size_t exact_scan_bytes(int64_t n, int32_t d, int32_t metric, int64_t nq) {
+// The line between the two forms: this one takes 35 to 60 us for its eight launches (bytes: seven;
+// four more per further 4096 queries) however small the call, k_exact_knn 7 to 11 us times `work`
+// here: rows, dimensions and rounds of workgroups count, and K, whose best it keeps per
+// query and wavefront (bytes: rows of a multiple of 16 bytes are read four dimensions at a time).
+// A pass among others in microseconds, this form / k_exact_knn, `work` in parentheses: 10,325 x 20,
+// 1000 queries, squared L2: K = 1 42 / 31 (2.7), K = 10 43 / 43 (4.1), K = 64 48 / 86 (12.8); 6000 x
+// 96, 1000 queries, bytes: K = 1 39 / 26 (1.8), K = 10 40 / 37 (3.2), K = 64 44 / 66 (11.9); 24,577 x
+// 96, 16 queries 44 / 152 (13).  Of 2400 calls just above the second line - n from one to 3.5 times
+// it, 4 to 128 dimensions, 16 to 4096 queries, K from 1 to 64, three metrics - 135 were slower in
+// this form, by up to 83 %, with that line alone; now 19, by up to 14 %, and 39 that it would have
+// taken in less time, a seventh on average, are left to the other.
+size_t exact_scan_bytes(int64_t n, int32_t d, int32_t metric, int64_t nq, int32_t K) {
   if (metric == kChi2F32 || d > 128 || n < 6000 || n > ((int64_t)1 << 27) || nq < 1 ||
       nq > ((int64_t)1 << 27))
     return 0;
   if (n * (nq < 256 ? 256 : nq) < ((int64_t)1 << 29) / (d + 32)) return 0;
+  const int c = exact_queries(nq);
+  const int64_t words = metric != kL2U8 ? d : d % 16 == 0 ? d / 4 : d + 32;
+  const double work =
+      (double)exact_rounds(nq, c) * ((double)((c + 4) * n * (words + 12)) / (1 << 20) + 0.04 * c * K);
+  if (work < 4.5) return 0;
   return search_layout(n, d, metric, nq).total;
 }
 

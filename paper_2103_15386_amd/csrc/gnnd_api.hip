@@ -1284,7 +1284,7 @@ size_t gnnd_exact_knn_workspace_bytes(int64_t n, int32_t d, int32_t metric, int6
   if (metric < GNND_L2SQ_F32 || metric > GNND_COSINE_F32 || n < 2 || n > ((int64_t)1 << 30) ||
       d < 1 || nq < 0 || K < 1 || K > 64)
     return 0;
-  return exact_scan_bytes(n, d, metric, nq);
+  return exact_scan_bytes(n, d, metric, nq, K);
 }
 
 int gnnd_exact_knn_ws(const void* vec, int64_t n, int32_t d, int32_t metric,
@@ -1299,7 +1299,7 @@ int gnnd_exact_knn_ws(const void* vec, int64_t n, int32_t d, int32_t metric,
   if ((uintptr_t)vec & 15) return fail(nullptr, GNND_EINVAL, "vectors must be 16-byte aligned");
   if ((uintptr_t)workspace & 255)
     return fail(nullptr, GNND_EINVAL, "workspace must be 256-byte aligned");
-  const size_t need = exact_scan_bytes(n, d, metric, nq);
+  const size_t need = exact_scan_bytes(n, d, metric, nq, K);
   const bool scan = need != 0 && workspace && workspace_bytes >= need;
   hipError_t e = scan ? launch_exact_scan(vec, n, d, metric, queries, nq, K, ids_out, dist_out,
                                           workspace, (hipStream_t)stream)

@@ -258,10 +258,22 @@ hipError_t launch_merge_final_wide(const Shape& sh, const DevState& ds, const Me
 hipError_t launch_exact_knn(const void* vec, int64_t n, int32_t d, int32_t metric,
                             const int32_t* queries, int64_t nq, int32_t K, int32_t* ids_out,
                             void* dist_out, hipStream_t st, const uint8_t* only = nullptr);
+// Queries per workgroup of k_exact_knn: one workgroup fills a CU and reads all rows once, so the
+// time is the number of rounds of 256 workgroups times what a round takes - Q distances per row
+// plus moving the row through LDS, about as much as two.
+inline int exact_rounds(int64_t nq, int queries) {
+  return (int)(((nq + queries - 1) / queries + 255) / 256);
+}
+inline int exact_queries(int64_t nq) {
+  int best = 1;
+  for (int c = 2; c <= 8; c *= 2)
+    if ((int64_t)exact_rounds(nq, c) * (c + 2) < (int64_t)exact_rounds(nq, best) * (best + 2)) best = c;
+  return best;
+}
 // The same results with the matrix cores turning rows away (exact_scan.hip), in a workspace of
 // exact_scan_bytes() bytes; 0: this form does not take such a call.  (launch_exact_knn answers the
 // queries it leaves over: those with only[q] == 1.)
-size_t exact_scan_bytes(int64_t n, int32_t d, int32_t metric, int64_t nq);
+size_t exact_scan_bytes(int64_t n, int32_t d, int32_t metric, int64_t nq, int32_t K);
 hipError_t launch_exact_scan(const void* vec, int64_t n, int32_t d, int32_t metric,
                              const int32_t* queries, int64_t nq, int32_t K, int32_t* ids_out,
                              void* dist_out, void* workspace, hipStream_t st);

@@ -35,10 +35,10 @@ def _both(x, q, K, metric):
 
 @pytest.mark.parametrize("metric", list(GEN))
 @pytest.mark.parametrize("n,d,nq,K", [
-    (6016, 128, 600, 10), (6017, 97, 700, 1), (6079, 96, 769, 64), (6080, 65, 1023, 10),
-    (6081, 64, 1025, 33), (7000, 63, 900, 10), (9000, 33, 1000, 7), (9001, 32, 1000, 10),
+    (6016, 128, 600, 20), (6017, 97, 700, 1), (6079, 96, 769, 64), (6080, 65, 1023, 10),
+    (6081, 64, 1025, 33), (7000, 63, 900, 10), (9000, 33, 1000, 10), (9001, 32, 1000, 20),
     (9000, 31, 1000, 64), (20000, 127, 257, 10), (20001, 76, 256, 64), (40000, 20, 300, 5),
-    (20000, 4, 4100, 10), (16400, 128, 3, 10),
+    (20000, 4, 4100, 10), (16400, 128, 3, 32),
 ])
 def test_scan_equals_brute_force(metric, n, d, nq, K):
     x = GEN[metric](n, d)
@@ -161,6 +161,21 @@ def test_scan_leaves_no_query_over(metric, n, d, nq, K, by_class):
                                  torch.cuda.current_stream().cuda_stream) == 0
     assert torch.equal(ids, want[0]) and torch.equal(dist, want[1])
     assert int((ws[:nq] != 0).sum()) == 0  # (the workspace begins with a byte per query)
+
+
+def test_scan_takes_what_it_is_faster_for():
+    """Sizes at which either form was clearly the faster one."""
+    import paper_2103_15386_amd as amd
+    need = amd.load_library().gnnd_exact_knn_workspace_bytes
+    for n, d, metric, nq, K in [(14914, 4, og.L2SQ_F32, 1000, 1), (10325, 20, og.L2SQ_F32, 1000, 1),
+                                (6711, 48, og.L2SQ_U8, 1000, 1), (26215, 48, og.L2SQ_U8, 16, 5),
+                                (6000, 96, og.L2SQ_U8, 1000, 1), (13108, 128, og.L2SQ_U8, 16, 10),
+                                (3000, 96, og.L2SQ_F32, 2000, 10)]:
+        assert need(n, d, metric, nq, K) == 0
+    for n, d, metric, nq, K in [(14914, 4, og.L2SQ_F32, 1000, 64), (10325, 20, og.L2SQ_F32, 1000, 64),
+                                (6000, 96, og.L2SQ_U8, 1000, 64), (24577, 96, og.L2SQ_F32, 16, 1),
+                                (10**6, 96, og.ANGULAR_F32, 16, 10), (10**6, 96, og.L2SQ_U8, 2000, 64)]:
+        assert need(n, d, metric, nq, K) > 0
 
 
 def test_scan_query_ids():
