@@ -749,13 +749,16 @@ int run_sharded(const gnnd_params* prm, const ShardPlan& pl, ShardStore& store,
   // (shards + m) % 2 - not in the one that holds the graph of the step before it.
   auto slot_of = [&](int m) { return (pl.shards + m) % 2; };
   auto shard_of = [&](int m, int h) { return h ? pairs[m].second : pairs[m].first; };
+  auto works_on = [&](int m, int s) {
+    return m < M && (pairs[m].first == s || pairs[m].second == s);
+  };
   // whether the step before merge m has worked on shard s (the last build comes before merge 0),
   // and then where in that step's results the shard's rows begin
   auto left_by_last = [&](int m, int s, size_t* rows_at) {
     *rows_at = 0;
     if (m == 0) return s == pl.shards - 1;
     if (s == pairs[m - 1].second) *rows_at = (size_t)rows_of(pairs[m - 1].first) * row_g;
-    return s == pairs[m - 1].first || s == pairs[m - 1].second;
+    return works_on(m - 1, s);
   };
   // What merge m needs from the host: the vectors, and the graphs that the step before it does
   // not work on.  Its slot was last read by the step before that, whose results were fetched
@@ -835,8 +838,9 @@ int run_sharded(const gnnd_params* prm, const ShardPlan& pl, ShardStore& store,
       if (rc != GNND_OK) goto done;
       GNND_HIP(hipEventRecord(ev_done[slot], comp), "hipEventRecord");
       GNND_HIP(hipStreamWaitEvent(copy, ev_done[slot], 0), "hipStreamWaitEvent");
-      // (merge 0 reads the last shard's graph where it is, and writes that shard's rows)
-      if (s + 1 < pl.shards) GNND_HIP(down_graph(slot, s, 0), "graph download");
+      // the last shard's graph stays here if merge 0 works on it: that reads it where it is and
+      // writes the shard's rows
+      if (s + 1 < pl.shards || !works_on(0, s)) GNND_HIP(down_graph(slot, s, 0), "graph download");
     }
   }
   GNND_HIP(hipEventRecord(t1, comp), "hipEventRecord");
@@ -873,7 +877,7 @@ int run_sharded(const gnnd_params* prm, const ShardPlan& pl, ShardStore& store,
     // until that has written its own
     for (int h = 0; h < 2; ++h) {
       const int s = shard_of(m, h);
-      if (m + 1 < M && (s == pairs[m + 1].first || s == pairs[m + 1].second)) continue;
+      if (works_on(m + 1, s)) continue;
       GNND_HIP(down_graph(slot, s, h ? (size_t)rows_of(sa) * row_g : 0), "merge download");
     }
   }

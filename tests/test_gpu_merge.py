@@ -126,6 +126,22 @@ def test_sharded_build_matches_oracle(metric, gen, shards, n):
     assert rec > 0.85, rec
 
 
+@pytest.mark.parametrize("shards,n,k,p", [(2, 401, 7, 5), (3, 1000, 7, 7), (5, 1503, 9, 8),
+                                          (6, 1501, 5, 5), (7, 2000, 33, 16), (8, 2047, 65, 12)])
+@pytest.mark.parametrize("metric", [og.L2SQ_U8, og.COSINE_F32])
+def test_sharded_build_hands_every_graph_over(metric, shards, n, k, p):
+    """Even and odd numbers of shards and of merges (both slots end either phase), rows of a
+    merge's second shard anywhere in its results, a last shard of another size."""
+    import paper_2103_15386_amd as amd
+    x = (W.sift_like_u8(n, 16, seed=304, n_comp=8) if metric == og.L2SQ_U8
+         else W.scaled_directions_f32(n, 16, seed=305, n_comp=5, zero_rows=1))
+    want = og.build_sharded(x, shards, k, p, metric, SEED, 3, 2)
+    ids, dist, _ = amd.gnnd_build_sharded(torch.from_numpy(x).pin_memory(), shards, k, p, metric,
+                                          SEED, 3, 2)
+    assert (ids.numpy() == want.ids).all()
+    assert (dist.numpy().astype(np.float64) == want.dist).all()
+
+
 @pytest.mark.parametrize("metric,gen,shards,n,staging", [
     (og.L2SQ_U8, lambda n: W.sift_like_u8(n, 128, seed=302, n_comp=8), 4, 4000, 1 << 20),
     (og.L2SQ_F32, lambda n: W.uniform_f32(n, 300, seed=306), 3, 3001, (1 << 20) + 4096),
