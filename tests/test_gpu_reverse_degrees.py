@@ -80,6 +80,34 @@ def test_builds_match_the_oracle_around_the_segment_rule(n, metric):
     ctx.close()
 
 
+@pytest.mark.parametrize("k,p,every", [(65, 5, False), (40, 33, False), (6, 4, True)])
+def test_builds_match_the_oracle_beyond_the_segment_rule(k, p, every):
+    """The forms of sampling and reverse selection for long lists and for every evaluated pair where
+    the forward samples are added up: a segment in a wrong place would mix two nodes' results."""
+    import paper_2103_15386_amd as amd
+    n = (1 << 18) + 33
+    x = W.uniform_f32(n, 4, seed=6)
+    ctx = amd.Gnnd(torch.from_numpy(x).cuda(), k, p, amd.L2SQ_F32, SEED, amd.JOIN_AUTO,
+                   amd.UPDATE_ALL_PAIRS if every else amd.UPDATE_SELECTIVE)
+    ctx.init_random()
+    g = og.init_random(x, k, og.L2SQ_F32, SEED)
+    for it in (1, 2):
+        ctx.step_sample()
+        got = [t.cpu().numpy() for t in ctx.samples()]
+        snew, cnew, sold, cold = og.sample(g.copy(), p, SEED, it)
+        for a, b in zip(got, (snew, cnew, sold, cold)):
+            assert (a == b).all()
+        ctx.step_join()
+        st = ctx.step_update()
+        want = og.iterate(x, og.L2SQ_F32, g, p, SEED, it, all_pairs=every)
+        assert st["dropped"] == 0
+        for key in ("inserts", "dist_evals", "sum_new", "sum_old", "proposals"):
+            assert st[key] == want[key], key
+    ids, dist = ctx.graph()
+    assert (ids.cpu().numpy() == g.ids).all() and (dist.cpu().numpy() == g.dist).all()
+    ctx.close()
+
+
 @pytest.mark.parametrize("n,k,p", [(12288, 10, 10), (12289, 10, 10), (12287, 11, 10),
                                    (4096, 32, 32), (4097, 33, 32), (2048, 128, 64), (2049, 100, 64),
                                    (1000, 70, 64), (65, 64, 40), (7, 5, 3)])
