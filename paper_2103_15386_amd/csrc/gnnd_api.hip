@@ -47,7 +47,10 @@ struct Layout {
 };
 
 constexpr int kHalfMinDim = 24;
-constexpr int64_t kStageLeastNodes = 1 << 14;  // up to here results are not staged by themselves
+// Up to here results are not staged by themselves (lists of more than 32 entries take more of them).
+constexpr int64_t stage_least_nodes(int32_t k, int32_t p) {
+  return k > 32 && p > 16 ? 11264 : 1 << 14;
+}
 
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -116,7 +119,7 @@ bool stage_possible(const gnnd_params* q, bool extra) {
 
 // Few nodes, and the library chooses: results are handed on one by one.
 bool stays_small(const gnnd_params* q) {
-  return q->join_path == GNND_JOIN_AUTO && q->n <= kStageLeastNodes;
+  return q->join_path == GNND_JOIN_AUTO && q->n <= stage_least_nodes(q->k, q->p);
 }
 
 // 16-bit copies of the vectors for the first pass of the float32 matrix-core join: from 24
@@ -253,9 +256,11 @@ void bind(gnnd_ctx* c, const Layout& L) {
   c->flag_dev = (int*)(w + L.off_flag);
   d.bk_cnt = (uint32_t*)(w + L.off_bkc);
   // (few nodes: one by one is the faster way, unless asked for; the place is kept, so that the
-  // workspace is the same.  Six iterations, staged / one by one in microseconds: 2000 x 128, p = 32:
-  // 423 / 262; 5000 x 100, 32: 657 / 501; 10,000 x 128, 32: 729 / 626; 20,000 x 100, 32: 1132 /
-  // 1109; 20,000 x 64, 16: 710 / 716; 30,000 x 100, 32: 1366 / 1469)
+  // workspace is the same.  Six iterations, staged / one by one in microseconds: k = p = 32: 2000 x
+  // 128 337 / 254, 8000 544 / 481, 12,000 667 / 655, 16,000 763 / 766, 20,000 874 / 913; k = p = 16:
+  // 16,000 x 64 610 / 570, 20,000 670 / 670, 24,000 718 / 741; k = 40, p = 20: 10,240 x 64 606 / 585,
+  // 12,000 626 / 635, 16,000 713 / 739; k = 64, p = 32: 8000 x 100 628 / 596, 10,240 717 / 731, 16,000
+  // 885 / 924; k = 100: 8000 x 128 774 / 761, 16,000 1108 / 1186)
   const bool staged = stage_possible(&c->prm, L.extra) && !stays_small(&c->prm);
   d.stg_ent = staged ? (uint64_t*)(w + L.off_stg_ent) : nullptr;
   d.stg_cur = staged ? (unsigned long long*)(w + L.off_stg_cur) : nullptr;

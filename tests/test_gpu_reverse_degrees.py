@@ -125,10 +125,11 @@ def test_builds_match_the_oracle_where_small_collections_end(n, k, p):
 
 
 @pytest.mark.parametrize("n,d,k,p", [(1 << 14, 20, 12, 10), ((1 << 14) + 1, 96, 20, 20),
-                                     (16000, 64, 33, 32), (16390, 128, 32, 32)])
+                                     (16000, 64, 33, 32), (16390, 128, 32, 32),
+                                     (11264, 30, 33, 17), (11265, 100, 33, 17)])
 def test_hand_out_of_small_byte_collections(n, d, k, p):
-    """Results one by one up to 2^14 nodes, staged beyond: the oracle's graph, and the counters
-    of the staged form."""
+    """Results one by one up to 2^14 nodes (k > 32, p > 16: 11,264), staged beyond: the oracle's graph,
+    and the counters of the staged form."""
     import paper_2103_15386_amd as amd
     x = torch.from_numpy(W.sift_like_u8(n, d, seed=9, n_comp=16)).cuda()
     seen = []
