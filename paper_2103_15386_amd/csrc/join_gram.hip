@@ -119,13 +119,14 @@ hipError_t launch_join_gram(const Shape& sh, const DevState& ds, bool merge_mode
   // the nodes with work to do, by class (few nodes: fewer per workgroup, so that more of the
   // chip lists them; many: fewer additions to the lists' lengths); not where all are of one
   // class (4096 x 16, p = 8: this launch and that of a second build took 12 of 58 us per iteration)
-  if (gram_one_class(sh.p)) {
-  } else if (sh.n <= (1 << 20))
-    k_gram_classify<4><<<grid_blocks((sh.n + 1023) / 1024), 256, 0, st>>>(
-        sh.n, mm, ds.cnew, ds.cold, ds.cls_nodes, ds.cls_count);
-  else
-    k_gram_classify<16><<<grid_blocks((sh.n + 4095) / 4096), 256, 0, st>>>(
-        sh.n, mm, ds.cnew, ds.cold, ds.cls_nodes, ds.cls_count);
+  if (!gram_one_class(sh.p)) {
+    if (sh.n <= (1 << 20))
+      k_gram_classify<4><<<grid_blocks((sh.n + 1023) / 1024), 256, 0, st>>>(
+          sh.n, mm, ds.cnew, ds.cold, ds.cls_nodes, ds.cls_count);
+    else
+      k_gram_classify<16><<<grid_blocks((sh.n + 4095) / 4096), 256, 0, st>>>(
+          sh.n, mm, ds.cnew, ds.cold, ds.cls_nodes, ds.cls_count);
+  }
   // one build per class, each with about four sets of resident wavefronts (the lists' lengths
   // are known on the device only) and never more wavefronts than nodes
   const int64_t cap = (int64_t)64 * compute_units();

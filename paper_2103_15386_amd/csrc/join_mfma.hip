@@ -943,26 +943,28 @@ hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode
   // lists of up to 32 samples are all of the first shape, and so is every node without OLD samples:
   // a random graph has none
   const bool more_shapes = sh.p > 16 && !lean;
-#define GNND_K(K)                                                                                  \
-  e = hipSuccess;                                                                                  \
-  if (!one_shape)                                                                                  \
-  e = lean ? launch_k<K, true, true, 1>(fcode, false, grid_slim, st, ds.shadow, ds.meta, dpad, sh, \
-                                        ds, sa)                                                    \
-           : launch_k<K, true, false, 1>(fcode, merge_mode, grid_slim, st, ds.shadow, ds.meta,     \
-                                         dpad, sh, ds, sa);                                        \
-  if (e == hipSuccess && more_shapes && !one_shape)                                                \
-    e = launch_k<K, true, false, 2>(fcode, merge_mode, grid_slim, st, ds.shadow, ds.meta, dpad,    \
-                                    sh, ds, sa);                                                   \
-  if (e == hipSuccess && more_shapes)                                                              \
-    e = launch_k<K, true, false, 0>(fcode, merge_mode, grid_for(join_waves(true, 0, K)), st,       \
-                                    ds.shadow, ds.meta, dpad, sh, ds, sa)
+  auto shapes = [&](auto steps) {
+    constexpr int K = decltype(steps)::value;
+    hipError_t r = hipSuccess;
+    if (!one_shape)
+      r = lean ? launch_k<K, true, true, 1>(fcode, false, grid_slim, st, ds.shadow, ds.meta, dpad, sh,
+                                            ds, sa)
+               : launch_k<K, true, false, 1>(fcode, merge_mode, grid_slim, st, ds.shadow, ds.meta,
+                                             dpad, sh, ds, sa);
+    if (r == hipSuccess && more_shapes && !one_shape)
+      r = launch_k<K, true, false, 2>(fcode, merge_mode, grid_slim, st, ds.shadow, ds.meta, dpad, sh,
+                                      ds, sa);
+    if (r == hipSuccess && more_shapes)
+      r = launch_k<K, true, false, 0>(fcode, merge_mode, grid_for(join_waves(true, 0, K)), st,
+                                      ds.shadow, ds.meta, dpad, sh, ds, sa);
+    return r;
+  };
   switch (ksteps) {
-    case 1: GNND_K(1); break;
-    case 2: GNND_K(2); break;
-    case 3: GNND_K(3); break;
-    default: GNND_K(4);
+    case 1: e = shapes(std::integral_constant<int, 1>{}); break;
+    case 2: e = shapes(std::integral_constant<int, 2>{}); break;
+    case 3: e = shapes(std::integral_constant<int, 3>{}); break;
+    default: e = shapes(std::integral_constant<int, 4>{});
   }
-#undef GNND_K
   if (after_join) (void)hipEventRecord(after_join, st);
   if (e != hipSuccess) return e;
   // (a region is shorter than 2^32 slots: n <= 2^22, 6p <= 192 slots per node)
