@@ -16,20 +16,23 @@
 //      itself: K other rows are at least that near.
 //   4. k_scan<.., true>: all tiles; rows whose upper bound reaches the threshold are listed.
 //   5. k_pick: canonical distances of the listed rows, the best K in order.  A query with more
-//      candidates than its list holds, or one outside the bounds' range, is left to k_exact_knn.
+//      candidates than its list holds, or one outside the bounds' range, is left to k_exact_knn;
+//      so are all of them where a row holds a NaN (2 to 4 are left out then).
 //
 // A workgroup of k_scan holds the operands of 256 queries in registers (64 per wavefront) and
 // streams tiles of 64 rows through LDS, double buffered, each read once for all 256.
 // Consecutive workgroups of one XCD take the same rows for different queries.
 //
-// 2000 queries x 10^6 x 96 angular, K = 10: 9.7 -> 0.84 ms (the second scan 0.51, the first 0.16,
-// the copies 0.10 at 5.9 TB/s); 2000 x 10^6 x 128 squared L2 15.0 -> 1.09 ms, 2000 x 10^6 x 96
-// bytes, K = 64: 4.5 -> 0.52 ms, 16 queries x 10^6 x 96: 6.6 -> 0.28 ms.  Bound: LDS reads of the row
-// operands (16 KiB per wavefront and tile, two thirds of the matrix instructions' own time) and
-// what is left between them; 128 queries per wavefront read half as much and took 0.73 ms on
-// the first of these calls, but 0.33 instead of 0.29 ms for up to 100 queries.  Data the copies do
-// not suit (distances small against the lengths, thousands of copies of a vector) cost the first
-// scan on top: 500 x 200,000 x 48, vectors 30 standard deviations off the origin, 0.69 -> 0.76 ms.
+// 10^6 rows, k_exact_knn alone / this form in ms: 2000 queries x 96 dimensions, angular, K = 10 9.7 /
+// 0.75 (the second scan 0.52, the first 0.17, the copies 0.11 at 5.3 TB/s); 2000 x 128 squared L2
+// 16.8 / 1.1; 2000 x 96 bytes, K = 64 4.5 / 0.51; 16 x 96 6.6 / 0.26; 4096 x 96, K = 64 22.3 / 1.6;
+// 10,000 x 96, K = 64 71.9 / 3.75.  The second scan reaches 0.75 PFLOP/s, half of what large products
+// do here: matrix unit 0.30 and vector unit 0.28 of the time busy (128 dimensions).  Every wavefront
+// reads the row operands from LDS for 64 queries; for 128 it reads half as much, which took 4 %
+// less on the first of these calls but 0.33 instead of 0.29 ms for up to 100 queries.
+// Data the copies do not suit (distances small against the lengths, thousands of copies of a vector)
+// cost the first scan on top: 500 x 200,000 x 48, unit vectors 30 off the origin in every dimension,
+// 0.69 / 0.79 ms; 1000 x 200,000 x 48, queries among 20,000 copies of a vector, 0.79 / 0.88.
 #include <cfloat>
 #include <type_traits>
 

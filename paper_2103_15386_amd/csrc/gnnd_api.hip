@@ -547,8 +547,10 @@ int merge_impl(const gnnd_params* prm, const void* vec1, int64_t n1, int64_t bas
 // alternate, so a copy stream moves the next step's data in and the previous
 // step's results out while the compute stream works.  A sub-graph that the next merge needs is
 // read where the step before has left it on the GPU; on its way down and up again (8 bytes per
-// entry each way) the compute stream had nothing to do: 4 x 600,000 x 128 bytes, k = 32,
-// 238 -> 192 ms.
+// entry each way) the compute stream had nothing to do: 4 x 600,000 x 128 bytes, k = 32, 238 to 246 ->
+// 191 ms.  (Where the copy stream is served by the same hardware queue as the compute stream - one
+// of eight streams of the pool that the Python call takes it from, so one call in eight - the two do
+// not overlap: 264 ms.)
 struct ShardPlan {
   int shards;
   int64_t size, last, maxs;  // rows per shard, rows of the last shard, larger of the two
