@@ -180,9 +180,8 @@ Layout make_layout(const gnnd_params* q, bool with_aside, bool extra = true) {
   const size_t half_bytes = half ? n * (size_t)half_row_elems(q->d) * 2 : 0;
   L.off_stg_ent = L.off_half = take(stage_bytes > half_bytes ? stage_bytes : half_bytes);
   L.off_stg_cur = take(staged ? (size_t)kStageBuckets * 8 : 0);
-  // (the float join lists its nodes in kGramClasses classes, the staged int8 join in three)
-  L.off_cls_nodes = take(gram ? (size_t)kGramClasses * n * 4 : staged ? (size_t)3 * n * 4 : 0);
-  L.off_cls_count = take(gram || staged ? 256 : 0);
+  L.off_cls_nodes = take(gram ? (size_t)kGramClasses * n * 4 : 0);
+  L.off_cls_count = take(gram ? 256 : 0);
   L.extra = extra;
   L.total = o;
   return L;
@@ -265,8 +264,8 @@ void bind(gnnd_ctx* c, const Layout& L) {
   d.stg_ent = staged ? (uint64_t*)(w + L.off_stg_ent) : nullptr;
   d.stg_cur = staged ? (unsigned long long*)(w + L.off_stg_cur) : nullptr;
   const bool gram = gram_possible(&c->prm);
-  d.cls_nodes = gram || staged ? (int32_t*)(w + L.off_cls_nodes) : nullptr;
-  d.cls_count = gram || staged ? (uint32_t*)(w + L.off_cls_count) : nullptr;
+  d.cls_nodes = gram ? (int32_t*)(w + L.off_cls_nodes) : nullptr;
+  d.cls_count = gram ? (uint32_t*)(w + L.off_cls_count) : nullptr;
   d.half_rows = L.extra && half_possible(&c->prm) ? (void*)(w + L.off_half) : nullptr;
   d.half_info = (uint32_t*)(w + L.off_flag) + 1;
 }

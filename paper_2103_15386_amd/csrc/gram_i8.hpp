@@ -41,6 +41,33 @@ __device__ inline int32_t tile_col_best(const v16i& g, const int32_t* negr_lds, 
   return best;
 }
 
+// The same for lists of up to 64 samples with a place of its own (in words, from `negr_lds`) for each
+// of the lane's four groups of rows.
+__device__ inline int32_t tile_col_best_at(const v16i& g, const int32_t* negr_lds,
+                                           const int (&at)[4]) {
+  int32_t best = kNone;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int4 nr = *reinterpret_cast<const int4*>(negr_lds + at[q]);
+    const int32_t negr[4] = {nr.x, nr.y, nr.z, nr.w};
+    int32_t t[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      t[i] = (int32_t)(((uint32_t)g[4 * q + i] << 7) + (uint32_t)negr[i]);
+    best = max(best, max(t[0], t[1]));
+    best = max(best, max(t[2], t[3]));
+  }
+  return best;
+}
+
+// Results of two column blocks, each spread over both halves: block 0's larger one in lanes 0..31,
+// block 1's in lanes 32..63.
+__device__ inline int32_t blocks_max(int32_t x0, int32_t x1) {
+  auto sw = __builtin_amdgcn_permlane32_swap((uint32_t)x0, (uint32_t)x1, false, false);
+  const int32_t a = (int32_t)sw[0], b = (int32_t)sw[1];
+  return a > b ? a : b;
+}
+
 __device__ inline int32_t both_halves_max(int32_t x) {
   auto sw = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
   int32_t a = (int32_t)sw[0], b = (int32_t)sw[1];

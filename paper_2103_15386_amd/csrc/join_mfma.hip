@@ -22,9 +22,8 @@ namespace gnnd {
 
 constexpr int kMB = 256;  // 4 waves = 4 nodes in flight per workgroup
 constexpr int64_t kJoinGrid = 256 * 3 * 2;  // 256 CUs x 3 resident workgroups x 2
-// staged hand-out: one workgroup of 8 waves per CU (2 per SIMD: the staging code needs the registers) shares the staging area
-constexpr int kStagedWaves = 8;       // four operand blocks of 128 bytes: 2 wavefronts per SIMD
-constexpr int kStagedWavesSlim = 12;  // three, or shorter rows: 3 wavefronts per SIMD
+// staged hand-out: one workgroup of 12 waves per CU (3 per SIMD) shares the staging area
+constexpr int kStagedWaves = 12;
 
 constexpr int32_t kFar = 1 << 24;  // "norm" of an absent row: above every real distance
 
@@ -194,11 +193,9 @@ struct StageArgs {
   const uint64_t* poff;     // segment offsets of the destinations (n + 1)
   int tb, nb;               // log2(destinations per bucket), number of buckets
   uint32_t threshold;       // fill count that triggers a flush
-  const int32_t* nodes;     // kJoinShapes lists of n places: the nodes of each shape
-  const uint32_t* count;    // their lengths
   bool count_passed;        // false when the pass behind the join counts what passes
 };
-constexpr size_t kStageLdsBytes = (size_t)kStageBuckets * kStageSlots * 8 + kStageBuckets * 20 + 16;
+constexpr size_t kStageLdsBytes = (size_t)kStageBuckets * kStageSlots * 8 + kStageBuckets * 12 + 16;
 // a staged result (see kStageDistShift) without its destination, and with it
 __device__ inline uint64_t stage_entry(int32_t dist, uint32_t id) {
   return ((uint64_t)(uint32_t)dist << kStageDistShift) | (uint64_t)id;
@@ -234,71 +231,51 @@ __device__ inline int32_t sample_norm(const Operand& b0, const Operand& b1, int 
 // handed on; k_result_csr<true> then applies the thresholds (staged hand-out; with the direct
 // hand-out the list update drops what cannot enter), so the same results reach the lists.
 // Faster only where the saved reads outweigh the extra arithmetic and the larger flow of results.
-// Staged, it is the only build launched then: no node of a random graph has OLD samples (with two
-// more launches over empty lists 10^6 x 128 took 26.08 instead of 25.92 ms).
-// SHAPE (staged hand-out only): which of the four operand blocks of 32 rows a node fills.
-// 0: any (NEW 0..31, NEW 32..63, OLD 0..31, OLD 32..63); 1: at most 32 OLD samples; 2: at
-// most 32 NEW samples.  Most nodes are of shape 1 (early iterations: many NEW, few OLD) or 2
-// (late ones); without the fourth block's 16 registers the kernel fits 3 wavefronts per SIMD,
-// which hide the per-node chain wait -> evaluate -> hand on better than 2 do (6 to 12 % less
-// time per iteration).  Rows of up to 96 bytes leave room for the fourth block: 157 registers,
-// 200,000 x 96 bytes with full lists, whole build 5.87 -> 5.76 ms.  k_join_shapes lists the nodes of each shape (those with nothing to
-// evaluate are in no list) and every build runs over its own list.
-constexpr int kJoinShapes = 3;
-__host__ __device__ constexpr int join_list_of_shape(int shape) { return shape == 0 ? 2 : shape - 1; }
-__host__ __device__ constexpr bool join_slim(int shape, int ksteps) { return shape || ksteps < 4; }
-__host__ __device__ constexpr int join_waves(bool staged, int shape, int ksteps) {
-  return !staged ? kMB / kWave : join_slim(shape, ksteps) ? kStagedWavesSlim : kStagedWaves;
-}
-__host__ __device__ constexpr int join_waves_per_simd(bool staged, int shape, int ksteps) {
-  return staged && !join_slim(shape, ksteps) ? 2 : 3;
-}
-
-// Few nodes: all of them by the build for any shape, one launch that fills and empties a staging
-// area instead of three.  Six iterations, three launches / one, microseconds: 17,000 x 128 879 /
-// 819; 30,000 x 100 1357 / 1281; 60,000 x 128 1707 / 1730; with three wavefronts per SIMD in
-// that build: 30,000 x 64 1094 / 995; 60,000 x 96 1660 / 1571; 130,000 x 64 2955 / 2887; 400,000 x
-// 64 8857 / 8764; 900,000 x 96 22,625 / 22,557.
-__host__ __device__ constexpr int64_t one_shape_nodes(int ksteps) {
-  return join_slim(0, ksteps) ? 1 << 20 : 1 << 15;
-}
-
-template <int KSTEPS, bool FCODE, bool MERGE, bool STAGED, bool LEAN = false, int SHAPE = 0>
-__global__ __launch_bounds__(join_waves(STAGED, SHAPE, KSTEPS) * kWave)
-__attribute__((amdgpu_waves_per_eu(join_waves_per_simd(STAGED, SHAPE, KSTEPS),
-                                   join_waves_per_simd(STAGED, SHAPE, KSTEPS)))) void k_join_mfma(
-    const int8_t* __restrict__ shadow, const NodeMeta* __restrict__ meta, int dpad, int64_t n,
+//
+// Between nodes a wavefront keeps as little as it can waiting for memory: nothing that is in
+// flight is moved or overwritten (see the loop), the search for objects in both lists runs before
+// the rows are needed, counts stay in registers until the end, and the terms a diagonal tile hides
+// are read from a place of their own instead of being masked.  Registers of absent samples are not
+// cleared either, which with 32-bit offsets brought the form for any node from 173 to 152 registers,
+// so that it runs 3 wavefronts per SIMD like the forms for nodes with at most 32 OLD or at most 32 NEW
+// samples that stood beside it: those, the lists of nodes per form and the launch that made them are
+// gone, and a wavefront walks over all nodes.  Iterations of 10^6 x 128 on average 1724 -> 1540 us,
+// 200,000 x 96 bytes with full lists 670 -> 605 us, the first iteration 1530 -> 1415 us.
+template <int KSTEPS, bool FCODE, bool MERGE, bool STAGED, bool LEAN = false>
+__global__ __launch_bounds__(STAGED ? kStagedWaves * kWave : kMB)
+__attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
+    const int8_t* __restrict__ shadow, const NodeMeta* __restrict__ meta, int64_t n,
     int p, int64_t split, const int32_t* __restrict__ snew, const int32_t* __restrict__ sold,
     uint64_t* pslot, uint64_t slots, uint64_t* __restrict__ bins, uint64_t* counters,
     StageArgs sa) {
-  constexpr int WAVES = join_waves(STAGED, SHAPE, KSTEPS);
-  constexpr bool kHasN1 = SHAPE != 2, kHasO1 = SHAPE != 1;
-  static_assert(STAGED || SHAPE == 0, "shapes come with the node lists of the staged form");
+  constexpr int WAVES = STAGED ? kStagedWaves : kMB / kWave;
+  constexpr bool kHasO1 = !(STAGED && LEAN);  // (no node of a random graph has OLD samples)
   // per wave, for the 128 rows (NEW 0..63, OLD 64..127): -((norm << 6) | position), the ids
-  // (absent = INT_MAX so that both halves stay ascending), and a scratch row
-  __shared__ __attribute__((aligned(16))) int32_t s_norm[WAVES][128];
-  __shared__ int32_t s_id[WAVES][128];
-  __shared__ int32_t s_eq[WAVES][64];
+  // (absent = INT_MAX so that both halves stay ascending), and what a NEW sample's own column of
+  // the diagonal tiles reads instead (see own_rows); the last first serves the search for objects
+  // in both lists
+  __shared__ __attribute__((aligned(16))) int32_t s_lists[WAVES][512];
   extern __shared__ __attribute__((aligned(16))) unsigned char stage_raw[];
   uint64_t* const st_ent = reinterpret_cast<uint64_t*>(stage_raw);
   uint64_t* const st_region = st_ent + kStageBuckets * kStageSlots;
-  uint64_t* const st_gbase = st_region + kStageBuckets;
-  uint32_t* const st_cnt = reinterpret_cast<uint32_t*>(st_gbase + kStageBuckets);
+  uint32_t* const st_cnt = reinterpret_cast<uint32_t*>(st_region + kStageBuckets);
   uint32_t* const st_fill = st_cnt + kStageBuckets;  // [0] results staged, [1] waves out of nodes
   // (the wave index as a vector value: measured 3 % faster here than the scalar form)
   const int wave = threadIdx.x >> 6, lane = lane_id(), half = lane >> 5, col = lane & 31;
-  // (with lists n <= 2^22: places, node numbers and offsets into the sample lists fit 32 bits)
+  int32_t* const s_norm = s_lists[wave];
+  int32_t* const s_id = s_norm + 128;
+  int32_t* const s_own = s_norm + 256;
+  // (staged n <= 2^22: node numbers and offsets into the sample lists fit 32 bits, and
+  // so do the byte offsets of everything that is gathered)
   using node_t = typename std::conditional<STAGED, int32_t, int64_t>::type;
-  const node_t W = (node_t)gridDim.x * WAVES;
-  // place `pos` of this build's list of nodes (staged) / of all nodes (direct)
-  node_t pos = (node_t)blockIdx.x * WAVES + wave;
-  const node_t places = STAGED ? (node_t)sa.count[join_list_of_shape(SHAPE)] : (node_t)n;
-  const int32_t* const list = STAGED ? sa.nodes + (int64_t)join_list_of_shape(SHAPE) * n : nullptr;
-  auto node_at = [&](node_t at) -> node_t {  // -1 beyond the end
-    if (at >= places) return (node_t)-1;
-    return STAGED ? (node_t)list[at] : (node_t)at;
+  using offset_t = typename std::conditional<STAGED, uint32_t, int64_t>::type;
+  auto at_offset = [](const void* base, offset_t bytes) {
+    return static_cast<const char*>(base) + bytes;
   };
-  if (!STAGED && pos >= n) return;
+  const node_t W = (node_t)gridDim.x * WAVES;
+  const node_t nodes = (node_t)n;
+  node_t s = (node_t)blockIdx.x * WAVES + wave;
+  if (!STAGED && s >= nodes) return;
   if (STAGED) {
     for (int b = threadIdx.x; b < sa.nb; b += WAVES * kWave) {
       st_cnt[b] = 0;
@@ -309,142 +286,198 @@ __attribute__((amdgpu_waves_per_eu(join_waves_per_simd(STAGED, SHAPE, KSTEPS),
     __syncthreads();
   }
   // One flush (all waves of the workgroup together).  Returns true when every wave has
-  // run out of nodes, i.e. when this was the last one.
+  // run out of nodes, i.e. when this was the last one.  A wave sees to a run of neighbouring
+  // buckets: each of its lanes claims the places of one (neighbouring counters: with a wave's
+  // buckets spread out instead the joins took 10 to 35 % longer), and then the results of one
+  // after the other leave as one contiguous piece each.
   auto flush = [&]() -> bool {
     __syncthreads();  // nobody is adding results any more
-    const uint32_t out_of_nodes = *reinterpret_cast<volatile uint32_t*>(st_fill + 1);
-    for (int b = threadIdx.x; b < sa.nb; b += WAVES * kWave) {
-      const uint32_t c = st_cnt[b] < (uint32_t)kStageSlots ? st_cnt[b] : (uint32_t)kStageSlots;
-      st_gbase[b] = c ? atomicAdd(&sa.cur[b], (unsigned long long)c) : 0ull;
-    }
-    __syncthreads();
-    // a wave per bucket: its results leave as one contiguous piece
-    for (int b = wave; b < sa.nb; b += WAVES) {
-      const uint32_t c = st_cnt[b] < (uint32_t)kStageSlots ? st_cnt[b] : (uint32_t)kStageSlots;
-      const uint64_t at = st_region[b] + st_gbase[b] + (uint32_t)lane;
-      if ((uint32_t)lane < c && at < slots) sa.ent[at] = st_ent[b * kStageSlots + lane];
-    }
-    __syncthreads();
-    for (int b = threadIdx.x; b < sa.nb; b += WAVES * kWave) st_cnt[b] = 0;
+    const uint32_t out_of_nodes = st_fill[1];
     if (threadIdx.x == 0) st_fill[0] = 0;
+    const int per = (sa.nb + WAVES - 1) / WAVES, first = wave_id() * per;
+    const int last = vmin(first + per, sa.nb), own = first + lane;
+    uint32_t c = 0;
+    uint64_t at = 0;
+    if (own < last) {
+      c = vmin(st_cnt[own], (uint32_t)kStageSlots);
+      st_cnt[own] = 0;
+      if (c) at = st_region[own] + atomicAdd(&sa.cur[own], (unsigned long long)c);
+    }
+    for (int i0 = 0; first + i0 < last; i0 += 4) {
+      uint64_t rec[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        rec[j] = st_ent[vmin(first + i0 + j, sa.nb - 1) * kStageSlots + lane];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {  // (lanes beyond the buckets hold no results)
+        const uint32_t count = (uint32_t)__builtin_amdgcn_readlane((int)c, i0 + j);
+        const uint64_t to = readlane64(at, i0 + j) + (uint32_t)lane;
+        if ((uint32_t)lane < count && to < slots) sa.ent[to] = rec[j];
+      }
+    }
     __syncthreads();
     return out_of_nodes == (uint32_t)WAVES;
   };
-  // this node, the next one and the one after: sample ids are requested two nodes ahead
-  node_t s = node_at(pos), s1 = node_at(pos + W), s2 = node_at(pos + 2 * W);
-  const bool have_nodes = s >= 0;
-  const int L = 2 * p;
-  const bool in_list = lane < L;
-
-  // unused list slots hold -1, so the ids alone say how long a list is
-  int32_t id_new = (have_nodes && in_list) ? snew[s * L + lane] : -1;
-  int32_t id_old = (have_nodes && in_list) ? sold[s * L + lane] : -1;
-  int32_t nx_new = -1, nx_old = -1;
-  if (s1 >= 0 && in_list) {
-    nx_new = snew[s1 * L + lane];
-    nx_old = sold[s1 * L + lane];
-  }
-  Operand N0, N1, O0, O1;
-  uint2 m_new, m_old;
-  auto request_rows = [&](int32_t idn, int32_t ido) {
-    // block b of a list = its rows 32b..32b+31; lane (col, half) holds bytes
-    // [32 step + 16 half, +16) of row `col` of the block for every step
-    N0 = load_block<KSTEPS>(shadow, dpad, __shfl(idn, col, kWave), half);
-    if (kHasN1) N1 = load_block<KSTEPS>(shadow, dpad, __shfl(idn, 32 + col, kWave), half);
-    O0 = load_block<KSTEPS>(shadow, dpad, __shfl(ido, col, kWave), half);
-    if (kHasO1) O1 = load_block<KSTEPS>(shadow, dpad, __shfl(ido, 32 + col, kWave), half);
-    m_new = m_old = make_uint2(0u, (uint32_t)kFar);  // an absent sample: far from everything
-    if (!LEAN) {  // one 8-byte gather per sampled object: list threshold and norm
-      if (idn >= 0) m_new = *reinterpret_cast<const uint2*>(meta + idn);
-      if (ido >= 0) m_old = *reinterpret_cast<const uint2*>(meta + ido);
-    }
+  // The sample ids of the next node are on their way while one is worked on.  What is requested goes to
+  // its registers without any branch or default, and is looked at no sooner than a whole node
+  // later: a register that is written or moved while its load is out would make the wavefront
+  // wait for everything it has requested.
+  const int L = 2 * p, at_list = lane < L ? lane : L - 1;
+  // (nodes beyond the end: the last one's ids, unused)
+  auto sample_of = [&](const int32_t* lists, node_t node) {
+    return *reinterpret_cast<const int32_t*>(at_offset(
+        lists, ((offset_t)vmin(node, (node_t)(nodes - 1)) * (offset_t)L + (offset_t)at_list) * 4));
   };
-  request_rows(id_new, id_old);
+  // unused list slots hold -1, so the ids alone say how long a list is
+  int32_t id_new = sample_of(snew, s), id_old = sample_of(sold, s);
+  int32_t nx_new = sample_of(snew, s + W), nx_old = sample_of(sold, s + W);
+  if (lane >= L) id_new = id_old = -1;
+  // Block b of a list = its rows 32b..32b+31; lane (col, half) holds bytes [32 step + 16 half, +16)
+  // of row `col` of the block for every step.  Registers of absent samples keep whatever they held:
+  // absent rows are kept out of every result by their norm (|2 G| <= 2^22 does not bring kFar down
+  // to a real distance), absent columns have no result.
+  Operand N0{}, N1{}, O0{}, O1{};
+  uint2 m_new = make_uint2(0u, 0u), m_old = m_new;  // list threshold and norm
+  auto load_rows = [&](Operand& o, uint32_t id) {
+    if ((int32_t)id < 0) return;
+    const char* const row = at_offset(shadow, (STAGED ? (offset_t)__umul24(id, 32 * KSTEPS)
+                                                      : (offset_t)id * (32 * KSTEPS)) +
+                                                  (offset_t)(16 * half));
+#pragma unroll
+    for (int k = 0; k < KSTEPS; ++k) o.k[k] = *reinterpret_cast<const v4i*>(row + 32 * k);
+  };
+  auto request_rows = [&](int32_t idn, int32_t ido) {
+    if (!LEAN) {  // one 8-byte gather per sampled object (an absent one: object 0, unused)
+      m_new = *reinterpret_cast<const uint2*>(at_offset(meta, (offset_t)vmax(idn, 0) * 8));
+      m_old = *reinterpret_cast<const uint2*>(at_offset(meta, (offset_t)vmax(ido, 0) * 8));
+    }
+    uint32_t i0, i1;
+    pair_lanes((uint32_t)idn, 32, i0, i1);
+    load_rows(N0, i0);
+    load_rows(N1, i1);
+    pair_lanes((uint32_t)ido, 32, i0, i1);
+    load_rows(O0, i0);
+    if (kHasO1) load_rows(O1, i1);
+  };
+  // how many samples the node has, and whether it has anything to evaluate; if not, nothing is read
+  int nn = 0, no = 0;
+  bool do_nn = false, active = false;
+  auto begin_node = [&]() {
+    nn = __popcll(__ballot(id_new >= 0));
+    no = __popcll(__ballot(id_old >= 0));
+    do_nn = !MERGE && nn > 1;
+    active = nn > 0 && (do_nn || no > 0);
+    if (active) request_rows(id_new, id_old);
+  };
+  if (s < nodes) begin_node();
 
-  while (have_nodes) {
-    const int nn = __popcll(__ballot(id_new >= 0)), no = __popcll(__ballot(id_old >= 0));
-    const bool do_nn = !MERGE && nn > 1;
-    const bool active = nn > 0 && (do_nn || no > 0);
-    uint2 cm_new = m_new, cm_old = m_old;  // this node's thresholds and norms
-    if (LEAN && active) {  // (all lanes take part in the exchange between the halves)
-      // (a block the shape does not have stands for samples that are absent)
-      const uint32_t norm_new = (uint32_t)sample_norm<KSTEPS>(N0, kHasN1 ? N1 : N0, half, lane);
-      if (id_new >= 0) cm_new.y = norm_new;
-      if (no > 0) {  // uniform
-        const uint32_t norm_old = (uint32_t)sample_norm<KSTEPS>(O0, kHasO1 ? O1 : O0, half, lane);
-        if (id_old >= 0) cm_old.y = norm_old;
+  // The diagonal tiles of NEW x NEW pair every object with itself.  Row `col` of a tile stands in
+  // one group of four rows, which the lane (col, half) that holds them reads from s_own, where its
+  // own row is as far as an absent one: nothing is masked element by element.
+  int own_rows[4];  // where this lane finds the terms of its four groups of rows
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    own_rows[q] = q == (col >> 3) && half == ((col >> 2) & 1)
+                      ? 256 + 64 * (col >> 3) + 4 * (col & 7)
+                      : 8 * q + 4 * half;
+  const int own_at = 64 * ((lane & 31) >> 3) + 32 * half + 4 * (lane & 7);
+
+  // what this wavefront has counted over its nodes (below 2^32: a node has at most 6112 pairs)
+  uint32_t all_found = 0, all_passed = 0, all_evals = 0, over = 0;
+
+  while (s < nodes) {
+    // What needs the ids only is done while the rows are on their way.
+    s_id[lane] = id_new >= 0 ? id_new : 0x7fffffff;
+    s_id[64 + lane] = id_old >= 0 ? id_old : 0x7fffffff;
+    // objects sampled both as NEW and as OLD: that pair is not a pair.  eq_old =
+    // position in the OLD list of this lane's NEW object (or -1), and vice versa.
+    // Both lists ascend, so each NEW lane binary-searches its id in the OLD list.
+    int eq_old = -1, eq_new = -1;
+    uint32_t dups = 0;
+    if (active && no > 0) {
+      wave_lds_fence();
+      const int32_t* at = s_id + 64;
+#pragma unroll
+      for (int step = 32; step > 0; step >>= 1) at = at[step - 1] < id_new ? at + step : at;
+      if (*at == id_new) eq_old = (int)(at - (s_id + 64));
+      dups = (uint32_t)__popcll(__ballot(eq_old >= 0));
+      if (dups) {
+        s_own[lane] = -1;
+        wave_lds_fence();
+        if (eq_old >= 0) s_own[eq_old] = lane;
+        wave_lds_fence();
+        eq_new = s_own[lane];
+        wave_lds_fence();
       }
     }
+    // per-lane exclusion masks (bit r = row r of the block is not a partner of
+    // this lane's column object); lanes l and l+32 serve column l%32 of block 0,
+    // results of block 1 are selected into lanes 32..63 at the end
+    const bool masked_no = MERGE || dups != 0;
+    uint32_t eq_old_c[2] = {~0u, ~0u}, eq_new_c[2] = {~0u, ~0u};
+    uint32_t cls_new[2] = {0u, 0u}, cls_old[2] = {0u, 0u};
+    uint32_t id_new_c[2] = {0u, 0u}, id_old_c[2] = {0u, 0u};
+    if (masked_no) {
+      pair_lanes((uint32_t)eq_old, 32, eq_old_c[0], eq_old_c[1]);
+      pair_lanes((uint32_t)eq_new, 32, eq_new_c[0], eq_new_c[1]);
+    }
+    // merge mode: rows whose set equals the column object's set are excluded
+    if (MERGE) {
+      const uint64_t cn = __ballot(id_new >= 0 && (int64_t)id_new >= split);
+      const uint64_t co = __ballot(id_old >= 0 && (int64_t)id_old >= split);
+      cls_new[0] = (uint32_t)cn; cls_new[1] = (uint32_t)(cn >> 32);
+      cls_old[0] = (uint32_t)co; cls_old[1] = (uint32_t)(co >> 32);
+      pair_lanes((uint32_t)id_new, 32, id_new_c[0], id_new_c[1]);
+      pair_lanes((uint32_t)id_old, 32, id_old_c[0], id_old_c[1]);
+    }
+    auto excl_rows = [&](uint32_t eq_row, int row_block, uint32_t cls_rows, uint32_t col_id) {
+      uint32_t m = 0;
+      if ((eq_row >> 5) == (uint32_t)row_block) m |= 1u << (eq_row & 31);  // (none: ~0)
+      if (MERGE) m |= ((int64_t)(int32_t)col_id >= split) ? cls_rows : ~cls_rows;
+      return m;
+    };
+
+    uint2 cm_new = m_new, cm_old = m_old;  // this node's thresholds and norms
+    if (LEAN && active) {  // (all lanes take part in the exchange between the halves)
+      cm_new.y = (uint32_t)sample_norm<KSTEPS>(N0, N1, half, lane);
+      if (no > 0)  // uniform
+        cm_old.y = (uint32_t)sample_norm<KSTEPS>(O0, kHasO1 ? O1 : O0, half, lane);
+    }
+    if (id_new < 0) cm_new.y = (uint32_t)kFar;  // an absent sample: far from everything
+    if (id_old < 0) cm_old.y = (uint32_t)kFar;
     int32_t a0 = kNone, a1 = kNone;  // NEW column blocks: nearest other NEW
     int32_t b0 = kNone, b1 = kNone;  // NEW column blocks: nearest OLD
     int32_t c0 = kNone, c1 = kNone;  // OLD column blocks: nearest NEW
-    uint32_t dups = 0;
-    uint32_t cls_new0 = 0, cls_new1 = 0, cls_old0 = 0, cls_old1 = 0;
     if (active) {
-      s_norm[wave][lane] = -(int32_t)((cm_new.y << 6) | (uint32_t)lane);
-      s_norm[wave][64 + lane] = -(int32_t)((cm_old.y << 6) | (uint32_t)lane);
-      s_id[wave][lane] = id_new >= 0 ? id_new : 0x7fffffff;
-      s_id[wave][64 + lane] = id_old >= 0 ? id_old : 0x7fffffff;
-      s_eq[wave][lane] = -1;
+      const int32_t neg_new = -(int32_t)((cm_new.y << 6) | (uint32_t)lane);
+      s_norm[lane] = neg_new;
+      s_norm[64 + lane] = -(int32_t)((cm_old.y << 6) | (uint32_t)lane);
+      if (do_nn) {
+        // the terms of the four samples of this lane's quad, its own as far as an absent one
+        const int32_t far = -(int32_t)(((uint32_t)kFar << 6) | (uint32_t)lane);
+        const int i = lane & 3;
+        int4 quad;  // (all lanes take part in the exchange)
+        quad.x = __builtin_amdgcn_mov_dpp(neg_new, 0x00, 0xF, 0xF, true);
+        quad.y = __builtin_amdgcn_mov_dpp(neg_new, 0x55, 0xF, 0xF, true);
+        quad.z = __builtin_amdgcn_mov_dpp(neg_new, 0xAA, 0xF, 0xF, true);
+        quad.w = __builtin_amdgcn_mov_dpp(neg_new, 0xFF, 0xF, 0xF, true);
+        quad.x = i == 0 ? far : quad.x;
+        quad.y = i == 1 ? far : quad.y;
+        quad.z = i == 2 ? far : quad.z;
+        quad.w = i == 3 ? far : quad.w;
+        *reinterpret_cast<int4*>(s_own + own_at) = quad;
+      }
       // the wave reads these back below: order its own LDS writes before its reads
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-      // objects sampled both as NEW and as OLD: that pair is not a pair.  eq_old =
-      // position in the OLD list of this lane's NEW object (or -1), and vice versa.
-      // Both lists ascend, so each NEW lane binary-searches its id in the OLD list.
-      int eq_old = -1, eq_new = -1;
-      if (no > 0) {
-        int lo = 0, hi = 64;  // lower bound of id_new in the OLD list, in [0, 64]
-#pragma unroll
-        for (int step = 0; step < 7; ++step) {
-          const bool go = lo < hi;
-          const int mid = (lo + hi) >> 1;  // <= 63 while lo < hi
-          const bool below = go && s_id[wave][64 + (mid & 63)] < id_new;
-          lo = below ? mid + 1 : lo;
-          hi = (go && !below) ? mid : hi;
-        }
-        if (id_new >= 0 && lo < 64 && s_id[wave][64 + lo] == id_new) eq_old = lo;
-        dups = (uint32_t)__popcll(__ballot(eq_old >= 0));
-        if (dups) {
-          if (eq_old >= 0) s_eq[wave][eq_old] = lane;
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-          __builtin_amdgcn_wave_barrier();
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-          eq_new = s_eq[wave][lane];
-        }
-      }
-      // per-lane exclusion masks (bit r = row r of the block is not a partner of
-      // this lane's column object); lanes l and l+32 serve column l%32 of block 0,
-      // results of block 1 are selected into lanes 32..63 at the end
-      const int eq_old_c0 = __shfl(eq_old, col, kWave), eq_old_c1 = __shfl(eq_old, 32 + col, kWave);
-      const int eq_new_c0 = __shfl(eq_new, col, kWave), eq_new_c1 = __shfl(eq_new, 32 + col, kWave);
-      const int32_t rid_n0 = __shfl(id_new, col, kWave), rid_n1 = __shfl(id_new, 32 + col, kWave);
-      const int32_t rid_o0 = __shfl(id_old, col, kWave), rid_o1 = __shfl(id_old, 32 + col, kWave);
-      // merge mode: rows whose set equals the column object's set are excluded
-      if (MERGE) {
-        const uint64_t cn = __ballot(id_new >= 0 && (int64_t)id_new >= split);
-        const uint64_t co = __ballot(id_old >= 0 && (int64_t)id_old >= split);
-        cls_new0 = (uint32_t)cn; cls_new1 = (uint32_t)(cn >> 32);
-        cls_old0 = (uint32_t)co; cls_old1 = (uint32_t)(co >> 32);
-      }
-      auto excl_rows = [&](int eq_row, int row_block, uint32_t cls_rows, int32_t col_id) {
-        uint32_t m = 0;
-        if (eq_row >= 0 && (eq_row >> 5) == row_block) m |= 1u << (eq_row & 31);
-        if (MERGE) m |= ((int64_t)col_id >= split) ? cls_rows : ~cls_rows;
-        return m;
-      };
-      const bool masked_no = MERGE || dups != 0;
-      const int32_t* normN = s_norm[wave];
-      const int32_t* normO = s_norm[wave] + 64;
+      wave_lds_fence();
+      const int32_t* normN = s_norm;
+      const int32_t* normO = s_norm + 64;
 
       if (do_nn) {
-        {  // rows N0, columns N0: the diagonal pairs an object with itself
+        {  // rows N0, columns N0
           v16i g = gram<KSTEPS>(N0, N0);
-          a0 = max(a0, tile_col_best<true>(g, normN, half, 1u << col));
+          a0 = max(a0, tile_col_best_at(g, normN, own_rows));
         }
-        if (kHasN1 && nn > 32) {
+        if (nn > 32) {
           {
             v16i g = gram<KSTEPS>(N1, N0);
             a0 = max(a0, tile_col_best<false>(g, normN + 32, half, 0u));
@@ -455,113 +488,88 @@ __attribute__((amdgpu_waves_per_eu(join_waves_per_simd(STAGED, SHAPE, KSTEPS),
           }
           {
             v16i g = gram<KSTEPS>(N1, N1);
-            a1 = max(a1, tile_col_best<true>(g, normN + 32, half, 1u << col));
+            a1 = max(a1, tile_col_best_at(g, normN + 32, own_rows));
           }
         }
       }
+      // one tile of NEW x OLD, columns = objects of one list, rows = a block of the other
+      auto cross = [&](const Operand& rows, const Operand& cols, const int32_t* norms, uint32_t eq,
+                       int row_block, uint32_t cls_rows, uint32_t col_id) {
+        const v16i g = gram<KSTEPS>(rows, cols);
+        return masked_no ? tile_col_best<true>(g, norms, half,
+                                               excl_rows(eq, row_block, cls_rows, col_id))
+                         : tile_col_best<false>(g, norms, half, 0u);
+      };
       if (no > 0) {
         // columns = NEW objects, rows = OLD objects: nearest OLD of every NEW
-        {
-          v16i g = gram<KSTEPS>(O0, N0);
-          b0 = max(b0, masked_no ? tile_col_best<true>(g, normO, half,
-                                                      excl_rows(eq_old_c0, 0, cls_old0, rid_n0))
-                                 : tile_col_best<false>(g, normO, half, 0u));
-        }
-        if (kHasO1 && no > 32) {
-          v16i g = gram<KSTEPS>(O1, N0);
-          b0 = max(b0, masked_no ? tile_col_best<true>(g, normO + 32, half,
-                                                      excl_rows(eq_old_c0, 1, cls_old1, rid_n0))
-                                 : tile_col_best<false>(g, normO + 32, half, 0u));
-        }
-        if (kHasN1 && nn > 32) {
-          {
-            v16i g = gram<KSTEPS>(O0, N1);
-            b1 = max(b1, masked_no ? tile_col_best<true>(g, normO, half,
-                                                        excl_rows(eq_old_c1, 0, cls_old0, rid_n1))
-                                   : tile_col_best<false>(g, normO, half, 0u));
-          }
-          if (kHasO1 && no > 32) {
-            v16i g = gram<KSTEPS>(O1, N1);
-            b1 = max(b1, masked_no ? tile_col_best<true>(g, normO + 32, half,
-                                                        excl_rows(eq_old_c1, 1, cls_old1, rid_n1))
-                                   : tile_col_best<false>(g, normO + 32, half, 0u));
-          }
+        b0 = max(b0, cross(O0, N0, normO, eq_old_c[0], 0, cls_old[0], id_new_c[0]));
+        if (kHasO1 && no > 32)
+          b0 = max(b0, cross(O1, N0, normO + 32, eq_old_c[0], 1, cls_old[1], id_new_c[0]));
+        if (nn > 32) {
+          b1 = max(b1, cross(O0, N1, normO, eq_old_c[1], 0, cls_old[0], id_new_c[1]));
+          if (kHasO1 && no > 32)
+            b1 = max(b1, cross(O1, N1, normO + 32, eq_old_c[1], 1, cls_old[1], id_new_c[1]));
         }
         // columns = OLD objects, rows = NEW objects: nearest NEW of every OLD
-        {
-          v16i g = gram<KSTEPS>(N0, O0);
-          c0 = max(c0, masked_no ? tile_col_best<true>(g, normN, half,
-                                                      excl_rows(eq_new_c0, 0, cls_new0, rid_o0))
-                                 : tile_col_best<false>(g, normN, half, 0u));
-        }
-        if (kHasN1 && nn > 32) {
-          v16i g = gram<KSTEPS>(N1, O0);
-          c0 = max(c0, masked_no ? tile_col_best<true>(g, normN + 32, half,
-                                                      excl_rows(eq_new_c0, 1, cls_new1, rid_o0))
-                                 : tile_col_best<false>(g, normN + 32, half, 0u));
-        }
+        c0 = max(c0, cross(N0, O0, normN, eq_new_c[0], 0, cls_new[0], id_old_c[0]));
+        if (nn > 32)
+          c0 = max(c0, cross(N1, O0, normN + 32, eq_new_c[0], 1, cls_new[1], id_old_c[0]));
         if (kHasO1 && no > 32) {
-          {
-            v16i g = gram<KSTEPS>(N0, O1);
-            c1 = max(c1, masked_no ? tile_col_best<true>(g, normN, half,
-                                                        excl_rows(eq_new_c1, 0, cls_new0, rid_o1))
-                                   : tile_col_best<false>(g, normN, half, 0u));
-          }
-          if (kHasN1 && nn > 32) {
-            v16i g = gram<KSTEPS>(N1, O1);
-            c1 = max(c1, masked_no ? tile_col_best<true>(g, normN + 32, half,
-                                                        excl_rows(eq_new_c1, 1, cls_new1, rid_o1))
-                                   : tile_col_best<false>(g, normN + 32, half, 0u));
-          }
+          c1 = max(c1, cross(N0, O1, normN, eq_new_c[1], 0, cls_new[0], id_old_c[1]));
+          if (nn > 32)
+            c1 = max(c1, cross(N1, O1, normN + 32, eq_new_c[1], 1, cls_new[1], id_old_c[1]));
         }
       }
     }
 
     // ---- hand the results out: lane l answers for sample l of its list -------
-    uint32_t found_total = 0, over_total = 0;
-    bool pass[3];
+    bool pass[3] = {false, false, false};
     uint64_t entry[3];
-    int32_t self[3];
     if (active) {
       // combine the two row halves; lanes 0..31 take column block 0, lanes 32..63 block 1
-      a0 = both_halves_max(a0); a1 = both_halves_max(a1);
-      b0 = both_halves_max(b0); b1 = both_halves_max(b1);
-      c0 = both_halves_max(c0); c1 = both_halves_max(c1);
-      const int32_t res3[3] = {half ? a1 : a0, half ? b1 : b0, half ? c1 : c0};
+      const int32_t res3[3] = {blocks_max(a0, a1), blocks_max(b0, b1), blocks_max(c0, c1)};
 #pragma unroll
       for (int kind = 0; kind < 3; ++kind) {
         const int32_t res = -res3[kind];  // ((row_norm - 2 G) << 6) | row position
-        self[kind] = kind == 2 ? id_old : id_new;
+        const int32_t self = kind == 2 ? id_old : id_new;
         const uint2 cm = kind == 2 ? cm_old : cm_new;
         const int32_t part = res >> 6;  // arithmetic shift; absent rows sit at kFar
-        const bool found = self[kind] >= 0 && res3[kind] != kNone && part < (kFar >> 1);
+        const bool found = self >= 0 && res3[kind] != kNone && part < (kFar >> 1);
         const int32_t dist = part + (int32_t)cm.y;
-        const int32_t other = found ? s_id[wave][(kind == 1 ? 64 : 0) + (res & 63)] : 0;
+        const int32_t other = s_id[(kind == 1 ? 64 : 0) + (res & 63)];
         const uint32_t code = FCODE ? ord_f32((float)dist) : ord_i32(dist);
         // a result that cannot beat the last entry of the destination list is dropped
         // (LEAN: every result goes on, k_result_csr applies the threshold)
         pass[kind] = found && (LEAN || code <= cm.x);
         entry[kind] = STAGED ? stage_entry(dist, (uint32_t)other)
                              : make_entry(code, (uint32_t)other, 3u);
-        found_total += (uint32_t)__popcll(__ballot(found));
+        all_found += (uint32_t)__popcll(__ballot(found));
       }
-    } else {
-      pass[0] = pass[1] = pass[2] = false;
+      if (MERGE) {
+        const uint32_t n1 = (uint32_t)(__popc(cls_new[0]) + __popc(cls_new[1]));
+        const uint32_t o1 = (uint32_t)(__popc(cls_old[0]) + __popc(cls_old[1]));
+        all_evals += n1 * ((uint32_t)no - o1) + ((uint32_t)nn - n1) * o1;
+      } else {
+        all_evals += (uint32_t)(nn * no) - dups;
+        if (do_nn) all_evals += (uint32_t)(nn * (nn - 1)) >> 1;
+      }
     }
     // slot requests for all three results first ...
     // (the two results of a NEW sample go to the same list: one request for both)
     const uint32_t want_n = (pass[0] ? 1u : 0u) + (pass[1] ? 1u : 0u);
-    const uint32_t passed_total =
+    const uint32_t passed =
         (uint32_t)__popcll(__ballot(pass[0])) + (uint32_t)__popcll(__ballot(pass[1])) +
         (uint32_t)__popcll(__ballot(pass[2]));
+    all_passed += passed;
     uint64_t word_n = 0, word_o = 0;  // direct hand-out: slot words of the destinations
     uint32_t place_n = 0, place_o = 0;  // staged hand-out: places in the buckets' LDS areas
+    uint32_t fill = 0;                  // results in the staging area, with this node's
     const int bucket_n = STAGED ? (int)((uint32_t)id_new >> sa.tb) : 0;
     const int bucket_o = STAGED ? (int)((uint32_t)id_old >> sa.tb) : 0;
     if (STAGED) {
       if (want_n) place_n = atomicAdd(&st_cnt[bucket_n], want_n);
       if (pass[2]) place_o = atomicAdd(&st_cnt[bucket_o], 1u);
-      if (passed_total && lane == 0) atomicAdd(&st_fill[0], passed_total);
+      if (lane == 0) fill = atomicAdd(&st_fill[0], passed) + passed;
     } else {
       // one returning add on the destination's slot word yields the segment start
       // and the place in it
@@ -583,7 +591,7 @@ __attribute__((amdgpu_waves_per_eu(join_waves_per_simd(STAGED, SHAPE, KSTEPS),
         } else {  // the bucket's places are taken: straight to its region
           const uint64_t at = st_region[bucket] + atomicAdd(&sa.cur[bucket], 1ull);
           if (at < slots) sa.ent[at] = rec;
-          else ++over_total;
+          else ++over;
         }
       };
       if (pass[0]) put(bucket_n, place_n, entry[0], id_new);
@@ -592,16 +600,13 @@ __attribute__((amdgpu_waves_per_eu(join_waves_per_simd(STAGED, SHAPE, KSTEPS),
     }
     // direct: with the operand registers free, the next node's rows are requested while
     // the slot words are still on their way ...
-    const bool more = s1 >= 0;
-    int32_t nn_new = -1, nn_old = -1;
-    node_t s3 = -1;
+    const bool more = s + W < nodes;
     if (more) {
-      request_rows(nx_new, nx_old);
-      if (s2 >= 0 && in_list) {
-        nn_new = snew[s2 * L + lane];
-        nn_old = sold[s2 * L + lane];
-      }
-      s3 = node_at(pos + 3 * W);
+      id_new = lane < L ? nx_new : -1;
+      id_old = lane < L ? nx_old : -1;
+      begin_node();
+      nx_new = sample_of(snew, s + 2 * W);
+      nx_old = sample_of(sold, s + 2 * W);
     }
     // ... and only now the slots are used
     if (!STAGED) {
@@ -610,51 +615,34 @@ __attribute__((amdgpu_waves_per_eu(join_waves_per_simd(STAGED, SHAPE, KSTEPS),
       if (pass[0] && pass[1]) {  // neighbouring slots: one 16-byte store
         if (at_n + 1 < slots)
           __builtin_nontemporal_store(EntryPair{entry[0], entry[1]}, reinterpret_cast<EntryPair*>(bins + at_n));
-        else over_total += 2;
+        else over += 2;
       } else if (want_n) {
         if (at_n < slots) __builtin_nontemporal_store(pass[0] ? entry[0] : entry[1], &bins[at_n]);
-        else ++over_total;
+        else ++over;
       }
       if (pass[2]) {
         if (at_o < slots) __builtin_nontemporal_store(entry[2], &bins[at_o]);
-        else ++over_total;
+        else ++over;
       }
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) over_total += __shfl_xor(over_total, off, kWave);
-    if (active && lane == 0) {
-      uint64_t ev;
-      if (MERGE) {
-        const uint64_t cn = ((uint64_t)cls_new1 << 32) | cls_new0;
-        const uint64_t co = ((uint64_t)cls_old1 << 32) | cls_old0;
-        const uint64_t n1 = __popcll(cn), o1 = __popcll(co);
-        ev = n1 * ((uint64_t)no - o1) + ((uint64_t)nn - n1) * o1;
-      } else {
-        ev = (do_nn ? (uint64_t)nn * (nn - 1) / 2 : 0) + (uint64_t)nn * no - dups;
-      }
-      uint64_t* cs = counters + (s & (kStripes - 1)) * C_SLOTS;
-      // (k_result_csr<true>, behind a launch with a LEAN build, counts what passes the
-      // thresholds)
-      // (direct hand-out with a LEAN build: every result found has been handed on)
-      if ((LEAN ? !STAGED : sa.count_passed) && passed_total)
-        atomicAdd(reinterpret_cast<unsigned long long*>(cs + C_PASSED),
-                  (unsigned long long)passed_total);
-      if (found_total) atomicAdd(reinterpret_cast<unsigned long long*>(cs + C_PROPS),
-                                 (unsigned long long)found_total);
-      if (over_total) atomicAdd(reinterpret_cast<unsigned long long*>(cs + C_OVERFLOW),
-                                (unsigned long long)over_total);
-      if (ev) atomicAdd(reinterpret_cast<unsigned long long*>(cs + C_EVALS), (unsigned long long)ev);
-    }
-    if (STAGED) {
-      // every wave looks at the fill count after every node (a wave-uniform LDS read)
-      const uint32_t fill = *reinterpret_cast<volatile uint32_t*>(st_fill);
-      if ((uint32_t)__builtin_amdgcn_readfirstlane((int)fill) >= sa.threshold) (void)flush();
-    }
+    // every wave looks at the fill count after every node
+    if (STAGED && (uint32_t)__builtin_amdgcn_readfirstlane((int)fill) >= sa.threshold) (void)flush();
     if (!more) break;
-    pos += W;
-    s = s1; s1 = s2; s2 = s3;
-    id_new = nx_new; id_old = nx_old;
-    nx_new = nn_new; nx_old = nn_old;
+    s += W;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) over += __shfl_xor(over, off, kWave);
+  if (lane == 0) {
+    unsigned long long* cs = reinterpret_cast<unsigned long long*>(
+        counters + ((blockIdx.x * WAVES + wave) & (kStripes - 1)) * C_SLOTS);
+    // (k_result_csr<true>, behind a launch with a LEAN build, counts what passes the
+    // thresholds)
+    // (direct hand-out with a LEAN build: every result found has been handed on)
+    if ((LEAN ? !STAGED : sa.count_passed) && all_passed)
+      atomicAdd(cs + C_PASSED, (unsigned long long)all_passed);
+    if (all_found) atomicAdd(cs + C_PROPS, (unsigned long long)all_found);
+    if (over) atomicAdd(cs + C_OVERFLOW, (unsigned long long)over);
+    if (all_evals) atomicAdd(cs + C_EVALS, (unsigned long long)all_evals);
   }
   if (STAGED) {
     if (lane == 0) atomicAdd(&st_fill[1], 1u);
@@ -833,31 +821,17 @@ __global__ __launch_bounds__(kRcBlock) void k_result_csr(int64_t n, int bucket_t
   }
 }
 
-// The nodes that have something to evaluate, listed by shape.
-// `one_shape`: all of them in the list of shape 0.
-__global__ __launch_bounds__(256) void k_join_shapes(int64_t n, int merge_mode, int one_shape,
-                                                     const int32_t* __restrict__ cnew,
-                                                     const int32_t* __restrict__ cold,
-                                                     int32_t* nodes, uint32_t* count) {
-  list_nodes_by_class<kJoinShapes, 4>(n, nodes, count, [&](int64_t s) {
-    const int nn = cnew[s], no = cold[s];
-    const bool do_nn = !merge_mode && nn > 1;
-    const int shape = one_shape ? 0 : no <= 32 ? 1 : nn <= 32 ? 2 : 0;
-    return nn > 0 && (do_nn || no > 0) ? join_list_of_shape(shape) : -1;
-  });
-}
-
-template <int KSTEPS, bool STAGED, bool LEAN = false, int SHAPE = 0>
+template <int KSTEPS, bool STAGED, bool LEAN = false>
 static hipError_t launch_k(bool fcode, bool merge, unsigned grid, hipStream_t st,
-                           const int8_t* shadow, const NodeMeta* meta, int dpad, const Shape& sh,
+                           const int8_t* shadow, const NodeMeta* meta, const Shape& sh,
                            const DevState& ds, const StageArgs& sa) {
-  constexpr int block = join_waves(STAGED, SHAPE, KSTEPS) * kWave;
+  constexpr int block = STAGED ? kStagedWaves * kWave : kMB;
   const size_t lds = STAGED ? kStageLdsBytes : 0;
-#define GNND_ARGS shadow, meta, dpad, sh.n, sh.p, sh.split, ds.snew, ds.sold, \
+#define GNND_ARGS shadow, meta, sh.n, sh.p, sh.split, ds.snew, ds.sold, \
                   ds.pslot, (uint64_t)sh.slots(), ds.bins, ds.counters, sa
 #define GNND_LAUNCH(F, M)                                                                      \
   do {                                                                                         \
-    auto* kern = k_join_mfma<KSTEPS, F, M, STAGED, LEAN, SHAPE>;                               \
+    auto* kern = k_join_mfma<KSTEPS, F, M, STAGED, LEAN>;                                      \
     if (STAGED) {                                                                              \
       static bool attr_set = false; /* per instantiation: a staging area beyond the default */ \
       if (!attr_set) {                                                                         \
@@ -900,73 +874,41 @@ static int compute_units() {
 
 hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode, bool first_look,
                             hipStream_t st, hipEvent_t after_join) {
-  const int dpad = (sh.d + 31) & ~31;
-  const int ksteps = dpad / 32;
+  const int ksteps = (sh.d + 31) / 32;
   const bool fcode = sh.metric != kL2U8;
   const bool staged = ds.stg_ent != nullptr;
   // the first iteration on a random graph: see LEAN
   const bool lean = first_look && !merge_mode;
-  StageArgs sa{ds.stg_ent, ds.stg_cur, ds.poff, 0, 0, 0, ds.cls_nodes, ds.cls_count, !(lean && staged)};
+  StageArgs sa{ds.stg_ent, ds.stg_cur, ds.poff, 0, 0, 0, !(lean && staged)};
   hipError_t e;
-  if (!staged) {
-    // persistent wavefronts: about two resident sets of workgroups, each wave strides over nodes
-    const int64_t want = (sh.n + 3) / 4;
-    const unsigned grid = (unsigned)(want < kJoinGrid ? want : kJoinGrid);
-#define GNND_K(K)                                                                               \
-  e = lean ? launch_k<K, false, true>(fcode, false, grid, st, ds.shadow, ds.meta, dpad, sh, ds, sa) \
-           : launch_k<K, false>(fcode, merge_mode, grid, st, ds.shadow, ds.meta, dpad, sh, ds, sa)
-    switch (ksteps) {
-      case 1: GNND_K(1); break;
-      case 2: GNND_K(2); break;
-      case 3: GNND_K(3); break;
-      default: GNND_K(4);
-    }
-#undef GNND_K
-    if (after_join) (void)hipEventRecord(after_join, st);
-    return e;
+  // persistent wavefronts.  Direct: about two resident sets of workgroups; staged: one workgroup per
+  // CU (the staging area takes most of a CU's LDS)
+  const int64_t want = (sh.n + (staged ? kStagedWaves : 4) - 1) / (staged ? kStagedWaves : 4);
+  const int64_t most = staged ? compute_units() : kJoinGrid;
+  const unsigned grid = (unsigned)(want < most ? want : most);
+  if (staged) {
+    sa.tb = stage_bucket_bits(sh.n);
+    sa.nb = (int)((sh.n + ((int64_t)1 << sa.tb) - 1) >> sa.tb);
+    // flush at half-full on average: few results find their bucket's places taken
+    sa.threshold = (uint32_t)(sa.nb * (kStageSlots / 2));
+    // (the sampling stage has cleared the region cursors)
   }
-  sa.tb = stage_bucket_bits(sh.n);
-  sa.nb = (int)((sh.n + ((int64_t)1 << sa.tb) - 1) >> sa.tb);
-  // flush at half-full on average: few results find their bucket's places taken
-  sa.threshold = (uint32_t)(sa.nb * (kStageSlots / 2));
-  // (the sampling stage has cleared the lists' lengths and the region cursors)
-  const bool one_shape = !lean && sh.p > 16 && sh.n <= one_shape_nodes(ksteps);
-  k_join_shapes<<<grid_blocks((sh.n + 1023) / 1024), 256, 0, st>>>(
-      sh.n, merge_mode ? 1 : 0, one_shape ? 1 : 0, ds.cnew, ds.cold, ds.cls_nodes, ds.cls_count);
-  // persistent workgroups, one per CU (the staging area takes most of a CU's LDS); one launch
-  // per shape, the common shapes first; all of them add to the same bucket regions
-  auto grid_for = [&](int waves) {
-    const int64_t want = (sh.n + waves - 1) / waves;
-    return (unsigned)(want < compute_units() ? want : compute_units());
-  };
-  const unsigned grid_slim = grid_for(kStagedWavesSlim);
-  // lists of up to 32 samples are all of the first shape, and so is every node without OLD samples:
-  // a random graph has none
-  const bool more_shapes = sh.p > 16 && !lean;
-  auto shapes = [&](auto steps) {
+  auto launch = [&](auto steps) {
     constexpr int K = decltype(steps)::value;
-    hipError_t r = hipSuccess;
-    if (!one_shape)
-      r = lean ? launch_k<K, true, true, 1>(fcode, false, grid_slim, st, ds.shadow, ds.meta, dpad, sh,
-                                            ds, sa)
-               : launch_k<K, true, false, 1>(fcode, merge_mode, grid_slim, st, ds.shadow, ds.meta,
-                                             dpad, sh, ds, sa);
-    if (r == hipSuccess && more_shapes && !one_shape)
-      r = launch_k<K, true, false, 2>(fcode, merge_mode, grid_slim, st, ds.shadow, ds.meta, dpad, sh,
-                                      ds, sa);
-    if (r == hipSuccess && more_shapes)
-      r = launch_k<K, true, false, 0>(fcode, merge_mode, grid_for(join_waves(true, 0, K)), st,
-                                      ds.shadow, ds.meta, dpad, sh, ds, sa);
-    return r;
+    if (staged)
+      return lean ? launch_k<K, true, true>(fcode, false, grid, st, ds.shadow, ds.meta, sh, ds, sa)
+                  : launch_k<K, true>(fcode, merge_mode, grid, st, ds.shadow, ds.meta, sh, ds, sa);
+    return lean ? launch_k<K, false, true>(fcode, false, grid, st, ds.shadow, ds.meta, sh, ds, sa)
+                : launch_k<K, false>(fcode, merge_mode, grid, st, ds.shadow, ds.meta, sh, ds, sa);
   };
   switch (ksteps) {
-    case 1: e = shapes(std::integral_constant<int, 1>{}); break;
-    case 2: e = shapes(std::integral_constant<int, 2>{}); break;
-    case 3: e = shapes(std::integral_constant<int, 3>{}); break;
-    default: e = shapes(std::integral_constant<int, 4>{});
+    case 1: e = launch(std::integral_constant<int, 1>{}); break;
+    case 2: e = launch(std::integral_constant<int, 2>{}); break;
+    case 3: e = launch(std::integral_constant<int, 3>{}); break;
+    default: e = launch(std::integral_constant<int, 4>{});
   }
   if (after_join) (void)hipEventRecord(after_join, st);
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || !staged) return e;
   // (a region is shorter than 2^32 slots: n <= 2^22, 6p <= 192 slots per node)
   const int part_tb = sa.tb < kRcBits ? sa.tb : kRcBits;
   const size_t lds = result_csr_lds_bytes(part_tb, lean);

@@ -60,9 +60,8 @@ struct DevState {
   // them into the destinations' segments of `bins`
   uint64_t* stg_ent;   // slots: staged results (see stage_record), bucket regions laid out like bins
   unsigned long long* stg_cur;  // kStageBuckets: results that have reached each bucket region
-  // float32 matrix-core join and staged int8 join (NULL when neither is in use): the nodes
-  // that have work to do, listed per class of node - kNodeClassesMax lists of n places, of
-  // which the float join uses kGramClasses and the int8 join three - and the lists' lengths
+  // float32 matrix-core join (NULL when it is not in use): the nodes that have work to do, listed
+  // per class of node - kGramClasses lists of n places - and the lists' lengths
   int32_t* cls_nodes;
   uint32_t* cls_count;
   // float32 matrix-core join: 16-bit copies of the rows divided by their norms (NULL: it reads
@@ -73,7 +72,6 @@ struct DevState {
 // Elements per 16-bit row: whole steps of 32.
 inline int64_t half_row_elems(int32_t d) { return ((int64_t)d + 31) & ~(int64_t)31; }
 constexpr int kGramClasses = 7;
-constexpr int kNodeClassesMax = 7;
 
 // Staged hand-out: destinations are cut into at most kStageBuckets buckets of 2^tb
 // consecutive ids; a workgroup of the join keeps kStageSlots results per bucket in LDS.

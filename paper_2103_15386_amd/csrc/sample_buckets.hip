@@ -203,7 +203,7 @@ __device__ inline void begin_iteration(const uint64_t* counters, uint64_t* snap,
                                        uint32_t* cls_count, unsigned long long* stg_cur) {
   for (int i = threadIdx.x; i < kStripes * C_SLOTS; i += kSB) snap[i] = counters[i];
   if (threadIdx.x == 0) *forms = FormTally::faded(*forms);
-  if (cls_count && threadIdx.x < kNodeClassesMax) cls_count[threadIdx.x] = 0u;
+  if (cls_count && threadIdx.x < kGramClasses) cls_count[threadIdx.x] = 0u;
   if (stg_cur)
     for (int i = threadIdx.x; i < kStageBuckets; i += kSB) stg_cur[i] = 0ull;
 }
