@@ -417,15 +417,20 @@ static size_t staged_lds_bytes(const BucketGeom& g) {
 
 // One workgroup per (bucket, kind): counting sort of the bucket's edges by
 // target.  LDS holds one counter per target of the bucket (dynamic size).
-template <bool PACKED>
-__global__ __launch_bounds__(kCsrBlock) void k_bucket_csr(int64_t n, BucketGeom g,
+// AT_ONCE > 0 (packed edges, at most 2^10 targets): where the bucket has no more than `fit` <= 1024
+// AT_ONCE edges, every thread keeps its edges and their ranks in registers, the sources are put in
+// order in LDS behind the counters, and the run leaves as it will stand.  One store of 4 bytes to a
+// place of its own per edge, 64 lines per instruction, was what the pass ran at, and it read every
+// edge twice and counted it twice: 10^6 nodes, p = 32, 233 -> 95 us; 1.5 million 393 -> 141 us.
+template <int AT_ONCE>
+__global__ __launch_bounds__(kCsrBlock) void k_bucket_csr(int64_t n, BucketGeom g, uint32_t fit,
                                                           const uint32_t* bcnt,
                                                           const uint2* edges_new,
                                                           const uint2* edges_old,
                                                           uint64_t* roff_new, uint64_t* roff_old,
                                                           int32_t* csr_new, int32_t* csr_old) {
-  extern __shared__ uint32_t cnt[];  // 2^tb counters, then running offsets
-  __shared__ uint32_t part[kCsrBlock];
+  constexpr bool PACKED = AT_ONCE > 0;
+  extern __shared__ uint32_t cnt[];  // 2^tb counters, then running offsets; the sources in order
   __shared__ uint64_t scan_tmp[kCsrBlock / kWave];
   const int kind = blockIdx.y;
   const int b = blockIdx.x;
@@ -435,7 +440,9 @@ __global__ __launch_bounds__(kCsrBlock) void k_bucket_csr(int64_t n, BucketGeom 
   uint64_t before = 0, unused;  // the edges of the buckets before this one
   for (int i = threadIdx.x; i < b; i += kCsrBlock) before += bcnt[kind * g.nb + i];
   const uint64_t beg = block_sum_1024(before, scan_tmp, &unused);
-  const uint64_t end = beg + bcnt[kind * g.nb + b];
+  const uint32_t size = bcnt[kind * g.nb + b];
+  const uint64_t end = beg + size;
+  const bool fits = PACKED && size <= fit;
   const int T = 1 << g.tb;
   const uint32_t mask = (uint32_t)T - 1u;
   for (int i = threadIdx.x; i < T; i += kCsrBlock) cnt[i] = 0;
@@ -443,16 +450,29 @@ __global__ __launch_bounds__(kCsrBlock) void k_bucket_csr(int64_t n, BucketGeom 
   constexpr int kAtOnce = 8;  // edges in flight per thread
   const uint32_t* const words = reinterpret_cast<const uint32_t*>(edges);
   const int sh = 32 - g.tb;  // packed edge: target inside the bucket above, source below
-  for (uint64_t e0 = beg + threadIdx.x; e0 < end; e0 += kAtOnce * kCsrBlock) {
-    uint32_t t[kAtOnce];
+  uint32_t word[PACKED ? AT_ONCE : 1], rank[PACKED ? AT_ONCE : 1];
+  if (fits) {
 #pragma unroll
-    for (int r = 0; r < kAtOnce; ++r) {
-      const uint64_t e = e0 + (uint64_t)r * kCsrBlock;
-      t[r] = e < end ? (PACKED ? words[e] >> sh : edges[e].x & mask) : 0xffffffffu;
+    for (int r = 0; r < AT_ONCE; ++r)
+      if ((uint32_t)r * kCsrBlock < size) {  // uniform
+        const uint32_t e = (uint32_t)r * kCsrBlock + threadIdx.x;
+        word[r] = words[beg + vmin(e, size - 1u)];
+      }
+#pragma unroll
+    for (int r = 0; r < AT_ONCE; ++r)
+      if ((uint32_t)r * kCsrBlock + threadIdx.x < size) rank[r] = atomicAdd(&cnt[word[r] >> sh], 1u);
+  } else {
+    for (uint64_t e0 = beg + threadIdx.x; e0 < end; e0 += kAtOnce * kCsrBlock) {
+      uint32_t t[kAtOnce];
+#pragma unroll
+      for (int r = 0; r < kAtOnce; ++r) {
+        const uint64_t e = e0 + (uint64_t)r * kCsrBlock;
+        t[r] = e < end ? (PACKED ? words[e] >> sh : edges[e].x & mask) : 0xffffffffu;
+      }
+#pragma unroll
+      for (int r = 0; r < kAtOnce; ++r)
+        if (t[r] != 0xffffffffu) atomicAdd(&cnt[t[r]], 1u);
     }
-#pragma unroll
-    for (int r = 0; r < kAtOnce; ++r)
-      if (t[r] != 0xffffffffu) atomicAdd(&cnt[t[r]], 1u);
   }
   __syncthreads();
   // exclusive scan over the T counters: T / 1024 consecutive counters per thread (fewer than
@@ -461,26 +481,9 @@ __global__ __launch_bounds__(kCsrBlock) void k_bucket_csr(int64_t n, BucketGeom 
   const int per = T > kCsrBlock ? T / kCsrBlock : (lo < T ? 1 : 0);
   uint32_t sum = 0;
   for (int i = 0; i < per; ++i) sum += cnt[lo + i];
-  part[threadIdx.x] = sum;
-  __syncthreads();
-  if (threadIdx.x < kWave) {  // scan of the 1024 partial sums by one wavefront, 16 each
-    uint32_t local[kCsrBlock / kWave];
-    uint32_t s2 = 0;
-    for (int i = 0; i < kCsrBlock / kWave; ++i) {
-      local[i] = s2;
-      s2 += part[threadIdx.x * (kCsrBlock / kWave) + i];
-    }
-    uint32_t inc = s2;
-    for (int off = 1; off < kWave; off <<= 1) {
-      uint32_t o = __shfl_up(inc, off, kWave);
-      if ((int)threadIdx.x >= off) inc += o;
-    }
-    const uint32_t before = inc - s2;
-    for (int i = 0; i < kCsrBlock / kWave; ++i)
-      part[threadIdx.x * (kCsrBlock / kWave) + i] = before + local[i];
-  }
-  __syncthreads();
-  uint32_t run = part[threadIdx.x];
+  uint64_t ahead;
+  block_sum_1024(sum, scan_tmp, &ahead);
+  uint32_t run = (uint32_t)ahead;
   const int64_t first = (int64_t)b << g.tb;
   for (int i = 0; i < per; ++i) {
     const uint32_t c = cnt[lo + i];
@@ -490,6 +493,16 @@ __global__ __launch_bounds__(kCsrBlock) void k_bucket_csr(int64_t n, BucketGeom 
   }
   if (b == g.nb - 1 && threadIdx.x == 0) roff[n] = end;
   __syncthreads();
+  if (fits) {
+    uint32_t* const sorted = cnt + T;
+#pragma unroll
+    for (int r = 0; r < AT_ONCE; ++r)
+      if ((uint32_t)r * kCsrBlock + threadIdx.x < size)
+        sorted[cnt[word[r] >> sh] + rank[r]] = word[r] & ((1u << sh) - 1u);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < size; i += kCsrBlock) csr[beg + i] = (int32_t)sorted[i];
+    return;
+  }
   for (uint64_t e0 = beg + threadIdx.x; e0 < end; e0 += kAtOnce * kCsrBlock) {
     uint2 ed[kAtOnce];  // (target inside the bucket, source); target 0xffffffff: none
 #pragma unroll
@@ -613,6 +626,9 @@ hipError_t launch_sample_direct(const Shape& sh, const DevState& ds, hipStream_t
   return hipGetLastError();
 }
 
+// Edges per thread of the two builds of k_bucket_csr for packed edges (tb <= 10).  12 leave room for
+// two workgroups per CU, 36 (with the counters 148 KB of LDS) for one.
+constexpr int kFewEdges = 12, kManyEdges = 36;
 // The bucket layout for n <= 2^27 targets: at most 4096 buckets of 2^tb <= 2^15 targets (one
 // workgroup's LDS counts a bucket's targets).  Small collections take smaller buckets and
 // fewer rows per workgroup, so that their passes still spread over the chip: buckets of 256
@@ -643,11 +659,13 @@ hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, int* group
   *group_rows = g.rows_per_wg;
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_bucket_csr<false>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 4 << 15);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_bucket_csr<true>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 4 << 15);
+    hipError_t e = hipSuccess;
+    const void* kernels[3] = {reinterpret_cast<const void*>(k_bucket_csr<0>),
+                              reinterpret_cast<const void*>(k_bucket_csr<kFewEdges>),
+                              reinterpret_cast<const void*>(k_bucket_csr<kManyEdges>)};
+    const int most[3] = {4 << 15, (kFewEdges + 1) * kCsrBlock * 4, (kManyEdges + 1) * kCsrBlock * 4};
+    for (int i = 0; i < 3 && e == hipSuccess; ++i)
+      e = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize, most[i]);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
@@ -700,12 +718,17 @@ hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, int* group
     else GNND_SCATTER(64, false);
   }
 #undef GNND_SCATTER
-  if (packed)
-    k_bucket_csr<true><<<dim3((unsigned)g.nb, 2), kCsrBlock, (size_t)4 << g.tb, st>>>(
-        sh.n, g, bcnt, edges_new, edges_old, ds.roff_new, ds.roff_old, ds.csr_new, ds.csr_old);
-  else
-    k_bucket_csr<false><<<dim3((unsigned)g.nb, 2), kCsrBlock, (size_t)4 << g.tb, st>>>(
-        sh.n, g, bcnt, edges_new, edges_old, ds.roff_new, ds.roff_old, ds.csr_new, ds.csr_old);
+#define GNND_CSR(AT_ONCE, FIT)                                                                    \
+  k_bucket_csr<AT_ONCE>                                                                           \
+      <<<dim3((unsigned)g.nb, 2), kCsrBlock, ((size_t)4 << g.tb) + (size_t)(FIT) * 4, st>>>(        \
+          sh.n, g, (uint32_t)(FIT), bcnt, edges_new, edges_old, ds.roff_new, ds.roff_old,           \
+          ds.csr_new, ds.csr_old)
+  // what an average bucket holds when all samples are of one kind, and an eighth more
+  const int64_t many = ((int64_t)sh.p << g.tb) + ((int64_t)sh.p << g.tb >> 3);
+  if (!packed) GNND_CSR(0, 0);
+  else if (many <= kFewEdges * kCsrBlock) GNND_CSR(kFewEdges, kFewEdges * kCsrBlock);
+  else GNND_CSR(kManyEdges, kManyEdges * kCsrBlock);
+#undef GNND_CSR
   return hipGetLastError();
 }
 
