@@ -78,17 +78,14 @@ struct Operand {
   v4i k[4];  // 4 steps of 32 dimensions, 16 bytes of this lane each
 };
 
+// This lane's pieces of row `id` (a block's rows: one per lane of either half); a negative id leaves
+// the registers as they are.
 template <int KSTEPS>
-__device__ inline Operand load_block(const int8_t* shadow, int dpad, int32_t id, int half) {
-  Operand o;
+__device__ inline void load_present(Operand& o, const int8_t* shadow, int32_t id, int half) {
+  if (id < 0) return;
+  const int8_t* row = shadow + (int64_t)id * (32 * KSTEPS) + 16 * half;
 #pragma unroll
-  for (int s = 0; s < 4; ++s) o.k[s] = v4i{0, 0, 0, 0};
-  if (id >= 0) {
-    const int8_t* row = shadow + (int64_t)id * dpad + 16 * half;
-#pragma unroll
-    for (int s = 0; s < KSTEPS; ++s) o.k[s] = *reinterpret_cast<const v4i*>(row + 32 * s);
-  }
-  return o;
+  for (int s = 0; s < KSTEPS; ++s) o.k[s] = *reinterpret_cast<const v4i*>(row + 32 * s);
 }
 
 template <int KSTEPS>

@@ -2,7 +2,7 @@
 // objects (p > 32) on byte-valued data of up to 128 dimensions: exact integer distances from
 // inner products on the matrix cores, the long-list form of k_join_mfma.
 //
-// One workgroup of BLOCKS wavefronts per node: 3 for lists of up to 96 samples (p <= 48), 4 beyond.
+// One workgroup of BLOCKS wavefronts per node at a time: 3 for lists of up to 96 samples (p <= 48), 4 beyond.
 // (A fourth wavefront without samples of its own kept its place and a quarter of the LDS: with
 // three, 3.75 instead of 3 busy wavefronts per SIMD; 100,000 x 128, p = 42, whole build 3.70 ->
 // 3.39 ms.)
@@ -12,9 +12,13 @@
 // epilogue keeps one column per lane (see tile_col_best), so nothing is reduced across lanes
 // but the two halves of a tile.
 //
-// 100,000 x 128 byte-valued vectors, k = 64, p = 42: 0.61 ms per iteration where the general
-// long join (k_join_long, float32 sums on the vector units) takes 5.5; build of 4 iterations
-// 24.3 -> 4.2 ms (3.4 with the three wavefronts and faster kernels around it).  Bound by the epilogue's vector instructions and the hand-out's atomics.
+// Persistent workgroups: the next node's sample ids are on their way while a node is worked on, and
+// its rows are requested as soon as the last tile has consumed the operand registers, together with
+// the places of this node's results, so that a node waits for memory once instead of five times
+// (list sizes, ids, rows, places, and the end of the workgroup).
+//
+// 100,000 x 128 byte-valued vectors, k = 64, p = 42: 0.475 ms per iteration (0.535 with a workgroup per
+// node) where the general long join (k_join_long, float32 sums on the vector units) takes 5.5.
 #include "gram_i8.hpp"
 #include "kernels.hpp"
 
@@ -26,7 +30,7 @@ constexpr int kLongBits = 7;
 constexpr int32_t kFarLong = 3 << 22;  // "norm" of an absent row: above every real distance
 
 template <int KSTEPS, int BLOCKS, bool FCODE, bool MERGE>
-__global__ __launch_bounds__(kWave* BLOCKS) void k_join_long_i8(
+__global__ __launch_bounds__(kWave* BLOCKS) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_join_long_i8(
     const int8_t* __restrict__ shadow, const NodeMeta* __restrict__ meta, int64_t n, int p,
     int64_t split, const int32_t* __restrict__ snew, const int32_t* __restrict__ sold,
     const int32_t* __restrict__ cnew, const int32_t* __restrict__ cold, uint64_t* pslot,
@@ -37,169 +41,210 @@ __global__ __launch_bounds__(kWave* BLOCKS) void k_join_long_i8(
                                    // consecutive rows touch different banks
   __shared__ __attribute__((aligned(16))) int8_t rows[2 * kLongList * kRow];  // NEW, then OLD
   __shared__ __attribute__((aligned(16))) int32_t neg[2 * kLongList];  // see tile_col_best
-  __shared__ int32_t ids[2 * kLongList];  // absent: INT_MAX, so that both lists stay ascending
+  __shared__ int32_t ids[2][128];  // absent: INT_MAX, so that both lists stay ascending
   __shared__ uint32_t second[2 * BLOCKS]; // MERGE: samples of the second set, per block of 32
-  __shared__ uint32_t tally[4];           // duplicates, found, passed, overflow
-  const int64_t s = block_linear();
-  if (s >= n) return;
-  const int nn = cnew[s], no = cold[s];
-  const bool do_nn = !MERGE && nn > 1;
-  if (nn == 0 || (!do_nn && no == 0)) return;  // nothing to evaluate (uniform)
   const int wave = wave_id(), lane = lane_id(), half = lane >> 5, col = lane & 31;
   const int pos = 32 * wave + col;  // lanes 0..31 stand for NEW sample pos, 32..63 for OLD
   const int L = 2 * p;
-  int32_t self = -1;
-  if (pos < (half ? no : nn)) self = (half ? sold : snew)[s * L + pos];
-  const int32_t id_n = __shfl(self, col, kWave), id_o = __shfl(self, 32 + col, kWave);
-  const Operand N = load_block<KSTEPS>(shadow, dpad, id_n, half);
-  const Operand O = load_block<KSTEPS>(shadow, dpad, id_o, half);
-  uint2 mine = make_uint2(0u, (uint32_t)kFarLong);  // threshold of the sample's list, norm
-  if (self >= 0) mine = *reinterpret_cast<const uint2*>(meta + self);
-  neg[kLongList * half + pos] = -(int32_t)((mine.y << kLongBits) | (uint32_t)pos);
-  ids[kLongList * half + pos] = self >= 0 ? self : 0x7fffffff;
-  if (threadIdx.x < 4) tally[threadIdx.x] = 0u;
-  if (MERGE) {
-    const uint64_t m = __ballot(self >= 0 && (int64_t)self >= split);
-    if (lane == 0) {
-      second[wave] = (uint32_t)m;
-      second[BLOCKS + wave] = (uint32_t)(m >> 32);
-    }
+  if (BLOCKS < 4) {  // the places no sample ever takes
+    for (int i = threadIdx.x; i < 2 * (128 - kLongList); i += kWave * BLOCKS)
+      ids[i & 1][kLongList + (i >> 1)] = 0x7fffffff;
   }
+  const int32_t* const lists = half ? sold : snew;
+  // (nodes beyond the end: the last one, unused)
+  auto id_of = [&](int64_t node) {
+    return lists[vmin(node, n - 1) * L + (pos < L ? pos : L - 1)];
+  };
+  int64_t s = blockIdx.x;
+  int nn = cnew[s], no = cold[s];
+  int32_t self = id_of(s);
+  if (pos >= (half ? no : nn)) self = -1;
+  int32_t nx_self = id_of(s + gridDim.x);
+  int nx_nn = cnew[vmin(s + gridDim.x, n - 1)], nx_no = cold[vmin(s + gridDim.x, n - 1)];
+  // (registers of absent samples keep what they held: an absent row is kept out of every result by
+  // its norm, |2 G| < 2^22, an absent column has no result)
+  Operand N{}, O{};
+  uint2 mine = make_uint2(0u, 0u);  // threshold of the sample's list, norm
+  bool do_nn = false, active = false;
+  auto begin_node = [&]() {
+    do_nn = !MERGE && nn > 1;
+    active = nn > 0 && (do_nn || no > 0);
+    if (!active) return;  // nothing to evaluate (uniform)
+    mine = *reinterpret_cast<const uint2*>(meta + vmax(self, 0));
+    uint32_t id_n, id_o;
+    pair_lanes((uint32_t)self, 32, id_n, id_o);
+    load_present<KSTEPS>(N, shadow, (int32_t)id_n, half);
+    load_present<KSTEPS>(O, shadow, (int32_t)id_o, half);
+  };
+  begin_node();
+  // what this wavefront has counted over its nodes
+  uint32_t all_found = 0, all_passed = 0, over = 0;
+  int64_t all_evals = 0;
+  for (;;) {
+    uint32_t want = 0;
+    uint64_t word = 0, entry[2] = {0ull, 0ull};
+    if (active) {
+      if (self < 0) mine.y = (uint32_t)kFarLong;
+      neg[kLongList * half + pos] = -(int32_t)((mine.y << kLongBits) | (uint32_t)pos);
+      ids[half][pos] = self >= 0 ? self : 0x7fffffff;
+      if (MERGE) {
+        const uint64_t m = __ballot(self >= 0 && (int64_t)self >= split);
+        if (lane == 0) {
+          second[wave] = (uint32_t)m;
+          second[BLOCKS + wave] = (uint32_t)(m >> 32);
+        }
+      }
 #pragma unroll
-  for (int k = 0; k < KSTEPS; ++k) {
-    *reinterpret_cast<v4i*>(rows + pos * kRow + 32 * k + 16 * half) = N.k[k];
-    *reinterpret_cast<v4i*>(rows + (kLongList + pos) * kRow + 32 * k + 16 * half) = O.k[k];
-  }
-  __syncthreads();
+      for (int k = 0; k < KSTEPS; ++k) {
+        *reinterpret_cast<v4i*>(rows + pos * kRow + 32 * k + 16 * half) = N.k[k];
+        *reinterpret_cast<v4i*>(rows + (kLongList + pos) * kRow + 32 * k + 16 * half) = O.k[k];
+      }
+      __syncthreads();
 
-  // An object sampled as NEW and as OLD is no pair: its place in the other list, or -1.
-  int eq = -1;
-  {
-    const int32_t* other = ids + (half ? 0 : kLongList);
-    int lo = 0, hi = kLongList;
+      // An object sampled as NEW and as OLD is no pair: its place in the other list, or -1.
+      int eq = -1;
+      if (no > 0) {
+        const int32_t* const other = ids[1 - half];
+        const int32_t* at = other;
 #pragma unroll
-    for (int step = 0; step < 8; ++step) {
-      const bool go = lo < hi;
-      const int mid = go ? (lo + hi) >> 1 : 0;  // < kLongList
-      const bool below = go && other[mid] < self;
-      lo = below ? mid + 1 : lo;
-      hi = (go && !below) ? mid : hi;
-    }
-    if (self >= 0 && lo < kLongList && other[lo] == self) eq = lo;
-  }
-  const uint64_t dup_lanes = __ballot(eq >= 0 && half == 0);
-  if (lane == 0 && dup_lanes) atomicAdd(&tally[0], (uint32_t)__popcll(dup_lanes));
-  const bool masked = MERGE || __ballot(eq >= 0) != 0ull;
-  const int eq_n = __shfl(eq, col, kWave), eq_o = __shfl(eq, 32 + col, kWave);
-  auto row_block = [&](int b) {  // 32 rows from LDS, this lane's pieces
-    Operand r;
+        for (int step = 64; step > 0; step >>= 1) at = at[step - 1] < self ? at + step : at;
+        if (*at == self) eq = (int)(at - other);
+      }
+      const uint64_t eq_lanes = __ballot(eq >= 0);
+      uint32_t eq_n = ~0u, eq_o = ~0u, id_n = 0, id_o = 0;
+      if (eq_lanes != 0ull) pair_lanes((uint32_t)eq, 32, eq_n, eq_o);
+      if (MERGE) pair_lanes((uint32_t)self, 32, id_n, id_o);
+      auto row_block = [&](int b) {  // 32 rows from LDS, this lane's pieces
+        Operand r;
 #pragma unroll
-    for (int k = 0; k < KSTEPS; ++k)
-      r.k[k] = *reinterpret_cast<const v4i*>(rows + (32 * b + col) * kRow + 32 * k + 16 * half);
-    return r;
-  };
-  // rows of block `b` (of the other list) that are no partners of the column object
-  auto excluded = [&](int eq_row, int b, uint32_t second_rows, int32_t col_id) {
-    uint32_t m = 0;
-    if (eq_row >= 0 && (eq_row >> 5) == b) m |= 1u << (eq_row & 31);
-    if (MERGE) m |= (int64_t)col_id >= split ? second_rows : ~second_rows;
-    return m;
-  };
-  const int nb_new = (nn + 31) >> 5, nb_old = (no + 31) >> 5;
-  int32_t near_nn = kNone, near_no = kNone, near_on = kNone;
-  if (wave < nb_new) {
-    if (do_nn)
+        for (int k = 0; k < KSTEPS; ++k)
+          r.k[k] = *reinterpret_cast<const v4i*>(rows + (32 * b + col) * kRow + 32 * k + 16 * half);
+        return r;
+      };
+      // rows of block `b` (of the other list) that are no partners of the column object
+      auto excluded = [&](uint32_t eq_row, int b, uint32_t second_rows, uint32_t col_id) {
+        uint32_t m = 0;
+        if ((eq_row >> 5) == (uint32_t)b) m |= 1u << (eq_row & 31);  // (none: ~0)
+        if (MERGE) m |= (int64_t)(int32_t)col_id >= split ? second_rows : ~second_rows;
+        return m;
+      };
+      const int nb_new = (nn + 31) >> 5, nb_old = (no + 31) >> 5;
+      int32_t near_nn = kNone, near_no = kNone, near_on = kNone;
+      // a tile whose columns have partners in all of its rows needs no mask
+      auto best_of = [&](const v16i& g, const int32_t* at, uint32_t skip) {
+        return __ballot(skip != 0u) ? tile_col_best<true, kLongBits>(g, at, half, skip)
+                                    : tile_col_best<false, kLongBits>(g, at, half, 0u);
+      };
+      // rows of NEW samples meet both kinds of columns
       for (int b = 0; b < nb_new; ++b) {
-        const v16i g = gram<KSTEPS>(row_block(b), N);
-        near_nn = max(near_nn, b == wave ? tile_col_best<true, kLongBits>(g, neg + 32 * b, half,
-                                                                          1u << col)
-                                         : tile_col_best<false, kLongBits>(g, neg + 32 * b, half, 0u));
+        const Operand r = row_block(b);
+        const bool new_cols = do_nn && wave < nb_new, old_cols = wave < nb_old;
+        v16i gn, go;
+        if (new_cols) gn = gram<KSTEPS>(r, N);
+        if (old_cols) go = gram<KSTEPS>(r, O);
+        if (new_cols) near_nn = max(near_nn, best_of(gn, neg + 32 * b, b == wave ? 1u << col : 0u));
+        if (old_cols)
+          near_on = max(near_on, best_of(go, neg + 32 * b,
+                                         excluded(eq_o, b, MERGE ? second[b] : 0u, id_o)));
       }
-    for (int b = 0; b < nb_old; ++b) {
-      const v16i g = gram<KSTEPS>(row_block(BLOCKS + b), N);
-      const int32_t* at = neg + kLongList + 32 * b;
-      near_no = max(near_no, masked ? tile_col_best<true, kLongBits>(
-                                          g, at, half, excluded(eq_n, b, MERGE ? second[BLOCKS + b] : 0u, id_n))
-                                    : tile_col_best<false, kLongBits>(g, at, half, 0u));
-    }
-  }
-  if (wave < nb_old) {
-    for (int b = 0; b < nb_new; ++b) {
-      const v16i g = gram<KSTEPS>(row_block(b), O);
-      const int32_t* at = neg + 32 * b;
-      near_on = max(near_on, masked ? tile_col_best<true, kLongBits>(
-                                          g, at, half, excluded(eq_o, b, MERGE ? second[b] : 0u, id_o))
-                                    : tile_col_best<false, kLongBits>(g, at, half, 0u));
-    }
-  }
-  near_nn = both_halves_max(near_nn);
-  near_no = both_halves_max(near_no);
-  near_on = both_halves_max(near_on);
+      if (wave < nb_new)
+        for (int b = 0; b < nb_old; ++b) {
+          const v16i g = gram<KSTEPS>(row_block(BLOCKS + b), N);
+          near_no = max(near_no, best_of(g, neg + kLongList + 32 * b,
+                                         excluded(eq_n, b, MERGE ? second[BLOCKS + b] : 0u, id_n)));
+        }
 
-  // ---- hand the results on: lanes 0..31 answer for NEW samples (two results, one request),
-  // lanes 32..63 for OLD samples -------------------------------------------------------------
-  uint64_t entry[2];
-  bool found[2], pass[2];
+      // ---- hand the results on: lanes 0..31 answer for NEW samples (two results, one request),
+      // lanes 32..63 for OLD samples -------------------------------------------------------------
+      const int32_t res[2] = {blocks_max(near_nn, near_on), both_halves_max(near_no)};
+      bool pass[2];
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int32_t best = half ? (t ? kNone : near_on) : (t ? near_no : near_nn);
-    const int32_t key = -best;  // ((row norm - 2 G) << kLongBits) | row position
-    const int32_t part = key >> kLongBits;
-    found[t] = self >= 0 && best != kNone && part < (1 << 23);
-    const int32_t dist = part + (int32_t)mine.y;
-    const uint32_t code = FCODE ? ord_f32((float)dist) : ord_i32(dist);
-    const int list = !half && t ? kLongList : 0;
-    const int32_t other = found[t] ? ids[list + (key & ((1 << kLongBits) - 1))] : 0;
-    pass[t] = found[t] && code <= mine.x;  // what cannot enter the list is dropped
-    entry[t] = make_entry(code, (uint32_t)other, 3u);
-  }
-  const uint32_t want = (pass[0] ? 1u : 0u) + (pass[1] ? 1u : 0u);
-  bool over = false;
-  if (want) {
-    // one returning add yields the segment start and the first result's place in it
-    const uint64_t w = atomicAdd(reinterpret_cast<unsigned long long*>(&pslot[self]),
-                                 (unsigned long long)want);
-    const uint64_t at = (w >> kSlotCountBits) + (w & kSlotCountMask);
-    if (at + want <= slots) {
-      bins[at] = pass[0] ? entry[0] : entry[1];
-      if (want == 2u) bins[at + 1] = entry[1];
-    } else {
-      over = true;
-    }
-  }
-  const uint32_t n_found = (uint32_t)(__popcll(__ballot(found[0])) + __popcll(__ballot(found[1])));
-  const uint32_t n_pass = (uint32_t)(__popcll(__ballot(pass[0])) + __popcll(__ballot(pass[1])));
-  const uint32_t n_over = (uint32_t)__popcll(__ballot(over));
-  if (lane == 0) {
-    if (n_found) atomicAdd(&tally[1], n_found);
-    if (n_pass) atomicAdd(&tally[2], n_pass);
-    if (n_over) atomicAdd(&tally[3], n_over);
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint64_t ev;
-    if (MERGE) {
-      uint64_t n2 = 0, o2 = 0;  // samples of the second set
-      for (int b = 0; b < BLOCKS; ++b) {
-        n2 += (uint64_t)__popc(second[b]);
-        o2 += (uint64_t)__popc(second[BLOCKS + b]);
+      for (int t = 0; t < 2; ++t) {
+        const int32_t best = half && t ? kNone : res[t];
+        const int32_t key = -best;  // ((row norm - 2 G) << kLongBits) | row position
+        const int32_t part = key >> kLongBits;
+        const bool found = self >= 0 && best != kNone && part < (1 << 23);
+        const int32_t dist = part + (int32_t)mine.y;
+        const uint32_t code = FCODE ? ord_f32((float)dist) : ord_i32(dist);
+        const int32_t other = ids[t][key & ((1 << kLongBits) - 1)];
+        pass[t] = found && code <= mine.x;  // what cannot enter the list is dropped
+        entry[t] = make_entry(code, (uint32_t)other, 3u);
+        all_found += (uint32_t)__popcll(__ballot(found));
+        all_passed += (uint32_t)__popcll(__ballot(pass[t]));
       }
-      ev = n2 * ((uint64_t)no - o2) + ((uint64_t)nn - n2) * o2;
-    } else {
-      ev = (do_nn ? (uint64_t)nn * (nn - 1) / 2 : 0) + (uint64_t)nn * no - tally[0];
+      if (!pass[0]) entry[0] = entry[1];
+      want = (pass[0] ? 1u : 0u) + (pass[1] ? 1u : 0u);
+      if (want)  // one returning add yields the segment start and the first result's place in it
+        word = atomicAdd(reinterpret_cast<unsigned long long*>(&pslot[self]),
+                         (unsigned long long)want);
+      // pairs evaluated: every wavefront takes off its NEW samples that are OLD ones too
+      if (MERGE) {
+        if (wave == 0) {
+          int n2 = 0, o2 = 0;  // samples of the second set
+          for (int b = 0; b < BLOCKS; ++b) {
+            n2 += __popc(second[b]);
+            o2 += __popc(second[BLOCKS + b]);
+          }
+          all_evals += (int64_t)n2 * (no - o2) + (int64_t)(nn - n2) * o2;
+        }
+      } else {
+        if (wave == 0) all_evals += (do_nn ? nn * (nn - 1) / 2 : 0) + nn * no;
+        all_evals -= __popc((uint32_t)eq_lanes);
+      }
     }
-    unsigned long long* cs =
-        reinterpret_cast<unsigned long long*>(counters + (s & (kStripes - 1)) * C_SLOTS);
-    if (tally[1]) atomicAdd(cs + C_PROPS, (unsigned long long)tally[1]);
-    if (tally[2]) atomicAdd(cs + C_PASSED, (unsigned long long)tally[2]);
-    if (tally[3]) atomicAdd(cs + C_OVERFLOW, (unsigned long long)tally[3]);
-    if (ev) atomicAdd(cs + C_EVALS, (unsigned long long)ev);
+    const bool worked = active, more = s + gridDim.x < n;
+    if (more) {
+      s += gridDim.x;
+      nn = nx_nn;
+      no = nx_no;
+      self = pos < (half ? no : nn) ? nx_self : -1;
+      begin_node();
+      nx_self = id_of(s + gridDim.x);
+      nx_nn = cnew[vmin(s + gridDim.x, n - 1)];
+      nx_no = cold[vmin(s + gridDim.x, n - 1)];
+    }
+    if (want) {
+      const uint64_t at = (word >> kSlotCountBits) + (word & kSlotCountMask);
+      if (at + want <= slots) {
+        bins[at] = entry[0];
+        if (want == 2u) bins[at + 1] = entry[1];
+      } else {
+        ++over;
+      }
+    }
+    if (!more) break;
+    if (worked) __syncthreads();  // the rows and lists have been read
   }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) over += __shfl_xor(over, off, kWave);
+  if (lane == 0) {
+    unsigned long long* cs = reinterpret_cast<unsigned long long*>(
+        counters + ((blockIdx.x * BLOCKS + wave) & (kStripes - 1)) * C_SLOTS);
+    if (all_found) atomicAdd(cs + C_PROPS, (unsigned long long)all_found);
+    if (all_passed) atomicAdd(cs + C_PASSED, (unsigned long long)all_passed);
+    if (over) atomicAdd(cs + C_OVERFLOW, (unsigned long long)over);
+    if (all_evals) atomicAdd(cs + C_EVALS, (unsigned long long)all_evals);
+  }
+}
+
+// Workgroups: as many as are resident (LDS: five of three wavefronts per CU, four of four).
+int long_join_groups(int blocks) {
+  static int cus = 0;
+  if (cus == 0) {
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
+      cus = v;
+    else
+      cus = 256;
+  }
+  return cus * (blocks == 3 ? 5 : 4);
 }
 
 template <int KSTEPS, int BLOCKS>
 void launch(const Shape& sh, const DevState& ds, bool merge, hipStream_t st) {
-  const dim3 grid = grid_blocks(sh.n);
+  const int64_t most = long_join_groups(BLOCKS);
+  const unsigned grid = (unsigned)(sh.n < most ? sh.n : most);
   const uint64_t slots = (uint64_t)sh.slots();
   const bool fcode = sh.metric != kL2U8;
   auto* const kernel = fcode ? (merge ? k_join_long_i8<KSTEPS, BLOCKS, true, true>

@@ -144,3 +144,33 @@ def test_hand_out_of_small_byte_collections(n, d, k, p):
     assert seen[0][0] == seen[1][0]
     for _, ids, dist in seen:
         assert (ids == g.ids).all() and (dist == g.dist).all()
+
+
+@pytest.mark.parametrize("n,k,targets,fit", [(13000, 8, 256, 12 * 1024),
+                                             ((1 << 18) + 100, 24, 512, 36 * 1024)])
+@pytest.mark.parametrize("more", [-1, 0, 1, 3000])
+@pytest.mark.parametrize("kind", [0, 1])
+def test_a_bucket_of_candidates_that_just_fits_or_does_not(n, k, targets, fit, more, kind):
+    """The first `targets` nodes (one bucket of the counting sort) are entries of one kind of fit + more
+    lists: the number a workgroup keeps in registers and LDS, and around it."""
+    import paper_2103_15386_amd as amd
+    rng = np.random.default_rng(7)
+    x = rng.random((n, 4), dtype=np.float32)
+    ids = (targets + (np.arange(n)[:, None] * 7 + 1 + np.arange(k) * 31) % (n - targets)).astype(np.int32)
+    ids += ids == np.arange(n, dtype=np.int32)[:, None]
+    ids[ids >= n] = targets
+    isnew = rng.integers(0, 2, (n, k)).astype(np.uint8)
+    at = targets * k + np.arange(fit + more)
+    ids.reshape(-1)[at] = at % targets
+    isnew.reshape(-1)[at] = kind
+    dist = np.broadcast_to(np.arange(1, k + 1, dtype=np.float64), (n, k)).copy()
+    g = og.init_random(x, k, og.L2SQ_F32, SEED)
+    g.ids[:], g.dist[:], g.isnew[:] = ids, dist, isnew
+    ctx = amd.Gnnd(torch.from_numpy(x).cuda(), k, k, amd.L2SQ_F32, SEED)
+    ctx.set_graph(torch.from_numpy(ids).cuda(), torch.from_numpy(dist.astype(np.float32)).cuda(),
+                  torch.from_numpy(isnew).cuda(), 2)
+    ctx.step_sample()
+    got = [t.cpu().numpy() for t in ctx.samples()]
+    for a, b in zip(got, og.sample(g, k, SEED, 3)):
+        assert (a == b).all()
+    ctx.close()
