@@ -160,7 +160,7 @@ Layout make_layout(const gnnd_params* q, bool with_aside, bool extra = true) {
   L.off_grp = take(sums ? (n / 32 + 1) * 8 : 0);
   L.off_pslot = take(n * 8);
   L.off_deg = take(sample_direct(q->n, q->p) ? n * 8 : 0);
-  L.off_cnt = take((size_t)kStripes * C_SLOTS * 8 + 8);  // (and DevState::forms)
+  L.off_cnt = take((size_t)kStripes * C_SLOTS * 8 + 16);  // (and DevState::forms)
   L.off_flag = take(256);
   L.clear_end = o;  // (off_pslot .. here: cleared by one launch)
   L.off_poff = take((n + 1) * 8);

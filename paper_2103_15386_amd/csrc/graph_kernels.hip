@@ -641,8 +641,8 @@ hipError_t launch_sample(const Shape& sh, const DevState& ds, uint64_t seed, uin
   // forward sampling, and the reverse candidates grouped by target
   const bool direct = sample_direct(sh.n, sh.p);
   int group_rows = 32;
-  hipError_t e = direct ? launch_sample_direct(sh, ds, st)
-                        : launch_sample_buckets(sh, ds, &group_rows, st);
+  hipError_t e = direct ? launch_sample_direct(sh, ds, iter, st)
+                        : launch_sample_buckets(sh, ds, iter, &group_rows, st);
   if (e != hipSuccess) return e;
   uint32_t* const clear = direct ? ds.degree : nullptr;
   if (2 * sh.p > kWave)  // two list entries per lane

@@ -193,7 +193,7 @@ struct StageArgs {
   const uint64_t* poff;     // segment offsets of the destinations (n + 1)
   int tb, nb;               // log2(destinations per bucket), number of buckets
   uint32_t threshold;       // fill count that triggers a flush
-  bool count_passed;        // false when the pass behind the join counts what passes
+  const uint64_t* all;      // not 0: the join hands on every result it finds; NULL: it does not
 };
 constexpr size_t kStageLdsBytes = (size_t)kStageBuckets * kStageSlots * 8 + kStageBuckets * 12 + 16;
 // a staged result (see kStageDistShift) without its destination, and with it
@@ -216,22 +216,35 @@ __device__ inline int32_t half_row_sq(const Operand& o) {
     for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_sdot4(o.k[s][i], o.k[s][i], acc, false);
   return acc;
 }
+// `two`: block 1 holds samples (uniform).
 template <int KSTEPS>
-__device__ inline int32_t sample_norm(const Operand& b0, const Operand& b1, int half, int lane) {
-  const int32_t p0 = half_row_sq<KSTEPS>(b0), p1 = half_row_sq<KSTEPS>(b1);
+__device__ inline int32_t sample_norm(const Operand& b0, const Operand& b1, bool two, int half,
+                                      int lane) {
+  const int32_t p0 = half_row_sq<KSTEPS>(b0);
+  int32_t p1 = 0;
+  if (two) p1 = half_row_sq<KSTEPS>(b1);
   const int32_t mine = half ? p1 : p0, give = half ? p0 : p1;
   return mine + (int32_t)xor_lanes((uint32_t)give, 32, lane);
 }
 
-// LEAN: the form for a launch in which the thresholds of the lists
-// decide little and the nodes have few OLD samples - the first iteration on a random graph,
-// where every result passes and a node's time is the time the memory system needs for its
-// scattered lines.  The 8-byte (threshold, norm) records, one more scattered line per sampled
-// object, are not read: the norms come from the operand registers and every result found is
-// handed on; k_result_csr<true> then applies the thresholds (staged hand-out; with the direct
-// hand-out the list update drops what cannot enter), so the same results reach the lists.
-// Faster only where the saved reads outweigh the extra arithmetic and the larger flow of results.
-//
+// Two ways to treat the thresholds of the lists.  Either the (threshold, norm) record of every
+// sampled object is gathered, 8 bytes but one more scattered line each, and a result that cannot
+// enter its list is dropped here; or neither is read: norms come from the operand registers (up to
+// 64 dot products per node), every result found is handed on, and what cannot enter is dropped one
+// pass later.  Staged, that pass is k_result_csr, which has the thresholds of its bucket in LDS, so
+// the same results reach the lists.  The rows and records of 45 million samples per iteration are
+// asked for at about the rate the memory system serves scattered lines, so records that decide little
+// are better not read: 10^6 x 128, iterations 2 to 5, 69 to 93 % of the results pass, join and
+// k_result_csr 8.25 -> 7.4 ms, build 23.7 -> 22.9 ms; 200,000 x 96 bytes, k = 96, 5.36 -> 5.21 ms.
+// Where fewer pass, what more there is to sort costs as much: with records for no iteration the
+// sharded build of 4 x 600,000 takes 176 to 178 ms instead of 174.  So they are read where less than
+// two thirds of the results of the iteration before passed (half: 176 ms; four fifths: 10^6 x 128 23.5
+// ms), which begin_iteration decides on the device, and where they are few enough to stay in every
+// XCD's cache (below kAllNodes: 100,000 x 128 bytes 2.20 instead of 2.26 ms), but never in the first
+// iteration on a random graph, where everything passes.
+// Direct hand-out: LEAN, the launch of that first iteration; what cannot enter is left to the update.
+constexpr int64_t kAllNodes = 1 << 17;
+
 // Between nodes a wavefront keeps as little as it can waiting for memory: nothing that is in
 // flight is moved or overwritten (see the loop), the search for objects in both lists runs before
 // the rows are needed, counts stay in registers until the end, and the terms a diagonal tile hides
@@ -249,7 +262,8 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
     uint64_t* pslot, uint64_t slots, uint64_t* __restrict__ bins, uint64_t* counters,
     StageArgs sa) {
   constexpr int WAVES = STAGED ? kStagedWaves : kMB / kWave;
-  constexpr bool kHasO1 = !(STAGED && LEAN);  // (no node of a random graph has OLD samples)
+  static_assert(!(STAGED && LEAN), "the staged form looks at StageArgs::all");
+  const bool lean = STAGED ? sa.all && *sa.all != 0ull : LEAN;
   // per wave, for the 128 rows (NEW 0..63, OLD 64..127): -((norm << 6) | position), the ids
   // (absent = INT_MAX so that both halves stay ascending), and what a NEW sample's own column of
   // the diagonal tiles reads instead (see own_rows); the last first serves the search for objects
@@ -347,7 +361,7 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
     for (int k = 0; k < KSTEPS; ++k) o.k[k] = *reinterpret_cast<const v4i*>(row + 32 * k);
   };
   auto request_rows = [&](int32_t idn, int32_t ido) {
-    if (!LEAN) {  // one 8-byte gather per sampled object (an absent one: object 0, unused)
+    if (!lean) {  // one 8-byte gather per sampled object (an absent one: object 0, unused)
       m_new = *reinterpret_cast<const uint2*>(at_offset(meta, (offset_t)vmax(idn, 0) * 8));
       m_old = *reinterpret_cast<const uint2*>(at_offset(meta, (offset_t)vmax(ido, 0) * 8));
     }
@@ -357,7 +371,7 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
     load_rows(N1, i1);
     pair_lanes((uint32_t)ido, 32, i0, i1);
     load_rows(O0, i0);
-    if (kHasO1) load_rows(O1, i1);
+    load_rows(O1, i1);
   };
   // how many samples the node has, and whether it has anything to evaluate; if not, nothing is read
   int nn = 0, no = 0;
@@ -438,10 +452,10 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
     };
 
     uint2 cm_new = m_new, cm_old = m_old;  // this node's thresholds and norms
-    if (LEAN && active) {  // (all lanes take part in the exchange between the halves)
-      cm_new.y = (uint32_t)sample_norm<KSTEPS>(N0, N1, half, lane);
+    if (lean && active) {  // (all lanes take part in the exchange between the halves)
+      cm_new.y = (uint32_t)sample_norm<KSTEPS>(N0, N1, nn > 32, half, lane);
       if (no > 0)  // uniform
-        cm_old.y = (uint32_t)sample_norm<KSTEPS>(O0, kHasO1 ? O1 : O0, half, lane);
+        cm_old.y = (uint32_t)sample_norm<KSTEPS>(O0, O1, no > 32, half, lane);
     }
     if (id_new < 0) cm_new.y = (uint32_t)kFar;  // an absent sample: far from everything
     if (id_old < 0) cm_old.y = (uint32_t)kFar;
@@ -496,25 +510,26 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
       auto cross = [&](const Operand& rows, const Operand& cols, const int32_t* norms, uint32_t eq,
                        int row_block, uint32_t cls_rows, uint32_t col_id) {
         const v16i g = gram<KSTEPS>(rows, cols);
-        return masked_no ? tile_col_best<true>(g, norms, half,
-                                               excl_rows(eq, row_block, cls_rows, col_id))
-                         : tile_col_best<false>(g, norms, half, 0u);
+        // (few tiles hold an object of both lists)
+        const uint32_t skip = masked_no ? excl_rows(eq, row_block, cls_rows, col_id) : 0u;
+        return __ballot(skip != 0u) ? tile_col_best<true>(g, norms, half, skip)
+                                    : tile_col_best<false>(g, norms, half, 0u);
       };
       if (no > 0) {
         // columns = NEW objects, rows = OLD objects: nearest OLD of every NEW
         b0 = max(b0, cross(O0, N0, normO, eq_old_c[0], 0, cls_old[0], id_new_c[0]));
-        if (kHasO1 && no > 32)
+        if (no > 32)
           b0 = max(b0, cross(O1, N0, normO + 32, eq_old_c[0], 1, cls_old[1], id_new_c[0]));
         if (nn > 32) {
           b1 = max(b1, cross(O0, N1, normO, eq_old_c[1], 0, cls_old[0], id_new_c[1]));
-          if (kHasO1 && no > 32)
+          if (no > 32)
             b1 = max(b1, cross(O1, N1, normO + 32, eq_old_c[1], 1, cls_old[1], id_new_c[1]));
         }
         // columns = OLD objects, rows = NEW objects: nearest NEW of every OLD
         c0 = max(c0, cross(N0, O0, normN, eq_new_c[0], 0, cls_new[0], id_old_c[0]));
         if (nn > 32)
           c0 = max(c0, cross(N1, O0, normN + 32, eq_new_c[0], 1, cls_new[1], id_old_c[0]));
-        if (kHasO1 && no > 32) {
+        if (no > 32) {
           c1 = max(c1, cross(N0, O1, normN, eq_new_c[1], 0, cls_new[0], id_old_c[1]));
           if (nn > 32)
             c1 = max(c1, cross(N1, O1, normN + 32, eq_new_c[1], 1, cls_new[1], id_old_c[1]));
@@ -539,8 +554,7 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
         const int32_t other = s_id[(kind == 1 ? 64 : 0) + (res & 63)];
         const uint32_t code = FCODE ? ord_f32((float)dist) : ord_i32(dist);
         // a result that cannot beat the last entry of the destination list is dropped
-        // (LEAN: every result goes on, k_result_csr applies the threshold)
-        pass[kind] = found && (LEAN || code <= cm.x);
+        pass[kind] = found && (lean || code <= cm.x);
         entry[kind] = STAGED ? stage_entry(dist, (uint32_t)other)
                              : make_entry(code, (uint32_t)other, 3u);
         all_found += (uint32_t)__popcll(__ballot(found));
@@ -635,11 +649,8 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
   if (lane == 0) {
     unsigned long long* cs = reinterpret_cast<unsigned long long*>(
         counters + ((blockIdx.x * WAVES + wave) & (kStripes - 1)) * C_SLOTS);
-    // (k_result_csr<true>, behind a launch with a LEAN build, counts what passes the
-    // thresholds)
-    // (direct hand-out with a LEAN build: every result found has been handed on)
-    if ((LEAN ? !STAGED : sa.count_passed) && all_passed)
-      atomicAdd(cs + C_PASSED, (unsigned long long)all_passed);
+    // (staged, every result handed on: k_result_csr counts what passes the thresholds)
+    if (!(STAGED && lean) && all_passed) atomicAdd(cs + C_PASSED, (unsigned long long)all_passed);
     if (all_found) atomicAdd(cs + C_PROPS, (unsigned long long)all_found);
     if (over) atomicAdd(cs + C_OVERFLOW, (unsigned long long)over);
     if (all_evals) atomicAdd(cs + C_EVALS, (unsigned long long)all_evals);
@@ -661,8 +672,8 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
 // destination's run) and writes it out run by run: neighbouring lanes then store to
 // neighbouring places.
 constexpr int kRcBlock = 1024;
-// FILTER (behind the LEAN join, which hands on every result): a result that cannot beat the
-// last entry of its destination's list is dropped here, and what is left is counted as passed.
+// `all` (FILTER; see StageArgs): where the join has handed on every result, those that cannot beat the
+// last entry of their destination's list are dropped here, and what is left is counted as passed.
 // Results per thread and tile: 12 (96 KB of LDS), 11 where the thresholds need room too.
 constexpr int rc_per_thread(bool filter) { return filter ? 11 : 12; }
 // A bucket of more than 2^kRcBits destinations (more than 2^20 nodes) is worked on by several
@@ -683,9 +694,9 @@ __global__ __launch_bounds__(kRcBlock) void k_result_csr(int64_t n, int bucket_t
                                                          uint64_t* __restrict__ bins,
                                                          uint64_t* __restrict__ pslot,
                                                          const NodeMeta* __restrict__ meta,
-                                                         uint64_t* counters) {
-  constexpr int kRcPerThread = rc_per_thread(FILTER);
-  constexpr int kRcTile = kRcBlock * kRcPerThread;
+                                                         uint64_t* counters, const uint64_t* all) {
+  constexpr int kRcPerThread = rc_per_thread(FILTER), kRcTile = kRcBlock * kRcPerThread;
+  const bool filter = FILTER && *all != 0ull;
   extern __shared__ __attribute__((aligned(16))) uint64_t rc_lds[];
   __shared__ uint32_t part[kRcBlock / kWave];
   uint64_t* const tile = rc_lds;
@@ -716,9 +727,9 @@ __global__ __launch_bounds__(kRcBlock) void k_result_csr(int64_t n, int bucket_t
   for (int t = tid; t < T_max; t += kRcBlock) {
     next[t] = t < T ? (uint32_t)(poff[first + t] - region) : (uint32_t)room;
     seg_end[t] = t < T ? (uint32_t)(poff[first + t + 1] - region) : (uint32_t)room;
-    if (FILTER) kth_s[t] = t < T ? meta[first + t].kth : 0u;
+    if (filter) kth_s[t] = t < T ? meta[first + t].kth : 0u;
   }
-  uint32_t kept = 0;  // FILTER: results that pass
+  uint32_t kept = 0;  // results that pass
   uint64_t count = cur[bucket];
   if (count > room) {  // cannot happen: a region holds what its destinations can receive
     if (tid == 0 && part_of == 0)
@@ -741,7 +752,7 @@ __global__ __launch_bounds__(kRcBlock) void k_result_csr(int64_t n, int bucket_t
 #pragma unroll
     for (int r = 0; r < kRcPerThread; ++r) {
       const uint32_t t = place_of(e[r]);
-      if (e[r] == ~0ull || t >= (uint32_t)T || (FILTER && code_of(e[r]) > kth_s[t])) {
+      if (e[r] == ~0ull || t >= (uint32_t)T || (filter && code_of(e[r]) > kth_s[t])) {
         e[r] = ~0ull;
       } else {
         rank[r] = atomicAdd(&run[t], 1u);
@@ -804,7 +815,7 @@ __global__ __launch_bounds__(kRcBlock) void k_result_csr(int64_t n, int bucket_t
     __syncthreads();
   }
   __syncthreads();
-  if (FILTER) {
+  if (filter) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) kept += __shfl_xor(kept, off, kWave);
     if (lane == 0 && kept)
@@ -877,9 +888,8 @@ hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode
   const int ksteps = (sh.d + 31) / 32;
   const bool fcode = sh.metric != kL2U8;
   const bool staged = ds.stg_ent != nullptr;
-  // the first iteration on a random graph: see LEAN
-  const bool lean = first_look && !merge_mode;
-  StageArgs sa{ds.stg_ent, ds.stg_cur, ds.poff, 0, 0, 0, !(lean && staged)};
+  const bool lean = first_look && !merge_mode;  // (direct hand-out only)
+  StageArgs sa{ds.stg_ent, ds.stg_cur, ds.poff, 0, 0, 0, sh.n >= kAllNodes || first_look ? ds.forms + 1 : nullptr};
   hipError_t e;
   // persistent wavefronts.  Direct: about two resident sets of workgroups; staged: one workgroup per
   // CU (the staging area takes most of a CU's LDS)
@@ -895,9 +905,7 @@ hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode
   }
   auto launch = [&](auto steps) {
     constexpr int K = decltype(steps)::value;
-    if (staged)
-      return lean ? launch_k<K, true, true>(fcode, false, grid, st, ds.shadow, ds.meta, sh, ds, sa)
-                  : launch_k<K, true>(fcode, merge_mode, grid, st, ds.shadow, ds.meta, sh, ds, sa);
+    if (staged) return launch_k<K, true>(fcode, merge_mode, grid, st, ds.shadow, ds.meta, sh, ds, sa);
     return lean ? launch_k<K, false, true>(fcode, false, grid, st, ds.shadow, ds.meta, sh, ds, sa)
                 : launch_k<K, false>(fcode, merge_mode, grid, st, ds.shadow, ds.meta, sh, ds, sa);
   };
@@ -911,15 +919,16 @@ hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode
   if (e != hipSuccess || !staged) return e;
   // (a region is shorter than 2^32 slots: n <= 2^22, 6p <= 192 slots per node)
   const int part_tb = sa.tb < kRcBits ? sa.tb : kRcBits;
-  const size_t lds = result_csr_lds_bytes(part_tb, lean);
-  auto* csr = lean ? (fcode ? &k_result_csr<true, true> : &k_result_csr<true, false>)
-                   : (fcode ? &k_result_csr<false, true> : &k_result_csr<false, false>);
+  const bool filter = sa.all != nullptr;
+  const size_t lds = result_csr_lds_bytes(part_tb, filter);
+  auto* csr = filter ? (fcode ? &k_result_csr<true, true> : &k_result_csr<true, false>)
+                     : (fcode ? &k_result_csr<false, true> : &k_result_csr<false, false>);
   e = hipFuncSetAttribute(reinterpret_cast<const void*>(csr),
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   const unsigned csr_grid = (unsigned)sa.nb << (sa.tb - part_tb);
   csr<<<csr_grid, kRcBlock, lds, st>>>(sh.n, sa.tb, ds.poff, ds.stg_cur, ds.stg_ent, ds.bins,
-                                             ds.pslot, ds.meta, ds.counters);
+                                             ds.pslot, ds.meta, ds.counters, sa.all);
   return hipGetLastError();
 }
 

@@ -51,7 +51,8 @@ struct DevState {
   uint64_t* bins;      // n*6p packed proposals, one segment per destination
   uint64_t* counters;  // kStripes * C_SLOTS
   uint64_t* snap;      // the counters as the current iteration's sampling stage found them
-  uint64_t* forms;     // joins with a faster first form: how it has gone so far (see FormTally)
+  uint64_t* forms;     // [0] joins with a faster first form: how it has gone so far (see FormTally);
+                       // [1] not 0: the staged int8 join hands on every result (see begin_iteration)
   uint64_t* aside;     // merge only: n * floor(k/2) set-aside entries
   int8_t* shadow;      // matrix-core path: n rows of dpad int8 (value - 128), zero padded
   uint32_t* bk_cnt;    // 2 x 4096 bucket sizes of the bucketed reverse-candidate sort
@@ -198,8 +199,8 @@ hipError_t launch_join_gram(const Shape& sh, const DevState& ds, bool merge_mode
 // results are staged per bucket when ds.stg_ent is set, handed on one by one otherwise;
 // `after_join` (may be NULL) is recorded behind the cross-matching kernel, in front of the
 // pass that moves staged results into the destinations' segments.  `first_look`: the graph is
-// a fresh random one (first iteration), so that no node has OLD samples; selects a form of the
-// staged join that leaves the lists' thresholds to the second pass; same results with or without it
+// a fresh random one (first iteration); results handed on one by one then do not look at the lists'
+// thresholds, which is left to the update; same graph with or without it
 hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode, bool first_look,
                             hipStream_t st, hipEvent_t after_join = nullptr);
 hipError_t launch_pack_i8(const Shape& sh, const DevState& ds, int* bad_flag_dev, hipStream_t st);
@@ -208,10 +209,10 @@ hipError_t launch_init_random_i8(const Shape& sh, const DevState& ds, uint64_t s
 // (also takes the snapshot of the counters and clears the joins' node list lengths and region
 // cursors: the first stage of an iteration).  `group_rows`: rows per workgroup of the forward
 // sampling (see SegmentRule).
-hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, int* group_rows,
-                                 hipStream_t st);
+hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, uint32_t iter,
+                                 int* group_rows, hipStream_t st);
 // the same where sample_direct() says so; the reverse selection then clears ds.degree
-hipError_t launch_sample_direct(const Shape& sh, const DevState& ds, hipStream_t st);
+hipError_t launch_sample_direct(const Shape& sh, const DevState& ds, uint32_t iter, hipStream_t st);
 // sample lists of 65..128 objects (p > 32): reverse selection and the join for long lists
 hipError_t launch_rev_select_long(const Shape& sh, const DevState& ds, uint64_t seed,
                                   uint32_t iter, int group_rows, uint32_t* clear, hipStream_t st);

@@ -1,8 +1,11 @@
 """The staged hand-out of the int8 join beyond 2^20 nodes, where a bucket of destinations is
 worked on by two or four workgroups: same graphs as the hand-out one by one, builds (the first
 iteration leaves the thresholds to the second pass) and merges, float codes and integer codes."""
+import numpy as np
 import pytest
 import torch
+
+import workloads as W
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +52,33 @@ def test_staged_merge_equals_a_direct_one():
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
     c1.close()
     c2.close()
+
+
+@pytest.mark.parametrize("n", [(1 << 17) - 1, 1 << 17])
+@pytest.mark.parametrize("as_float", [False, True])
+def test_results_handed_on_with_and_without_a_look_at_the_thresholds(n, as_float):
+    """From 2^17 nodes on the staged join hands on every result where most of the iteration before
+    passed; what reaches the lists, and the counts, are those of the general join at every iteration,
+    also in a second build of the same context and from a loaded graph."""
+    import paper_2103_15386_amd as amd
+    x = W.sift_like_u8(n, 40, seed=12, n_comp=64)
+    metric = amd.L2SQ_F32 if as_float else amd.L2SQ_U8
+    xd = torch.from_numpy(x.astype(np.float32) if as_float else x).cuda()
+    ctxs = [amd.Gnnd(xd, 12, 12, metric, W.ALGO_SEED, path) for path in (amd.JOIN_AUTO, amd.JOIN_VALU)]
+    rates = []
+    for begin in ("random", "random", "loaded"):
+        if begin == "loaded":
+            graph = [t.clone() for t in ctxs[1].graph()]
+            isnew = (torch.arange(n * 12, device="cuda").reshape(n, 12) % 3 == 0).to(torch.uint8)
+        for c in ctxs:
+            c.init_random() if begin == "random" else c.set_graph(*graph, isnew, 9)
+        for _ in range(8):
+            a, b = [c.iterate() for c in ctxs]
+            for key in ("inserts", "dist_evals", "sum_new", "sum_old", "proposals", "passed", "dropped"):
+                assert a[key] == b[key], key
+            rates.append(a["passed"] / max(1, a["proposals"]))
+        for a, b in zip(*[c.graph() for c in ctxs]):
+            assert torch.equal(a, b)
+    assert min(rates) < 0.3 and max(rates) > 0.9  # both forms were met
+    for c in ctxs:
+        c.close()
