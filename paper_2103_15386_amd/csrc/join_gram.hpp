@@ -81,8 +81,12 @@ struct GramLds {
     };
     unsigned long long best[192];
   };
-  unsigned long long cmask[192];  // the partners left (bit per partner)
 };
+// The partners left (bit per partner) stand in front of the LDS tile of step 4, which takes their
+// place once the pairs have been listed from them: without it LDS held 3.1 to 3.4 wavefronts per SIMD
+// where the registers leave room for 4 (1.5 million x 96 angular,
+// twelve iterations, 108.3 -> 107.0 ms; with the early requests of step 4 106.0).
+constexpr int kMaskWords = 2 * 192;
 // Step 4 keeps the pairs to be summed and the rows they need in place of the weights.
 struct PairList {
   uint16_t pair[64 * kWItems];  // row a | row b << 7 | "also the nearest-object search of b" << 14
@@ -164,6 +168,7 @@ __device__ __forceinline__ bool gram_node(GramLds& S, float* tile, const VecSrc&
                                           GramTally& tally) {
   using TR = JoinTraits<METRIC>;
   constexpr int NB = RBM + COM;  // operand blocks: NEW blocks first, then OLD blocks
+  unsigned long long* const cmask = reinterpret_cast<unsigned long long*>(tile);
   auto tile_row = [](int row) { return row < 64 ? row : row - 64 + 16 * RBM; };
   constexpr uint32_t kNone = 0xffffffffu;
   const float kInf = __uint_as_float(0x7f800000u), kNaN = __uint_as_float(0x7fc00000u);
@@ -188,7 +193,7 @@ __device__ __forceinline__ bool gram_node(GramLds& S, float* tile, const VecSrc&
 #pragma unroll
   for (int t = 0; t < 3; ++t) {
     S.upper[64 * t + lane] = kNone;
-    S.cmask[64 * t + lane] = 0ull;
+    cmask[64 * t + lane] = 0ull;
   }
   __syncthreads();
 
@@ -602,8 +607,8 @@ __device__ __forceinline__ bool gram_node(GramLds& S, float* tile, const VecSrc&
           float v = bound(acc[r], base_r[r] + base_c, fac_r[r], fac_c);
           v = is_pair(arow, brow, r, id_r[r], idc) ? v : kNaN;
           const int R = arow + g4 + r;
-          if (v <= lim[r]) atomicOr(&S.cmask[(nn_block ? 0 : 64) + R], 1ull << (col & 63));
-          if (v <= col_limit) atomicOr(&S.cmask[col_slot], 1ull << R);
+          if (v <= lim[r]) atomicOr(&cmask[(nn_block ? 0 : 64) + R], 1ull << (col & 63));
+          if (v <= col_limit) atomicOr(&cmask[col_slot], 1ull << R);
         }
       };
       if (COM > 0 && CO > 0) {
@@ -623,8 +628,8 @@ __device__ __forceinline__ bool gram_node(GramLds& S, float* tile, const VecSrc&
   if (special)
     over_pairs([&](float dot, int R, int C) {
       if (dot != dot) {
-        atomicOr(&S.cmask[C < 64 ? R : 64 + R], 1ull << (C & 63));
-        atomicOr(&S.cmask[C < 64 ? C : 64 + C], 1ull << R);
+        atomicOr(&cmask[C < 64 ? R : 64 + R], 1ull << (C & 63));
+        atomicOr(&cmask[C < 64 ? C : 64 + C], 1ull << R);
       }
       return dot;
     });
@@ -634,16 +639,16 @@ __device__ __forceinline__ bool gram_node(GramLds& S, float* tile, const VecSrc&
   // The pairs of all samples and directions are listed, a pair that serves both of its samples
   // once (by the one with the smaller number, or the NEW one), and dealt to the lanes,
   // kWItems each in one pass over the vectors.
-  uint64_t todo[3] = {0ull, 0ull, S.cmask[128 + lane]};  // partners left to be listed, by direction
+  uint64_t todo[3] = {0ull, 0ull, cmask[128 + lane]};  // partners left to be listed, by direction
   uint64_t mutual[2];
   {
-    const uint64_t c_nn = S.cmask[lane], c_no = S.cmask[64 + lane];
+    const uint64_t c_nn = cmask[lane], c_no = cmask[64 + lane];
     mutual[0] = mutual[1] = 0ull;
     for (uint64_t left = c_nn; __ballot(left != 0ull) != 0ull;) {
       if (left != 0ull) {
         const int v = __ffsll((unsigned long long)left) - 1;
         left &= left - 1;
-        const bool both = ((S.cmask[v] >> lane) & 1ull) != 0ull;
+        const bool both = ((cmask[v] >> lane) & 1ull) != 0ull;
         if (both) mutual[0] |= 1ull << v;
         if (!both || lane < v) todo[0] |= 1ull << v;
       }
@@ -652,7 +657,7 @@ __device__ __forceinline__ bool gram_node(GramLds& S, float* tile, const VecSrc&
       if (left != 0ull) {
         const int v = __ffsll((unsigned long long)left) - 1;
         left &= left - 1;
-        if (((S.cmask[128 + v] >> lane) & 1ull) != 0ull) mutual[1] |= 1ull << v;
+        if (((cmask[128 + v] >> lane) & 1ull) != 0ull) mutual[1] |= 1ull << v;
       }
     }
     todo[1] = c_no;
@@ -660,7 +665,7 @@ __device__ __forceinline__ bool gram_node(GramLds& S, float* tile, const VecSrc&
       if (left != 0ull) {
         const int v = __ffsll((unsigned long long)left) - 1;
         left &= left - 1;
-        if (((S.cmask[64 + v] >> lane) & 1ull) != 0ull) todo[2] &= ~(1ull << v);
+        if (((cmask[64 + v] >> lane) & 1ull) != 0ull) todo[2] &= ~(1ull << v);
       }
     }
   }
@@ -724,12 +729,13 @@ __device__ __forceinline__ bool gram_node(GramLds& S, float* tile, const VecSrc&
       pb[i] = tile + tile_row((int)((pair[i] >> 7) & 127u)) * kWLD;
       sum[i] = 0.f;
     }
-    auto sums = [&](const float4* op, int d0) {
+    auto sums = [&](const float4* op, int d0, auto then) {
       __syncthreads();  // the tile has been read
 #pragma unroll
       for (int q = 0; q < NB; ++q)
         *reinterpret_cast<float4*>(tile + (16 * q + l16) * kWLD + g4) = op[q];
       __syncthreads();
+      then();
       const int width = (d - d0) < kWC ? (d - d0) : kWC;
       int j = 0;
       for (; j + 3 < width; j += 4) {
@@ -752,11 +758,14 @@ __device__ __forceinline__ bool gram_node(GramLds& S, float* tile, const VecSrc&
     };
     fetch2(opa, opb, 0);
     for (int d0 = 0;;) {
-      sums(opa, d0);
-      if (d0 + kWC < d) sums(opb, d0 + kWC);
+      // (the next two steps are requested before the sums of the second of these two, whose operands
+      // are in LDS by then: 150,000 x 960 49.5 -> 47.9 ms, 1.5 million x 96 108.3 -> 107.1 ms)
+      auto next = [&]() { if (d0 + 2 * kWC < d) fetch2(opa, opb, d0 + 2 * kWC); };
+      auto none = []() {};
+      sums(opa, d0, none);
+      if (d0 + kWC < d) sums(opb, d0 + kWC, next);
       d0 += 2 * kWC;
       if (d0 >= d) break;
-      fetch2(opa, opb, d0);
     }
 #pragma unroll
     for (int i = 0; i < kWItems; ++i) {
@@ -851,6 +860,7 @@ __attribute__((amdgpu_waves_per_eu(gram_shape(CLS).waves, gram_shape(CLS).waves)
   constexpr int cls = CLS;
   __shared__ __attribute__((aligned(16))) GramLds S;
   // step 4: 16 dimensions of every vector the build can hold, operand block after operand block
+  static_assert(NB * 16 * kWLD >= kMaskWords, "the tile holds the partners' masks");
   __shared__ __attribute__((aligned(16))) float tile[NB * 16 * kWLD];
   // (count NULL: every node is this build's)
   const uint32_t mine = count ? count[cls] : (uint32_t)n;
