@@ -24,12 +24,12 @@
 // Consecutive workgroups of one XCD take the same rows for different queries.
 //
 // 10^6 rows, k_exact_knn alone / this form in ms: 2000 queries x 96 dimensions, angular, K = 10 9.7 /
-// 0.75 (the second scan 0.52, the first 0.17, the copies 0.11 at 5.3 TB/s); 2000 x 128 squared L2
-// 16.8 / 1.1; 2000 x 96 bytes, K = 64 4.5 / 0.51; 16 x 96 6.6 / 0.26; 4096 x 96, K = 64 22.3 / 1.6;
-// 10,000 x 96, K = 64 71.9 / 3.75.  The second scan reaches 0.75 PFLOP/s, half of what large products
-// do here: matrix unit 0.30 and vector unit 0.28 of the time busy (128 dimensions).  Every wavefront
-// reads the row operands from LDS for 64 queries; for 128 it reads half as much, which took 4 %
-// less on the first of these calls but 0.33 instead of 0.29 ms for up to 100 queries.
+// 0.58 (0.75 while the tile on its way stood in scratch memory); 2000 x 128 squared L2 16.8 / 0.84
+// (1.16); 2000 x 96 bytes, K = 64 4.5 / 0.42 (0.52); 100 x 96 0.24 (0.29).  Before that change, and
+// not measured since: 16 x 96 6.6 / 0.26; 4096 x 96, K = 64 22.3 / 1.6; 10,000 x 96, K = 64 71.9 /
+// 3.75; operands of 128 queries per wavefront, which reads half as much from LDS, 4 % less on the
+// first of these calls but 0.33 instead of 0.29 ms for up to 100 queries.  Two tiles on their way
+// instead of one: no change at 96 dimensions, registers spilled.
 // Data the copies do not suit (distances small against the lengths, thousands of copies of a vector)
 // cost the first scan on top: 500 x 200,000 x 48, unit vectors 30 off the origin in every dimension,
 // 0.69 / 0.79 ms; 1000 x 200,000 x 48, queries among 20,000 copies of a vector, 0.79 / 0.88.
@@ -45,6 +45,7 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kGroupQueries = 256;  // queries per workgroup of k_scan
@@ -339,7 +340,7 @@ __device__ inline i32x4 mfma(const uint4& a, const uint4& b, i32x4 c) {
 // COLLECT: rows whose score reaches bound[q] are listed in cand[q * kCap ..], counted in found[q];
 // otherwise the largest score per query and row-modulo-16 goes to bound[q * 16 strips + ..].
 template <int METRIC, int CH, bool COLLECT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_scan(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CH < 4 ? 4 : 3))) void k_scan(
     const uint4* __restrict__ rows, const typename ScoreOf<METRIC>::type* __restrict__ term,
     int64_t tiles, int step, int strips, int qgroups, int64_t n, const uint4* __restrict__ qfrag,
     const int32_t* __restrict__ queries, typename ScoreOf<METRIC>::type* bound, uint32_t* found,
@@ -403,17 +404,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     for (int q = 0; q < kQB; ++q)
       if (over[wave][16 * q + (lane & 15)]) limit[q] = score_never(T{});
   };
-  uint4 reg[CH];
+  // (a plain vector type: as uint4, a class, the tile on its way stood in scratch memory, for which every
+  // wavefront waited for it at once)
+  u32x4 reg[CH];
   T reg_term = T{};
   auto fetch = [&](int64_t t) {
-    const uint4* src = rows + t * (kRB * CH * kWave);
+    const u32x4* src = reinterpret_cast<const u32x4*>(rows) + t * (kRB * CH * kWave);
 #pragma unroll
     for (int c = 0; c < CH; ++c) reg[c] = src[c * 256 + tid];
     if (tid < kTileRows) reg_term = term[t * kTileRows + tid];
   };
   auto put = [&](int at) {
 #pragma unroll
-    for (int c = 0; c < CH; ++c) tile[at][c * 256 + tid] = reg[c];
+    for (int c = 0; c < CH; ++c)
+      *reinterpret_cast<u32x4*>(&tile[at][c * 256 + tid]) = reg[c];
     if (tid < kTileRows) terms[at][tid] = reg_term;
   };
   int64_t t = strip;
