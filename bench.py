@@ -33,8 +33,8 @@ PEAK_INT8_TOPS = 5000.0
 # mean of the first T entries; T beyond the table also gives null.
 JOIN_TRAFFIC = {
     ("sift1m", 1_000_000, 128, 32, 32, "k_join_mfma", "selective"): {
-        "fetch_raw_mib": [3930.8, 4592.3, 5184.2, 5013.2, 5055.2, 4731.6, 4191.9],
-        "write_raw_mib": [577.5, 478.0, 740.7, 591.7, 446.0, 250.8, 140.9],
+        "fetch_raw_mib": [3904.9, 2613.8, 2941.3, 2812.0, 2850.0, 2668.1, 4194.4],
+        "write_raw_mib": [509.6, 512.5, 691.8, 671.4, 510.5, 427.4, 56.6],
         "fetch_scale": 2.0, "write_scale": 1.0},
 }
 
@@ -341,10 +341,8 @@ def main():
     roof["kernel"] = kernel_name
     if gram:  # one launch per class of nodes; the figures are per iteration, all seven together
         roof["launches_per_iteration"] = 7
-    elif kernel_name == "k_join_mfma" and args.n <= (1 << 22):
-        # staged hand-out: one build per shape of node (<= 32 OLD samples, <= 32 NEW samples,
-        # the rest); the figures are per iteration, the three launches together
-        roof["launches_per_iteration"] = 3
+    elif kernel_name == "k_join_mfma":
+        roof["launches_per_iteration"] = 1
     roof["avg_launch_ms"] = avg_join_s * 1e3
     roof["algorithmic_bytes_per_launch"] = alg_bytes
 
