@@ -181,11 +181,17 @@ typedef uint64_t EntryPair __attribute__((ext_vector_type(2), aligned(8)));
 // the segment of its first destination starts, so it can hold whatever its
 // destinations can receive); k_result_csr then moves every result into its
 // destination's segment.  A result that finds its bucket's places taken goes to the
-// bucket's region directly.
+// bucket's region directly, and asks for a flush ahead of time: where results gather in few
+// buckets (a merge with a small set, hubs with neighbouring ids) those are full long before half of
+// all places are, and one returning atomic per result on a few addresses is what the kernel then
+// waits for.  Merge of 300,000 with 30,000 x 96 bytes, k = p = 32, five iterations, without / with
+// early flushes 26.9 / 12.6 ms; 300,000 x 128 bytes in the order of their distance from the mean, eight
+// iterations 102 / 66 ms; results spread evenly: no difference (sharded build of 4 x 600,000 172.3 ms).
 //
 // The waves of a workgroup run at their own pace, so a flush is a rendezvous: every
 // wave looks at the fill count after each node and joins the flush once it has reached
-// the threshold (the count only falls inside a flush, so every wave gets there); a wave
+// the threshold (the count only falls inside a flush, so every wave gets there; asking for
+// one adds the threshold to it, at most once per wave and node); a wave
 // that has run out of nodes keeps joining flushes until all waves have run out.
 struct StageArgs {
   uint64_t* ent;            // bucket regions: staged results
@@ -199,6 +205,12 @@ constexpr size_t kStageLdsBytes = (size_t)kStageBuckets * kStageSlots * 8 + kSta
 // a staged result (see kStageDistShift) without its destination, and with it
 __device__ inline uint64_t stage_entry(int32_t dist, uint32_t id) {
   return ((uint64_t)(uint32_t)dist << kStageDistShift) | (uint64_t)id;
+}
+// the code of its distance
+template <bool FCODE>
+__device__ inline uint32_t stage_code(uint64_t entry) {
+  const int32_t dist = (int32_t)(entry >> kStageDistShift);
+  return FCODE ? ord_f32((float)dist) : ord_i32(dist);
 }
 __device__ inline uint64_t stage_record(uint64_t entry, uint32_t dest, int tb) {
   return entry | ((uint64_t)(dest & ((1u << tb) - 1u)) << kStageIdBits);
@@ -242,6 +254,10 @@ __device__ inline int32_t sample_norm(const Operand& b0, const Operand& b1, bool
 // ms), which begin_iteration decides on the device, and where they are few enough to stay in every
 // XCD's cache (below kAllNodes: 100,000 x 128 bytes 2.20 instead of 2.26 ms), but never in the first
 // iteration on a random graph, where everything passes.
+// A result that goes to its bucket's region directly is held against its threshold first: those that do
+// not pass are mostly for the same few destinations, and one atomic each for them costs more than the
+// records save (the merge and the build above, with early flushes, without / with this look 14.2 /
+// 12.6 and 112 / 66 ms; with neither 39.0 and 163, or 21.3 and 98 with the records in every iteration).
 // Direct hand-out: LEAN, the launch of that first iteration; what cannot enter is left to the update.
 constexpr int64_t kAllNodes = 1 << 17;
 
@@ -598,11 +614,14 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
     // (segments and bucket regions cannot overflow, see the sampling stage; the tests
     // against the array size only keep a violated bound from writing outside the array)
     if (STAGED) {
+      bool full = false;
       auto put = [&](int bucket, uint32_t place, uint64_t e, int32_t dest) {
         const uint64_t rec = stage_record(e, (uint32_t)dest, sa.tb);
         if (place < (uint32_t)kStageSlots) {
           st_ent[bucket * kStageSlots + (int)place] = rec;
         } else {  // the bucket's places are taken: straight to its region
+          full = true;
+          if (lean && stage_code<FCODE>(e) > meta[dest].kth) return;  // (see kAllNodes)
           const uint64_t at = st_region[bucket] + atomicAdd(&sa.cur[bucket], 1ull);
           if (at < slots) sa.ent[at] = rec;
           else ++over;
@@ -611,6 +630,7 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
       if (pass[0]) put(bucket_n, place_n, entry[0], id_new);
       if (pass[1]) put(bucket_n, place_n + (pass[0] ? 1u : 0u), entry[1], id_new);
       if (pass[2]) put(bucket_o, place_o, entry[2], id_old);
+      if (__ballot(full) != 0ull && lane == 0) atomicAdd(&st_fill[0], sa.threshold);
     }
     // direct: with the operand registers free, the next node's rows are requested while
     // the slot words are still on their way ...
@@ -720,10 +740,7 @@ __global__ __launch_bounds__(kRcBlock) void k_result_csr(int64_t n, int bucket_t
         (uint32_t)(x >> kStageIdBits) & ((1u << (kStageDistShift - kStageIdBits)) - 1u);
     return in_bucket - (uint32_t)(part_of * T_max);
   };
-  auto code_of = [](uint64_t x) {
-    const int32_t dist = (int32_t)(x >> kStageDistShift);
-    return FCODE ? ord_f32((float)dist) : ord_i32(dist);
-  };
+  auto code_of = [](uint64_t x) { return stage_code<FCODE>(x); };
   for (int t = tid; t < T_max; t += kRcBlock) {
     next[t] = t < T ? (uint32_t)(poff[first + t] - region) : (uint32_t)room;
     seg_end[t] = t < T ? (uint32_t)(poff[first + t + 1] - region) : (uint32_t)room;

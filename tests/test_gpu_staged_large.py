@@ -82,3 +82,49 @@ def test_results_handed_on_with_and_without_a_look_at_the_thresholds(n, as_float
     assert min(rates) < 0.3 and max(rates) > 0.9  # both forms were met
     for c in ctxs:
         c.close()
+
+
+@pytest.mark.parametrize("n1,n2,as_float", [(262_000, 9_001, False), (9_001, 262_000, True), (60_000, 2_000, False)])
+def test_staged_merge_with_a_small_set_equals_a_direct_one(n1, n2, as_float):
+    """Most results are for the few nodes of the small set: their buckets are full long before half of
+    all places are, flushes come early and what goes to a region directly meets its threshold first."""
+    import paper_2103_15386_amd as amd
+    d, k, p = 24, 20, 20
+    x = _vectors(n1 + n2, d, torch.float32 if as_float else torch.uint8)
+    metric = amd.L2SQ_F32 if as_float else amd.L2SQ_U8
+    a, b = x[:n1].contiguous(), x[n1:].contiguous()
+    ids1, dist1, c1 = amd.gnnd_build(a, k, p, metric, 42, 4)
+    ids2, dist2, c2 = amd.gnnd_build(b, k, p, metric, 43, 4)
+    ids2 = ids2 + n1
+    out = [amd.gnnd_merge(a, b, ids1, dist1, ids2, dist2, k, p, metric, 42, 4, path, want_stats=True)
+           for path in (amd.JOIN_MFMA, amd.JOIN_MFMA_DIRECT)]
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    for s, t in zip(out[0][2], out[1][2]):
+        for key in ("inserts", "dist_evals", "proposals", "passed", "dropped"):
+            assert s[key] == t[key], key
+        assert s["dropped"] == 0
+    c1.close()
+    c2.close()
+
+
+@pytest.mark.parametrize("n", [20_000, (1 << 18) + 77])
+def test_staged_build_with_hubs_at_neighbouring_ids_equals_a_direct_one(n):
+    """Rows in the order of their distance from the mean, a tenth of them equal: the first nodes are in
+    everybody's lists, and nearly all that is found for them does not pass."""
+    import paper_2103_15386_amd as amd
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = 30 * torch.randn((n, 48), generator=g, device="cuda")
+    x = x[(x * x).sum(1).argsort()]
+    x[n // 20:n // 20 + n // 10] = 0
+    x = x.add_(128).clamp_(0, 255).to(torch.uint8)
+    graphs = []
+    for path in (amd.JOIN_MFMA, amd.JOIN_MFMA_DIRECT):
+        ctx = amd.Gnnd(x, 20, 20, amd.L2SQ_U8, 42, path)
+        ctx.init_random()
+        stats = [ctx.iterate() for _ in range(5)]
+        counts = [[s[f] for f in ("inserts", "dist_evals", "proposals", "dropped")] for s in stats]
+        counts.append([s["passed"] for s in stats[1:]])
+        graphs.append((*ctx.graph(with_flags=True), counts))
+        ctx.close()
+    assert all(torch.equal(a, b) for a, b in zip(graphs[0][:3], graphs[1][:3]))
+    assert graphs[0][3] == graphs[1][3]
