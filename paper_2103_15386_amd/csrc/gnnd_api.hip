@@ -162,12 +162,12 @@ Layout make_layout(const gnnd_params* q, bool with_aside, bool extra = true) {
   L.off_deg = take(sample_direct(q->n, q->p) ? n * 8 : 0);
   L.off_cnt = take((size_t)kStripes * C_SLOTS * 8 + 16);  // (and DevState::forms)
   L.off_flag = take(256);
+  L.off_snap = take((size_t)kStripes * C_SLOTS * 8);  // (read by the first sampling stage already)
   L.clear_end = o;  // (off_pslot .. here: cleared by one launch)
   L.off_poff = take((n + 1) * 8);
   const size_t slots_per_node =
       q->update_mode == GNND_UPDATE_ALL_PAIRS ? 2 * p * (6 * p - 1) : 6 * p;
   L.off_bins = take(n * slots_per_node * 8);
-  L.off_snap = take((size_t)kStripes * C_SLOTS * 8);
   L.off_aside = take(with_aside ? n * (k / 2) * 8 : 0);
   const bool shadow = mfma_possible(q) || (extra && long_i8_possible(q));
   L.off_shadow = take(shadow ? n * (size_t)((q->d + 31) & ~31) : 0);
@@ -304,8 +304,8 @@ int init_ctx(gnnd_ctx* c, const gnnd_params* prm, const Layout& L, const void* v
   c->prof_count = 0;
   c->prof_missed = 0;
   bind(c, L);
-  // the statistics counters start at zero, and so do the reverse degrees and the flags; the slot
-  // words read "nothing received" until the first sampling stage writes them
+  // the statistics counters and their snapshot start at zero, and so do the reverse degrees and the
+  // flags; the slot words read "nothing received" until the first sampling stage writes them
   hipError_t e = launch_zero_u32((uint32_t*)c->ds.pslot, (L.clear_end - L.off_pslot) / 4, c->stream);
   if (e != hipSuccess) return hip_fail(nullptr, e, "clearing workspace counters");
   // matrix-core path: build the int8 copy; float data qualifies only when every
