@@ -202,6 +202,7 @@ struct gnnd_ctx {
   int stage;          // 0 = ready for sample, 1 = sampled, 2 = joined
   bool has_graph;
   bool fresh_random;  // the graph is what gnnd_init_random left: no update has touched it yet
+  Expect expect;      // of the next iteration's results
   bool merge_mode;
   bool use_mfma;
   bool use_long_i8;   // sample lists beyond 64 on byte-valued data
@@ -298,6 +299,7 @@ int init_ctx(gnnd_ctx* c, const gnnd_params* prm, const Layout& L, const void* v
   c->stage = 0;
   c->has_graph = false;
   c->fresh_random = false;
+  c->expect = kExpectUnknown;
   c->merge_mode = merge_mode;
   c->have_events = false;
   c->prof_on = false;
@@ -422,7 +424,8 @@ int step_sample(gnnd_ctx* c) {
   if (!c->has_graph) return fail(c, GNND_ESTATE, "no graph: call gnnd_init_random or gnnd_set_graph first");
   if (c->stage != 0) return fail(c, GNND_ESTATE, "stage order is sample, join, update");
   // (the counters only grow: the stage begins by keeping their values from before this iteration)
-  hipError_t e = launch_sample(c->sh, c->ds, c->prm.seed, (uint32_t)(c->iter + 1), c->stream);
+  hipError_t e = launch_sample(c->sh, c->ds, c->prm.seed, (uint32_t)(c->iter + 1), c->expect,
+                               c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "sampling kernels");
   c->stage = 1;
   return GNND_OK;
@@ -454,6 +457,7 @@ int step_update(gnnd_ctx* c) {
   c->stage = 0;
   c->iter += 1;
   c->fresh_random = false;
+  c->expect = kExpectAsBefore;
   return GNND_OK;
 }
 
@@ -526,6 +530,7 @@ int merge_impl(const gnnd_params* prm, const void* vec1, int64_t n1, int64_t bas
     rc = hip_fail(nullptr, e, "merge init kernel");
   } else {
     c->has_graph = true;
+    c->expect = kExpectAll;
     for (int32_t t = 0; t < iters && rc == GNND_OK; ++t)
       rc = iterate_impl(c, stats ? stats + t : nullptr);
     if (rc == GNND_OK) {
@@ -1038,6 +1043,7 @@ int gnnd_init_random(gnnd_ctx* c) {
   if (e != hipSuccess) return hip_fail(c, e, "init kernel");
   c->has_graph = true;
   c->fresh_random = true;
+  c->expect = kExpectAll;
   c->iter = 0;
   c->stage = 0;
   return GNND_OK;
@@ -1110,6 +1116,7 @@ int gnnd_set_graph(gnnd_ctx* c, const int32_t* ids, const void* dist, const uint
   }
   c->has_graph = true;
   c->fresh_random = false;
+  c->expect = kExpectUnknown;
   c->iter = iter;
   c->stage = 0;
   return GNND_OK;

@@ -637,12 +637,12 @@ hipError_t launch_init_random(const Shape& sh, const DevState& ds, uint64_t seed
 // us.  Beyond, there are enough of them either way, and four nodes at a time hide their reads.
 constexpr int64_t kOneNodePerWave = 1 << 14;
 hipError_t launch_sample(const Shape& sh, const DevState& ds, uint64_t seed, uint32_t iter,
-                         hipStream_t st) {
+                         Expect expect, hipStream_t st) {
   // forward sampling, and the reverse candidates grouped by target
   const bool direct = sample_direct(sh.n, sh.p);
   int group_rows = 32;
-  hipError_t e = direct ? launch_sample_direct(sh, ds, iter, st)
-                        : launch_sample_buckets(sh, ds, iter, &group_rows, st);
+  hipError_t e = direct ? launch_sample_direct(sh, ds, expect, st)
+                        : launch_sample_buckets(sh, ds, expect, &group_rows, st);
   if (e != hipSuccess) return e;
   uint32_t* const clear = direct ? ds.degree : nullptr;
   if (2 * sh.p > kWave)  // two list entries per lane

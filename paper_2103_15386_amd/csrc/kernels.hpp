@@ -74,6 +74,12 @@ struct DevState {
 inline int64_t half_row_elems(int32_t d) { return ((int64_t)d + 31) & ~(int64_t)31; }
 constexpr int kGramClasses = 7;
 
+// What is known, when an iteration begins, of how many of its results will pass the thresholds of
+// their lists (see begin_iteration): they will be about as many as in the iteration before, nearly all
+// of them (the lists hold random objects: a fresh random graph, or half of every list when a merge
+// begins), or nothing (a loaded graph).
+enum Expect : int { kExpectAsBefore, kExpectAll, kExpectUnknown };
+
 // Staged hand-out: destinations are cut into at most kStageBuckets buckets of 2^tb
 // consecutive ids; a workgroup of the join keeps kStageSlots results per bucket in LDS.
 // A staged result is one 64-bit word: squared distance (23: at most 128 x 255^2) | destination
@@ -187,7 +193,7 @@ hipError_t launch_init_random(const Shape& sh, const DevState& ds, uint64_t seed
 // reads them
 hipError_t launch_row_norms(const Shape& sh, float* norms, NodeMeta* meta, hipStream_t st);
 hipError_t launch_sample(const Shape& sh, const DevState& ds, uint64_t seed, uint32_t iter,
-                         hipStream_t st);
+                         Expect expect, hipStream_t st);
 hipError_t launch_join(const Shape& sh, const DevState& ds, int path, bool merge_mode,
                        hipStream_t st);
 // The 16-bit copies of the rows into ds.half_rows (ds.half_info is 0 before), and (cosine: not; sh.norms must be set) the
@@ -209,10 +215,10 @@ hipError_t launch_init_random_i8(const Shape& sh, const DevState& ds, uint64_t s
 // (also takes the snapshot of the counters and clears the joins' node list lengths and region
 // cursors: the first stage of an iteration).  `group_rows`: rows per workgroup of the forward
 // sampling (see SegmentRule).
-hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, uint32_t iter,
+hipError_t launch_sample_buckets(const Shape& sh, const DevState& ds, Expect expect,
                                  int* group_rows, hipStream_t st);
 // the same where sample_direct() says so; the reverse selection then clears ds.degree
-hipError_t launch_sample_direct(const Shape& sh, const DevState& ds, uint32_t iter, hipStream_t st);
+hipError_t launch_sample_direct(const Shape& sh, const DevState& ds, Expect expect, hipStream_t st);
 // sample lists of 65..128 objects (p > 32): reverse selection and the join for long lists
 hipError_t launch_rev_select_long(const Shape& sh, const DevState& ds, uint64_t seed,
                                   uint32_t iter, int group_rows, uint32_t* clear, hipStream_t st);
