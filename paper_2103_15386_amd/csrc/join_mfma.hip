@@ -185,8 +185,8 @@ typedef uint64_t EntryPair __attribute__((ext_vector_type(2), aligned(8)));
 // buckets (a merge with a small set, hubs with neighbouring ids) those are full long before half of
 // all places are, and one returning atomic per result on a few addresses is what the kernel then
 // waits for.  Merge of 300,000 with 30,000 x 96 bytes, k = p = 32, five iterations, without / with
-// early flushes 26.9 / 12.6 ms; 300,000 x 128 bytes in the order of their distance from the mean, eight
-// iterations 102 / 66 ms; results spread evenly: no difference (sharded build of 4 x 600,000 172.3 ms).
+// early flushes 26.9 / 12.6 ms; 600,000 x 64 bytes in the order of their distance from the mean, eight
+// iterations 194 / 116 ms; results spread evenly: no difference (sharded build of 4 x 600,000 172.3 ms).
 //
 // The waves of a workgroup run at their own pace, so a flush is a rendezvous: every
 // wave looks at the fill count after each node and joins the flush once it has reached
@@ -251,15 +251,32 @@ __device__ inline int32_t sample_norm(const Operand& b0, const Operand& b1, bool
 // Where fewer pass, what more there is to sort costs as much: with records for no iteration the
 // sharded build of 4 x 600,000 takes 176 to 178 ms instead of 174.  So they are read where less than
 // two thirds of the results of the iteration before passed (half: 176 ms; four fifths: 10^6 x 128 23.5
-// ms), which begin_iteration decides on the device, and where they are few enough to stay in every
-// XCD's cache (below kAllNodes: 100,000 x 128 bytes 2.20 instead of 2.26 ms), but never in the first
-// iteration on a random graph, where everything passes.
+// ms), which begin_iteration decides on the device, and wherever worth_leaving_out() says so; never in
+// the first iteration on a random graph, where everything passes.
 // A result that goes to its bucket's region directly is held against its threshold first: those that do
 // not pass are mostly for the same few destinations, and one atomic each for them costs more than the
 // records save (the merge and the build above, with early flushes, without / with this look 14.2 /
-// 12.6 and 112 / 66 ms; with neither 39.0 and 163, or 21.3 and 98 with the records in every iteration).
+// 12.6 and 190 / 116 ms; with neither 39.0 and 295, or 21.3 and 185 with the records in every iteration).
 // Direct hand-out: LEAN, the launch of that first iteration; what cannot enter is left to the update.
-constexpr int64_t kAllNodes = 1 << 17;
+//
+// Calls in which the records are left out where most results pass.  The more nodes and the longer
+// their lists, the less of the records and lists stands in the caches, and the more the records cost.
+// Time with the records in every iteration but a random graph's first / by the rule above, whole builds
+// of 4 and 8 iterations on 32 and 128 bytes (four ratios), staged int8 join:
+//   k = p = 32: 262,144 nodes 0.98 to 0.98, 400,000 0.98 to 1.01, 700,000 0.99 to 1.05, 10^6 1.01 to 1.07
+//   k = 64, p = 32: 200,000 nodes 0.98 to 1.01, 262,144 1.00 to 1.02, 10^6 1.05 to 1.14
+//   k = 96, p = 32: 140,000 nodes 0.97 to 0.99, 200,000 0.99 to 1.01, 262,144 1.01 to 1.03
+//   p = 8: 0.95 to 1.00 everywhere; k = p = 20 0.96 to 1.01, k = p = 24 0.98 to 1.04 at 0.7 to 10^6
+//   3.5 million (k_result_csr reads every bucket four times): 0.92 to 1.01
+//   merges, k = p = 32: 200,000 nodes 0.97 to 1.00, 300,000 0.97 to 1.01, 500,000 1.02 to 1.08, 1.4
+//   million 1.06 to 1.15; k = 64: 120,000 0.97 to 1.02, 300,000 1.00 to 1.06; p = 8 0.94 to 1.00
+// (a merge of 300,000 with 30,000: 0.68 to 0.92, but either way half of what it took without early
+// flushes).
+static bool worth_leaving_out(const Shape& sh, bool merge) {
+  const int64_t entries = sh.n * sh.k;
+  return sh.p > 8 && sh.n <= (1 << 21) &&
+         (merge ? entries >= 1 << 23 : entries >= 1 << 24 && sh.k > 24);
+}
 
 // Between nodes a wavefront keeps as little as it can waiting for memory: nothing that is in
 // flight is moved or overwritten (see the loop), the search for objects in both lists runs before
@@ -621,7 +638,7 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
           st_ent[bucket * kStageSlots + (int)place] = rec;
         } else {  // the bucket's places are taken: straight to its region
           full = true;
-          if (lean && stage_code<FCODE>(e) > meta[dest].kth) return;  // (see kAllNodes)
+          if (lean && stage_code<FCODE>(e) > meta[dest].kth) return;  // (see worth_leaving_out)
           const uint64_t at = st_region[bucket] + atomicAdd(&sa.cur[bucket], 1ull);
           if (at < slots) sa.ent[at] = rec;
           else ++over;
@@ -906,7 +923,8 @@ hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode
   const bool fcode = sh.metric != kL2U8;
   const bool staged = ds.stg_ent != nullptr;
   const bool lean = first_look && !merge_mode;  // (direct hand-out only)
-  StageArgs sa{ds.stg_ent, ds.stg_cur, ds.poff, 0, 0, 0, sh.n >= kAllNodes || first_look ? ds.forms + 1 : nullptr};
+  const bool all = first_look || worth_leaving_out(sh, merge_mode);  // (staged only)
+  StageArgs sa{ds.stg_ent, ds.stg_cur, ds.poff, 0, 0, 0, all ? ds.forms + 1 : nullptr};
   hipError_t e;
   // persistent wavefronts.  Direct: about two resident sets of workgroups; staged: one workgroup per
   // CU (the staging area takes most of a CU's LDS)

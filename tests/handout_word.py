@@ -18,3 +18,12 @@ def handout_word(ws, stats):
 def next_word(stats):
     """What the word has to be in an iteration that follows one with these statistics."""
     return int(3 * stats["passed"] >= 2 * stats["proposals"])
+
+
+def region_cursors(ws, handed):
+    """How many results each of the 256 bucket regions has received in the last staged join, `handed`
+    in all: those of the iteration's proposals that passed, or all of them."""
+    w = ws.view(torch.int64)
+    at = (w.unfold(0, 256, 32).sum(1) == handed).nonzero().flatten().tolist()
+    assert at and at[-1] - at[0] < 8  # (fewer buckets: the last words are zero, and so may those before be)
+    return w[at[-1] * 32:at[-1] * 32 + 256]
