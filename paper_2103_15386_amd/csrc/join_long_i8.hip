@@ -2,15 +2,13 @@
 // objects (p > 32) on byte-valued data of up to 128 dimensions: exact integer distances from
 // inner products on the matrix cores, the long-list form of k_join_mfma.
 //
-// One workgroup of BLOCKS wavefronts per node at a time: 3 for lists of up to 96 samples (p <= 48), 4 beyond.
-// (A fourth wavefront without samples of its own kept its place and a quarter of the LDS: with
+// One workgroup of BLOCKS wavefronts per node at a time: 3 for lists of up to 96 samples (p <= 48), 4
+// beyond.  (A fourth wavefront without samples of its own kept its place and a quarter of the LDS: with
 // three, 3.75 instead of 3 busy wavefronts per SIMD; 100,000 x 128, p = 42, whole build 3.70 ->
-// 3.39 ms.)
-// Wavefront w brings blocks w (32 samples) of the
-// NEW and of the OLD list, keeps them as column operands and leaves them in LDS as row operands
-// for all four; its columns then meet every block of rows they have partners in.  A tile's
-// epilogue keeps one column per lane (see tile_col_best), so nothing is reduced across lanes
-// but the two halves of a tile.
+// 3.39 ms.)  Wavefront w brings blocks w (32 samples) of the NEW and of the OLD list, keeps them as
+// column operands and leaves them in LDS as row operands for all of them; its columns then meet every
+// block of rows they have partners in.  A tile's epilogue keeps one column per lane (see
+// tile_col_best), so nothing is reduced across lanes but the two halves of a tile.
 //
 // Persistent workgroups: the next node's sample ids are on their way while a node is worked on, and
 // its rows are requested as soon as the last tile has consumed the operand registers, together with
@@ -29,8 +27,15 @@ namespace {
 constexpr int kLongBits = 7;
 constexpr int32_t kFarLong = 3 << 22;  // "norm" of an absent row: above every real distance
 
+// Wavefronts per SIMD.  Short rows keep few registers, and more wavefronts wait for memory at once: an
+// iteration of 600,000 x 16 bytes, p = 64, takes 3.53 ms with 4, 3.44 with 5 and 3.42 with 7 of them,
+// 100,000 x 16 0.507, 0.493 and 0.482, 600,000 x 64, p = 42, 2.75 with 4 and 2.71 with 5.  (6 of them in
+// workgroups of three: the eight workgroups did not fit at once, 600,000 x 16, p = 42, 2.83 -> 3.31.)
+constexpr int long_waves(int ksteps) { return ksteps == 1 ? 7 : ksteps <= 3 ? 5 : 4; }
+
 template <int KSTEPS, int BLOCKS, bool FCODE, bool MERGE>
-__global__ __launch_bounds__(kWave* BLOCKS) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_join_long_i8(
+__global__ __launch_bounds__(kWave* BLOCKS)
+__attribute__((amdgpu_waves_per_eu(long_waves(KSTEPS), long_waves(KSTEPS)))) void k_join_long_i8(
     const int8_t* __restrict__ shadow, const NodeMeta* __restrict__ meta, int64_t n, int p,
     int64_t split, const int32_t* __restrict__ snew, const int32_t* __restrict__ sold,
     const int32_t* __restrict__ cnew, const int32_t* __restrict__ cold, uint64_t* pslot,
@@ -51,16 +56,20 @@ __global__ __launch_bounds__(kWave* BLOCKS) __attribute__((amdgpu_waves_per_eu(4
       ids[i & 1][kLongList + (i >> 1)] = 0x7fffffff;
   }
   const int32_t* const lists = half ? sold : snew;
-  // (nodes beyond the end: the last one, unused)
-  auto id_of = [&](int64_t node) {
-    return lists[vmin(node, n - 1) * L + (pos < L ? pos : L - 1)];
+  // (nodes beyond the end: the last one, unused.  The sizes are known one node ahead of the ids, whose
+  // unused places are not read: on average half of both lists, 3.59 -> 3.42 ms at 600,000 x 16, p = 64)
+  auto id_of = [&](int64_t node, int nn_of, int no_of) {
+    int32_t id = -1;
+    if (pos < (half ? no_of : nn_of)) id = lists[vmin(node, n - 1) * L + pos];
+    return id;
   };
   int64_t s = blockIdx.x;
   int nn = cnew[s], no = cold[s];
-  int32_t self = id_of(s);
-  if (pos >= (half ? no : nn)) self = -1;
-  int32_t nx_self = id_of(s + gridDim.x);
-  int nx_nn = cnew[vmin(s + gridDim.x, n - 1)], nx_no = cold[vmin(s + gridDim.x, n - 1)];
+  int32_t self = id_of(s, nn, no);
+  const int64_t stride = gridDim.x;
+  int nx_nn = cnew[vmin(s + stride, n - 1)], nx_no = cold[vmin(s + stride, n - 1)];
+  int32_t nx_self = id_of(s + stride, nx_nn, nx_no);
+  int nx2_nn = cnew[vmin(s + 2 * stride, n - 1)], nx2_no = cold[vmin(s + 2 * stride, n - 1)];
   // (registers of absent samples keep what they held: an absent row is kept out of every result by
   // its norm, |2 G| < 2^22, an absent column has no result)
   Operand N{}, O{};
@@ -139,12 +148,12 @@ __global__ __launch_bounds__(kWave* BLOCKS) __attribute__((amdgpu_waves_per_eu(4
       for (int b = 0; b < nb_new; ++b) {
         const Operand r = row_block(b);
         const bool new_cols = do_nn && wave < nb_new, old_cols = wave < nb_old;
-        v16i gn, go;
-        if (new_cols) gn = gram<KSTEPS>(r, N);
-        if (old_cols) go = gram<KSTEPS>(r, O);
-        if (new_cols) near_nn = max(near_nn, best_of(gn, neg + 32 * b, b == wave ? 1u << col : 0u));
+        // (one after the other: both tiles at once are 16 registers more)
+        if (new_cols)
+          near_nn = max(near_nn, best_of(gram<KSTEPS>(r, N), neg + 32 * b,
+                                         b == wave ? 1u << col : 0u));
         if (old_cols)
-          near_on = max(near_on, best_of(go, neg + 32 * b,
+          near_on = max(near_on, best_of(gram<KSTEPS>(r, O), neg + 32 * b,
                                          excluded(eq_o, b, MERGE ? second[b] : 0u, id_o)));
       }
       if (wave < nb_new)
@@ -192,16 +201,18 @@ __global__ __launch_bounds__(kWave* BLOCKS) __attribute__((amdgpu_waves_per_eu(4
         all_evals -= __popc((uint32_t)eq_lanes);
       }
     }
-    const bool worked = active, more = s + gridDim.x < n;
+    const bool worked = active, more = s + stride < n;
     if (more) {
-      s += gridDim.x;
+      s += stride;
       nn = nx_nn;
       no = nx_no;
-      self = pos < (half ? no : nn) ? nx_self : -1;
+      self = nx_self;
       begin_node();
-      nx_self = id_of(s + gridDim.x);
-      nx_nn = cnew[vmin(s + gridDim.x, n - 1)];
-      nx_no = cold[vmin(s + gridDim.x, n - 1)];
+      nx_nn = nx2_nn;
+      nx_no = nx2_no;
+      nx_self = id_of(s + stride, nx_nn, nx_no);
+      nx2_nn = cnew[vmin(s + 2 * stride, n - 1)];
+      nx2_no = cold[vmin(s + 2 * stride, n - 1)];
     }
     if (want) {
       const uint64_t at = (word >> kSlotCountBits) + (word & kSlotCountMask);
@@ -227,8 +238,8 @@ __global__ __launch_bounds__(kWave* BLOCKS) __attribute__((amdgpu_waves_per_eu(4
   }
 }
 
-// Workgroups: as many as are resident (LDS: five of three wavefronts per CU, four of four).
-int long_join_groups(int blocks) {
+// Workgroups: as many as are resident.
+int long_join_groups(int blocks, int waves) {
   static int cus = 0;
   if (cus == 0) {
     int dev = 0, v = 0;
@@ -238,12 +249,12 @@ int long_join_groups(int blocks) {
     else
       cus = 256;
   }
-  return cus * (blocks == 3 ? 5 : 4);
+  return cus * (4 * waves / blocks);  // (their LDS fits: at most 151 KB)
 }
 
 template <int KSTEPS, int BLOCKS>
 void launch(const Shape& sh, const DevState& ds, bool merge, hipStream_t st) {
-  const int64_t most = long_join_groups(BLOCKS);
+  const int64_t most = long_join_groups(BLOCKS, long_waves(KSTEPS));
   const unsigned grid = (unsigned)(sh.n < most ? sh.n : most);
   const uint64_t slots = (uint64_t)sh.slots();
   const bool fcode = sh.metric != kL2U8;
