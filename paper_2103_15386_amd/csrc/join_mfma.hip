@@ -181,17 +181,19 @@ typedef uint64_t EntryPair __attribute__((ext_vector_type(2), aligned(8)));
 // the segment of its first destination starts, so it can hold whatever its
 // destinations can receive); k_result_csr then moves every result into its
 // destination's segment.  A result that finds its bucket's places taken goes to the
-// bucket's region directly, and asks for a flush ahead of time: where results gather in few
-// buckets (a merge with a small set, hubs with neighbouring ids) those are full long before half of
-// all places are, and one returning atomic per result on a few addresses is what the kernel then
-// waits for.  Merge of 300,000 with 30,000 x 96 bytes, k = p = 32, five iterations, without / with
-// early flushes 26.9 / 12.6 ms; 600,000 x 64 bytes in the order of their distance from the mean, eight
-// iterations 194 / 116 ms; results spread evenly: no difference (sharded build of 4 x 600,000 172.3 ms).
+// bucket's region directly.  Where results gather in few buckets (a merge with a smaller set, hubs
+// with neighbouring ids) those are full long before half of all places are, and one returning atomic
+// per result on a few addresses is what the kernel then waits for; so a flush is due as well as soon as
+// three quarters of one bucket's places are taken, which leaves room for what the other waves still add.
+// Without / due when a bucket is full / this: merge of 300,000 with 30,000 x 96 bytes, k = p = 32, five
+// iterations, 26.9 / 12.6 / 7.5 ms; of 97,631 with 36,081 x 45, k = 64, p = 32, - / 6.1 / 3.5; 600,000 x
+// 64 bytes in the order of their distance from the mean, eight iterations 194 / 116 / 91; results spread
+// evenly: no difference (10^6 x 128 23.0, sharded build of 4 x 600,000 172.4 ms).
 //
 // The waves of a workgroup run at their own pace, so a flush is a rendezvous: every
 // wave looks at the fill count after each node and joins the flush once it has reached
-// the threshold (the count only falls inside a flush, so every wave gets there; asking for
-// one adds the threshold to it, at most once per wave and node); a wave
+// the threshold (the count only falls inside a flush, so every wave gets there; a bucket
+// that asks for one adds the threshold to it, once between two flushes); a wave
 // that has run out of nodes keeps joining flushes until all waves have run out.
 struct StageArgs {
   uint64_t* ent;            // bucket regions: staged results
@@ -201,6 +203,7 @@ struct StageArgs {
   uint32_t threshold;       // fill count that triggers a flush
   const uint64_t* all;      // not 0: the join hands on every result it finds; NULL: it does not
 };
+constexpr uint32_t kStageSoon = kStageSlots * 3 / 4;  // results in a bucket that make a flush due
 constexpr size_t kStageLdsBytes = (size_t)kStageBuckets * kStageSlots * 8 + kStageBuckets * 12 + 16;
 // a staged result (see kStageDistShift) without its destination, and with it
 __device__ inline uint64_t stage_entry(int32_t dist, uint32_t id) {
@@ -261,21 +264,22 @@ __device__ inline int32_t sample_norm(const Operand& b0, const Operand& b1, bool
 //
 // Calls in which the records are left out where most results pass.  The more nodes and the longer
 // their lists, the less of the records and lists stands in the caches, and the more the records cost.
-// Time with the records in every iteration but a random graph's first / by the rule above, whole builds
-// of 4 and 8 iterations on 32 and 128 bytes (four ratios), staged int8 join:
-//   k = p = 32: 262,144 nodes 0.98 to 0.98, 400,000 0.98 to 1.01, 700,000 0.99 to 1.05, 10^6 1.01 to 1.07
-//   k = 64, p = 32: 200,000 nodes 0.98 to 1.01, 262,144 1.00 to 1.02, 10^6 1.05 to 1.14
-//   k = 96, p = 32: 140,000 nodes 0.97 to 0.99, 200,000 0.99 to 1.01, 262,144 1.01 to 1.03
-//   p = 8: 0.95 to 1.00 everywhere; k = p = 20 0.96 to 1.01, k = p = 24 0.98 to 1.04 at 0.7 to 10^6
-//   3.5 million (k_result_csr reads every bucket four times): 0.92 to 1.01
-//   merges, k = p = 32: 200,000 nodes 0.97 to 1.00, 300,000 0.97 to 1.01, 500,000 1.02 to 1.08, 1.4
-//   million 1.06 to 1.15; k = 64: 120,000 0.97 to 1.02, 300,000 1.00 to 1.06; p = 8 0.94 to 1.00
-// (a merge of 300,000 with 30,000: 0.68 to 0.92, but either way half of what it took without early
-// flushes).
+// Time by the rule above over that with the records in every iteration but a random graph's first, whole
+// builds of 4 and 8 iterations and merges of 2 and 5 on rows of 32 and 128 bytes:
+//   k = p = 32: 262,144 nodes 1.02 to 1.03, 400,000 1.01 to 1.02, 700,000 0.96 to 1.01, 10^6 0.94 to 1.00
+//   k = 64, p = 32: 200,000 nodes 1.02 to 1.04, 262,144 0.99 to 1.01, 10^6 0.88 to 0.95
+//   k = 96, p = 32: 200,000 nodes 1.01 to 1.02, 262,144 0.98 to 1.00, 10^6 0.86 to 0.94
+//   p = 8 1.02 to 1.06 everywhere; k = 12 to 20, p <= k, up to 2 million nodes 0.97 to 1.05
+//   3.5 million (k_result_csr reads every bucket four times) 0.99 to 1.08
+//   merges, k = p = 32: 2 x 150,000 nodes 0.99 to 1.03, 2 x 250,000 0.93 to 0.98, 300,000 + 150,000 0.95 to
+//   1.01, 2 x 700,000 0.85 to 0.95; k = 64: 2 x 100,000 0.98 to 1.02, 2 x 150,000 0.95 to 1.00
+//   merges with a set of less than half the other's size: 300,000 + 30,000 1.08 to 1.19, 250,000 + 90,000
+//   1.01 to 1.06
 static bool worth_leaving_out(const Shape& sh, bool merge) {
-  const int64_t entries = sh.n * sh.k;
+  const int64_t entries = sh.n * (sh.k < 64 ? sh.k : 64);
+  const int64_t smaller = sh.split < sh.n - sh.split ? sh.split : sh.n - sh.split;  // (a merge's sets)
   return sh.p > 8 && sh.n <= (1 << 21) &&
-         (merge ? entries >= 1 << 23 : entries >= 1 << 24 && sh.k > 24);
+         (merge ? entries >= 3 << 22 && 3 * smaller >= sh.n : entries >= 1 << 24 && sh.k > 24);
 }
 
 // Between nodes a wavefront keeps as little as it can waiting for memory: nothing that is in
@@ -617,6 +621,10 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
       if (want_n) place_n = atomicAdd(&st_cnt[bucket_n], want_n);
       if (pass[2]) place_o = atomicAdd(&st_cnt[bucket_o], 1u);
       if (lane == 0) fill = atomicAdd(&st_fill[0], passed) + passed;
+      // (the one result that takes a bucket's place number kStageSoon asks)
+      if ((place_n < kStageSoon && place_n + want_n >= kStageSoon) ||
+          (pass[2] && place_o == kStageSoon - 1))
+        atomicAdd(&st_fill[0], sa.threshold);
     } else {
       // one returning add on the destination's slot word yields the segment start
       // and the place in it
@@ -631,13 +639,11 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
     // (segments and bucket regions cannot overflow, see the sampling stage; the tests
     // against the array size only keep a violated bound from writing outside the array)
     if (STAGED) {
-      bool full = false;
       auto put = [&](int bucket, uint32_t place, uint64_t e, int32_t dest) {
         const uint64_t rec = stage_record(e, (uint32_t)dest, sa.tb);
         if (place < (uint32_t)kStageSlots) {
           st_ent[bucket * kStageSlots + (int)place] = rec;
         } else {  // the bucket's places are taken: straight to its region
-          full = true;
           if (lean && stage_code<FCODE>(e) > meta[dest].kth) return;  // (see worth_leaving_out)
           const uint64_t at = st_region[bucket] + atomicAdd(&sa.cur[bucket], 1ull);
           if (at < slots) sa.ent[at] = rec;
@@ -647,7 +653,6 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
       if (pass[0]) put(bucket_n, place_n, entry[0], id_new);
       if (pass[1]) put(bucket_n, place_n + (pass[0] ? 1u : 0u), entry[1], id_new);
       if (pass[2]) put(bucket_o, place_o, entry[2], id_old);
-      if (__ballot(full) != 0ull && lane == 0) atomicAdd(&st_fill[0], sa.threshold);
     }
     // direct: with the operand registers free, the next node's rows are requested while
     // the slot words are still on their way ...

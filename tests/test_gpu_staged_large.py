@@ -100,10 +100,11 @@ def test_results_handed_on_with_and_without_a_look_at_the_thresholds(n, k, p, of
         c.close()
 
 
-@pytest.mark.parametrize("n1,n2,as_float", [(262_000, 9_001, False), (9_001, 262_000, True), (60_000, 2_000, False)])
+@pytest.mark.parametrize("n1,n2,as_float", [
+    (262_000, 9_001, False), (9_001, 262_000, True), (60_000, 2_000, False), (400_000, 200_001, True)])
 def test_staged_merge_with_a_small_set_equals_a_direct_one(n1, n2, as_float):
-    """Most results are for the few nodes of the small set: their buckets are full long before half of
-    all places are, flushes come early and what goes to a region directly meets its threshold first."""
+    """Most results are for the few nodes of the smaller set: their buckets are full long before half of
+    all places are, and flushes come early.  (The last merge hands on every result.)"""
     import paper_2103_15386_amd as amd
     d, k, p = 24, 32, 20
     x = _vectors(n1 + n2, d, torch.float32 if as_float else torch.uint8)
@@ -126,7 +127,8 @@ def test_staged_merge_with_a_small_set_equals_a_direct_one(n1, n2, as_float):
 @pytest.mark.parametrize("n", [20_000, (1 << 19) + 77])
 def test_staged_build_with_hubs_at_neighbouring_ids_equals_a_direct_one(n):
     """Rows in the order of their distance from the mean, a tenth of them equal: the first nodes are in
-    everybody's lists, and nearly all that is found for them does not pass."""
+    everybody's lists, and nearly all that is found for them does not pass: what goes to a region
+    directly meets its threshold first (the larger build hands on every result)."""
     import paper_2103_15386_amd as amd
     g = torch.Generator(device="cuda").manual_seed(n)
     x = 30 * torch.randn((n, 48), generator=g, device="cuda")
