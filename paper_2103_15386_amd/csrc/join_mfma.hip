@@ -275,8 +275,13 @@ __device__ inline int32_t sample_norm(const Operand& b0, const Operand& b1, bool
 //   1.01, 2 x 700,000 0.85 to 0.95; k = 64: 2 x 100,000 0.98 to 1.02, 2 x 150,000 0.95 to 1.00
 //   merges with a set of less than half the other's size: 300,000 + 30,000 1.08 to 1.19, 250,000 + 90,000
 //   1.01 to 1.06
+// and on rows of 96 bytes, every second of which lies in two lines, so that the rows fill more of the
+// caches and of the line rate:
+//   k = p = 32: 200,000 nodes 1.00 to 1.01, 262,144 0.98 to 0.99, 700,000 0.96; k = 64, p = 32: 140,000
+//   1.01 to 1.03, 200,000 0.96 to 0.98; k = 96, p = 32: 140,000 0.99 to 1.01, 200,000 0.96 to 0.97
+//   merges, k = p = 32: 2 x 100,000 nodes 0.96 to 1.00, 2 x 150,000 0.93 to 0.97
 static bool worth_leaving_out(const Shape& sh, bool merge) {
-  const int64_t entries = sh.n * (sh.k < 64 ? sh.k : 64);
+  const int64_t entries = sh.n * (sh.k < 64 ? sh.k : 64) * (sh.d > 64 && sh.d <= 96 ? 2 : 1);
   const int64_t smaller = sh.split < sh.n - sh.split ? sh.split : sh.n - sh.split;  // (a merge's sets)
   return sh.p > 8 && sh.n <= (1 << 21) &&
          (merge ? entries >= 3 << 22 && 3 * smaller >= sh.n : entries >= 1 << 24 && sh.k > 24);

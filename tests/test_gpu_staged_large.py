@@ -56,18 +56,19 @@ def test_staged_merge_equals_a_direct_one():
     c2.close()
 
 
-@pytest.mark.parametrize("n,k,p,often", [
-    ((1 << 18) - 1, 64, 24, False), (1 << 18, 64, 24, True), (1 << 18, 64, 8, False),
-    ((1 << 19) - 1, 32, 16, False), (1 << 19, 32, 16, True), (700_000, 24, 16, False),
-    ((1 << 21) + 1, 32, 16, False), (1 << 21, 32, 16, True)])
+@pytest.mark.parametrize("n,d,k,p,often", [
+    ((1 << 18) - 1, 24, 64, 24, False), (1 << 18, 24, 64, 24, True), (1 << 18, 24, 64, 8, False),
+    ((1 << 19) - 1, 24, 32, 16, False), (1 << 19, 24, 32, 16, True), (700_000, 24, 24, 16, False),
+    ((1 << 17) - 1, 65, 100, 24, False), (1 << 17, 65, 100, 24, True),
+    ((1 << 21) + 1, 24, 32, 16, False), (1 << 21, 24, 32, 16, True)])
 @pytest.mark.parametrize("as_float", [False, True])
-def test_results_handed_on_with_and_without_a_look_at_the_thresholds(n, k, p, often, as_float):
+def test_results_handed_on_with_and_without_a_look_at_the_thresholds(n, d, k, p, often, as_float):
     """Where it pays (`often`) the staged join hands on every result in iterations after one in which
     most passed, elsewhere only in the first on a random graph; what reaches the lists, and the counts,
     are those of the general join at every iteration, also in a second build of the same context and
     from a loaded graph.  Which form it took is seen from the number of results in the bucket regions."""
     import paper_2103_15386_amd as amd
-    x = W.sift_like_u8(n, 24, seed=12, n_comp=64)
+    x = W.sift_like_u8(n, d, seed=12, n_comp=64)
     metric = amd.L2SQ_F32 if as_float else amd.L2SQ_U8
     xd = torch.from_numpy(x.astype(np.float32) if as_float else x).cuda()
     ctxs = [amd.Gnnd(xd, k, p, metric, W.ALGO_SEED, path) for path in (amd.JOIN_AUTO, amd.JOIN_VALU)]
