@@ -23,16 +23,16 @@
 // streams tiles of 64 rows through LDS, double buffered, each read once for all 256.
 // Consecutive workgroups of one XCD take the same rows for different queries.
 //
-// 10^6 rows, k_exact_knn alone / this form in ms: 2000 queries x 96 dimensions, angular, K = 10 9.7 /
-// 0.58 (0.75 while the tile on its way stood in scratch memory); 2000 x 128 squared L2 16.8 / 0.84
-// (1.16); 2000 x 96 bytes, K = 64 4.5 / 0.42 (0.52); 100 x 96 0.24 (0.29).  Before that change, and
-// not measured since: 16 x 96 6.6 / 0.26; 4096 x 96, K = 64 22.3 / 1.6; 10,000 x 96, K = 64 71.9 /
-// 3.75; operands of 128 queries per wavefront, which reads half as much from LDS, 4 % less on the
+// 10^6 rows, k_exact_knn alone / this form in ms, a call among others: 2000 queries x 96 dimensions,
+// angular, K = 10 9.8 / 0.58 (0.75 while the tile on its way stood in scratch memory); 2000 x 128 squared
+// L2 14.7 / 0.74; 2000 x 96 bytes, K = 64 4.4 / 0.37; 100 x 96 6.9 / 0.21; 16 x 96 6.6 / 0.21; 4096 x 96,
+// K = 64 22.6 / 1.11; 10,000 x 96, K = 64 72.5 / 2.64.  Tried with the tile in scratch memory, and not
+// since: operands of 128 queries per wavefront, which reads half as much from LDS, 4 % less on the
 // first of these calls but 0.33 instead of 0.29 ms for up to 100 queries.  Two tiles on their way
 // instead of one: no change at 96 dimensions, registers spilled.
 // Data the copies do not suit (distances small against the lengths, thousands of copies of a vector)
 // cost the first scan on top: 500 x 200,000 x 48, unit vectors 30 off the origin in every dimension,
-// 0.69 / 0.79 ms; 1000 x 200,000 x 48, queries among 20,000 copies of a vector, 0.79 / 0.88.
+// 0.68 / 0.74 ms; 1000 x 200,000 x 48, queries among 20,000 copies of a vector, 0.78 / 0.84.
 #include <cfloat>
 #include <type_traits>
 
@@ -771,12 +771,12 @@ hipError_t search_metric(const void* vec, int64_t n, int32_t d, const int32_t* q
 // here: rows, dimensions and rounds of workgroups count, and K, whose best it keeps per
 // query and wavefront (bytes: rows of a multiple of 16 bytes are read four dimensions at a time).
 // A pass among others in microseconds, this form / k_exact_knn, `work` in parentheses: 10,325 x 20,
-// 1000 queries, squared L2: K = 1 42 / 31 (2.7), K = 10 43 / 43 (4.1), K = 64 48 / 86 (12.8); 6000 x
-// 96, 1000 queries, bytes: K = 1 39 / 26 (1.8), K = 10 40 / 37 (3.2), K = 64 44 / 66 (11.9); 24,577 x
-// 96, 16 queries 44 / 152 (13).  Of 2400 calls just above the second line - n from one to 3.5 times
-// it, 4 to 128 dimensions, 16 to 4096 queries, K from 1 to 64, three metrics - 135 were slower in
-// this form, by up to 83 %, with that line alone; now 19, by up to 14 %, and 39 that it would have
-// taken in less time, a seventh on average, are left to the other.
+// 1000 queries, squared L2: K = 1 42 / 31 (2.7), K = 10 43 / 44 (4.1), K = 64 48 / 85 (12.8); 6000 x
+// 96, 1000 queries, bytes: K = 1 38 / 27 (1.8), K = 10 38 / 37 (3.2), K = 64 43 / 66 (11.9); 24,577 x
+// 96, 16 queries 41 / 150 (13).  Of 1200 calls just above the second line - n from one to 3.5 times
+// it, 4 to 128 dimensions, 16 to 4096 queries, K from 1 to 64, three metrics - none is slower in this
+// form than in the other by 2 % or more; 9 are left to the other though it takes 2 % more or worse, the
+// three worst of them, of 5 to 10 dimensions, 1.9 to 2.9 times as long.
 size_t exact_scan_bytes(int64_t n, int32_t d, int32_t metric, int64_t nq, int32_t K) {
   if (metric == kChi2F32 || d > 128 || n < 6000 || n > ((int64_t)1 << 27) || nq < 1 ||
       nq > ((int64_t)1 << 27))

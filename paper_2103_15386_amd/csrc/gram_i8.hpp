@@ -14,11 +14,20 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 // (G << (BITS + 1)) + negR is -(((norm_r - 2 G) << BITS) | position_r), so the maximum of t over the rows is
 // the row with the smallest (norm_r - 2 G), ties to the smallest position -
 // one shift-add and half a max3 per accumulator register.  Adding the column's
-// own norm to ((-t) >> 6) gives the squared distance; |.| stays below 2^31
-// because norms are below 2^22 (absent rows, BITS = 6: 2^24 with G = 0; BITS = 7: 3 x 2^22,
-// still above every norm_r - 2 G, which is at most 128 x 255^2 < 2^23).  Rows flagged
-// in `excl` are skipped.  Row of register r for this lane: 8*(r/4) + 4*half + r%4.
+// own norm to ((-t) >> BITS) gives the squared distance.  A row that is not there has a norm
+// far beyond (see far_enough) and whatever an earlier node left in its place, so its G is that of
+// any two rows; so is that of a row with itself.  Rows flagged in `excl` are skipped.  Row of
+// register r for this lane: 8*(r/4) + 4*half + r%4.
 constexpr int32_t kNone = (int32_t)0x80000000;
+
+// Rows of up to 128 int8: norms up to 2^21, 2 G from -2 128 128 127 to 2 128 128 128, squared
+// distances up to 128 255^2 (and norm_r - 2 G no more than that).  A row with the norm `far` is told
+// from every row that is there if what it gives is `limit` or more and a distance is less, and the key
+// of the farthest one still fits 32 bits.
+constexpr bool far_enough(int64_t far, int64_t limit, int bits) {
+  return far - 2 * 128 * 128 * 128 >= limit && limit > 128 * 255 * 255 &&
+         ((far + 2 * 128 * 128 * 127) << bits) + ((int64_t)1 << bits) - 1 < ((int64_t)1 << 31);
+}
 
 template <bool MASKED, int BITS = 6>
 __device__ inline int32_t tile_col_best(const v16i& g, const int32_t* negr_lds, int half,

@@ -25,7 +25,9 @@ namespace gnnd {
 namespace {
 
 constexpr int kLongBits = 7;
-constexpr int32_t kFarLong = 3 << 22;  // "norm" of an absent row: above every real distance
+// "norm" of an absent row, and what no distance reaches
+constexpr int32_t kFarLong = 3 << 22, kLongLimit = 1 << 23;
+static_assert(far_enough(kFarLong, kLongLimit, kLongBits), "absent rows are told from present ones");
 
 // Wavefronts per SIMD.  Short rows keep few registers, and more wavefronts wait for memory at once: an
 // iteration of 600,000 x 16 bytes, p = 64, takes 3.53 ms with 4, 3.44 with 5 and 3.42 with 7 of them,
@@ -71,7 +73,7 @@ __attribute__((amdgpu_waves_per_eu(long_waves(KSTEPS), long_waves(KSTEPS)))) voi
   int32_t nx_self = id_of(s + stride, nx_nn, nx_no);
   int nx2_nn = cnew[vmin(s + 2 * stride, n - 1)], nx2_no = cold[vmin(s + 2 * stride, n - 1)];
   // (registers of absent samples keep what they held: an absent row is kept out of every result by
-  // its norm, |2 G| < 2^22, an absent column has no result)
+  // its norm, see far_enough, an absent column has no result)
   Operand N{}, O{};
   uint2 mine = make_uint2(0u, 0u);  // threshold of the sample's list, norm
   bool do_nn = false, active = false;
@@ -172,7 +174,7 @@ __attribute__((amdgpu_waves_per_eu(long_waves(KSTEPS), long_waves(KSTEPS)))) voi
         const int32_t best = half && t ? kNone : res[t];
         const int32_t key = -best;  // ((row norm - 2 G) << kLongBits) | row position
         const int32_t part = key >> kLongBits;
-        const bool found = self >= 0 && best != kNone && part < (1 << 23);
+        const bool found = self >= 0 && best != kNone && part < kLongLimit;
         const int32_t dist = part + (int32_t)mine.y;
         const uint32_t code = FCODE ? ord_f32((float)dist) : ord_i32(dist);
         const int32_t other = ids[t][key & ((1 << kLongBits) - 1)];

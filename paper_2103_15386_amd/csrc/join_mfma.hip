@@ -26,6 +26,7 @@ constexpr int64_t kJoinGrid = 256 * 3 * 2;  // 256 CUs x 3 resident workgroups x
 constexpr int kStagedWaves = 12;
 
 constexpr int32_t kFar = 1 << 24;  // "norm" of an absent row: above every real distance
+static_assert(far_enough(kFar, kFar >> 1, 6), "absent rows are told from present ones, keys fit");
 
 // Convert float32 rows holding integers 0..255 (or uint8 rows) to int8 rows
 // (value - 128) of `dpad` bytes, zero padded, and store the squared norm of
@@ -390,7 +391,7 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
   if (lane >= L) id_new = id_old = -1;
   // Block b of a list = its rows 32b..32b+31; lane (col, half) holds bytes [32 step + 16 half, +16)
   // of row `col` of the block for every step.  Registers of absent samples keep whatever they held:
-  // absent rows are kept out of every result by their norm (|2 G| <= 2^22 does not bring kFar down
+  // absent rows are kept out of every result by their norm (far_enough: G does not bring kFar down
   // to a real distance), absent columns have no result.
   Operand N0{}, N1{}, O0{}, O1{};
   uint2 m_new = make_uint2(0u, 0u), m_old = m_new;  // list threshold and norm

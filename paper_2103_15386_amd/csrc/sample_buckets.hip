@@ -15,9 +15,11 @@
 //   3. k_fwd_scatter_staged - every workgroup writes its (target, source)
 //                      edges into its runs, sorted by bucket in LDS first.
 //   4. k_bucket_csr  - one workgroup per bucket: LDS counters per target,
-//                      block scan = the targets' segment offsets, second sweep
-//                      places the sources.  Buckets are in target order, so the
-//                      result is the same CSR a global scan would give.
+//                      block scan = the targets' segment offsets; the edges, kept
+//                      in registers, put the sources in order in LDS (a bucket with
+//                      too many edges is swept a second time instead).  Buckets are
+//                      in target order, so the result is the same CSR a global scan
+//                      would give.
 // The loops over rows and edges keep several independent loads in flight per
 // thread; with one load per trip they are bound by memory latency.
 #include "device_utils.hpp"
@@ -647,7 +649,11 @@ hipError_t launch_sample_direct(const Shape& sh, const DevState& ds, Expect expe
 }
 
 // Edges per thread of the two builds of k_bucket_csr for packed edges (tb <= 10).  12 leave room for
-// two workgroups per CU, 36 (with the counters 148 KB of LDS) for one.
+// two workgroups per CU, 36 (with the counters 148 KB of LDS) for one.  p >= 37 beyond 2^19 nodes: while
+// nearly all samples are of one kind the buckets hold more and are swept twice, one workgroup per CU
+// instead of two; the sampling stage then takes what it took with less LDS and no registers for edges
+// (first iteration, 600,000 nodes, p = 42 1.25 / 1.26 ms, p = 64 1.43 / 1.42; 2 million, p = 42 4.38 /
+// 4.23), and less as soon as the kinds are mixed (fourth 1.50 / 1.29, 1.45 / 1.39, 4.48 / 4.02).
 constexpr int kFewEdges = 12, kManyEdges = 36;
 // The bucket layout for n <= 2^27 targets: at most 4096 buckets of 2^tb <= 2^15 targets (one
 // workgroup's LDS counts a bucket's targets).  Small collections take smaller buckets and
