@@ -33,8 +33,8 @@ PEAK_INT8_TOPS = 5000.0
 # mean of the first T entries; T beyond the table also gives null.
 JOIN_TRAFFIC = {
     ("sift1m", 1_000_000, 128, 32, 32, "k_join_mfma", "selective"): {
-        "fetch_raw_mib": [3904.9, 2613.8, 2941.3, 2812.0, 2850.0, 2668.1, 4194.4],
-        "write_raw_mib": [509.6, 512.5, 691.8, 671.4, 510.5, 427.4, 56.6],
+        "fetch_raw_mib": [3905.2, 2615.7, 2944.0, 2816.7, 2852.9, 2670.6, 4194.8],
+        "write_raw_mib": [513.4, 522.6, 708.1, 684.1, 517.8, 433.5, 57.0],
         "fetch_scale": 2.0, "write_scale": 1.0},
 }
 

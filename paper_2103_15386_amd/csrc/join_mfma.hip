@@ -185,11 +185,11 @@ typedef uint64_t EntryPair __attribute__((ext_vector_type(2), aligned(8)));
 // bucket's region directly.  Where results gather in few buckets (a merge with a smaller set, hubs
 // with neighbouring ids) those are full long before half of all places are, and one returning atomic
 // per result on a few addresses is what the kernel then waits for; so a flush is due as well as soon as
-// three quarters of one bucket's places are taken, which leaves room for what the other waves still add.
+// 52 of one bucket's 64 places are taken, which leaves room for what the other waves still add.
 // Without / due when a bucket is full / this: merge of 300,000 with 30,000 x 96 bytes, k = p = 32, five
-// iterations, 26.9 / 12.6 / 7.5 ms; of 97,631 with 36,081 x 45, k = 64, p = 32, - / 6.1 / 3.5; 600,000 x
-// 64 bytes in the order of their distance from the mean, eight iterations 194 / 116 / 91; results spread
-// evenly: no difference (10^6 x 128 23.0, sharded build of 4 x 600,000 172.4 ms).
+// iterations, 26.9 / 12.6 / 7.0 ms; of 97,631 with 36,081 x 45, k = 64, p = 32, - / 6.1 / 3.3; 600,000 x
+// 64 bytes in the order of their distance from the mean, eight iterations 194 / 116 / 94; results spread
+// evenly: no difference (10^6 x 128 23.0, sharded build of 4 x 600,000 172.1 ms).
 //
 // The waves of a workgroup run at their own pace, so a flush is a rendezvous: every
 // wave looks at the fill count after each node and joins the flush once it has reached
@@ -204,7 +204,9 @@ struct StageArgs {
   uint32_t threshold;       // fill count that triggers a flush
   const uint64_t* all;      // not 0: the join hands on every result it finds; NULL: it does not
 };
-constexpr uint32_t kStageSoon = kStageSlots * 3 / 4;  // results in a bucket that make a flush due
+// results in a bucket that make a flush due (at 48 evenly spread results leave in more and shorter
+// pieces, 10^6 x 128 0.3 % of the join; at 56 the merges above take 5 to 8 % longer)
+constexpr uint32_t kStageSoon = kStageSlots * 13 / 16;
 constexpr size_t kStageLdsBytes = (size_t)kStageBuckets * kStageSlots * 8 + kStageBuckets * 12 + 16;
 // a staged result (see kStageDistShift) without its destination, and with it
 __device__ inline uint64_t stage_entry(int32_t dist, uint32_t id) {
