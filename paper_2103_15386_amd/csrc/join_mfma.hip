@@ -12,6 +12,7 @@
 // directions are needed (NEW->OLD and OLD->NEW) instead of reducing across
 // lanes.  Sample lists are sorted by id, so the row position inside a list
 // breaks distance ties exactly like the id does.
+#include <numeric>
 #include <type_traits>
 
 #include "device_utils.hpp"
@@ -167,8 +168,8 @@ typedef uint64_t EntryPair __attribute__((ext_vector_type(2), aligned(8)));
 // FCODE: distances are reported as float32 codes (float input data) instead of
 // int32 codes.  MERGE: GGM mode - no NEW x NEW, only pairs from different sets.
 //
-// Each wavefront walks over nodes s, s + W, s + 2W, ... (W = wavefronts in the
-// grid) as a software pipeline, because a node costs three dependent memory
+// Each wavefront walks over the nodes of places s, s + W, s + 2W, ... (W = wavefronts in the
+// grid; see StageArgs for their order) as a software pipeline, because a node costs three dependent memory
 // round trips (sample ids -> vector rows -> result slots): while the tiles of
 // node i are evaluated the ids of node i+1 are already in flight, and as soon
 // as the last tile has consumed the operand registers the rows of node i+1 are
@@ -191,6 +192,14 @@ typedef uint64_t EntryPair __attribute__((ext_vector_type(2), aligned(8)));
 // 64 bytes in the order of their distance from the mean, eight iterations 194 / 116 / 94; results spread
 // evenly: no difference (10^6 x 128 23.0, sharded build of 4 x 600,000 172.1 ms).
 //
+// Neighbours in the collection are often neighbours in space (rows stored class by class), and then
+// results for one node's samples go to a few buckets, the same ones as its neighbours'.  Were all waves
+// at work on one stretch of ids, a few buckets' places and cursors would serve the whole chip; so the
+// nodes are taken in an order that spreads those under way over all ids.  600,000 x 64 bytes sorted by
+// cluster, k = p = 32, six iterations 166 -> 19 ms (in the order of the ids with the records read and no
+// early flushes 108), a fifth of 600,000 rows zero, eight iterations, 197 -> 134; rows in random order as
+// before (10^6 x 128 23.0 ms, sharded build of 4 x 600,000 172 to 173).
+//
 // The waves of a workgroup run at their own pace, so a flush is a rendezvous: every
 // wave looks at the fill count after each node and joins the flush once it has reached
 // the threshold (the count only falls inside a flush, so every wave gets there; a bucket
@@ -202,6 +211,8 @@ struct StageArgs {
   const uint64_t* poff;     // segment offsets of the destinations (n + 1)
   int tb, nb;               // log2(destinations per bucket), number of buckets
   uint32_t threshold;       // fill count that triggers a flush
+  uint32_t spread, stride;  // the nodes are taken in the order 0, spread, 2 spread, ... mod n, each once;
+                            // stride: from a wave's node to its next
   const uint64_t* all;      // not 0: the join hands on every result it finds; NULL: it does not
 };
 // results in a bucket that make a flush due (at 48 evenly spread results leave in more and shorter
@@ -382,14 +393,21 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
   // later: a register that is written or moved while its load is out would make the wavefront
   // wait for everything it has requested.
   const int L = 2 * p, at_list = lane < L ? lane : L - 1;
-  // (nodes beyond the end: the last one's ids, unused)
+  // (beyond the last node: any node's ids, unused)
   auto sample_of = [&](const int32_t* lists, node_t node) {
     return *reinterpret_cast<const int32_t*>(at_offset(
         lists, ((offset_t)vmin(node, (node_t)(nodes - 1)) * (offset_t)L + (offset_t)at_list) * 4));
   };
+  // s counts the nodes; the node of place s is s itself or, staged, s * spread mod n (see StageArgs)
+  node_t node = STAGED ? (node_t)((uint64_t)s * sa.spread % (uint64_t)n) : s;
+  auto next_node = [&]() {
+    node += STAGED ? (node_t)sa.stride : W;
+    if (STAGED && node >= nodes) node -= nodes;
+  };
   // unused list slots hold -1, so the ids alone say how long a list is
-  int32_t id_new = sample_of(snew, s), id_old = sample_of(sold, s);
-  int32_t nx_new = sample_of(snew, s + W), nx_old = sample_of(sold, s + W);
+  int32_t id_new = sample_of(snew, node), id_old = sample_of(sold, node);
+  next_node();
+  int32_t nx_new = sample_of(snew, node), nx_old = sample_of(sold, node);
   if (lane >= L) id_new = id_old = -1;
   // Block b of a list = its rows 32b..32b+31; lane (col, half) holds bytes [32 step + 16 half, +16)
   // of row `col` of the block for every step.  Registers of absent samples keep whatever they held:
@@ -669,8 +687,9 @@ __attribute__((amdgpu_waves_per_eu(3, 3))) void k_join_mfma(
       id_new = lane < L ? nx_new : -1;
       id_old = lane < L ? nx_old : -1;
       begin_node();
-      nx_new = sample_of(snew, s + 2 * W);
-      nx_old = sample_of(sold, s + 2 * W);
+      next_node();
+      nx_new = sample_of(snew, node);
+      nx_old = sample_of(sold, node);
     }
     // ... and only now the slots are used
     if (!STAGED) {
@@ -937,7 +956,7 @@ hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode
   const bool staged = ds.stg_ent != nullptr;
   const bool lean = first_look && !merge_mode;  // (direct hand-out only)
   const bool all = first_look || worth_leaving_out(sh, merge_mode);  // (staged only)
-  StageArgs sa{ds.stg_ent, ds.stg_cur, ds.poff, 0, 0, 0, all ? ds.forms + 1 : nullptr};
+  StageArgs sa{ds.stg_ent, ds.stg_cur, ds.poff, 0, 0, 0, 1, 0, all ? ds.forms + 1 : nullptr};
   hipError_t e;
   // persistent wavefronts.  Direct: about two resident sets of workgroups; staged: one workgroup per
   // CU (the staging area takes most of a CU's LDS)
@@ -950,6 +969,11 @@ hipError_t launch_join_mfma(const Shape& sh, const DevState& ds, bool merge_mode
     // flush at half-full on average: few results find their bucket's places taken
     sa.threshold = (uint32_t)(sa.nb * (kStageSlots / 2));
     // (the sampling stage has cleared the region cursors)
+    // the first number from the golden section of n on that has no divisor in common with n
+    int64_t spread = (int64_t)(0.6180339887 * (double)sh.n) + 1;
+    while (std::gcd(spread, sh.n) != 1) ++spread;
+    sa.spread = (uint32_t)spread;  // (at most n + 1, below 2^23)
+    sa.stride = (uint32_t)((int64_t)grid * kStagedWaves * spread % sh.n);
   }
   auto launch = [&](auto steps) {
     constexpr int K = decltype(steps)::value;

@@ -147,3 +147,24 @@ def test_staged_build_with_hubs_at_neighbouring_ids_equals_a_direct_one(n):
         ctx.close()
     assert all(torch.equal(a, b) for a, b in zip(graphs[0][:3], graphs[1][:3]))
     assert graphs[0][3] == graphs[1][3]
+
+
+@pytest.mark.parametrize("n", [23, 64, 4099, 1 << 14, 30_030, 100_003, (1 << 19) + 2])
+def test_staged_build_of_rows_stored_class_by_class_equals_a_direct_one(n):
+    """Nodes are taken in a spread order, each once: numbers of nodes with many divisors, with none, and
+    powers of two."""
+    import paper_2103_15386_amd as amd
+    k, c = min(20, n // 2), max(2, n // 5000)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = (torch.rand((c, 40), generator=g, device="cuda") * 255).repeat_interleave(-(-n // c), 0)[:n]
+    x = (x + 12 * torch.randn((n, 40), generator=g, device="cuda")).clamp_(0, 255).to(torch.uint8)
+    graphs = []
+    for path in (amd.JOIN_MFMA, amd.JOIN_MFMA_DIRECT):
+        ctx = amd.Gnnd(x, k, k, amd.L2SQ_U8, 42, path)
+        ctx.init_random()
+        stats = [ctx.iterate() for _ in range(4)]
+        counts = [[s[f] for f in ("inserts", "dist_evals", "proposals", "dropped")] for s in stats]
+        graphs.append((*ctx.graph(with_flags=True), counts))
+        ctx.close()
+    assert all(torch.equal(a, b) for a, b in zip(graphs[0][:3], graphs[1][:3]))
+    assert graphs[0][3] == graphs[1][3]
